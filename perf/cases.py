@@ -351,8 +351,9 @@ def tolerance(case):
     if c["kind"] == "hard":
         return "exact"                      # counts, and their order
     if c["kind"] == "prefill":
-        # a sign may turn where a projection is within the rounding of its 32-bit sum of zero
-        return {"rel": 2e-6, "max": 2e-5, "differ": 1e-4}
+        # a sign may turn where a projection is within the rounding of its 32-bit sum of zero: 1e-7 of the
+        # bytes against 64 bits; norms are 3e-8 off
+        return {"rel": 4e-7, "max": 4e-6, "differ": 1e-6}
     # scores are 5e-8 off 64 bits and fp32 outputs 1e-6 to 7e-6 (the logits reach 100), outputs rounded to bf16 1.7e-3
     if c["out_f32"]:
         return {"rel": 2e-5, "max": 8e-4, "differ": 1e-4}
