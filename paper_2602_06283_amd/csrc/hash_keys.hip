@@ -9,10 +9,14 @@
 //                      (v_mfma_f32_32x32x16_bf16, fp32 accumulate), W held in registers,
 //                      key tiles staged through LDS, sign bits taken from the accumulators'
 //                      sign bit and packed into a per-key bit matrix in LDS.
-//   hash_rows_kernel   fp32 keys, or a handful of appended rows: fp32 FMA, one thread per
-//                      projection column, sign bits gathered with a wavefront ballot.
-// The last two end in pack_codes(), which cuts the bit matrix into P-bit bucket ids and writes
+//   hash_f32_kernel    fp32 keys, or fewer than 64 rows of bf16 keys: fp32 MFMA
+//                      (v_mfma_f32_32x32x2_f32), W held in registers.
+//   hash_rows_kernel   up to four rows, or groups too wide for hash_f32_kernel: fp32 FMA, one
+//                      thread per projection column, sign bits gathered with a wavefront ballot.
+// The last three end in pack_codes(), which cuts the bit matrix into P-bit bucket ids and writes
 // them in the rotated order the scoring kernel reads.
+#include <type_traits>
+
 #include "socket_internal.h"
 
 namespace sk {
@@ -184,6 +188,144 @@ __global__ __launch_bounds__(256) void hash_rows_kernel(HashArgs a) {
         pack_codes_packed(bits, bw, ROWS, tok, grow, a.codes, a.L, a.P, a.Lpad, a.GT, 0, a.L, a.Lpad / a.GT, tid, 256);
     else
         pack_codes(bits, bw, ROWS, tok, grow, a.codes, a.L, a.P, a.Lpad, a.S, a.cb, 0, a.L, true, tid, 256);
+}
+
+// ---------------------------------------------------------------------------------------
+// fp32 MFMA kernel: fp32 caches, and short runs of bf16 keys.  Long runs are bound by the fp32
+// matrix rate (147 TFLOP/s in a large product on this card): 8 heads x 8192 keys, 32 tables of
+// 8 planes 42 us = 101 TFLOP/s, 128 us through the FMA kernel above, which re-reads W from L2 for
+// every 16 rows; 64 tables 74 us = 114 TFLOP/s (245).  Short runs are bound by the fetch of W:
+// 17 rows of 64 tables 13 us (33 through the FMA kernel, whose W loads wait for each other).
+// v_mfma_f32_32x32x2_f32 adds its two products to the accumulator one after the other, each
+// as an FMA, channel 2 s before channel 2 s + 1: a projection here is bit for bit the sum that
+// hash_rows_kernel forms, so the two give the same ids.
+// A wavefront owns 32 columns and keeps their W in registers (A operand: d/2 words a lane) for
+// the whole kernel; the workgroup walks its rows in tiles of 32 keys staged through LDS.  A
+// staged row is [even channels][odd channels], so that a lane of half g (B operand: channel
+// 2 s + g of key n) reads four k-steps with one ds_read_b128; the 16-byte row pad spreads the
+// rows over all banks.  One barrier per tile, as in hash_mfma_kernel below.
+// 32 columns a wavefront rather than 64: the registers then allow four wavefronts per SIMD at
+// d = 128, and 10-plane groups (320 columns) fill ten wavefronts instead of leaving three of
+// eight idle.
+// ---------------------------------------------------------------------------------------
+constexpr int kF32Tile = 32;               // keys per tile
+constexpr int kF32BitWords = 17;           // words per bit row: 512 columns and a pad
+template <int D> constexpr int f32_min_threads() { return D == 64 ? 256 : 512; }   // (fewer would stage more pieces a thread than registers allow)
+
+template <typename T, int D>
+__global__ __launch_bounds__(D <= 128 ? 1024 : 512) void hash_f32_kernel(HashArgs a) {
+    typedef typename std::conditional<sizeof(T) == 2, uint2, uint4>::type Quad;   // four channels as stored
+    constexpr int KS = D / 2;                  // MFMA k-steps
+    constexpr int TILE = kF32Tile, BW = kF32BitWords;
+    constexpr int ROWW = D + 4;                // words of a staged key row
+    constexpr int NST = TILE * D / 4 / f32_min_threads<D>();   // 16-byte pieces of a tile per thread of the smallest workgroup
+    extern __shared__ uint32_t smem[];
+    float *kt = (float *)smem;                         // [2][TILE][ROWW]
+    uint32_t *bits = smem + 2 * TILE * ROWW;           // [2][TILE][BW]
+    int64_t *grow = (int64_t *)(bits + 2 * TILE * BW); // [3][TILE]
+    int *tok = (int *)(grow + 3 * TILE);               // [3][TILE]
+
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 31, g = lane >> 5;
+    const int chunk = blockIdx.y % a.n_chunks, h = blockIdx.y / a.n_chunks, b = blockIdx.z;
+    const int count = a.row_count[b];
+    const int wg_r0 = blockIdx.x * a.rows_per_wg;
+    if (wg_r0 >= count) return;
+    const int wg_r1 = min(count, wg_r0 + a.rows_per_wg);
+    const int begin = a.row_begin[b];
+    const int first_table = chunk * a.tables_per_chunk;
+    const int ntab = max(0, min(a.tables_per_chunk, a.L - first_table));   // 0: a group of padding tables only
+    const int ncols = ntab * a.P;
+
+    Quad stage[NST];
+    auto fetch = [&](int r0, int slot) {       // slot: which third of the row bookkeeping
+#pragma unroll
+        for (int v = 0; v < NST; ++v) {
+            const int i = tid + v * nt, row = i / (D / 4), seg = i % (D / 4);
+            if (i >= TILE * (D / 4)) break;
+            const int t = begin + r0 + row;
+            const bool live = r0 + row < wg_r1 && t >= 0 && t < a.map.max_n;
+            const int64_t gr = live ? a.map.row(b, h, t) : -1;
+            if (seg == 0) {
+                tok[slot * TILE + row] = t;
+                grow[slot * TILE + row] = gr;
+            }
+            stage[v] = gr >= 0 ? *((const Quad *)((const T *)a.K + gr * D) + seg) : Quad{};
+        }
+    };
+    auto commit = [&](int buf) {
+#pragma unroll
+        for (int v = 0; v < NST; ++v) {
+            const int i = tid + v * nt, row = i / (D / 4), seg = i % (D / 4);
+            if (i >= TILE * (D / 4)) break;
+            uint32_t *dst = (uint32_t *)(kt + (buf * TILE + row) * ROWW) + 2 * seg;
+            if constexpr (sizeof(T) == 2) {
+                *(uint2 *)dst = make_uint2(stage[v].x << 16, stage[v].y << 16);
+                *(uint2 *)(dst + D / 2) = make_uint2(stage[v].x & 0xffff0000u, stage[v].y & 0xffff0000u);
+            } else {
+                *(uint2 *)dst = make_uint2(stage[v].x, stage[v].z);
+                *(uint2 *)(dst + D / 2) = make_uint2(stage[v].y, stage[v].w);
+            }
+        }
+    };
+    fetch(wg_r0, 0);
+
+    // ---- this wavefront's 32 columns of W: lane (column n, half g) holds channels 2 s + g
+    const int col = wave * 32 + n;
+    const T *Wg = (const T *)a.W + (int64_t)h * D * a.LP + first_table * a.P;
+    // (a lane beyond the last column reads that column again: its bits are never packed)
+    float wr[KS];
+    if (wave * 32 < ncols) {
+        const T *Wc = Wg + (int64_t)g * a.LP + min(col, ncols - 1);
+        T raw[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) raw[s] = Wc[(int64_t)(2 * s) * a.LP];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) wr[s] = load_elem<T>(raw + s);
+    }
+
+    const bool whole = a.n_chunks == 1 || (a.tables_per_chunk & 63) == 0;
+    commit(0);
+    __syncthreads();
+
+    int buf = 0, slot = 0;
+    for (int r0 = wg_r0; r0 < wg_r1; r0 += TILE) {
+        const bool more = r0 + TILE < wg_r1;
+        const int nslot = slot == 2 ? 0 : slot + 1;
+        if (more) fetch(r0 + TILE, nslot);
+        uint32_t *bt = bits + buf * (TILE * BW);
+        if (wave * 32 < ncols) {
+            floatx16_t acc;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+            const float4 *src = (const float4 *)(kt + (buf * TILE + n) * ROWW + g * (D / 2));
+#pragma unroll
+            for (int s4 = 0; s4 < KS / 4; ++s4) {
+                const float4 kf = src[s4];
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4], kf.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4 + 1], kf.y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4 + 2], kf.z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4 + 3], kf.w, acc, 0, 0, 0);
+            }
+            // accumulator i of lane (n, g) is plane 8 (i/4) + 4g + i%4 of key n
+            uint32_t word = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) word |= (acc[i] >= 0.0f ? 1u : 0u) << (8 * (i / 4) + i % 4);
+            word <<= 4 * g;
+            auto both = __builtin_amdgcn_permlane32_swap(word, word, false, false);
+            if (lane < 32) bt[n * BW + wave] = both[0] | both[1];
+        }
+        if (more) commit(buf ^ 1);
+        __syncthreads();   // bit matrix complete, next tile staged, every wave done with this key tile
+        const int *tk = tok + slot * TILE;
+        const int64_t *gr = grow + slot * TILE;
+        if (a.GT)
+            pack_codes_packed(bt, BW, TILE, tk, gr, a.codes, a.L, a.P, a.Lpad, a.GT, first_table, ntab, 1, tid, nt);
+        else
+            pack_codes(bt, BW, TILE, tk, gr, a.codes, a.L, a.P, a.Lpad, a.S, a.cb, first_table, ntab, whole, tid, nt);
+        buf ^= 1;
+        slot = nslot;
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -795,6 +937,56 @@ static int launch_mfma10(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_r
                       : launch_mfma10<D, 1>(a, wfrag, Hkv, batch, max_rows, st);
 }
 
+// Runs of up to four rows stay with the FMA kernel's one-row workgroups while W is small: both are a
+// prologue of W loads, and theirs are spread over more workgroups (rows = 4, 8 heads: 512 columns x
+// 128 channels 11.6 us there, 13.2 here; 600 x 128 16.1 / 10.9; 512 x 256 19.5 / 13.2; five rows of
+// 512 x 128, where that kernel takes sixteen rows a workgroup: 32.6 / 13.2).
+static bool f32_fma_rows(const HashArgs &a, int max_rows) { return max_rows <= 4 && (a.LP + 255) / 256 * a.d <= 256; }
+// columns of W a workgroup of hash_f32_kernel holds at most (32 a wavefront)
+template <int D> constexpr int f32_columns() { return D <= 128 ? 512 : 256; }
+
+template <typename T, int D>
+static int launch_f32(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
+    if (a.GT) {
+        a.tables_per_chunk = a.GT;             // packed ids: whole groups, padding groups included
+        a.n_chunks = a.Lpad / a.GT;
+    } else {
+        a.tables_per_chunk = f32_columns<D>() / a.P;
+        if (a.tables_per_chunk > a.L) a.tables_per_chunk = a.L;
+        a.n_chunks = (a.L + a.tables_per_chunk - 1) / a.tables_per_chunk;
+    }
+    int waves = (a.tables_per_chunk * a.P + 31) / 32;
+    if (waves < f32_min_threads<D>() / 64) waves = f32_min_threads<D>() / 64;
+    // rows per workgroup: one round of resident workgroups (16 wavefronts a CU, 8 at d = 256), at
+    // most 16 tiles each so that ragged batches still spread
+    const int slots = 256 * ((D <= 128 ? 16 : 8) / waves);
+    const int64_t tiles = (int64_t)((max_rows + kF32Tile - 1) / kF32Tile) * Hkv * batch * a.n_chunks;
+    int64_t per = (tiles + slots - 1) / slots;
+    per = per < 1 ? 1 : per > 16 ? 16 : per;
+    a.rows_per_wg = (int)per * kF32Tile;
+    const size_t lds = 2 * kF32Tile * (D + 4) * 4 + 2 * kF32Tile * kF32BitWords * 4 + 3 * kF32Tile * 12;
+    dim3 grid((max_rows + a.rows_per_wg - 1) / a.rows_per_wg, Hkv * a.n_chunks, batch);
+    static_assert(2 * kF32Tile * (D + 4) * 4 + 2 * kF32Tile * kF32BitWords * 4 + 3 * kF32Tile * 12 <= 80 * 1024, "two workgroups a CU");
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute((const void *)hash_f32_kernel<T, D>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return SOCKET_EHIP;
+    hipLaunchKernelGGL((hash_f32_kernel<T, D>), grid, dim3(64 * waves), lds, st, a);
+    return SOCKET_OK;
+}
+
+template <typename T>
+static int launch_f32(const HashArgs &a, int Hkv, int batch, int max_rows, hipStream_t st) {
+    // (a group of 32 tables of 9 or 10 planes is wider than a workgroup at d = 256)
+    if (f32_fma_rows(a, max_rows) || a.GT * a.P > (a.d <= 128 ? f32_columns<128>() : f32_columns<256>()))
+        return launch_rows<T>(a, Hkv, batch, max_rows, st);
+    switch (a.d) {
+        case 64: return launch_f32<T, 64>(a, Hkv, batch, max_rows, st);
+        case 128: return launch_f32<T, 128>(a, Hkv, batch, max_rows, st);
+        case 256: return launch_f32<T, 256>(a, Hkv, batch, max_rows, st);
+        default: return SOCKET_EUNSUPPORTED;
+    }
+}
+
 template <int D>
 static int launch_mfma(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
     constexpr int TILE = 64, KSTRIDE = D * 2 + 16, BSTRIDE = 17;
@@ -837,9 +1029,9 @@ int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int
         return launch_project(ctx, nullptr, proj, 1.0f, K, codes, block_table, row_begin, row_count,
                               nullptr, batch, st);
     } else if (g.kv_dtype == SOCKET_F32) {
-        rc = launch_rows<float>(a, g.Hkv, batch, max_rows, st);
+        rc = launch_f32<float>(a, g.Hkv, batch, max_rows, st);
     } else if (max_rows < 64) {
-        rc = launch_rows<uint16_t>(a, g.Hkv, batch, max_rows, st);
+        rc = launch_f32<uint16_t>(a, g.Hkv, batch, max_rows, st);
     } else {
         const bool fast8 = ctx->wfrag != nullptr && (g.P == 8 || g.P == 4);   // one-byte ids of 8 or 4 planes, d <= 128
         const bool fast10 = ctx->wfrag != nullptr && g.P == 10;    // packed ids in groups of 32 tables, d <= 128

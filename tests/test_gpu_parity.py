@@ -149,6 +149,27 @@ def test_hash_keys_unaligned_row_ranges_through_the_mfma_kernels():
         ctx.close()
 
 
+@pytest.mark.parametrize("d,L,P", [(64, 32, 8), (128, 32, 8), (128, 60, 10), (128, 11, 10), (128, 16, 4), (128, 100, 8),
+                                   (128, 40, 12), (256, 64, 8), (256, 16, 10), (256, 13, 7), (256, 40, 10)])
+def test_hash_keys_fp32_sums_do_not_depend_on_the_run(d, L, P):
+    """fp32 keys, and bf16 keys in runs below 64 rows: five rows and more go through the fp32 matrix
+    kernel (tiles of 32 keys, 32 columns a wavefront), runs of up to four through the FMA kernel where
+    W is small.  Both add the channels in the same order with one rounding each, so the ids are the
+    same bit for bit, whatever run a key is hashed in."""
+    _need_gpu()
+    for kv_dtype, counts, step in ((wl.F32, [97, 161], 161), (wl.BF16, [37, 63], 63)):
+        layer = small_layer(seed=15, B=2, Hq=2, Hkv=2, d=d, n=256, L=L, P=P, kv_dtype=kv_dtype, k=16)
+        ctx = hz.make_ctx(layer)
+        begins = [3, 50]
+        codes = run_hash(ctx, layer, begins, counts, step)
+        check_codes(layer, codes, lambda b: (begins[b], counts[b]))
+        short = hz.new_codes((2, 2), layer.n, L, P, fill=0x55)
+        for at in range(0, step, 4):
+            run_hash(ctx, layer, [b + at for b in begins], [max(0, min(4, c - at)) for c in counts], 4, short)
+        assert torch.equal(codes, short)
+        ctx.close()
+
+
 # ------------------------------------------------------------------ a2 + a3: socket_score
 
 def run_score(ctx, layer, codes_nat, tau, vnorm=None, seq_len=None, q=None):
