@@ -1,8 +1,8 @@
 // Alg. 1 (PrecomputeKeyHashes): sign random projections of cached keys, packed into bucket ids.
 //
 // Kernels:
-//   hash_mfma8_kernel  bf16 keys, 8- or 4-plane tables (one-byte ids), d <= 128: the W slab of a
-//                      chunk of up to 64 tables sits in LDS as MFMA fragments, keys go from
+//   hash_mfma8_kernel  bf16 keys, 8- or 4-plane tables (one-byte ids): the W slab of a
+//                      chunk of up to 64 tables (half a chunk at d = 256) sits in LDS as MFMA fragments, keys go from
 //                      memory straight into registers, the ids are assembled in registers.
 //   hash_mfma10_kernel the same structure for 10-plane tables with packed 10-bit ids.
 //   hash_mfma_kernel   bf16 keys, any other shape: K[rows x d] * W[d x L*P] on bf16 MFMA
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(512, D <= 128 ? 4 : 2) void hash_mfma_kernel(HashAr
 }
 
 // ---------------------------------------------------------------------------------------
-// bf16 MFMA kernel for 8-plane tables (one-byte ids), d <= 128: the fast path.
+// bf16 MFMA kernel for 8- and 4-plane tables (one-byte ids): the fast path.
 // A workgroup keeps the W slab of one 64-table chunk (512 columns) in LDS, already cut into
 // MFMA A-operand fragments, and each of its 16 wavefronts works on 64-key blocks of its own:
 // the keys go from memory straight into B-operand registers, so there is no staging, no
@@ -549,43 +549,57 @@ template <int V> struct IntTag { static constexpr int value = V; };
 
 constexpr int kHash8Threads = 1024;
 
+// the A fragments of `N` 16-byte pieces a workgroup works with, into LDS, up to eight loads in flight per thread
+template <int N, int NT>
+__device__ __forceinline__ void fragments_to_lds(uint4 *wl, const uint4 *src, int tid) {
+    constexpr int PER = (N + NT - 1) / NT, NB = PER < 8 ? PER : 8;
+    constexpr bool EVEN = PER * NT == N && PER % NB == 0;
+#pragma unroll 1
+    for (int u0 = 0; u0 < PER; u0 += NB) {
+        uint4 v[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int i = tid + (u0 + u) * NT;
+            v[u] = src[EVEN || i < N ? i : N - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int i = tid + (u0 + u) * NT;
+            if (EVEN || i < N) wl[i] = v[u];
+        }
+    }
+}
+
+// Shape of a workgroup: NG of the chunk's S position groups (a chunk's workgroups are its S / NG
+// parts), their fragments in LDS.  d = 256: a block's fragments are 16 KB, so eight blocks, and a
+// 64-key block of keys takes 128 registers, so eight wavefronts; the keys are read once per part
+// (4 heads x 32768 keys, 64 tables of 8 planes: 36.6 us = 0.94 PFLOP/s, against 72.9 through
+// hash_mfma_kernel, which stages the keys through LDS and packs ids generically).
+template <int D, int S, int P> constexpr int hash8_groups() { return D <= 128 || S * P / 2 <= 8 ? S : S / 2; }
+template <int D> constexpr int hash8_threads() { return D <= 128 ? kHash8Threads : 512; }
+
 template <int D, int S, int P>
-__global__ __launch_bounds__(kHash8Threads) void hash_mfma8_kernel(HashArgs a, const uint4 *wfrag) {
+__global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs a, const uint4 *wfrag) {
     static_assert(P == 8 || P == 4, "one-byte ids of 8 planes, or of 4 (a block's eight nibbles are spread over two words)");
     constexpr int KS = D / 16;                 // MFMA k-steps
     constexpr int BPG = P / 2;                 // 32-column blocks per position group of 16 ids
-    constexpr int NCB = BPG * S;               // 32-column blocks of a chunk (S position groups)
-    constexpr int NW = kHash8Threads / 64;
+    constexpr int NG = hash8_groups<D, S, P>();
+    constexpr int NCB = BPG * NG;              // 32-column blocks of the workgroup
+    constexpr int NT = hash8_threads<D>(), NW = NT / 64;
     extern __shared__ uint32_t smem[];
     uint4 *wl = (uint4 *)smem;                         // [NCB][KS][64 lanes] A fragments
     uint32_t *bits = smem + NCB * KS * 64 * 4;         // [NW waves][64 keys][4 words]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int chunk = blockIdx.y % a.n_chunks, h = blockIdx.y / a.n_chunks, b = blockIdx.z;
+    const int part = blockIdx.y % (S / NG), hc = blockIdx.y / (S / NG);
+    const int chunk = hc % a.n_chunks, h = hc / a.n_chunks, b = blockIdx.z;
+    const int sub0 = part * NG;                        // the workgroup's first position group
     const int count = a.row_count[b];
     const int begin = a.row_begin[b];
     const int first_table = chunk * 64;
     const int ntab = min(64, a.L - first_table);
 
-    // ---- W slab -> LDS
-    {
-        const uint4 *src = wfrag + (int64_t)blockIdx.y * NCB * KS * 64;
-        constexpr int N = NCB * KS * 64;
-        if constexpr (N % kHash8Threads == 0) {
-            constexpr int PER = N / kHash8Threads, NB = PER < 8 ? PER : 8;
-            static_assert(PER % NB == 0, "whole batches of copies per thread");
-#pragma unroll 1
-            for (int u0 = 0; u0 < PER; u0 += NB) {
-                uint4 v[NB];
-#pragma unroll
-                for (int u = 0; u < NB; ++u) v[u] = src[tid + (u0 + u) * kHash8Threads];
-#pragma unroll
-                for (int u = 0; u < NB; ++u) wl[tid + (u0 + u) * kHash8Threads] = v[u];
-            }
-        } else {
-            for (int i = tid; i < N; i += kHash8Threads) wl[i] = src[i];
-        }
-    }
+    fragments_to_lds<NCB * KS * 64, NT>(wl, wfrag + (int64_t)blockIdx.y * NCB * KS * 64, tid);
     __syncthreads();
 
     uint32_t *mybits = bits + wave * 256;
@@ -628,10 +642,10 @@ __global__ __launch_bounds__(kHash8Threads) void hash_mfma8_kernel(HashArgs a, c
         const int r0 = blk * 64;
         const int64_t prow = key_row(r0 + lane);        // the key this lane packs
         const int rot = (begin + r0 + lane) & 15;
-        uint4 done[S > 1 ? S - 1 : 1];                  // the key's position groups before the last, kept until the row is whole
+        uint4 done[NG > 1 ? NG - 1 : 1];                // the key's position groups before the last, kept until the row is whole
 #pragma unroll 1
         for (int p = 0; p < NCB; ++p) {
-            const int sub = p / BPG, q = p % BPG;
+            const int sl = p / BPG, sub = sub0 + sl, q = p % BPG;
             const uint4 *af = wl + (p * KS) * 64 + lane;
             floatx16_t acc0, acc1;
 #pragma unroll
@@ -675,16 +689,16 @@ __global__ __launch_bounds__(kHash8Threads) void hash_mfma8_kernel(HashArgs a, c
                 o.y = __builtin_amdgcn_alignbyte(x2, x1, sh);
                 o.z = __builtin_amdgcn_alignbyte(x3, x2, sh);
                 o.w = __builtin_amdgcn_alignbyte(x0, x3, sh);
-                // the four groups of a key go out together: 64 adjacent bytes, written back as one
-                // whole line instead of four partial ones a quarter of the block apart
-                if (S > 1 && sub == 0) done[0] = o;
-                else if (S > 2 && sub == 1) done[S > 2 ? 1 : 0] = o;
-                else if (S > 2 && sub == 2) done[S > 2 ? 2 : 0] = o;
+                // the groups of a key go out together: 64 adjacent bytes (four groups), written back
+                // as one whole line instead of four partial ones a quarter of the block apart
+                if (NG > 1 && sl == 0) done[0] = o;
+                else if (NG > 2 && sl == 1) done[NG > 2 ? 1 : 0] = o;
+                else if (NG > 2 && sl == 2) done[NG > 2 ? 2 : 0] = o;
                 else if (prow >= 0) {
-                    uint4 *dst = (uint4 *)(Cb + prow * (int64_t)a.Lpad + first_table);
+                    uint4 *dst = (uint4 *)(Cb + prow * (int64_t)a.Lpad + first_table) + sub0;
 #pragma unroll
-                    for (int i = 0; i + 1 < S; ++i) dst[i] = done[i];
-                    dst[S - 1] = o;
+                    for (int i = 0; i + 1 < NG; ++i) dst[i] = done[i];
+                    dst[NG - 1] = o;
                 }
             }
         }
@@ -693,9 +707,9 @@ __global__ __launch_bounds__(kHash8Threads) void hash_mfma8_kernel(HashArgs a, c
 }
 
 // ---------------------------------------------------------------------------------------
-// The same structure for 10-plane tables with packed ids (groups of 16 S tables, S = 1 or 2,
-// d <= 128): a workgroup keeps the W slab of one group (S x 160 columns = 5 S 32-column blocks)
-// in LDS as MFMA fragments; every wavefront works on 64-key blocks of its own.
+// The same structure for 10-plane tables with packed ids (groups of 16 S tables, S = 1 or 2): a
+// workgroup keeps the W slab of one group (S x 160 columns = 5 S 32-column blocks; one string's
+// 5 at d = 256) in LDS as MFMA fragments; every wavefront works on 64-key blocks of its own.
 //
 // Column order.  String `sub` (< S) of a token's group holds, before its rotation by the token
 // position, the ids of tables sub, sub + S, .., sub + 15 S in bits [10 j, 10 j + 10): 160 bits =
@@ -731,26 +745,28 @@ __global__ __launch_bounds__(256) void hash_wfrag10_kernel(HashArgs a, uint4 *wf
     }
 }
 
+// (d = 256: one string per workgroup, 80 KB of fragments)
+template <int D, int S> constexpr int hash10_strings() { return D <= 128 ? S : 1; }
+
 template <int D, int S>
-__global__ __launch_bounds__(kHash8Threads) void hash_mfma10_kernel(HashArgs a, const uint4 *wfrag) {
+__global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArgs a, const uint4 *wfrag) {
     constexpr int KS = D / 16;                 // MFMA k-steps
-    constexpr int NCB = 5 * S;                 // 32-column blocks of a group
+    constexpr int NS = hash10_strings<D, S>(); // strings of the workgroup
+    constexpr int NCB = 5 * NS;                // its 32-column blocks
     constexpr int GT = 16 * S;                 // tables of a group
-    constexpr int NW = kHash8Threads / 64;
+    constexpr int NT = hash8_threads<D>(), NW = NT / 64;
     extern __shared__ uint32_t smem[];
     uint4 *wl = (uint4 *)smem;                         // [NCB][KS][64 lanes] A fragments
     uint32_t *bits = smem + NCB * KS * 64 * 4;         // [NW waves][64 keys][5 words]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int grp = blockIdx.y % a.n_chunks, h = blockIdx.y / a.n_chunks, b = blockIdx.z;
+    const int sub0 = blockIdx.y % (S / NS), hc = blockIdx.y / (S / NS);   // (S / NS > 1: the workgroup's string)
+    const int grp = hc % a.n_chunks, h = hc / a.n_chunks, b = blockIdx.z;
     const int count = a.row_count[b];
     const int begin = a.row_begin[b];
     const int ntab = max(0, min(GT, a.L - grp * GT));
 
-    {
-        const uint4 *src = wfrag + (int64_t)blockIdx.y * NCB * KS * 64;
-        for (int i = tid; i < NCB * KS * 64; i += kHash8Threads) wl[i] = src[i];
-    }
+    fragments_to_lds<NCB * KS * 64, NT>(wl, wfrag + (int64_t)blockIdx.y * NCB * KS * 64, tid);
     __syncthreads();
 
     uint32_t *mybits = bits + wave * 320;
@@ -793,7 +809,7 @@ __global__ __launch_bounds__(kHash8Threads) void hash_mfma10_kernel(HashArgs a, 
         uint32_t tail0 = 0;
 #pragma unroll 1
         for (int p = 0; p < NCB; ++p) {
-            const int sub = p >= 5 ? 1 : 0, q = p - 5 * sub;
+            const int sl = p >= 5 ? 1 : 0, sub = sub0 + sl, q = p - 5 * sl;
             const uint4 *af = wl + (p * KS) * 64 + lane;
             floatx16_t acc0, acc1;
 #pragma unroll
@@ -826,20 +842,20 @@ __global__ __launch_bounds__(kHash8Threads) void hash_mfma10_kernel(HashArgs a, 
                 o.z = __builtin_amdgcn_alignbit(x3, x2, sh);
                 o.w = __builtin_amdgcn_alignbit(x4, x3, sh);
                 const uint32_t ot = __builtin_amdgcn_alignbit(x0, x4, sh);
-                if (S == 2 && sub == 0) {
+                if (NS == 2 && sl == 0) {
                     head0 = o;
                     tail0 = ot;
                 } else if (prow >= 0) {
                     // the strings of the key's group together: 16 S adjacent bytes of the tile's
                     // main rows and 4 S of its tail rows
                     uint4 *dst = (uint4 *)(Cb + packed_main_row(prow, grp, a.Lpad, GT));
-                    if (S == 2) {
+                    if (NS == 2) {
                         dst[0] = head0;
                         dst[1] = o;
                         *(uint2 *)(Cb + packed_tail_row(prow, grp, a.Lpad, GT)) = make_uint2(tail0, ot);
                     } else {
-                        dst[0] = o;
-                        *(uint32_t *)(Cb + packed_tail_row(prow, grp, a.Lpad, GT)) = ot;
+                        dst[sub] = o;
+                        ((uint32_t *)(Cb + packed_tail_row(prow, grp, a.Lpad, GT)))[sub] = ot;
                     }
                 }
             }
@@ -867,41 +883,47 @@ static int launch_rows(const HashArgs &a, int Hkv, int batch, int max_rows, hipS
 
 // dynamic LDS of hash_mfma8_kernel: the W slab as fragments, one id-word row per key of every wavefront's block
 template <int D, int S, int P> constexpr size_t hash8_lds() {
-    return (size_t)(P / 2 * S) * (D / 16) * 64 * 16 + (size_t)(kHash8Threads / 64) * 64 * 16;
+    return (size_t)(P / 2 * hash8_groups<D, S, P>()) * (D / 16) * 64 * 16 + (size_t)hash8_threads<D>() * 16;
 }
 
 template <int D, int S> constexpr size_t hash10_lds() {
-    return (size_t)(5 * S) * (D / 16) * 64 * 16 + (size_t)(kHash8Threads / 64) * 64 * 20;
+    return (size_t)(5 * hash10_strings<D, S>()) * (D / 16) * 64 * 16 + (size_t)hash8_threads<D>() * 20;
 }
 
 // once per context that uses a fast hash: more than 64 KB of dynamic LDS has to be allowed
 // before the first launch
-int hash_prepare(int d) {
+template <int D> static int hash_prepare_d() {
     hipError_t e = hipSuccess;
-    if (d == 128) e = hipFuncSetAttribute((const void *)hash_mfma10_kernel<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hash10_lds<128, 2>());
-    if (e != hipSuccess) return SOCKET_EHIP;
-    if (d == 64) e = hipFuncSetAttribute((const void *)hash_mfma8_kernel<64, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hash8_lds<64, 4, 8>());
-    if (d == 128) e = hipFuncSetAttribute((const void *)hash_mfma8_kernel<128, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hash8_lds<128, 4, 8>());
-    if (e == hipSuccess && d == 128) e = hipFuncSetAttribute((const void *)hash_mfma8_kernel<128, 2, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hash8_lds<128, 2, 8>());
-    if (e == hipSuccess && d == 128) e = hipFuncSetAttribute((const void *)hash_mfma8_kernel<128, 4, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hash8_lds<128, 4, 4>());
+    auto allow = [&](auto kernel, size_t lds) {
+        if (e == hipSuccess && lds > 64 * 1024)
+            e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    };
+    allow(hash_mfma8_kernel<D, 4, 8>, hash8_lds<D, 4, 8>());
+    allow(hash_mfma8_kernel<D, 2, 8>, hash8_lds<D, 2, 8>());
+    allow(hash_mfma8_kernel<D, 1, 8>, hash8_lds<D, 1, 8>());
+    allow(hash_mfma8_kernel<D, 4, 4>, hash8_lds<D, 4, 4>());
+    allow(hash_mfma8_kernel<D, 2, 4>, hash8_lds<D, 2, 4>());
+    allow(hash_mfma10_kernel<D, 2>, hash10_lds<D, 2>());
+    allow(hash_mfma10_kernel<D, 1>, hash10_lds<D, 1>());
     return e == hipSuccess ? SOCKET_OK : SOCKET_EHIP;
 }
+int hash_prepare(int d) { return d == 64 ? hash_prepare_d<64>() : d == 128 ? hash_prepare_d<128>() : hash_prepare_d<256>(); }
 
 template <int D, int S, int P>
 static int launch_mfma8(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_rows, hipStream_t st) {
-    constexpr int NW = kHash8Threads / 64;
+    constexpr int NT = hash8_threads<D>(), NW = NT / 64, PARTS = S / hash8_groups<D, S, P>();
     a.tables_per_chunk = 16 * S;
     a.n_chunks = S == 4 ? (a.L + 63) / 64 : 1;
     // W as MFMA fragments, once per call
     hipLaunchKernelGGL((hash_wfrag_kernel<D, S, P>), dim3(P / 2 * S, Hkv * a.n_chunks), dim3(256), 0, st, a, wfrag);
     // one workgroup per CU (the W slab fills most of its LDS); each wavefront takes 64-key blocks
-    int per = 256 / (Hkv * a.n_chunks * batch);
+    int per = 256 / (Hkv * a.n_chunks * PARTS * batch);
     const int nblocks = (max_rows + 63) / 64;
     if (per > (nblocks + NW - 1) / NW) per = (nblocks + NW - 1) / NW;
     if (per < 1) per = 1;
-    dim3 grid(per, Hkv * a.n_chunks, batch);
+    dim3 grid(per, Hkv * a.n_chunks * PARTS, batch);
     constexpr size_t lds = hash8_lds<D, S, P>();
-    hipLaunchKernelGGL((hash_mfma8_kernel<D, S, P>), grid, dim3(kHash8Threads), lds, st, a, (const uint4 *)wfrag);
+    hipLaunchKernelGGL((hash_mfma8_kernel<D, S, P>), grid, dim3(NT), lds, st, a, (const uint4 *)wfrag);
     return SOCKET_OK;
 }
 template <int D, int P>
@@ -918,17 +940,17 @@ static int launch_mfma8(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_ro
 
 template <int D, int S>
 static int launch_mfma10(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_rows, hipStream_t st) {
-    constexpr int NW = kHash8Threads / 64;
+    constexpr int NT = hash8_threads<D>(), NW = NT / 64, PARTS = S / hash10_strings<D, S>();
     a.tables_per_chunk = 16 * S;
     a.n_chunks = a.Lpad / (16 * S);            // groups, padding groups included (their ids are zero)
     hipLaunchKernelGGL((hash_wfrag10_kernel<D, S>), dim3(5 * S, Hkv * a.n_chunks), dim3(256), 0, st, a, wfrag);
-    int per = 256 / (Hkv * a.n_chunks * batch);
+    int per = 256 / (Hkv * a.n_chunks * PARTS * batch);
     const int nblocks = (max_rows + 63) / 64;
     if (per > (nblocks + NW - 1) / NW) per = (nblocks + NW - 1) / NW;
     if (per < 1) per = 1;
-    dim3 grid(per, Hkv * a.n_chunks, batch);
+    dim3 grid(per, Hkv * a.n_chunks * PARTS, batch);
     constexpr size_t lds = hash10_lds<D, S>();
-    hipLaunchKernelGGL((hash_mfma10_kernel<D, S>), grid, dim3(kHash8Threads), lds, st, a, (const uint4 *)wfrag);
+    hipLaunchKernelGGL((hash_mfma10_kernel<D, S>), grid, dim3(NT), lds, st, a, (const uint4 *)wfrag);
     return SOCKET_OK;
 }
 template <int D>
@@ -1033,8 +1055,8 @@ int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int
     } else if (max_rows < 64) {
         rc = launch_f32<uint16_t>(a, g.Hkv, batch, max_rows, st);
     } else {
-        const bool fast8 = ctx->wfrag != nullptr && (g.P == 8 || g.P == 4);   // one-byte ids of 8 or 4 planes, d <= 128
-        const bool fast10 = ctx->wfrag != nullptr && g.P == 10;    // packed ids in groups of 32 tables, d <= 128
+        const bool fast8 = ctx->wfrag != nullptr && (g.P == 8 || g.P == 4);   // one-byte ids of 8 or 4 planes
+        const bool fast10 = ctx->wfrag != nullptr && g.P == 10;    // packed ids in groups of 32 or 16 tables
         switch (g.d) {
             case 64: rc = fast8 ? launch_mfma8<64>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
                           : fast10 ? launch_mfma10<64>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
@@ -1042,7 +1064,9 @@ int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int
             case 128: rc = fast8 ? launch_mfma8<128>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
                            : fast10 ? launch_mfma10<128>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
                                     : launch_mfma<128>(a, g.Hkv, batch, max_rows, st); break;
-            case 256: rc = launch_mfma<256>(a, g.Hkv, batch, max_rows, st); break;
+            case 256: rc = fast8 ? launch_mfma8<256>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
+                           : fast10 ? launch_mfma10<256>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
+                                    : launch_mfma<256>(a, g.Hkv, batch, max_rows, st); break;
             default: return SOCKET_EUNSUPPORTED;
         }
     }

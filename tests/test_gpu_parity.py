@@ -149,6 +149,31 @@ def test_hash_keys_unaligned_row_ranges_through_the_mfma_kernels():
         ctx.close()
 
 
+@pytest.mark.parametrize("L,P", [(64, 8), (100, 8), (24, 8), (9, 8), (64, 4), (65, 4), (31, 4), (7, 4), (60, 10), (20, 10), (11, 10)])
+def test_hash_keys_wide_heads(L, P):
+    """d = 256: a chunk's position groups (strings, for packed ids) are shared out to two workgroups;
+    ragged runs from odd positions, rows beyond them untouched, paged blocks in random order."""
+    _need_gpu()
+    layer = small_layer(seed=16, B=2, Hq=4, Hkv=2, d=256, n=768, L=L, P=P, k=16)
+    begins, counts = [5, 77], [700, 131]
+    ctx = hz.make_ctx(layer)
+    codes = run_hash(ctx, layer, begins, counts, 700)
+    check_codes(layer, codes, lambda b: (begins[b], counts[b]))
+    raw = hz.rows_from_device(codes, L, P)
+    for b in range(2):
+        assert (raw[b, :, :begins[b]] == hz.fill_id(P)).all() and (raw[b, :, begins[b] + counts[b]:] == hz.fill_id(P)).all()
+    ctx.close()
+    table, num_blocks = wl.make_block_table(3, [768, 768], 48)
+    ctx = hz.make_ctx(layer, page=48, max_blocks=table.shape[1], num_blocks=num_blocks)
+    paged = hz.new_codes((num_blocks, 2), 48, L, P, fill=0x55)
+    Kp = wl.to_paged(layer.K, layer.seq_len, table, num_blocks, 48)
+    ctx.hash_keys(hz.dev(Kp, layer.kv_dtype), hz.dev(layer.W, layer.kv_dtype), hz.i32(begins), hz.i32(counts), 2, 700, paged,
+                  block_table=hz.i32(table))
+    flat = paged[torch.from_numpy(table.astype(np.int64)).cuda()].transpose(1, 2).reshape(codes.shape)
+    assert torch.equal(flat, codes)
+    ctx.close()
+
+
 @pytest.mark.parametrize("d,L,P", [(64, 32, 8), (128, 32, 8), (128, 60, 10), (128, 11, 10), (128, 16, 4), (128, 100, 8),
                                    (128, 40, 12), (256, 64, 8), (256, 16, 10), (256, 13, 7), (256, 40, 10)])
 def test_hash_keys_fp32_sums_do_not_depend_on_the_run(d, L, P):
