@@ -242,7 +242,28 @@ __device__ __forceinline__ void topk_resolve_body(const TopkArgs &a, int bh, uin
             chosen[1] = thr[4];
         }
         __syncthreads();
-        int level = a.adaptive ? 0 : 2;
+        int level = 2;
+        if (a.adaptive) {                         // the digits that all candidates share: nothing to refine there
+            if (tid < 2) res[tid] = tid ? 0u : 0xffffffffu;
+            __syncthreads();
+            uint32_t kmin = 0xffffffffu, kmax = 0;
+            for (uint32_t i = tid; i < n_cand; i += kTopkThreads) {
+                const uint32_t key = ckey[i];
+                kmin = min(kmin, key);
+                kmax = max(kmax, key);
+            }
+            atomicMin(&res[0], kmin);
+            atomicMax(&res[1], kmax);
+            __syncthreads();
+            kmin = res[0];
+            kmax = res[1];
+            level = 0;
+            while (level < 3 && refine_digit(level, kmin, 0) == refine_digit(level, kmax, 0)) {
+                if (tid == 0) chosen[level] = refine_digit(level, kmin, 0);
+                ++level;
+            }
+            __syncthreads();
+        }
         while (need > 0 && need < remaining && level < kLevels) {
             for (int i = tid; i < padded_size<kRefineBins, RPER>(); i += kTopkThreads) h[i] = 0;
             if (tid < 4) res[tid] = 0;

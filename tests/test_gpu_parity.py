@@ -381,6 +381,33 @@ def test_topk_long_row_uses_several_bitmap_passes():
     ctx.close()
 
 
+@pytest.mark.parametrize("n", [16, 1024, 4096, 4096 + 16, 32768 + 48, 520 * 4096 + 16])
+def test_topk_rows_of_one_to_many_regions(n):
+    """The select bins a row by 512 of its scores, sweeps it in regions of 4096 and writes the index
+    row region by region: exact on spread scores, forced (+inf) ones, few distinct values (more tied
+    candidates than a workgroup ranks), scores the sample says little about, absent ones."""
+    _need_gpu()
+    rng = np.random.default_rng(n)
+    s = np.empty((1, 6, n), dtype=np.float32)
+    s[0, 0] = 0.25 + 0.02 * rng.standard_normal(n)
+    s[0, 1] = s[0, 0]
+    s[0, 1, :5] = np.inf                                # sink and window tokens
+    s[0, 1, n - n // 4:] = np.inf
+    s[0, 2] = rng.integers(0, 300, size=n) * 0.25       # collision counts
+    s[0, 3] = 1.5                                       # all equal
+    s[0, 4] = rng.standard_normal(n) * np.exp(8 * rng.standard_normal(n))
+    s[0, 4, ::7] = -np.inf                              # absent blocks
+    s[0, 4, 3::11] = np.nan
+    s[0, 5] = np.where(rng.random(n) < 0.5, np.inf, 0.125 * rng.integers(-1, 2, size=n))
+    want = np.where(np.isnan(s), -np.inf, s)
+    max_k = min(n, 3000)
+    ctx = sk.Context(sk.make_params(128, 6, 6, 64, 8, sk.BF16, 1, n, max_k))
+    for length, k in ((n, 1), (n, max_k), (n - 3, max_k // 2), (n // 2 + 1, max_k // 3 + 1), (5, 7), (0, 3)):
+        idx, nsel = run_topk(ctx, s, [length], [k], 1, 6, max_k)
+        check_topk(idx, nsel, want, [length], [k])
+    ctx.close()
+
+
 # ------------------------------------------------------------------ a5: socket_sparse_decode
 
 def run_decode(ctx, layer, idx, nsel, out_dtype=torch.float32, scale=1.0):
