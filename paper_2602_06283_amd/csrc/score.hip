@@ -1616,7 +1616,16 @@ __global__ __launch_bounds__(kScoreThreads, (MODE == kDirect && S == 4 && PAGED)
                 float4 *dst = (float4 *)tbl;
                 const int n4 = (int)(a.table_words >> 2);
                 constexpr int B8 = 8;                // independent loads in flight per thread
-                for (int i0 = tid; i0 < n4; i0 += B8 * kScoreThreads) {
+                int i0 = tid;
+                if constexpr (!BATCHED)              // whole batches (a 64 KB table is one): no load under a condition (128K keys: 15.0 -> 14.5 us; where the table changes inside a run it measured slower)
+                    for (; i0 + (B8 - 1) * kScoreThreads < n4; i0 += B8 * kScoreThreads) {
+                        f32x4_t t[B8];
+#pragma unroll
+                        for (int j = 0; j < B8; ++j) t[j] = ((const f32x4_t *)src)[i0 + j * kScoreThreads];
+#pragma unroll
+                        for (int j = 0; j < B8; ++j) ((f32x4_t *)dst)[i0 + j * kScoreThreads] = t[j];
+                    }
+                for (; i0 < n4; i0 += B8 * kScoreThreads) {
                     float4 t[B8];
 #pragma unroll
                     for (int j = 0; j < B8; ++j) {
@@ -2215,9 +2224,15 @@ int launch_score_keys(socket_ctx *ctx, const void *codes, const float *vnorm,
     }
     // Two resident workgroups per CU over the whole launch (fewer when there is less than one
     // unit per wavefront): each KV head's units are dealt out evenly to its workgroups.
+    // One per CU where the second would not pay for its table load:
+    //  - rows of 16 ids: registers allow no second one, a grid of two per CU runs in two rounds
+    //    (4 x 65536 keys, 8 heads 22.1 us, 16.8 with one);
+    //  - one sequence with less than two units per wavefront on two per CU (32768 keys, 8 heads
+    //    7.5 us, 7.0 with one; 49152 8.5 / 8.3; from 65536 on two are faster, 9.3 / 9.8).
     const int wg_keys = (kScoreThreads / 64) * kScoreU * (64 / g.S);
     int64_t nslot = ((int64_t)batch * g.max_n + wg_keys - 1) / wg_keys;
-    const int per_head = (256 * 1024 / kScoreThreads) / g.Hkv;
+    const bool one_per_cu = g.mode == kDirect && (g.S == 1 || (batch == 1 && nslot < 2 * (512 / g.Hkv)));
+    const int per_head = (one_per_cu ? 256 : 512) / g.Hkv;
     if (nslot > per_head) nslot = per_head;
     if (nslot < 1) nslot = 1;
     dim3 grid((unsigned)nslot, g.Hkv);
