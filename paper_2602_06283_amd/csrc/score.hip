@@ -2227,11 +2227,13 @@ int launch_score_keys(socket_ctx *ctx, const void *codes, const float *vnorm,
     // One per CU where the second would not pay for its table load:
     //  - rows of 16 ids: registers allow no second one, a grid of two per CU runs in two rounds
     //    (4 x 65536 keys, 8 heads 22.1 us, 16.8 with one);
+    //  - two 64-table chunks of 256 buckets: LDS holds one workgroup (4 x 65536 keys, 8 heads, 128
+    //    tables 70.4 us in two rounds, 54.6 in one; 32768 keys 16.7 / 11.6);
     //  - one sequence with less than two units per wavefront on two per CU (32768 keys, 8 heads
     //    7.5 us, 7.0 with one; 49152 8.5 / 8.3; from 65536 on two are faster, 9.3 / 9.8).
     const int wg_keys = (kScoreThreads / 64) * kScoreU * (64 / g.S);
     int64_t nslot = ((int64_t)batch * g.max_n + wg_keys - 1) / wg_keys;
-    const bool one_per_cu = g.mode == kDirect && (g.S == 1 || (batch == 1 && nslot < 2 * (512 / g.Hkv)));
+    const bool one_per_cu = g.mode == kDirect && (g.S == 1 || g.table_words * 4 > 72 * 1024 || (batch == 1 && nslot < 2 * (512 / g.Hkv)));
     const int per_head = (one_per_cu ? 256 : 512) / g.Hkv;
     if (nslot > per_head) nslot = per_head;
     if (nslot < 1) nslot = 1;
