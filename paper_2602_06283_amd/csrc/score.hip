@@ -2224,16 +2224,27 @@ int launch_score_keys(socket_ctx *ctx, const void *codes, const float *vnorm,
     }
     // Two resident workgroups per CU over the whole launch (fewer when there is less than one
     // unit per wavefront): each KV head's units are dealt out evenly to its workgroups.
-    // One per CU where the second would not pay for its table load:
+    // One per CU where the second would not pay for its table load (times one / two, id rows and
+    // scores of 8 heads unless said; the rule goes by the context's capacity, the lengths are on
+    // the device: a context that holds less than it was made for keeps the grid of its capacity):
     //  - rows of 16 ids: registers allow no second one, a grid of two per CU runs in two rounds
-    //    (4 x 65536 keys, 8 heads 22.1 us, 16.8 with one);
-    //  - two 64-table chunks of 256 buckets: LDS holds one workgroup (4 x 65536 keys, 8 heads, 128
-    //    tables 70.4 us in two rounds, 54.6 in one; 32768 keys 16.7 / 11.6);
-    //  - one sequence with less than two units per wavefront on two per CU (32768 keys, 8 heads
-    //    7.5 us, 7.0 with one; 49152 8.5 / 8.3; from 65536 on two are faster, 9.3 / 9.8).
+    //    (4 x 65536 keys 16.8 / 22.1 us);
+    //  - two 64-table chunks of 256 buckets: LDS holds one workgroup (128 tables: 4 x 65536 keys
+    //    52.3 / 67.7, 30000 keys 9.9 / 13.3).  Not from 20 heads on when the ids exceed the 256 MB
+    //    cache: the few workgroups of a head then fall behind (32 heads: 131072 keys 124.6 / 109.0,
+    //    2 x 65536 112.2 / 104.2; 65536 keys 56.7 / 55.8, 32768 29.6 / 33.7; 16 heads, 131072 keys
+    //    54.5 / 55.4);
+    //  - one sequence of one chunk of 256 buckets, up to three units a wavefront (64 tables: 49152
+    //    keys 7.4 / 8.2, 32768 5.5 / 5.7; 54000 8.6 / 8.2).  A single head: two (262144 keys 6.3 /
+    //    5.9).  Smaller tables load too fast to be worth it (64 tables of 6 planes, 50000 keys
+    //    7.8 / 6.9; of 5, 32768 keys 5.1 / 4.9);
+    //  - one sequence of several chunks, between two and three units a wavefront: two per CU then
+    //    leave most of the second turn idle (100 tables of 6 planes, 40960 keys 11.5 / 14.0).
     const int wg_keys = (kScoreThreads / 64) * kScoreU * (64 / g.S);
     int64_t nslot = ((int64_t)batch * g.max_n + wg_keys - 1) / wg_keys;
-    const bool one_per_cu = g.mode == kDirect && (g.S == 1 || g.table_words * 4 > 72 * 1024 || (batch == 1 && nslot < 2 * (512 / g.Hkv)));
+    const bool single = batch == 1 && nslot <= (g.Hkv > 1 ? 768 : 512) / g.Hkv + 1 && (g.R == 256 || (g.rounds > 1 && nslot > 512 / g.Hkv));
+    const bool wide = g.table_words * 4 > 72 * 1024 && (g.Hkv <= 16 || (int64_t)batch * g.Hkv * g.max_n * g.Lpad < (224ll << 20));
+    const bool one_per_cu = g.mode == kDirect && (g.S == 1 || wide || single);
     const int per_head = (one_per_cu ? 256 : 512) / g.Hkv;
     if (nslot > per_head) nslot = per_head;
     if (nslot < 1) nslot = 1;
