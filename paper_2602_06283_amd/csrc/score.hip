@@ -1617,7 +1617,7 @@ __global__ __launch_bounds__(kScoreThreads, (MODE == kDirect && S == 4 && PAGED)
                 const int n4 = (int)(a.table_words >> 2);
                 constexpr int B8 = 8;                // independent loads in flight per thread
                 int i0 = tid;
-                if constexpr (!BATCHED)              // whole batches (a 64 KB table is one): no load under a condition (128K keys: 15.0 -> 14.5 us; where the table changes inside a run it measured slower)
+                if (!BATCHED && S == 4 && gridDim.y <= 16)   // whole batches (a 64 KB table is one): no load under a condition (8 heads: 131072 keys 13.6 -> 13.4 us, 32768 of a capacity of 131072 6.9 -> 6.5; 32 heads measured slower, 26.8 -> 27.9 at 65536 keys, rows of 32 ids too, and so did a table that changes inside a run)
                     for (; i0 + (B8 - 1) * kScoreThreads < n4; i0 += B8 * kScoreThreads) {
                         f32x4_t t[B8];
 #pragma unroll
