@@ -2235,7 +2235,7 @@ int launch_score_keys(socket_ctx *ctx, const void *codes, const float *vnorm,
     //    2 x 65536 112.2 / 104.2; 65536 keys 56.7 / 55.8, 32768 29.6 / 33.7; 16 heads, 131072 keys
     //    54.5 / 55.4);
     //  - one sequence of one chunk of 256 buckets, up to three units a wavefront (64 tables: 49152
-    //    keys 7.4 / 8.2, 32768 5.5 / 5.7; 54000 8.6 / 8.2).  A single head: two (262144 keys 6.3 /
+    //    keys 7.4 / 8.2, 32768 5.5 / 5.7; 56000 8.6 / 8.1).  A single head: two (262144 keys 6.3 /
     //    5.9).  Smaller tables load too fast to be worth it (64 tables of 6 planes, 50000 keys
     //    7.8 / 6.9; of 5, 32768 keys 5.1 / 4.9);
     //  - one sequence of several chunks, between two and three units a wavefront: two per CU then

@@ -246,6 +246,7 @@ template <> struct Row8<uint16_t> {
     __device__ __forceinline__ void load(const void *p) { raw = *(const u32x4_t *)p; }
     __device__ __forceinline__ void zero() { raw = 0; }
     __device__ __forceinline__ void store(void *p) const { *(u32x4_t *)p = raw; }
+    __device__ __forceinline__ void settle() const { asm volatile("" ::"v"(raw)); }   // (a use on every path: its load is waited for here)
     __device__ __forceinline__ void get(float *f) const {
         const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
@@ -260,6 +261,7 @@ template <> struct Row8<float> {
     __device__ __forceinline__ void load(const void *p) { a = ((const f32x4_t *)p)[0]; b = ((const f32x4_t *)p)[1]; }
     __device__ __forceinline__ void zero() { a = 0.0f; b = 0.0f; }
     __device__ __forceinline__ void store(void *p) const { ((f32x4_t *)p)[0] = a; ((f32x4_t *)p)[1] = b; }
+    __device__ __forceinline__ void settle() const { asm volatile("" ::"v"(a), "v"(b)); }
     __device__ __forceinline__ void get(float *f) const {
         f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
     }

@@ -225,6 +225,14 @@ __device__ __forceinline__ bool decode_body(const DecodeArgs &a, int split, int 
             }
         }
     }
+    // (d = 256 reuses the queries' registers for value rows; to the wavefronts that skipped the
+    // stores the loads above would still look pending there, and the value rows would wait for the
+    // whole K rows: 20000 bf16 rows, k = 1024, 8 heads, G = 2 10.8 us, 10.2 with the loads settled
+    // here; G = 4 11.3 / 10.8.  Narrower rows lose 1-2 % by it.)
+    if (SRC == kRowsIdx && D == 256) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) qr[g].settle();
+    }
     // kRowsSweep: the K/V row of this thread's entry (paged: a block-table lookup, in flight while
     // the candidates are ranked)
     const int n_first = count > sub_i ? (count - sub_i + sub_n - 1) / sub_n : 0;   // entries of this split in its first region
