@@ -15,6 +15,7 @@
 //                      thread per projection column, sign bits gathered with a wavefront ballot.
 // The last three end in pack_codes(), which cuts the bit matrix into P-bit bucket ids and writes
 // them in the rotated order the scoring kernel reads.
+#include <algorithm>
 #include <type_traits>
 
 #include "socket_internal.h"
@@ -36,6 +37,38 @@ struct HashArgs {
     int rows_per_wg;
     int tables_per_chunk;  // tables one workgroup covers (mfma kernel)
     int n_chunks;
+    int batch, max_rows;   // sequences, and a bound on every row_count
+    int group;             // sequences whose runs a workgroup shares out as one (SeqUnits), at most 64
+};
+
+// The runs of keys of the `group` sequences of blockIdx.z as one row of units of 2^SHIFT keys,
+// sequence after sequence: what a wavefront has to know to find the keys of a unit.  Lane i holds
+// sequence i's run and the units up to its end.  Workgroups that share units out over this row do
+// equal work whatever the lengths are; shared out sequence by sequence, one long run in a batch of
+// short ones was left to the few workgroups of its own sequence (16384 keys among 15 x 100, 8 heads:
+// bf16, d = 256, 64 tables of 8 planes 323 us, 47 now; fp32, d = 64, 60 tables of 10 690 / 153; in a
+// batch of equal lengths the look-up costs 1 to 2 us).
+template <int SHIFT> struct SeqUnits {
+    int count, begin, group;
+    uint32_t end;
+    __device__ __forceinline__ explicit SeqUnits(const HashArgs &a) {
+        const int i = threadIdx.x & 63, b = blockIdx.z * a.group + i;
+        const bool mine = i < a.group && b < a.batch;
+        count = mine ? min(a.row_count[b], a.max_rows) : 0;
+        begin = mine ? a.row_begin[b] : 0;
+        group = a.group;
+        end = wave_incl_scan((uint32_t)(max(count, 0) + (1 << SHIFT) - 1) >> SHIFT);
+    }
+    __device__ __forceinline__ int total() const { return __builtin_amdgcn_readlane((int)end, 63); }
+    // sequence, run and first row of `unit` < total()
+    __device__ __forceinline__ void find(int unit, int *b, int *b_count, int *b_begin, int *r0) const {
+        const int s = __popcll(__ballot(end <= (uint32_t)unit));
+        const int before = s > 0 ? __builtin_amdgcn_readlane((int)end, s - 1) : 0;
+        *b = blockIdx.z * group + s;
+        *b_count = __builtin_amdgcn_readlane(count, s);
+        *b_begin = __builtin_amdgcn_readlane(begin, s);
+        *r0 = (unit - before) << SHIFT;
+    }
 };
 
 // Cut `nrows` bit rows (LDS, stride `stride` words, bit j of a row = sign bit of the
@@ -208,11 +241,13 @@ __global__ __launch_bounds__(256) void hash_rows_kernel(HashArgs a) {
 // d = 128, and 10-plane groups (320 columns) fill ten wavefronts instead of leaving three of
 // eight idle.
 // ---------------------------------------------------------------------------------------
-constexpr int kF32Tile = 32;               // keys per tile
+constexpr int kF32TileShift = 5, kF32Tile = 1 << kF32TileShift;   // keys per tile
 constexpr int kF32BitWords = 17;           // words per bit row: 512 columns and a pad
 template <int D> constexpr int f32_min_threads() { return D == 64 ? 256 : 512; }   // (fewer would stage more pieces a thread than registers allow)
 
-template <typename T, int D>
+// SHARE: a workgroup's tiles are an equal share of those of a group of sequences (SeqUnits), else a
+// piece of one sequence
+template <typename T, int D, bool SHARE>
 __global__ __launch_bounds__(D <= 128 ? 1024 : 512) void hash_f32_kernel(HashArgs a) {
     typedef typename std::conditional<sizeof(T) == 2, uint2, uint4>::type Quad;   // four channels as stored
     constexpr int KS = D / 2;                  // MFMA k-steps
@@ -227,12 +262,28 @@ __global__ __launch_bounds__(D <= 128 ? 1024 : 512) void hash_f32_kernel(HashArg
 
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, g = lane >> 5;
-    const int chunk = blockIdx.y % a.n_chunks, h = blockIdx.y / a.n_chunks, b = blockIdx.z;
-    const int count = a.row_count[b];
-    const int wg_r0 = blockIdx.x * a.rows_per_wg;
-    if (wg_r0 >= count) return;
-    const int wg_r1 = min(count, wg_r0 + a.rows_per_wg);
-    const int begin = a.row_begin[b];
+    const int chunk = blockIdx.y % a.n_chunks, h = blockIdx.y / a.n_chunks;
+    int b = blockIdx.z, count, begin;
+    int wg_r0, wg_r1, left = 0;                // rows of a sequence to do, tiles of later sequences after them
+    if constexpr (!SHARE) {
+        count = a.row_count[b];
+        wg_r0 = blockIdx.x * a.rows_per_wg;
+        if (wg_r0 >= count) return;
+        wg_r1 = min(count, wg_r0 + a.rows_per_wg);
+        begin = a.row_begin[b];
+    } else {
+        const SeqUnits<kF32TileShift> units(a);
+        const int total = units.total(), share = total / (int)gridDim.x, extra = total % (int)gridDim.x, x = blockIdx.x;
+        left = share + (x < extra);
+        if (left == 0) return;
+        units.find(x * share + min(x, extra), &b, &count, &begin, &wg_r0);
+    }
+    auto take = [&]() {                        // as many of the tiles left as sequence b has from wg_r0 on
+        const int tiles = min(left, (count - wg_r0 + TILE - 1) >> kF32TileShift);
+        wg_r1 = min(count, wg_r0 + (tiles << kF32TileShift));
+        left -= tiles;
+    };
+    if (SHARE) take();
     const int first_table = chunk * a.tables_per_chunk;
     const int ntab = max(0, min(a.tables_per_chunk, a.L - first_table));   // 0: a group of padding tables only
     const int ncols = ntab * a.P;
@@ -285,46 +336,56 @@ __global__ __launch_bounds__(D <= 128 ? 1024 : 512) void hash_f32_kernel(HashArg
     }
 
     const bool whole = a.n_chunks == 1 || (a.tables_per_chunk & 63) == 0;
-    commit(0);
-    __syncthreads();
-
-    int buf = 0, slot = 0;
-    for (int r0 = wg_r0; r0 < wg_r1; r0 += TILE) {
-        const bool more = r0 + TILE < wg_r1;
-        const int nslot = slot == 2 ? 0 : slot + 1;
-        if (more) fetch(r0 + TILE, nslot);
-        uint32_t *bt = bits + buf * (TILE * BW);
-        if (wave * 32 < ncols) {
-            floatx16_t acc;
+    int buf = 0, slot = 0;                     // (turn on over sequences: the same waits cover their first tiles)
+    for (;;) {
+        commit(buf);
+        __syncthreads();
+        for (int r0 = wg_r0; r0 < wg_r1; r0 += TILE) {
+            const bool more = r0 + TILE < wg_r1;
+            const int nslot = slot == 2 ? 0 : slot + 1;
+            if (more) fetch(r0 + TILE, nslot);
+            uint32_t *bt = bits + buf * (TILE * BW);
+            if (wave * 32 < ncols) {
+                floatx16_t acc;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-            const float4 *src = (const float4 *)(kt + (buf * TILE + n) * ROWW + g * (D / 2));
+                for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+                const float4 *src = (const float4 *)(kt + (buf * TILE + n) * ROWW + g * (D / 2));
 #pragma unroll
-            for (int s4 = 0; s4 < KS / 4; ++s4) {
-                const float4 kf = src[s4];
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4], kf.x, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4 + 1], kf.y, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4 + 2], kf.z, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4 + 3], kf.w, acc, 0, 0, 0);
+                for (int s4 = 0; s4 < KS / 4; ++s4) {
+                    const float4 kf = src[s4];
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4], kf.x, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4 + 1], kf.y, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4 + 2], kf.z, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[4 * s4 + 3], kf.w, acc, 0, 0, 0);
+                }
+                // accumulator i of lane (n, g) is plane 8 (i/4) + 4g + i%4 of key n
+                uint32_t word = 0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) word |= (acc[i] >= 0.0f ? 1u : 0u) << (8 * (i / 4) + i % 4);
+                word <<= 4 * g;
+                auto both = __builtin_amdgcn_permlane32_swap(word, word, false, false);
+                if (lane < 32) bt[n * BW + wave] = both[0] | both[1];
             }
-            // accumulator i of lane (n, g) is plane 8 (i/4) + 4g + i%4 of key n
-            uint32_t word = 0;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) word |= (acc[i] >= 0.0f ? 1u : 0u) << (8 * (i / 4) + i % 4);
-            word <<= 4 * g;
-            auto both = __builtin_amdgcn_permlane32_swap(word, word, false, false);
-            if (lane < 32) bt[n * BW + wave] = both[0] | both[1];
+            if (more) commit(buf ^ 1);
+            __syncthreads();   // bit matrix complete, next tile staged, every wave done with this key tile
+            const int *tk = tok + slot * TILE;
+            const int64_t *gr = grow + slot * TILE;
+            if (a.GT)
+                pack_codes_packed(bt, BW, TILE, tk, gr, a.codes, a.L, a.P, a.Lpad, a.GT, first_table, ntab, 1, tid, nt);
+            else
+                pack_codes(bt, BW, TILE, tk, gr, a.codes, a.L, a.P, a.Lpad, a.S, a.cb, first_table, ntab, whole, tid, nt);
+            buf ^= 1;
+            slot = nslot;
         }
-        if (more) commit(buf ^ 1);
-        __syncthreads();   // bit matrix complete, next tile staged, every wave done with this key tile
-        const int *tk = tok + slot * TILE;
-        const int64_t *gr = grow + slot * TILE;
-        if (a.GT)
-            pack_codes_packed(bt, BW, TILE, tk, gr, a.codes, a.L, a.P, a.Lpad, a.GT, first_table, ntab, 1, tid, nt);
-        else
-            pack_codes(bt, BW, TILE, tk, gr, a.codes, a.L, a.P, a.Lpad, a.S, a.cb, first_table, ntab, whole, tid, nt);
-        buf ^= 1;
-        slot = nslot;
+        if (!SHARE || left <= 0) return;
+        do {                                   // (tiles are left, so a sequence behind has them)
+            if (++b >= a.batch) return;
+            count = min(a.row_count[b], a.max_rows);
+        } while (count <= 0);
+        begin = a.row_begin[b];
+        wg_r0 = 0;
+        take();
+        fetch(wg_r0, slot);
     }
 }
 
@@ -570,6 +631,12 @@ __device__ __forceinline__ void fragments_to_lds(uint4 *wl, const uint4 *src, in
     }
 }
 
+struct OneSequence {                                   // (what stands for SeqUnits where there is nothing to share out)
+    __device__ __forceinline__ explicit OneSequence(const HashArgs &) {}
+    __device__ __forceinline__ int total() const { return 0; }
+    __device__ __forceinline__ void find(int, int *, int *, int *, int *) const {}
+};
+
 // Shape of a workgroup: NG of the chunk's S position groups (a chunk's workgroups are its S / NG
 // parts), their fragments in LDS.  d = 256: a block's fragments are 16 KB, so eight blocks, and a
 // 64-key block of keys takes 128 registers, so eight wavefronts; the keys are read once per part
@@ -578,7 +645,7 @@ __device__ __forceinline__ void fragments_to_lds(uint4 *wl, const uint4 *src, in
 template <int D, int S, int P> constexpr int hash8_groups() { return D <= 128 || S * P / 2 <= 8 ? S : S / 2; }
 template <int D> constexpr int hash8_threads() { return D <= 128 ? kHash8Threads : 512; }
 
-template <int D, int S, int P>
+template <int D, int S, int P, bool SHARE>
 __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs a, const uint4 *wfrag) {
     static_assert(P == 8 || P == 4, "one-byte ids of 8 planes, or of 4 (a block's eight nibbles are spread over two words)");
     constexpr int KS = D / 16;                 // MFMA k-steps
@@ -591,15 +658,21 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     uint32_t *bits = smem + NCB * KS * 64 * 4;         // [NW waves][64 keys][4 words]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int part = blockIdx.y % (S / NG), hc = blockIdx.y / (S / NG);
-    const int chunk = hc % a.n_chunks, h = hc / a.n_chunks, b = blockIdx.z;
+    const int row = SHARE ? blockIdx.x : blockIdx.y, slot = SHARE ? blockIdx.y : blockIdx.x, slots = SHARE ? gridDim.y : gridDim.x;
+    const int part = row % (S / NG), hc = row / (S / NG);
+    const int chunk = hc % a.n_chunks, h = hc / a.n_chunks;
+    // the 64-key blocks it takes part in: those of sequence blockIdx.z, or (SHARE) of that group
+    int b = blockIdx.z, count = 0, begin = 0, shared_r0 = 0;
+    const typename std::conditional<SHARE, SeqUnits<6>, OneSequence>::type runs(a);
+    if (!SHARE) {
+        count = a.row_count[b];
+        begin = a.row_begin[b];
+    }
     const int sub0 = part * NG;                        // the workgroup's first position group
-    const int count = a.row_count[b];
-    const int begin = a.row_begin[b];
     const int first_table = chunk * 64;
     const int ntab = min(64, a.L - first_table);
 
-    fragments_to_lds<NCB * KS * 64, NT>(wl, wfrag + (int64_t)blockIdx.y * NCB * KS * 64, tid);
+    fragments_to_lds<NCB * KS * 64, NT>(wl, wfrag + (int64_t)row * NCB * KS * 64, tid);
     __syncthreads();
 
     uint32_t *mybits = bits + wave * 256;
@@ -614,7 +687,9 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     // Branch-free: a key that does not exist reads row 0 of the cache instead (its ids are never
     // stored).
     bf16x8_t kf[2][KS];
-    auto load_keys = [&](int r0) {
+    auto load_keys = [&](int blk) {
+        if (SHARE) runs.find(blk, &b, &count, &begin, &shared_r0);
+        const int r0 = SHARE ? shared_r0 : blk * 64;
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb) {
             const int64_t row = key_row(r0 + nb * 32 + n);
@@ -636,12 +711,12 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     // 64-key blocks are dealt round-robin, to the workgroups before their wavefronts: short runs and
     // last rounds then spread over the compute units (8 heads, 64 tables of 8 planes: 8192 keys
     // 18.6 us, 29.0 with whole workgroups filled first; 40000 keys 44 / 55; full rounds alike)
-    const int nblocks = (count + 63) >> 6;
-    const int stride = gridDim.x * NW;
-    int blk = blockIdx.x + wave * gridDim.x;
-    if (blk < nblocks) load_keys(blk * 64);
+    const int nblocks = SHARE ? runs.total() : (count + 63) >> 6;   // (not before the slab: nothing there waits for the lengths)
+    const int stride = slots * NW;
+    int blk = slot + wave * slots;
+    if (blk < nblocks) load_keys(blk);
     for (; blk < nblocks; blk += stride) {
-        const int r0 = blk * 64;
+        const int r0 = SHARE ? shared_r0 : blk * 64;
         const int64_t prow = key_row(r0 + lane);        // the key this lane packs
         const int rot = (begin + r0 + lane) & 15;
         uint4 done[NG > 1 ? NG - 1 : 1];                // the key's position groups before the last, kept until the row is whole
@@ -704,7 +779,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
                 }
             }
         }
-        if (blk + stride < nblocks) load_keys((blk + stride) * 64);
+        if (blk + stride < nblocks) load_keys(blk + stride);
     }
 }
 
@@ -750,7 +825,7 @@ __global__ __launch_bounds__(256) void hash_wfrag10_kernel(HashArgs a, uint4 *wf
 // (d = 256: one string per workgroup, 80 KB of fragments)
 template <int D, int S> constexpr int hash10_strings() { return D <= 128 ? S : 1; }
 
-template <int D, int S>
+template <int D, int S, bool SHARE>
 __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArgs a, const uint4 *wfrag) {
     constexpr int KS = D / 16;                 // MFMA k-steps
     constexpr int NS = hash10_strings<D, S>(); // strings of the workgroup
@@ -762,13 +837,19 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
     uint32_t *bits = smem + NCB * KS * 64 * 4;         // [NW waves][64 keys][5 words]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int sub0 = blockIdx.y % (S / NS), hc = blockIdx.y / (S / NS);   // (S / NS > 1: the workgroup's string)
-    const int grp = hc % a.n_chunks, h = hc / a.n_chunks, b = blockIdx.z;
-    const int count = a.row_count[b];
-    const int begin = a.row_begin[b];
+    const int row = SHARE ? blockIdx.x : blockIdx.y, slot = SHARE ? blockIdx.y : blockIdx.x, slots = SHARE ? gridDim.y : gridDim.x;
+    const int sub0 = row % (S / NS), hc = row / (S / NS);   // (S / NS > 1: the workgroup's string)
+    const int grp = hc % a.n_chunks, h = hc / a.n_chunks;
+    // the 64-key blocks it takes part in: those of sequence blockIdx.z, or (SHARE) of that group
+    int b = blockIdx.z, count = 0, begin = 0, shared_r0 = 0;
+    const typename std::conditional<SHARE, SeqUnits<6>, OneSequence>::type runs(a);
+    if (!SHARE) {
+        count = a.row_count[b];
+        begin = a.row_begin[b];
+    }
     const int ntab = max(0, min(GT, a.L - grp * GT));
 
-    fragments_to_lds<NCB * KS * 64, NT>(wl, wfrag + (int64_t)blockIdx.y * NCB * KS * 64, tid);
+    fragments_to_lds<NCB * KS * 64, NT>(wl, wfrag + (int64_t)row * NCB * KS * 64, tid);
     __syncthreads();
 
     uint32_t *mybits = bits + wave * 320;
@@ -782,7 +863,9 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
     };
     // (a key that does not exist reads row 0 of the cache instead; its ids are never stored)
     bf16x8_t kf[2][KS];
-    auto load_keys = [&](int r0) {
+    auto load_keys = [&](int blk) {
+        if (SHARE) runs.find(blk, &b, &count, &begin, &shared_r0);
+        const int r0 = SHARE ? shared_r0 : blk * 64;
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb) {
             const int64_t row = key_row(r0 + nb * 32 + n);
@@ -799,12 +882,12 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
         return ~(both[0] | (both[1] << 16));
     };
 
-    const int nblocks = (count + 63) >> 6;
-    const int stride = gridDim.x * NW;
-    int blk = blockIdx.x + wave * gridDim.x;   // (as in hash_mfma8_kernel: workgroups first)
-    if (blk < nblocks) load_keys(blk * 64);
+    const int nblocks = SHARE ? runs.total() : (count + 63) >> 6;   // (not before the slab: nothing there waits for the lengths)
+    const int stride = slots * NW;
+    int blk = slot + wave * slots;   // (as in hash_mfma8_kernel: workgroups first)
+    if (blk < nblocks) load_keys(blk);
     for (; blk < nblocks; blk += stride) {
-        const int r0 = blk * 64;
+        const int r0 = SHARE ? shared_r0 : blk * 64;
         const int64_t prow = key_row(r0 + lane);        // the key this lane packs
         const uint32_t turn = 10u * (uint32_t)((begin + r0 + lane) & 15);   // bits the string is rotated by
         uint4 head0 = make_uint4(0, 0, 0, 0);           // string 0, kept until string 1 is there too
@@ -862,7 +945,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
                 }
             }
         }
-        if (blk + stride < nblocks) load_keys((blk + stride) * 64);
+        if (blk + stride < nblocks) load_keys(blk + stride);
     }
 }
 
@@ -883,6 +966,33 @@ static int launch_rows(const HashArgs &a, int Hkv, int batch, int max_rows, hipS
     return SOCKET_OK;
 }
 
+// the sequences in groups of equal size, for SeqUnits; returns their number
+static int share_groups(HashArgs *a) {
+    const int groups = (a->batch + 63) / 64;
+    a->group = (a->batch + groups - 1) / groups;
+    return (a->batch + a->group - 1) / a->group;
+}
+
+// Launch of a kernel that deals 64-key blocks to wavefronts: one workgroup per CU (the W slab fills
+// most of its LDS) over `rows` heads, chunks and parts.  `shared` (null: there is none): the kernel
+// that deals the blocks of several sequences out as one, for batches in which a wavefront of
+// `alone` would have more than one block of the longest run, or one round of workgroups would not do.
+// (A workgroup without a block copies its slab for nothing; asking for the run's length first cost
+// every short run 0.3 us, 4 % at 5000 keys of 16 tables, and gained nothing in ragged batches.)
+typedef void (*fragment_kernel_t)(HashArgs, const uint4 *);
+static void launch_blocks(fragment_kernel_t alone, fragment_kernel_t shared, HashArgs a, const uint4 *wfrag, int rows,
+                          int batch, int max_rows, int threads, size_t lds, hipStream_t st) {
+    const int nblocks = (max_rows + 63) / 64;
+    int groups = batch, per = std::max(1, std::min(nblocks, 256 / (rows * batch)));
+    const bool share = shared && batch > 1 && (nblocks > per * (threads / 64) || rows * batch > 256);
+    if (share) {
+        groups = share_groups(&a);
+        per = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)nblocks * a.group, 256 / (rows * groups)));
+    }
+    // (shared: slab by slab, so that few of the slabs go through each XCD's L2)
+    hipLaunchKernelGGL(share ? shared : alone, share ? dim3(rows, per, groups) : dim3(per, rows, groups), dim3(threads), lds, st, a, wfrag);
+}
+
 // dynamic LDS of hash_mfma8_kernel: the W slab as fragments, one id-word row per key of every wavefront's block
 template <int D, int S, int P> constexpr size_t hash8_lds() {
     return (size_t)(P / 2 * hash8_groups<D, S, P>()) * (D / 16) * 64 * 16 + (size_t)hash8_threads<D>() * 16;
@@ -900,13 +1010,18 @@ template <int D> static int hash_prepare_d() {
         if (e == hipSuccess && lds > 64 * 1024)
             e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     };
-    allow(hash_mfma8_kernel<D, 4, 8>, hash8_lds<D, 4, 8>());
-    allow(hash_mfma8_kernel<D, 2, 8>, hash8_lds<D, 2, 8>());
-    allow(hash_mfma8_kernel<D, 1, 8>, hash8_lds<D, 1, 8>());
-    allow(hash_mfma8_kernel<D, 4, 4>, hash8_lds<D, 4, 4>());
-    allow(hash_mfma8_kernel<D, 2, 4>, hash8_lds<D, 2, 4>());
-    allow(hash_mfma10_kernel<D, 2>, hash10_lds<D, 2>());
-    allow(hash_mfma10_kernel<D, 1>, hash10_lds<D, 1>());
+    auto both = [&](auto share) {
+        constexpr bool SHARE = decltype(share)::value;
+        allow(hash_mfma8_kernel<D, 4, 8, SHARE>, hash8_lds<D, 4, 8>());
+        allow(hash_mfma8_kernel<D, 2, 8, SHARE>, hash8_lds<D, 2, 8>());
+        allow(hash_mfma8_kernel<D, 1, 8, SHARE>, hash8_lds<D, 1, 8>());
+        allow(hash_mfma8_kernel<D, 4, 4, SHARE>, hash8_lds<D, 4, 4>());
+        allow(hash_mfma8_kernel<D, 2, 4, SHARE>, hash8_lds<D, 2, 4>());
+        allow(hash_mfma10_kernel<D, 2, SHARE>, hash10_lds<D, 2>());
+        allow(hash_mfma10_kernel<D, 1, SHARE>, hash10_lds<D, 1>());
+    };
+    both(std::false_type());
+    if constexpr (D == 256) both(std::true_type());
     return e == hipSuccess ? SOCKET_OK : SOCKET_EHIP;
 }
 int hash_prepare(int d) { return d == 64 ? hash_prepare_d<64>() : d == 128 ? hash_prepare_d<128>() : hash_prepare_d<256>(); }
@@ -918,14 +1033,9 @@ static int launch_mfma8(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_ro
     a.n_chunks = S == 4 ? (a.L + 63) / 64 : 1;
     // W as MFMA fragments, once per call
     hipLaunchKernelGGL((hash_wfrag_kernel<D, S, P>), dim3(P / 2 * S, Hkv * a.n_chunks), dim3(256), 0, st, a, wfrag);
-    // one workgroup per CU (the W slab fills most of its LDS); each wavefront takes 64-key blocks
-    int per = 256 / (Hkv * a.n_chunks * PARTS * batch);
-    const int nblocks = (max_rows + 63) / 64;
-    if (per > nblocks) per = nblocks;
-    if (per < 1) per = 1;
-    dim3 grid(per, Hkv * a.n_chunks * PARTS, batch);
-    constexpr size_t lds = hash8_lds<D, S, P>();
-    hipLaunchKernelGGL((hash_mfma8_kernel<D, S, P>), grid, dim3(NT), lds, st, a, (const uint4 *)wfrag);
+    fragment_kernel_t shared = nullptr;
+    if constexpr (D == 256) shared = hash_mfma8_kernel<D, S, P, true>;
+    launch_blocks(hash_mfma8_kernel<D, S, P, false>, shared, a, wfrag, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash8_lds<D, S, P>(), st);
     return SOCKET_OK;
 }
 template <int D, int P>
@@ -946,13 +1056,9 @@ static int launch_mfma10(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_r
     a.tables_per_chunk = 16 * S;
     a.n_chunks = a.Lpad / (16 * S);            // groups, padding groups included (their ids are zero)
     hipLaunchKernelGGL((hash_wfrag10_kernel<D, S>), dim3(5 * S, Hkv * a.n_chunks), dim3(256), 0, st, a, wfrag);
-    int per = 256 / (Hkv * a.n_chunks * PARTS * batch);
-    const int nblocks = (max_rows + 63) / 64;
-    if (per > nblocks) per = nblocks;
-    if (per < 1) per = 1;
-    dim3 grid(per, Hkv * a.n_chunks * PARTS, batch);
-    constexpr size_t lds = hash10_lds<D, S>();
-    hipLaunchKernelGGL((hash_mfma10_kernel<D, S>), grid, dim3(NT), lds, st, a, (const uint4 *)wfrag);
+    fragment_kernel_t shared = nullptr;
+    if constexpr (D == 256) shared = hash_mfma10_kernel<D, S, true>;
+    launch_blocks(hash_mfma10_kernel<D, S, false>, shared, a, wfrag, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash10_lds<D, S>(), st);
     return SOCKET_OK;
 }
 template <int D>
@@ -981,20 +1087,33 @@ static int launch_f32(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t 
     }
     int waves = (a.tables_per_chunk * a.P + 31) / 32;
     if (waves < f32_min_threads<D>() / 64) waves = f32_min_threads<D>() / 64;
-    // rows per workgroup: one round of resident workgroups (16 wavefronts a CU, 8 at d = 256), at
-    // most 16 tiles each so that ragged batches still spread
-    const int slots = 256 * ((D <= 128 ? 16 : 8) / waves);
-    const int64_t tiles = (int64_t)((max_rows + kF32Tile - 1) / kF32Tile) * Hkv * batch * a.n_chunks;
-    int64_t per = (tiles + slots - 1) / slots;
-    per = per < 1 ? 1 : per > 16 ? 16 : per;
-    a.rows_per_wg = (int)per * kF32Tile;
-    const size_t lds = 2 * kF32Tile * (D + 4) * 4 + 2 * kF32Tile * kF32BitWords * 4 + 3 * kF32Tile * 12;
-    dim3 grid((max_rows + a.rows_per_wg - 1) / a.rows_per_wg, Hkv * a.n_chunks, batch);
-    static_assert(2 * kF32Tile * (D + 4) * 4 + 2 * kF32Tile * kF32BitWords * 4 + 3 * kF32Tile * 12 <= 80 * 1024, "two workgroups a CU");
-    if (lds > 64 * 1024 &&
-        hipFuncSetAttribute((const void *)hash_f32_kernel<T, D>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    // one round of resident workgroups (16 wavefronts a CU, 8 at d = 256), at most 16 tiles each
+    const int slots = 256 * ((D <= 128 ? 16 : 8) / waves), rows = Hkv * a.n_chunks;
+    const int seq_tiles = (max_rows + kF32Tile - 1) / kF32Tile;
+    int64_t share = ((int64_t)seq_tiles * rows * batch + slots - 1) / slots;
+    if (share > 16) share = 16;
+    a.rows_per_wg = (int)share * kF32Tile;
+    int64_t per = (seq_tiles + share - 1) / share;
+    int groups = batch;
+    // Batches with more than three tiles to a workgroup, by the bound on the lengths: shares of
+    // all sequences' tiles, in up to four rounds where 16 tiles a share or a last round that is an
+    // eighth empty ask for it
+    const bool shared = batch > 1 && share > 3;
+    if (shared) {
+        groups = share_groups(&a);
+        const int64_t tiles = (int64_t)seq_tiles * a.group, all = (int64_t)rows * groups;
+        per = slots / all;
+        for (int r = 1; r < 4 && (per * all * 8 < (int64_t)r * slots * 7 || tiles > 16 * per); ++r) per = (r + 1) * slots / all;
+        if (per < 1) per = 1;
+        share = (tiles + per - 1) / per;
+        per = (tiles + share - 1) / share;
+    }
+    const auto kernel = shared ? hash_f32_kernel<T, D, true> : hash_f32_kernel<T, D, false>;
+    constexpr size_t lds = 2 * kF32Tile * (D + 4) * 4 + 2 * kF32Tile * kF32BitWords * 4 + 3 * kF32Tile * 12;
+    static_assert(lds <= 80 * 1024, "two workgroups a CU");
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return SOCKET_EHIP;
-    hipLaunchKernelGGL((hash_f32_kernel<T, D>), grid, dim3(64 * waves), lds, st, a);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)per, rows, groups), dim3(64 * waves), lds, st, a);
     return SOCKET_OK;
 }
 
@@ -1046,7 +1165,7 @@ int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int
     a.map = row_map(g, block_table);
     a.d = g.d; a.L = g.L; a.P = g.P; a.LP = g.L * g.P; a.Lpad = g.Lpad; a.S = g.S; a.cb = g.cb;
     a.GT = g.mode == kSplit ? g.GT : 0;
-    a.rows_per_wg = 0; a.tables_per_chunk = g.L; a.n_chunks = 1;
+    a.rows_per_wg = 0; a.tables_per_chunk = g.L; a.n_chunks = 1; a.batch = batch; a.max_rows = max_rows; a.group = 0;
     int rc;
     if (max_rows == 1) {
         // one appended key per sequence: the projection kernel with its W slab staged in LDS

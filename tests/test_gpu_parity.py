@@ -195,6 +195,119 @@ def test_hash_keys_fp32_sums_do_not_depend_on_the_run(d, L, P):
         ctx.close()
 
 
+def _hash_device(ctx, K, W, begins, counts, codes, table=None):
+    ctx.hash_keys(K, W, hz.i32(begins), hz.i32(counts), len(counts), max(counts), codes, block_table=table)
+
+
+@pytest.mark.parametrize("kv_dtype,d,L,P,Hkv,counts", [
+    # bf16, sequence by sequence: more 64-key blocks than wavefronts, so that every wavefront of a
+    # workgroup has blocks and comes round for a second one
+    (wl.BF16, 128, 64, 8, 32, [9000, 4500]), (wl.BF16, 128, 32, 8, 32, [9000, 4500]), (wl.BF16, 128, 16, 8, 32, [9000, 4500]),
+    (wl.BF16, 128, 31, 4, 32, [9000, 4500]), (wl.BF16, 128, 65, 4, 16, [9000, 4500]), (wl.BF16, 128, 60, 10, 16, [9000, 4500]),
+    (wl.BF16, 128, 16, 10, 32, [9000, 4500]), (wl.BF16, 64, 64, 8, 32, [9000, 4500]), (wl.BF16, 64, 60, 10, 16, [9000, 4500]),
+    (wl.BF16, 256, 64, 8, 32, [4500]), (wl.BF16, 256, 31, 4, 32, [9000]), (wl.BF16, 256, 60, 10, 16, [4500]),
+    # d = 256, several sequences dealt out as one: empty ones, one row, whole and ragged blocks
+    (wl.BF16, 256, 64, 8, 16, [2100, 0, 1, 3000, 64, 65, 700]), (wl.BF16, 256, 100, 8, 8, [2100, 0, 1, 3000, 64, 65, 700]),
+    (wl.BF16, 256, 16, 8, 16, [2100, 0, 1, 3000]), (wl.BF16, 256, 31, 4, 16, [0, 2100, 63, 5000]), (wl.BF16, 256, 65, 4, 16, [0, 2100, 63, 3000]),
+    (wl.BF16, 256, 60, 10, 16, [2100, 0, 1, 3000, 0]), (wl.BF16, 256, 16, 10, 16, [5, 2100, 0, 5000]),
+    (wl.BF16, 256, 64, 8, 8, [64] * 40), (wl.BF16, 256, 60, 10, 2, [130, 0, 17] * 30),       # (90 sequences: two groups)
+    # fp32: more than three tiles of 32 keys to a workgroup; all turns of the row bookkeeping
+    (wl.F32, 64, 64, 8, 8, [9000]), (wl.F32, 64, 60, 10, 8, [5000, 0, 1203, 3, 4000]), (wl.F32, 128, 64, 8, 8, [5000, 4000]),
+    (wl.F32, 128, 32, 8, 8, [1, 8000, 0, 31, 32, 33, 6000]), (wl.F32, 128, 60, 10, 8, [0, 0, 5000, 1203, 1]),
+    (wl.F32, 128, 40, 12, 8, [5000, 1203]), (wl.F32, 256, 64, 8, 8, [3000, 0, 1203]), (wl.F32, 256, 24, 5, 8, [3000, 0, 1203]),
+    (wl.F32, 64, 64, 8, 4, [700, 0, 1, 95] * 20),                                             # (80 sequences: two groups)
+    (wl.F32, 128, 64, 8, 70, [600, 40]),                                                      # (heads and chunks divide a round badly)
+])
+def test_hash_keys_long_and_ragged_batches(kv_dtype, d, L, P, Hkv, counts):
+    """One call against the same keys hashed in short pieces, sequence by sequence (one block or tile
+    to a workgroup: the runs the oracle tests cover): the same ids bit for bit, other rows untouched."""
+    _need_gpu()
+    B, begins = len(counts), [(7 * b) % 23 for b in range(len(counts))]
+    n = (max(counts) + 23 + 47) // 48 * 48
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    dt = torch.bfloat16 if kv_dtype == wl.BF16 else torch.float32
+    K = torch.randn((B, Hkv, n, d), generator=gen, device="cuda", dtype=dt)
+    W = torch.randn((Hkv, d, L * P), generator=gen, device="cuda", dtype=dt)
+    ctx = sk.Context(sk.make_params(d, Hkv, Hkv, L, P, sk.BF16 if kv_dtype == wl.BF16 else sk.F32, B, n, 16))
+    whole, pieces = (hz.new_codes((B, Hkv), n, L, P, fill=0x55) for _ in range(2))
+    _hash_device(ctx, K, W, begins, counts, whole)
+    step = 256 if kv_dtype == wl.BF16 else 96
+    for b in range(B):
+        for at in range(0, counts[b], step):
+            # (at least 64 rows to a call, bf16: shorter runs go through the fp32 kernel)
+            c = min(step, counts[b] - at)
+            ctx.hash_keys(K[b:b + 1], W, hz.i32([begins[b] + at]), hz.i32([c]), 1, max(c, 64), pieces[b:b + 1])
+    assert torch.equal(whole, pieces)
+    ctx.close()
+
+
+@pytest.mark.parametrize("kv_dtype,d,L,P,counts", [
+    (wl.F32, 128, 32, 8, [97, 161, 0]), (wl.F32, 64, 60, 10, [97, 161, 5]), (wl.F32, 256, 64, 8, [161, 33, 1]),
+    (wl.F32, 128, 40, 12, [97, 161, 2]), (wl.BF16, 128, 64, 8, [37, 63, 2]), (wl.BF16, 64, 16, 10, [63, 5, 0]), (wl.BF16, 256, 24, 5, [37, 63, 9]),
+])
+def test_hash_keys_fp32_kernel_on_paged_caches(kv_dtype, d, L, P, counts):
+    """The fp32 matrix kernel on blocks in random order, one of them absent: the ids of the contiguous
+    cache, and nothing written for the absent block's tokens."""
+    _need_gpu()
+    page, n, B, Hkv, begins = 16, 192, 3, 2, [3, 21, 50]
+    layer = small_layer(seed=17, B=B, Hq=Hkv, Hkv=Hkv, d=d, n=n, L=L, P=P, kv_dtype=kv_dtype, k=16)
+    ctx = hz.make_ctx(layer)
+    flat = run_hash(ctx, layer, begins, counts, max(counts))
+    check_codes(layer, flat, lambda b: (begins[b], counts[b]))
+    ctx.close()
+    table, num_blocks = wl.make_block_table(3, [n] * B, page)
+    table = np.array(table)
+    order = torch.from_numpy(table.astype(np.int64)).cuda()
+    Kp = wl.to_paged(layer.K, layer.seq_len, table, num_blocks, page)
+    gone = table.copy()
+    gone[0, 1] = num_blocks                      # tokens 16..31 of sequence 0 have no block
+    gone[1, 3] = -1                              # tokens 48..63 of sequence 1
+    ctx = hz.make_ctx(layer, page=page, max_blocks=table.shape[1], num_blocks=num_blocks)
+    paged = hz.new_codes((num_blocks, Hkv), page, L, P, fill=0x55)
+    _hash_device(ctx, hz.dev(Kp, kv_dtype), hz.dev(layer.W, kv_dtype), begins, counts, paged, table=hz.i32(gone))
+    want = flat.view(B, Hkv, n // page, -1).clone()
+    blank = hz.new_codes((1, Hkv), page, L, P, fill=0x55).view(Hkv, -1)
+    want[0, :, 1] = blank
+    want[1, :, 3] = blank
+    assert torch.equal(paged[order].transpose(1, 2).reshape(want.shape), want)
+    ctx.close()
+
+
+def _least_us(f, reps=20, rounds=6):
+    """Least mean time of a call over a few batches of them."""
+    f()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    times = []
+    for _ in range(rounds):
+        a.record()
+        for _ in range(reps):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / reps)
+    return min(times)
+
+
+@pytest.mark.parametrize("kv_dtype,d,L,P", [(wl.BF16, 256, 64, 8), (wl.BF16, 256, 60, 10), (wl.F32, 64, 60, 10), (wl.F32, 128, 64, 8)])
+def test_hash_keys_a_long_run_among_short_ones_is_shared_out(kv_dtype, d, L, P):
+    """One run of 16384 keys in a batch with fifteen of 100 is a tenth more work than the long run
+    alone.  Left to the workgroups of its own sequence it took four to nine times as long."""
+    _need_gpu()
+    B, Hkv, n = 16, 8, 16384
+    dt = torch.bfloat16 if kv_dtype == wl.BF16 else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    K = torch.randn((B, Hkv, n, d), generator=gen, device="cuda", dtype=dt)
+    W = torch.randn((Hkv, d, L * P), generator=gen, device="cuda", dtype=dt)
+    ctx = sk.Context(sk.make_params(d, Hkv, Hkv, L, P, sk.BF16 if kv_dtype == wl.BF16 else sk.F32, B, n, 16))
+    codes = hz.new_codes((B, Hkv), n, L, P)
+    zero, counts = hz.i32([0] * B), hz.i32([100] * 7 + [n] + [100] * 8)
+    full = hz.i32([n])
+    alone = _least_us(lambda: ctx.hash_keys(K, W, zero, full, 1, n, codes))
+    batch = _least_us(lambda: ctx.hash_keys(K, W, zero, counts, B, n, codes))
+    assert batch <= 2.5 * alone, (batch, alone)
+    ctx.close()
+
+
 # ------------------------------------------------------------------ a2 + a3: socket_score
 
 def run_score(ctx, layer, codes_nat, tau, vnorm=None, seq_len=None, q=None):
