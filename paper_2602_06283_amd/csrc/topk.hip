@@ -1,19 +1,22 @@
-// Alg. 3, TopK step: exact selection of the k largest scores per (sequence, KV head) by a
-// most-significant-digit radix select on the fp32 bit patterns, spread over many workgroups.
+// Alg. 3, TopK step: exact selection of the k largest scores per (sequence, KV head), spread over
+// many workgroups: a histogram, a sweep with the threshold bin it gives, and an ordered emit.
 //
-//   topk_hist_kernel    adaptive histogram (bins from a sample of the row) of every valid score;
-//                       the fused decode step gets it from the scoring pass instead, with bins
-//                       sized from the bucket-probability tables.
-//   topk_filter_kernel<true>  finds the threshold bin, then sweeps: scores above it are selected,
-//                       scores in it are candidates (a few dozen unless many scores tie).
+//   topk_hist_kernel    histogram of every valid score, in bins from a sample of the row and the
+//                       scores' exponents (sampled_bin); the fused decode step gets an adaptive
+//                       one from the scoring pass instead, with bins sized from the
+//                       bucket-probability tables (score_bin).
+//   topk_filter_kernel<true, .>  finds the threshold bin, then sweeps: scores above it are selected,
+//                       scores in it are candidates: a few dozen where the bins fit the row, any
+//                       number where many scores lie close together or tie.  More than kSplitMin
+//                       of sampled bins are counted by sub-bin.
 //   topk_emit_kernel    a workgroup per region of the sweep ranks the candidates on the score and
-//                       then on the token position (smaller position wins a tie) and writes its
-//                       part of the index row in ascending order.  Leaves histograms and counters
-//                       at zero.
+//                       then on the token position (smaller position wins a tie; emit_long: long
+//                       lists, by sub-bin) and writes its part of the index row in ascending
+//                       order.  Leaves histograms and counters at zero.
 // Where the scoring pass could not size bins it leaves a histogram of leading 11-bit digits:
 //   topk_hist2_kernel   finds the threshold digit, then histograms the next 11 bits over the
 //                       scores in that digit.
-//   topk_filter_kernel<false>  the sweep with the two-digit threshold.
+//   topk_filter_kernel<false, .>  the sweep with the two-digit threshold.
 // Stages talk through global memory across kernel boundaries only: no workgroup waits on
 // another and no fence is needed.  LDS arrays that a thread walks in runs of PER consecutive
 // words carry one pad word per run, which makes those walks free of bank conflicts.
@@ -21,16 +24,33 @@
 
 namespace sk {
 
-// Adaptive histogram of a row nobody has binned yet.  The bins need a mean and a spread: every
-// workgroup takes them from the same 512 scores of the row, spread evenly, so all of them (and,
-// through the threshold record, the sweep) bin alike.  Scores further than four deviations from
-// the mean are left out and both taken again, so that a few spikes do not widen the bins.
-// At most a share f of any numbers lies sqrt(f / (1 - f)) deviations below their mean or higher
-// (one-sided Chebyshev), so the k-th largest score is above mean - 0.34 deviations for f = 0.1 and
-// mean - 0.58 for f = 0.25: the bins start half a deviation or one below the mean there, and are
-// a 256th of a deviation wide where thresholds usually lie.  Which bins only decides how short
-// the candidate list is; the select is exact for any.  (Laying the bins between two order
-// statistics of 256 sampled scores instead bore any distribution, but cost 3.7 us more.)
+// Bin of a score in a row nobody has binned yet: the sum of an adaptive bin (512 equal ones per
+// octave of 1 + (v - lo) * inv over the first two octaves, 256 over the next two) and of the
+// score's sign and exponent.  Both are non-decreasing in v, so the sum is too, and two scores share
+// a bin only if they share both parts: fine steps where (lo, inv) fit the row, never more than an
+// octave where they do not.
+static_assert(kHistBins == 2048, "1536 adaptive bins and 511 for sign and exponent");
+__device__ __forceinline__ uint32_t sampled_bin(float v, float lo, float inv) {
+    const float y = fmaf(fmaxf(v - lo, 0.0f), inv, 1.0f);
+    const uint32_t fine = (__float_as_uint(y) - 0x3f800000u) >> 14;
+    return min(min(fine, 512 + (fine >> 1)), 1535u) + (order_key(v) >> 23);   // (the halved steps are the smaller from 1024 on)
+}
+
+// (lo, inv) from a sample: every workgroup takes a mean and a deviation from the same 512 scores of
+// the row, spread evenly, so all of them (and, through the threshold record, the sweep) bin alike.
+// Scores further than four deviations from the mean are left out and both taken again, so that a
+// few spikes do not widen the bins.  A share f of a row's scores that lies all below its mean - c
+// deviations has c < sqrt((1 - f) / f) (one-sided Chebyshev, with the row's own mean and deviation),
+// and the largest f of them lies above mean - sqrt(f / (1 - f)) deviations: 0.34 for f = 0.1, 0.58
+// for 0.25.  The bins start half a deviation or one below the mean there, a 512th of a deviation
+// wide at their start.  That is a rule of thumb: a sample stands for the row, and a cluster of close
+// scores, or a spread over decades, can leave many scores in the bin of the cut.  The sweep then
+// counts them by sub-bin and emit_long goes on from there; the select is exact for any bins.
+// 131072 scores x 8 heads, k = 2048, us, with adaptive bins alone / now (sign and exponent in the bin,
+// sub-bins): a bell 14.3 / 14.8, 6 % in a tight cluster far up 130 / 24, clusters in a cluster 84 / 24,
+// counts with a small soft part 59 / 24, a long tail below 257 / 21, seventy decades 685 / 17; 32768
+// scores, k = 1024: 13.3 / 13.6, 51 / 20, 54 / 21, 41 / 19, 66 / 19, 155 / 14.  (Laying the bins between
+// two order statistics of 256 sampled scores cost every row 3.7.)
 __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(TopkArgs a) {
     constexpr int NW = kTopkThreads / 64;
     __shared__ uint32_t h[kHistBins];
@@ -88,11 +108,40 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(TopkArgs a) {
     if (key0 >= key1) return;
 #pragma unroll
     for (int j = 0; j < kPer; ++j)
-        if (i + j < key1 && selectable(e[j])) atomicAdd(&h[score_bin(e[j], lo, inv)], 1u);
+        if (i + j < key1 && selectable(e[j])) atomicAdd(&h[sampled_bin(e[j], lo, inv)], 1u);
     __syncthreads();
     uint32_t *gh = a.hist + (int64_t)bh * kHistBins;
     for (int j = tid; j < kHistBins; j += kTopkThreads)
         if (h[j]) atomicAdd(&gh[j], h[j]);
+}
+
+// Sub-bins of a threshold bin of sampled_bin: equal steps of the score key between the bin's two
+// ends.  Non-decreasing in the score, and the same for all workgroups of a row.
+struct SubBins {
+    uint32_t lo;
+    int shift;
+    __device__ __forceinline__ uint32_t of(uint32_t key) const {
+        return key <= lo ? 0u : min((key - lo) >> shift, (uint32_t)(kHistBins - 1));
+    }
+};
+// (whole wavefronts: the lower half searches for the bin's first key, the upper half for the next bin's)
+__device__ __forceinline__ SubBins sub_bins(uint32_t bin, float bin_lo, float bin_inv) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t want = bin + (lane >> 5);
+    uint32_t below = 0;                                          // a key below the one sought, or 0
+#pragma unroll 1
+    for (int sh = 27; sh >= 0; sh -= sh > 2 ? 5 : 2) {           // 32 probes a step
+        const uint32_t probe = below + ((uint32_t)(lane & 31) << sh);
+        const uint32_t key = min(max(probe, 0x007fffffu), 0xff800000u);   // -inf .. +inf
+        const float v = __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
+        const uint64_t hit = __ballot(probe <= 0xff800000u && sampled_bin(v, bin_lo, bin_inv) < want);
+        const int n = __popc(lane < 32 ? (uint32_t)hit : (uint32_t)(hit >> 32));
+        below += (uint32_t)max(n - 1, 0) << sh;
+    }
+    const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)below, 0) + 1, k1 = (uint32_t)__builtin_amdgcn_readlane((int)below, 32) + 1;
+    const uint32_t last = k1 > k0 + 1 ? k1 - k0 - 1 : 1u;        // the largest offset
+    const int bits = 32 - __clz((int)last);
+    return SubBins{k0, bits > kHistBits ? bits - kHistBits : 0};
 }
 
 // First threshold digit, then the histogram of the second digit over the scores in it.
@@ -153,7 +202,8 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist2_kernel(TopkArgs a) {
 // Threshold, then the sweep.  ADAPT = false: the second threshold digit from the histogram of
 // topk_hist2_kernel, lead = the two leading digits of the score key.  ADAPT = true: the
 // threshold bin of the adaptive histogram, lead = that bin.
-template <bool ADAPT>
+// REFINE: the bins are sampled_bin's, and a long list is counted by sub-bin.
+template <bool ADAPT, bool REFINE>
 __global__ __launch_bounds__(kTopkThreads) void topk_filter_kernel(TopkArgs a) {
     constexpr int PER = kHistBins / kTopkThreads;
     __shared__ uint32_t h[padded_size<kHistBins, PER>()];
@@ -235,7 +285,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_filter_kernel(TopkArgs a) {
     for (int j = 0; j < kPer; ++j) {
         const bool ok = i + j < key1 && selectable(e[j]);
         keys[j] = order_key(e[j]);
-        const uint32_t lead = ADAPT ? score_bin(e[j], bin_lo, bin_inv) : keys[j] >> kDigit2Shift;
+        const uint32_t lead = !ADAPT ? keys[j] >> kDigit2Shift : REFINE ? sampled_bin(e[j], bin_lo, bin_inv) : score_bin(e[j], bin_lo, bin_inv);
         if (ok && lead > pair) flags |= 1u << j;
         if (ok && lead == pair) flags |= 1u << (16 + j);
     }
@@ -258,17 +308,171 @@ __global__ __launch_bounds__(kTopkThreads) void topk_filter_kernel(TopkArgs a) {
             ++at_cand;
         }
     }
+    // a long list: the candidates' sub-bins, for the emit kernel
+    if (REFINE && n_cand > (uint32_t)kSplitMin && (total >> 16 || blockIdx.x == 0)) {
+        const SubBins sub = sub_bins(pair, bin_lo, bin_inv);
+        if (blockIdx.x == 0 && tid == 0) {
+            thr[kThrSubLo] = sub.lo;
+            thr[kThrSubShift] = (uint32_t)sub.shift;
+        }
+        for (int j = tid; j < kHistBins; j += kTopkThreads) h[j] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+            if (flags & (1u << (16 + j))) atomicAdd(&h[sub.of(keys[j])], 1u);
+        __syncthreads();
+        uint32_t *gh2 = a.hist2 + (int64_t)bh * kHistBins;
+        for (int j = tid; j < kHistBins; j += kTopkThreads)
+            if (h[j]) atomicAdd(&gh2[j], h[j]);
+    }
 }
+
+// the rest of the index row, the count, and the scratch for the next call
+__device__ __forceinline__ void finish_row(const TopkArgs &a, int bh, uint32_t k_eff, bool clear2) {
+    const int tid = threadIdx.x;
+    for (int i = (int)k_eff + tid; i < a.max_k; i += kTopkThreads) a.idx[(int64_t)bh * a.max_k + i] = -1;
+    uint32_t *gh1 = a.hist + (int64_t)bh * kHistBins, *gh2 = a.hist2 + (int64_t)bh * kHistBins;
+    for (int i = tid; i < kHistBins; i += kTopkThreads) {
+        gh1[i] = 0;
+        if (clear2) gh2[i] = 0;
+    }
+    if (tid < 2) a.counters[(int64_t)bh * kCounterStride + tid] = 0;
+    if (tid == 0) a.n_selected[bh] = (int32_t)k_eff;
+}
+
+// A region's part of the index row where the threshold bin holds more scores than are ranked in
+// pairs (a.refine: the sweep has counted them by sub-bin).  Every workgroup of the row finds the
+// threshold sub-bin and goes through the whole list: candidates above that sub-bin are kept, those
+// in it counted by what is left of their keys (a bin spans an octave at most, so a sub-bin 4096
+// keys), and of those that tie on the last key the smallest positions are kept.  The region is
+// written through a bitmap; nobody waits for another workgroup.  Returns false where the sub-bin
+// holds more than LDS does (mass ties).
+//   (Bound by the list, which each of the row's workgroups reads from L2.)
+__device__ __forceinline__ bool emit_long(const TopkArgs &a, int bh, int reg, uint32_t k_eff, uint32_t above, uint32_t n_cand,
+                                          uint32_t *lds) {
+    constexpr int NT = kTopkThreads, PER = kHistBins / NT, RPER = kRefineBins / NT;
+    static_assert(kSlice == 8 * NT, "a thread emits the eight positions of a bitmap byte");
+    static_assert(kRefineBins >= 1 << (23 - kHistBits), "a refinement bin for every key of a sub-bin");
+    __shared__ uint32_t tmp[16], res[4], s_n;
+    const int tid = threadIdx.x;
+    unsigned long long *ck = (unsigned long long *)lds;          // [kRankMax + 4] candidates of the threshold sub-bin
+    uint32_t *h = (uint32_t *)(ck + kRankMax + 4);               // [padded kRefineBins]
+    uint32_t *bitmap = h + padded_size<kRefineBins, RPER>();     // [kSlice / 32] kept positions of the region
+    uint32_t *ties = bitmap + kSlice / 32;                       // [kSlice / 32] its candidates that tie on the last key kept
+    uint32_t *gh2 = a.hist2 + (int64_t)bh * kHistBins;
+    for (int j = tid; j < kHistBins; j += NT) h[padded<PER>(j)] = gh2[j];
+    for (int j = tid; j < kSlice / 32; j += NT) bitmap[j] = ties[j] = 0;
+    if (tid < 4) res[tid] = 0;
+    if (tid == 0) s_n = 0;
+    const uint32_t *thr = a.thr + (int64_t)bh * kThrStride;
+    const SubBins sub{thr[kThrSubLo], (int)thr[kThrSubShift]};
+    __syncthreads();
+    const uint32_t need = k_eff - above;
+    find_threshold<kHistBins>(h, need, res, tmp);                // 1 <= need <= n_cand
+    const uint32_t t2 = res[0], need2 = need - res[1], n2 = res[2];
+    // the row's last workgroup to have read hist2 clears it for the next call
+    uint32_t *ticket = a.counters + (int64_t)bh * kCounterStride + kTicket;
+    uint32_t turn = 0;
+    if (tid == 0) turn = atomicAdd(ticket, 1u);
+    auto clear = [&]() {                                         // (late: the ticket is a round trip to memory)
+        if (tid == 0) s_n = turn == gridDim.x - 1;
+        __syncthreads();
+        if (s_n) {
+            for (int j = tid; j < kHistBins; j += NT) gh2[j] = 0;
+            if (tid == 0) *ticket = 0;
+        }
+    };
+    if (n2 > (uint32_t)kRankMax) {
+        clear();
+        return false;
+    }
+    if (reg == 0) finish_row(a, bh, k_eff, false);
+    // ---- the candidates, and what earlier regions hold
+    const uint32_t *selcnt = a.sel_cnt + (int64_t)bh * a.n_regions;
+    const uint32_t *ckey = a.cand_key + (int64_t)bh * a.max_n;
+    const int32_t *cidx = a.cand_idx + (int64_t)bh * a.max_n;
+    const int32_t *entries = a.sel_regions + ((int64_t)bh * a.n_regions + reg) * kSlice;
+    for (int j = tid; j < padded_size<kRefineBins, RPER>(); j += NT) h[j] = 0;
+    if (tid < 4) res[tid] = 0;
+    auto mark = [&](uint32_t *map, int32_t pos) { atomicOr(&map[(pos % kSlice) >> 5], 1u << (pos & 31)); };
+    uint32_t earlier = 0;
+    for (int r = tid; r < reg; r += NT) earlier += selcnt[r];
+    const uint32_t cnt = selcnt[reg];
+    for (uint32_t i = tid; i < cnt; i += NT) mark(bitmap, entries[i]);
+    __syncthreads();
+    auto keep = [&](int32_t pos) {
+        const int r = pos / kSlice;
+        if (r < reg) ++earlier;
+        if (r == reg) mark(bitmap, pos);
+    };
+    constexpr int U = 4;                                         // loads in flight
+    for (uint32_t i0 = tid; i0 < n_cand; i0 += U * NT) {
+        uint32_t key[U];
+        int32_t pos[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = min(i0 + u * NT, n_cand - 1);
+            key[u] = ckey[i];
+            pos[u] = cidx[i];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t d = i0 + u * NT < n_cand ? sub.of(key[u]) + 1 : 0u;
+            if (d > t2 + 1) keep(pos[u]);
+            if (d == t2 + 1) {
+                const uint32_t at = atomicAdd(&s_n, 1u);         // (n2 of them)
+                if (at < (uint32_t)kRankMax) ck[at] = ((unsigned long long)key[u] << 32) | (0x7fffffffu - (uint32_t)pos[u]);
+            }
+        }
+    }
+    __syncthreads();
+    // ---- the threshold sub-bin, key by key
+    const uint32_t k0 = sub.lo + (t2 << sub.shift);
+    auto digit = [&](unsigned long long c) { const uint32_t key = (uint32_t)(c >> 32); return key <= k0 ? 0u : min(key - k0, (uint32_t)(kRefineBins - 1)); };
+    for (uint32_t i = tid; i < n2; i += NT) atomicAdd(&h[padded<RPER>((int)digit(ck[i]))], 1u);
+    __syncthreads();
+    find_threshold<kRefineBins>(h, need2, res, tmp);             // 1 <= need2 <= n2
+    const uint32_t t3 = res[0];
+    uint32_t ties_earlier = 0;
+    for (uint32_t i = tid; i < n2; i += NT) {
+        const unsigned long long c = ck[i];
+        const uint32_t d = digit(c);
+        const int32_t pos = (int32_t)(0x7fffffffu - (uint32_t)c);
+        if (d > t3) keep(pos);
+        if (d == t3) {
+            if (pos / kSlice < reg) ++ties_earlier;
+            if (pos / kSlice == reg) mark(ties, pos);
+        }
+    }
+    uint32_t base, before, total;
+    block_excl_scan(earlier, &base, tmp);                        // (barriers: the bitmaps are complete)
+    block_excl_scan(ties_earlier, &before, tmp);
+    const uint32_t need3 = need2 - res[1];                       // ties to keep: the smallest positions
+    base += min(before, need3);
+    const uint32_t left = need3 - min(before, need3);            // of them in this region and later ones
+    uint32_t mine = (ties[tid >> 2] >> (8 * (tid & 3))) & 0xffu;
+    uint32_t rank = block_excl_scan(__popc(mine), &total, tmp);
+    uint32_t byte = (bitmap[tid >> 2] >> (8 * (tid & 3))) & 0xffu;
+    for (; mine != 0 && rank < left; mine &= mine - 1, ++rank) byte |= mine & (0u - mine);
+    uint32_t at = base + block_excl_scan(__popc(byte), &total, tmp);
+    int32_t *out = a.idx + (int64_t)bh * a.max_k;
+    for (int j = 0; j < 8; ++j)
+        if ((byte & (1u << j)) && at < k_eff) out[at++] = reg * kSlice + 8 * tid + j;
+    clear();
+    return true;
+}
+constexpr size_t kLongLds = (size_t)(kRankMax + 4) * 8 + (size_t)(padded_size<kRefineBins, kRefineBins / kTopkThreads>() + 2 * (kSlice / 32)) * 4;
+static_assert(kLongLds <= kResolveLds, "the long list's LDS fits the emit kernel's");
 
 // The index row, from the sweep's regions and candidates: one workgroup per region, each ranking
 // the few candidates itself.  The regions one after the other are the positions selected outright
 // in ascending order, so an entry's slot is the number of entries in earlier regions, its index
 // in its own, and the kept candidates before it; a kept candidate's slot is the same counts for
 // its position.  (One workgroup per row, walking all regions, took 8.4-9.5 us at 32768 scores, 8
-// heads.  A whole select, launches back to back: 13.3 us, 19.6 with that kernel and two digit
-// histograms; 131072 scores 15.2 / 22.9; 16 x 20000 scores 24.4 / 28.7; 4 M scores 39 us / 7.6 ms.)
-// A list of more candidates than two per thread (mass ties) is left to the row's first workgroup
-// (topk_resolve_body).
+// heads.  A whole select, launches back to back: 13.6 us, 19.6 with that kernel and two digit
+// histograms; 131072 scores 14.8 / 22.9; 16 x 20000 scores 24.4 / 28.7; 4 M scores 39 us / 7.6 ms.)
+// A list too long for pairs goes to emit_long (sampled bins) or, beyond two candidates per thread,
+// to the row's first workgroup (topk_resolve_body: bins of the scoring pass, and mass ties).
 __global__ __launch_bounds__(kTopkThreads, 4) void topk_emit_kernel(TopkArgs a) {
     extern __shared__ __align__(16) uint32_t emit_lds[];
     constexpr int NT = kTopkThreads, NW = NT / 64;
@@ -296,21 +500,14 @@ __global__ __launch_bounds__(kTopkThreads, 4) void topk_emit_kernel(TopkArgs a) 
     asm volatile("" ::: "memory");               // (keeps the loads together, ahead of what uses them)
     const uint32_t k_eff = t0, above = k_eff ? t5 : 0u, n_cand = k_eff ? t6 : 0u;
     const uint32_t need = k_eff - above;
-    if (n_cand > (uint32_t)kRankMax) {
-        if (reg == 0) topk_resolve_body(a, bh, emit_lds);
+    if (n_cand > (uint32_t)(a.refine ? kSplitMin : kRankMax)) {
+        if (!a.refine || !emit_long(a, bh, reg, k_eff, above, n_cand, emit_lds)) {
+            if (reg == 0) topk_resolve_body(a, bh, emit_lds);
+        }
         return;
     }
     int32_t *out = a.idx + (int64_t)bh * a.max_k;
-    if (reg == 0) {                              // the rest of the row, the count, and the scratch for the next call
-        for (int i = (int)k_eff + tid; i < a.max_k; i += NT) out[i] = -1;
-        uint32_t *gh1 = a.hist + (int64_t)bh * kHistBins, *gh2 = a.hist2 + (int64_t)bh * kHistBins;
-        for (int i = tid; i < kHistBins; i += NT) {
-            gh1[i] = 0;
-            gh2[i] = 0;
-        }
-        if (tid < 2) a.counters[(int64_t)bh * kCounterStride + tid] = 0;
-        if (tid == 0) a.n_selected[bh] = (int32_t)k_eff;
-    }
+    if (reg == 0) finish_row(a, bh, k_eff, !a.refine);   // (nobody wrote hist2 where the list is short)
     if (k_eff == 0) return;
     // ---- rank the candidates on (score, smaller position first); kept ones in earlier regions
     //      are counted, those of this region listed
@@ -331,6 +528,7 @@ __global__ __launch_bounds__(kTopkThreads, 4) void topk_emit_kernel(TopkArgs a) 
         const int32_t pos = (int32_t)(0x7fffffffu - (uint32_t)me);
         if (pos / kSlice > reg) continue;        // (the same for the lanes that share a candidate)
         uint32_t rank = 0;
+#pragma unroll 2
         for (uint32_t o = 4 * (tid & ((1 << lg) - 1)); o < n_cand; o += 4 << lg) {
             const ulonglong2 c0 = *(const ulonglong2 *)&ck[o], c1 = *(const ulonglong2 *)&ck[o + 2];
             rank += (c0.x > me) + (c0.y > me) + (c1.x > me) + (c1.y > me);
@@ -377,34 +575,32 @@ constexpr size_t kEmitLds = (size_t)(kRankMax + 4) * 8 + (size_t)kRankMax * 4;
 
 // Everything up to the sweep: the threshold and the two unordered lists (selected outright,
 // candidates in the threshold bin).  The fused decode step continues from those lists.
-int launch_topk_sweep(socket_ctx *ctx, const float *scores, const int32_t *seq_len, const int32_t *k,
-                      int batch, int32_t *idx, int32_t *n_selected, int hist_mode, hipStream_t st) {
-    const Geometry &g = ctx->g;
-    const TopkArgs a = topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode);
-    dim3 grid((g.max_n + kSlice - 1) / kSlice, batch * g.Hkv);
-    if (hist_mode == kHistAdaptive) {
-        hipLaunchKernelGGL(topk_filter_kernel<true>, grid, dim3(kTopkThreads), 0, st, a);
+static void launch_sweep(const TopkArgs &a, dim3 grid, hipStream_t st) {
+    if (a.adaptive) {
+        hipLaunchKernelGGL((a.refine ? topk_filter_kernel<true, true> : topk_filter_kernel<true, false>), grid, dim3(kTopkThreads), 0, st, a);
     } else {
         hipLaunchKernelGGL(topk_hist2_kernel, grid, dim3(kTopkThreads), 0, st, a);
-        hipLaunchKernelGGL(topk_filter_kernel<false>, grid, dim3(kTopkThreads), 0, st, a);
+        hipLaunchKernelGGL((topk_filter_kernel<false, false>), grid, dim3(kTopkThreads), 0, st, a);
     }
+}
+int launch_topk_sweep(socket_ctx *ctx, const float *scores, const int32_t *seq_len, const int32_t *k,
+                      int batch, int32_t *idx, int32_t *n_selected, int hist_mode, hipStream_t st) {
+    launch_sweep(topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode), dim3(ctx->g.n_regions, batch * ctx->g.Hkv), st);
     return record_hip(ctx, hipGetLastError());
 }
 
 int launch_topk(socket_ctx *ctx, const float *scores, const int32_t *seq_len, const int32_t *k,
                 int batch, int32_t *idx, int32_t *n_selected, int hist_mode, hipStream_t st) {
-    const Geometry &g = ctx->g;
+    const dim3 grid(ctx->g.n_regions, batch * ctx->g.Hkv);
+    TopkArgs a = topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode);
     if (hist_mode == kHistNone) {                // bins from the scores themselves
-        hist_mode = kHistAdaptive;
-        hipLaunchKernelGGL(topk_hist_kernel, dim3(g.n_regions, batch * g.Hkv), dim3(kTopkThreads), 0, st,
-                           topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode));
+        a.adaptive = a.refine = 1;
+        hipLaunchKernelGGL(topk_hist_kernel, grid, dim3(kTopkThreads), 0, st, a);
     }
-    int rc = launch_topk_sweep(ctx, scores, seq_len, k, batch, idx, n_selected, hist_mode, st);
-    if (rc != SOCKET_OK) return rc;
-    const TopkArgs a = topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode);
+    launch_sweep(a, grid, st);
     constexpr size_t lds = kResolveLds > kEmitLds ? kResolveLds : kEmitLds;
     static_assert(lds <= 64 * 1024, "within the default dynamic LDS limit");
-    hipLaunchKernelGGL(topk_emit_kernel, dim3(g.n_regions, batch * g.Hkv), dim3(kTopkThreads), lds, st, a);
+    hipLaunchKernelGGL(topk_emit_kernel, grid, dim3(kTopkThreads), lds, st, a);
     return record_hip(ctx, hipGetLastError());
 }
 

@@ -16,7 +16,8 @@ static_assert(kDigit2Shift >= 0 && kDigit2Shift <= 12, "the low score bits fit o
 constexpr int kRankMax = 2 * kTopkThreads;       // candidates the all-pairs ranking handles
 // threshold record: [0] k_eff, [1] first digit, [2] scores above it, [3] scores in it,
 //                   [4] second digit, [5] scores selected outright, [6] candidates,
-//                   [kThrBinLo], [kThrBinInv] adaptive binning written by the scoring pass
+//                   [kThrBinLo], [kThrBinInv] adaptive binning written by the scoring pass or topk_hist_kernel,
+//                   [kThrSubLo], [kThrSubShift] sub-bins of the threshold bin
 
 struct TopkArgs {
     const float *scores;
@@ -37,7 +38,14 @@ struct TopkArgs {
     int pre_shift;        // the ordering step fetches the first 2^pre_shift entries of every region up front
     int Hkv, max_n, max_k;
     int adaptive;         // candidates share an adaptive bin, not the two leading digits
+    int refine;           // bins from a sample: hist2 splits a threshold bin that holds more than kSplitMin
+                          // scores into sub-bins; the emit kernel clears it itself (counters[kTicket])
 };
+// (short lists are ranked in pairs by every workgroup of the row: 191 candidates 19.6 us a select
+// of 32768 x 8, 314 22.8, 641 41; by sub-bin 19 to 20 whatever their number)
+constexpr int kSplitMin = 256;
+constexpr int kThrSubLo = 10, kThrSubShift = 11; // words of the record: the sub-bins (first key, step)
+constexpr int kTicket = 2;                       // counter: workgroups of the row that have read hist2
 
 // the argument block for a context's scratch buffers
 inline TopkArgs topk_args(socket_ctx *ctx, const float *scores, const int32_t *seq_len, const int32_t *k,
@@ -52,6 +60,7 @@ inline TopkArgs topk_args(socket_ctx *ctx, const float *scores, const int32_t *s
     a.pre_shift = 0;                                   // 16 * 512 preloads spread over the regions
     while (a.pre_shift < 12 && ((int64_t)g.n_regions << (a.pre_shift + 1)) <= 16 * kTopkThreads) ++a.pre_shift;
     a.Hkv = g.Hkv; a.max_n = g.max_n; a.max_k = g.max_k; a.adaptive = hist_mode == kHistAdaptive;
+    a.refine = 0;
     return a;
 }
 
@@ -410,7 +419,7 @@ __device__ __forceinline__ void topk_resolve_body(const TopkArgs &a, int bh, uin
     // leave the shared scratch clean for the next call
     for (int i = tid; i < kHistBins; i += kTopkThreads) {
         gh1[i] = 0;
-        gh2[i] = 0;
+        if (!a.refine) gh2[i] = 0;                // (else other workgroups of the row may yet read it)
     }
     if (tid < 2) cnt[tid] = 0;
 }

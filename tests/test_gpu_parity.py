@@ -477,6 +477,67 @@ def test_topk_degenerate_inputs():
     ctx.close()
 
 
+def _skewed_row(rng, name, n):
+    """Rows whose cut falls among many scores that any bins of equal width put together."""
+    z, u = rng.standard_normal(n), rng.random(n)
+    row = {
+        "bell": lambda: 0.25 + 0.02 * z,
+        "hot keys": lambda: np.where(u < 0.06, 10.0 + 0.001 * z, z),           # a tight cluster far up
+        "hot block": lambda: np.where((np.arange(n) > n // 3) & (np.arange(n) < n // 3 + n // 16), 0.6 + 0.002 * z, 0.25 + 0.02 * z),
+        "cluster in a cluster": lambda: np.where(u < 0.08, np.where(u < 0.04, 5.0 + 1e-5 * z, 5.0 + 0.01 * z), z),
+        "counts with a soft part": lambda: np.maximum(np.round(8 + 2.5 * z), 0.0) + 1e-4 * u,
+        "counts": lambda: np.maximum(np.round(40 + 6 * z), 0.0),
+        "heavy tail": lambda: np.exp(4 * z),
+        "negative tail": lambda: -np.exp(3 * z),
+        "seventy decades": lambda: z * np.exp(20 * rng.standard_normal(n)),
+        "next to each other": lambda: np.float32(1.0) + (rng.integers(0, 3000, n) * 2.0 ** -23),   # every float from 1 on
+        "two values": lambda: np.where(u < 0.5, 1.0, 2.0),
+        "infinities": lambda: np.where(u < 0.3, np.inf, np.where(u < 0.6, -np.inf, z)),
+    }[name]()
+    with np.errstate(over="ignore"):
+        return row.astype(np.float32)
+
+
+SKEWED = ["bell", "hot keys", "hot block", "cluster in a cluster", "counts with a soft part", "counts", "heavy tail",
+          "negative tail", "seventy decades", "next to each other", "two values", "infinities"]
+
+
+@pytest.mark.parametrize("n,ks", [(300, [1, 130, 300]), (4096, [1000]), (4097, [260, 3000]), (40000, [1, 1300, 20000]), (131072, [2048, 327])])
+def test_topk_rows_of_any_shape(n, ks):
+    """Exact for every shape of row, in one context, row kinds in turn: the counts of sub-bins that a
+    long candidate list leaves behind are cleared for the next call, and for the other entry points."""
+    _need_gpu()
+    rng = np.random.default_rng(n)
+    rows = [np.stack([_skewed_row(rng, SKEWED[(i + j) % len(SKEWED)], n) for j in range(4)]) for i in range(len(SKEWED))]
+    cap = (n + 15) // 16 * 16
+    ctx = sk.Context(sk.make_params(64, 4, 4, 16, 4, sk.BF16, 1, cap, max(ks)))
+    pad = np.full((1, 4, cap), np.nan, dtype=np.float32)
+    for s in rows:
+        pad[0, :, :n] = s
+        for k in ks:
+            idx, nsel = run_topk(ctx, pad, [n], [k], 1, 4, max(ks))
+            check_topk(idx, nsel, pad[:, :, :n], [n], [k])
+    ctx.close()
+
+
+@pytest.mark.parametrize("name", ["hot keys", "cluster in a cluster", "counts with a soft part", "negative tail", "seventy decades"])
+def test_topk_time_does_not_depend_on_the_rows_shape(name):
+    """No row costs three times what a bell costs, unless thousands of its scores are equal."""
+    _need_gpu()
+    n, k, H = 131072, 2048, 8
+    rng = np.random.default_rng(3)
+    ctx = sk.Context(sk.make_params(64, H, H, 16, 4, sk.BF16, 1, n, k))
+    idx = torch.zeros((1, H, k), dtype=torch.int32, device="cuda")
+    nsel = torch.zeros((1, H), dtype=torch.int32, device="cuda")
+    lens, kk, us = hz.i32([n]), hz.i32([k]), []
+    for kind in ("bell", name):
+        sc = torch.from_numpy(np.stack([_skewed_row(rng, kind, n) for _ in range(H)])[None]).cuda()
+        us.append(_least_us(lambda: ctx.topk_select(sc, lens, kk, 1, idx, nsel)))
+    assert us[1] <= 3 * us[0], us
+    ctx.close()
+
+
+
 def test_topk_long_row_uses_several_bitmap_passes():
     _need_gpu()
     n = 131072 * 2 + 64
