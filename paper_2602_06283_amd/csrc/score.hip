@@ -1617,7 +1617,7 @@ __global__ __launch_bounds__(kScoreThreads, (MODE == kDirect && S == 4 && PAGED)
                 const int n4 = (int)(a.table_words >> 2);
                 constexpr int B8 = 8;                // independent loads in flight per thread
                 int i0 = tid;
-                if (!BATCHED && S == 4 && gridDim.y <= 16)   // whole batches (a 64 KB table is one): no load under a condition (8 heads: 131072 keys 13.6 -> 13.4 us, 32768 of a capacity of 131072 6.9 -> 6.5; 32 heads measured slower, 26.8 -> 27.9 at 65536 keys, rows of 32 ids too, and so did a table that changes inside a run)
+                if (!BATCHED && gridDim.y <= 16)     // whole batches (a 64 KB table is one): no load under a condition (8 heads of 64 tables: 131072 keys 13.6 -> 13.4 us, 32768 of a capacity of 131072 6.9 -> 6.5; 32 heads measured slower, 26.8 -> 27.9 at 65536 keys, and so did a table that changes inside a run)
                     for (; i0 + (B8 - 1) * kScoreThreads < n4; i0 += B8 * kScoreThreads) {
                         f32x4_t t[B8];
 #pragma unroll
@@ -2238,11 +2238,14 @@ int launch_score_keys(socket_ctx *ctx, const void *codes, const float *vnorm,
     //    keys 7.4 / 8.2, 32768 5.5 / 5.7; 56000 8.6 / 8.1).  A single head: two (262144 keys 6.3 /
     //    5.9).  Smaller tables load too fast to be worth it (64 tables of 6 planes, 50000 keys
     //    7.8 / 6.9; of 5, 32768 keys 5.1 / 4.9);
-    //  - one sequence of several chunks, between two and three units a wavefront: two per CU then
-    //    leave most of the second turn idle (100 tables of 6 planes, 40960 keys 11.5 / 14.0).
+    //  - one sequence of several chunks, from two to four units a wavefront: two per CU then leave
+    //    most of the second turn idle (100 tables of 6 planes, 40960 keys 11.5 / 14.0, 64000 14.4 /
+    //    15.7).  Paged caches to three (40960 keys 13.6 / 14.8, 64000 18.1 / 16.9); one head: two.
     const int wg_keys = (kScoreThreads / 64) * kScoreU * (64 / g.S);
     int64_t nslot = ((int64_t)batch * g.max_n + wg_keys - 1) / wg_keys;
-    const bool single = batch == 1 && nslot <= (g.Hkv > 1 ? 768 : 512) / g.Hkv + 1 && (g.R == 256 || (g.rounds > 1 && nslot > 512 / g.Hkv));
+    const int units = 256 / g.Hkv;                 // a workgroup per CU: one unit for each of its wavefronts
+    const bool single = batch == 1 && (g.R == 256 && g.rounds == 1 ? nslot <= (g.Hkv > 1 ? 3 : 2) * units + 1
+                                       : g.Hkv > 1 && g.rounds > 1 && nslot > 2 * units && nslot <= (g.page > 0 ? 3 : 4) * units);
     const bool wide = g.table_words * 4 > 72 * 1024 && (g.Hkv <= 16 || (int64_t)batch * g.Hkv * g.max_n * g.Lpad < (224ll << 20));
     const bool one_per_cu = g.mode == kDirect && (g.S == 1 || wide || single);
     const int per_head = (one_per_cu ? 256 : 512) / g.Hkv;
