@@ -11,7 +11,8 @@
 //                      sign bit and packed into a per-key bit matrix in LDS.
 //   hash_f32_kernel    fp32 keys, or fewer than 64 rows of bf16 keys: fp32 MFMA
 //                      (v_mfma_f32_32x32x2_f32), W held in registers.
-//   hash_rows_kernel   up to four rows, or groups too wide for hash_f32_kernel: fp32 FMA, one
+//   hash_rows_kernel   up to four rows, or groups too wide for hash_f32_kernel (9 or 10 planes at
+//                      d = 256, in groups of 32 tables): fp32 FMA, one
 //                      thread per projection column, sign bits gathered with a wavefront ballot.
 // The last three end in pack_codes(), which cuts the bit matrix into P-bit bucket ids and writes
 // them in the rotated order the scoring kernel reads.
@@ -46,7 +47,7 @@ struct HashArgs {
 // sequence i's run and the units up to its end.  Workgroups that share units out over this row do
 // equal work whatever the lengths are; shared out sequence by sequence, one long run in a batch of
 // short ones was left to the few workgroups of its own sequence (16384 keys among 15 x 100, 8 heads:
-// bf16, d = 256, 64 tables of 8 planes 323 us, 47 now; fp32, d = 64, 60 tables of 10 690 / 153; in a
+// bf16, d = 256, 64 tables of 8 planes 323 us, 47 now; fp32, d = 64, 60 tables of 10 682 / 175; in a
 // batch of equal lengths the look-up costs 1 to 2 us).
 template <int SHIFT> struct SeqUnits {
     int count, begin, group;

@@ -64,7 +64,7 @@ def check_codes(layer, codes_t, rows_of):
 # ------------------------------------------------------------------ a1: hash_keys
 
 @pytest.mark.parametrize("kv_dtype,n,L,P", [
-    (wl.F32, 4096, 32, 8),      # the tiny configuration's shape (fp32 FMA kernel)
+    (wl.F32, 4096, 32, 8),      # the tiny configuration's shape (fp32 matrix kernel)
     (wl.BF16, 3000 // 16 * 16 + 16, 64, 8),   # MFMA kernel, several 64-row tiles, ragged count below
     (wl.BF16, 2048, 16, 4),
     (wl.BF16, 2048, 128, 8),    # two column chunks of 64 tables
@@ -116,7 +116,7 @@ def test_hash_keys_append_one_row(kv_dtype, P):
     raw = hz.rows_from_device(codes, layer.L, P)
     fill = hz.fill_id(P)
     assert (raw[0, :, :100] == fill).all() and (raw[0, :, 101:] == fill).all()
-    # a short unaligned range goes through the 16-row kernel
+    # a short unaligned range goes through the fp32 matrix kernel
     codes = run_hash(ctx, layer, [3, 490, 0], [21, 22, 0], 22)
     check_codes(layer, codes, lambda b: ([3, 490, 0][b], [21, 22, 0][b]))
     ctx.close()
@@ -842,7 +842,8 @@ def test_decode_step_select_paths_agree(case):
     """Inside socket_decode_step the select starts from what the scoring pass leaves: a
     histogram with bins sized from the bucket-probability tables when the scores are
     unweighted, and, when k is a small part of the sequence, lists of the scores above a guessed
-    bin.  The separate socket_topk_select call histograms leading digits of the scores itself.
+    bin.  The separate socket_topk_select call lays its bins from a sample of the scores, and the
+    scores' exponents; it shares the sweep with the fused step, the oracle tests share nothing.
     All are exact, so they must pick the same tokens - also when nearly all scores tie (tau -> 0
     makes them collision counts, tau -> inf makes them all L/R, identical keys make them one
     value), when k covers the whole sequence, and with value norms (bins then also scaled by a
