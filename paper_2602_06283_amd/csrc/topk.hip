@@ -39,13 +39,13 @@ __device__ __forceinline__ uint32_t sampled_bin(float v, float lo, float inv) {
 // (lo, inv) from a sample: every workgroup takes a mean and a deviation from the same 512 scores of
 // the row, spread evenly, so all of them (and, through the threshold record, the sweep) bin alike.
 // Scores further than four deviations from the mean are left out and both taken again, so that a
-// few spikes do not widen the bins.  A share f of a row's scores that lies all below its mean - c
-// deviations has c < sqrt((1 - f) / f) (one-sided Chebyshev, with the row's own mean and deviation),
-// and the largest f of them lies above mean - sqrt(f / (1 - f)) deviations: 0.34 for f = 0.1, 0.58
-// for 0.25.  The bins start half a deviation or one below the mean there, a 512th of a deviation
-// wide at their start.  That is a rule of thumb: a sample stands for the row, and a cluster of close
-// scores, or a spread over decades, can leave many scores in the bin of the cut.  The sweep then
-// counts them by sub-bin and emit_long goes on from there; the select is exact for any bins.
+// few spikes do not widen the bins.  By the one-sided Chebyshev inequality the largest share f of
+// any numbers lies above their mean - sqrt(f / (1 - f)) deviations: 0.34 for f = 0.1, 0.58 for 0.25.
+// The bins start half a deviation or one below the mean there, a 512th of a deviation wide at their
+// start.  That is a rule of thumb, for a (trimmed) sample only stands for the row; where the cut
+// lies below, or a cluster of close scores or a spread over decades puts many scores into one bin,
+// the sweep counts them by sub-bin and emit_long goes on from there.  The select is exact for any
+// bins.
 // 131072 scores x 8 heads, k = 2048, us, with adaptive bins alone / now (sign and exponent in the bin,
 // sub-bins): a bell 14.3 / 14.8, 6 % in a tight cluster far up 130 / 24, clusters in a cluster 84 / 24,
 // counts with a small soft part 59 / 24, a long tail below 257 / 21, seventy decades 685 / 17; 32768

@@ -534,6 +534,20 @@ def test_topk_time_does_not_depend_on_the_rows_shape(name):
         sc = torch.from_numpy(np.stack([_skewed_row(rng, kind, n) for _ in range(H)])[None]).cuda()
         us.append(_least_us(lambda: ctx.topk_select(sc, lens, kk, 1, idx, nsel)))
     assert us[1] <= 3 * us[0], us
+    check_topk(idx.cpu().numpy(), nsel.cpu().numpy(), sc.cpu().numpy(), [n], [k])     # after a hundred calls on the same scratch
+    # and as a graph, eager calls on other rows between the replays
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with sk.Graph.capture(stream) as graph:
+        ctx.topk_select(sc, lens, kk, 1, idx, nsel, stream=stream)
+    other, idx2, nsel2 = sc.flip(-1).contiguous(), torch.zeros_like(idx), torch.zeros_like(nsel)
+    for _ in range(3):
+        idx.zero_()
+        graph.launch(torch.cuda.current_stream())
+        ctx.topk_select(other, lens, kk, 1, idx2, nsel2)
+        torch.cuda.synchronize()
+        check_topk(idx.cpu().numpy(), nsel.cpu().numpy(), sc.cpu().numpy(), [n], [k])
+    graph.close()
     ctx.close()
 
 
