@@ -345,10 +345,11 @@ __device__ __forceinline__ void finish_row(const TopkArgs &a, int bh, uint32_t k
 // threshold sub-bin and goes through the whole list: candidates above that sub-bin are kept, those
 // in it counted by what is left of their keys (a bin spans an octave at most, so a sub-bin 4096
 // keys), and of those that tie on the last key the smallest positions are kept.  The region is
-// written through a bitmap; nobody waits for another workgroup.  Returns false where the sub-bin
-// holds more than LDS does (mass ties).
-//   (Bound by the list, which each of the row's workgroups reads from L2.)
-__device__ __forceinline__ bool emit_long(const TopkArgs &a, int bh, int reg, uint32_t k_eff, uint32_t above, uint32_t n_cand,
+// written through a bitmap; nobody waits for another workgroup.
+//   (Bound by the list, which each of the row's workgroups reads from L2: once, three times where
+//   the sub-bin holds more than LDS does.  131072 x 8 equal scores, k = 2048: 192 us; 1387 refined
+//   digit by digit by one workgroup.)
+__device__ __forceinline__ void emit_long(const TopkArgs &a, int bh, int reg, uint32_t k_eff, uint32_t above, uint32_t n_cand,
                                           uint32_t *lds) {
     constexpr int NT = kTopkThreads, PER = kHistBins / NT, RPER = kRefineBins / NT;
     static_assert(kSlice == 8 * NT, "a thread emits the eight positions of a bitmap byte");
@@ -374,24 +375,13 @@ __device__ __forceinline__ bool emit_long(const TopkArgs &a, int bh, int reg, ui
     uint32_t *ticket = a.counters + (int64_t)bh * kCounterStride + kTicket;
     uint32_t turn = 0;
     if (tid == 0) turn = atomicAdd(ticket, 1u);
-    auto clear = [&]() {                                         // (late: the ticket is a round trip to memory)
-        if (tid == 0) s_n = turn == gridDim.x - 1;
-        __syncthreads();
-        if (s_n) {
-            for (int j = tid; j < kHistBins; j += NT) gh2[j] = 0;
-            if (tid == 0) *ticket = 0;
-        }
-    };
-    if (n2 > (uint32_t)kRankMax) {
-        clear();
-        return false;
-    }
     if (reg == 0) finish_row(a, bh, k_eff, false);
     // ---- the candidates, and what earlier regions hold
     const uint32_t *selcnt = a.sel_cnt + (int64_t)bh * a.n_regions;
     const uint32_t *ckey = a.cand_key + (int64_t)bh * a.max_n;
     const int32_t *cidx = a.cand_idx + (int64_t)bh * a.max_n;
     const int32_t *entries = a.sel_regions + ((int64_t)bh * a.n_regions + reg) * kSlice;
+    __syncthreads();                                             // (every thread has its t2, need2, n2)
     for (int j = tid; j < padded_size<kRefineBins, RPER>(); j += NT) h[j] = 0;
     if (tid < 4) res[tid] = 0;
     auto mark = [&](uint32_t *map, int32_t pos) { atomicOr(&map[(pos % kSlice) >> 5], 1u << (pos & 31)); };
@@ -405,45 +395,61 @@ __device__ __forceinline__ bool emit_long(const TopkArgs &a, int bh, int reg, ui
         if (r < reg) ++earlier;
         if (r == reg) mark(bitmap, pos);
     };
-    constexpr int U = 4;                                         // loads in flight
-    for (uint32_t i0 = tid; i0 < n_cand; i0 += U * NT) {
-        uint32_t key[U];
-        int32_t pos[U];
+    auto for_list = [&](auto f) {
+        constexpr int U = 4;                                     // loads in flight
+        for (uint32_t i0 = tid; i0 < n_cand; i0 += U * NT) {
+            uint32_t key[U];
+            int32_t pos[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t i = min(i0 + u * NT, n_cand - 1);
-            key[u] = ckey[i];
-            pos[u] = cidx[i];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t d = i0 + u * NT < n_cand ? sub.of(key[u]) + 1 : 0u;
-            if (d > t2 + 1) keep(pos[u]);
-            if (d == t2 + 1) {
-                const uint32_t at = atomicAdd(&s_n, 1u);         // (n2 of them)
-                if (at < (uint32_t)kRankMax) ck[at] = ((unsigned long long)key[u] << 32) | (0x7fffffffu - (uint32_t)pos[u]);
+            for (int u = 0; u < U; ++u) {
+                const uint32_t i = min(i0 + u * NT, n_cand - 1);
+                key[u] = ckey[i];
+                pos[u] = cidx[i];
             }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i0 + u * NT < n_cand) f(sub.of(key[u]), key[u], pos[u]);
         }
-    }
+    };
+    const bool fits = n2 <= (uint32_t)kRankMax;
+    for_list([&](uint32_t d, uint32_t key, int32_t pos) {
+        if (d > t2) keep(pos);
+        if (d == t2 && fits) {
+            const uint32_t at = atomicAdd(&s_n, 1u);             // (n2 of them)
+            if (at < (uint32_t)kRankMax) ck[at] = ((unsigned long long)key << 32) | (uint32_t)pos;
+        }
+    });
     __syncthreads();
     // ---- the threshold sub-bin, key by key
+    auto for_sub = [&](auto f) {
+        if (fits)
+            for (uint32_t i = tid; i < n2; i += NT) f((uint32_t)(ck[i] >> 32), (int32_t)(uint32_t)ck[i]);
+        else
+            for_list([&](uint32_t d, uint32_t key, int32_t pos) {
+                if (d == t2) f(key, pos);
+            });
+    };
     const uint32_t k0 = sub.lo + (t2 << sub.shift);
-    auto digit = [&](unsigned long long c) { const uint32_t key = (uint32_t)(c >> 32); return key <= k0 ? 0u : min(key - k0, (uint32_t)(kRefineBins - 1)); };
-    for (uint32_t i = tid; i < n2; i += NT) atomicAdd(&h[padded<RPER>((int)digit(ck[i]))], 1u);
+    auto digit = [&](uint32_t key) { return key <= k0 ? 0u : min(key - k0, (uint32_t)(kRefineBins - 1)); };
+    for_sub([&](uint32_t key, int32_t) {
+        // (lanes with the first one's digit add together: equal scores come by the thousand)
+        const uint32_t d = digit(key), first = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+        const uint64_t same = __ballot(d == first);
+        if (d != first) atomicAdd(&h[padded<RPER>((int)d)], 1u);
+        else if ((tid & 63) == __ffsll((unsigned long long)same) - 1) atomicAdd(&h[padded<RPER>((int)d)], (uint32_t)__popcll(same));
+    });
     __syncthreads();
     find_threshold<kRefineBins>(h, need2, res, tmp);             // 1 <= need2 <= n2
     const uint32_t t3 = res[0];
     uint32_t ties_earlier = 0;
-    for (uint32_t i = tid; i < n2; i += NT) {
-        const unsigned long long c = ck[i];
-        const uint32_t d = digit(c);
-        const int32_t pos = (int32_t)(0x7fffffffu - (uint32_t)c);
+    for_sub([&](uint32_t key, int32_t pos) {
+        const uint32_t d = digit(key);
         if (d > t3) keep(pos);
         if (d == t3) {
             if (pos / kSlice < reg) ++ties_earlier;
             if (pos / kSlice == reg) mark(ties, pos);
         }
-    }
+    });
     uint32_t base, before, total;
     block_excl_scan(earlier, &base, tmp);                        // (barriers: the bitmaps are complete)
     block_excl_scan(ties_earlier, &before, tmp);
@@ -458,11 +464,15 @@ __device__ __forceinline__ bool emit_long(const TopkArgs &a, int bh, int reg, ui
     int32_t *out = a.idx + (int64_t)bh * a.max_k;
     for (int j = 0; j < 8; ++j)
         if ((byte & (1u << j)) && at < k_eff) out[at++] = reg * kSlice + 8 * tid + j;
-    clear();
-    return true;
+    // (late: the ticket is a round trip to memory)
+    if (tid == 0) s_n = turn == gridDim.x - 1;
+    __syncthreads();
+    if (s_n) {
+        for (int j = tid; j < kHistBins; j += NT) gh2[j] = 0;
+        if (tid == 0) *ticket = 0;
+    }
 }
 constexpr size_t kLongLds = (size_t)(kRankMax + 4) * 8 + (size_t)(padded_size<kRefineBins, kRefineBins / kTopkThreads>() + 2 * (kSlice / 32)) * 4;
-static_assert(kLongLds <= kResolveLds, "the long list's LDS fits the emit kernel's");
 
 // The index row, from the sweep's regions and candidates: one workgroup per region, each ranking
 // the few candidates itself.  The regions one after the other are the positions selected outright
@@ -472,7 +482,8 @@ static_assert(kLongLds <= kResolveLds, "the long list's LDS fits the emit kernel
 // heads.  A whole select, launches back to back: 13.6 us, 19.6 with that kernel and two digit
 // histograms; 131072 scores 14.8 / 22.9; 16 x 20000 scores 24.4 / 28.7; 4 M scores 39 us / 7.6 ms.)
 // A list too long for pairs goes to emit_long (sampled bins) or, beyond two candidates per thread,
-// to the row's first workgroup (topk_resolve_body: bins of the scoring pass, and mass ties).
+// to the row's first workgroup (topk_resolve_body: bins of the scoring pass).
+template <bool REFINE>
 __global__ __launch_bounds__(kTopkThreads, 4) void topk_emit_kernel(TopkArgs a) {
     extern __shared__ __align__(16) uint32_t emit_lds[];
     constexpr int NT = kTopkThreads, NW = NT / 64;
@@ -500,14 +511,13 @@ __global__ __launch_bounds__(kTopkThreads, 4) void topk_emit_kernel(TopkArgs a) 
     asm volatile("" ::: "memory");               // (keeps the loads together, ahead of what uses them)
     const uint32_t k_eff = t0, above = k_eff ? t5 : 0u, n_cand = k_eff ? t6 : 0u;
     const uint32_t need = k_eff - above;
-    if (n_cand > (uint32_t)(a.refine ? kSplitMin : kRankMax)) {
-        if (!a.refine || !emit_long(a, bh, reg, k_eff, above, n_cand, emit_lds)) {
-            if (reg == 0) topk_resolve_body(a, bh, emit_lds);
-        }
+    if (n_cand > (uint32_t)(REFINE ? kSplitMin : kRankMax)) {
+        if constexpr (REFINE) emit_long(a, bh, reg, k_eff, above, n_cand, emit_lds);
+        else if (reg == 0) topk_resolve_body(a, bh, emit_lds);
         return;
     }
     int32_t *out = a.idx + (int64_t)bh * a.max_k;
-    if (reg == 0) finish_row(a, bh, k_eff, !a.refine);   // (nobody wrote hist2 where the list is short)
+    if (reg == 0) finish_row(a, bh, k_eff, !REFINE);   // (nobody wrote hist2 where the list is short)
     if (k_eff == 0) return;
     // ---- rank the candidates on (score, smaller position first); kept ones in earlier regions
     //      are counted, those of this region listed
@@ -598,9 +608,10 @@ int launch_topk(socket_ctx *ctx, const float *scores, const int32_t *seq_len, co
         hipLaunchKernelGGL(topk_hist_kernel, grid, dim3(kTopkThreads), 0, st, a);
     }
     launch_sweep(a, grid, st);
-    constexpr size_t lds = kResolveLds > kEmitLds ? kResolveLds : kEmitLds;
-    static_assert(lds <= 64 * 1024, "within the default dynamic LDS limit");
-    hipLaunchKernelGGL(topk_emit_kernel, grid, dim3(kTopkThreads), lds, st, a);
+    constexpr size_t long_lds = kLongLds > kEmitLds ? kLongLds : kEmitLds, resolve_lds = kResolveLds > kEmitLds ? kResolveLds : kEmitLds;
+    static_assert(long_lds <= 64 * 1024 && resolve_lds <= 64 * 1024, "within the default dynamic LDS limit");
+    if (a.refine) hipLaunchKernelGGL(topk_emit_kernel<true>, grid, dim3(kTopkThreads), long_lds, st, a);
+    else hipLaunchKernelGGL(topk_emit_kernel<false>, grid, dim3(kTopkThreads), resolve_lds, st, a);
     return record_hip(ctx, hipGetLastError());
 }
 

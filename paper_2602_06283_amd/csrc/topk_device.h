@@ -419,7 +419,7 @@ __device__ __forceinline__ void topk_resolve_body(const TopkArgs &a, int bh, uin
     // leave the shared scratch clean for the next call
     for (int i = tid; i < kHistBins; i += kTopkThreads) {
         gh1[i] = 0;
-        if (!a.refine) gh2[i] = 0;                // (else other workgroups of the row may yet read it)
+        gh2[i] = 0;
     }
     if (tid < 2) cnt[tid] = 0;
 }

@@ -520,9 +520,9 @@ def test_topk_rows_of_any_shape(n, ks):
     ctx.close()
 
 
-@pytest.mark.parametrize("name", ["hot keys", "cluster in a cluster", "counts with a soft part", "negative tail", "seventy decades"])
+@pytest.mark.parametrize("name", ["counts", "hot keys", "cluster in a cluster", "counts with a soft part", "negative tail", "seventy decades"])
 def test_topk_time_does_not_depend_on_the_rows_shape(name):
-    """No row costs three times what a bell costs, unless thousands of its scores are equal."""
+    """No row costs three times what a bell costs, unless tens of thousands of its scores are equal."""
     _need_gpu()
     n, k, H = 131072, 2048, 8
     rng = np.random.default_rng(3)
