@@ -1,6 +1,8 @@
 // Alg. 3, TopK step: exact selection of the k largest scores per (sequence, KV head), spread over
 // many workgroups: a histogram, a sweep with the threshold bin it gives, and an ordered emit.
 //
+//   topk_row_kernel     short rows: the whole select of a row in one workgroup, one launch.
+// Longer rows:
 //   topk_hist_kernel    histogram of every valid score, in bins from a sample of the row and the
 //                       scores' exponents (sampled_bin); the fused decode step gets an adaptive
 //                       one from the scoring pass instead, with bins sized from the
@@ -115,6 +117,24 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(TopkArgs a) {
         if (h[j]) atomicAdd(&gh[j], h[j]);
 }
 
+// First score key of a bin and of the bin after it (the bin function is non-decreasing in the
+// score).  Whole wavefronts: the lower half searches for the one, the upper half for the other.
+template <typename F> __device__ __forceinline__ uint2 bin_keys(uint32_t bin, F bin_of) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t want = bin + (lane >> 5);
+    uint32_t below = 0;                                          // a key below the one sought, or 0
+#pragma unroll 1
+    for (int sh = 27; sh >= 0; sh -= sh > 2 ? 5 : 2) {           // 32 probes a step
+        const uint32_t probe = below + ((uint32_t)(lane & 31) << sh);
+        const uint32_t key = min(max(probe, 0x007fffffu), 0xff800000u);   // -inf .. +inf
+        const float v = __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
+        const uint64_t hit = __ballot(probe <= 0xff800000u && bin_of(v) < want);
+        const int n = __popc(lane < 32 ? (uint32_t)hit : (uint32_t)(hit >> 32));
+        below += (uint32_t)max(n - 1, 0) << sh;
+    }
+    return make_uint2((uint32_t)__builtin_amdgcn_readlane((int)below, 0) + 1, (uint32_t)__builtin_amdgcn_readlane((int)below, 32) + 1);
+}
+
 // Sub-bins of a threshold bin of sampled_bin: equal steps of the score key between the bin's two
 // ends.  Non-decreasing in the score, and the same for all workgroups of a row.
 struct SubBins {
@@ -124,24 +144,11 @@ struct SubBins {
         return key <= lo ? 0u : min((key - lo) >> shift, (uint32_t)(kHistBins - 1));
     }
 };
-// (whole wavefronts: the lower half searches for the bin's first key, the upper half for the next bin's)
 __device__ __forceinline__ SubBins sub_bins(uint32_t bin, float bin_lo, float bin_inv) {
-    const int lane = threadIdx.x & 63;
-    const uint32_t want = bin + (lane >> 5);
-    uint32_t below = 0;                                          // a key below the one sought, or 0
-#pragma unroll 1
-    for (int sh = 27; sh >= 0; sh -= sh > 2 ? 5 : 2) {           // 32 probes a step
-        const uint32_t probe = below + ((uint32_t)(lane & 31) << sh);
-        const uint32_t key = min(max(probe, 0x007fffffu), 0xff800000u);   // -inf .. +inf
-        const float v = __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
-        const uint64_t hit = __ballot(probe <= 0xff800000u && sampled_bin(v, bin_lo, bin_inv) < want);
-        const int n = __popc(lane < 32 ? (uint32_t)hit : (uint32_t)(hit >> 32));
-        below += (uint32_t)max(n - 1, 0) << sh;
-    }
-    const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)below, 0) + 1, k1 = (uint32_t)__builtin_amdgcn_readlane((int)below, 32) + 1;
-    const uint32_t last = k1 > k0 + 1 ? k1 - k0 - 1 : 1u;        // the largest offset
+    const uint2 k = bin_keys(bin, [&](float v) { return sampled_bin(v, bin_lo, bin_inv); });
+    const uint32_t last = k.y > k.x + 1 ? k.y - k.x - 1 : 1u;    // the largest offset
     const int bits = 32 - __clz((int)last);
-    return SubBins{k0, bits > kHistBits ? bits - kHistBits : 0};
+    return SubBins{k.x, bits > kHistBits ? bits - kHistBits : 0};
 }
 
 // First threshold digit, then the histogram of the second digit over the scores in it.
@@ -583,6 +590,307 @@ __global__ __launch_bounds__(kTopkThreads, 4) void topk_emit_kernel(TopkArgs a) 
 }
 constexpr size_t kEmitLds = (size_t)(kRankMax + 4) * 8 + (size_t)kRankMax * 4;
 
+// ---------------------------------------------------------------------------------------
+// Short rows in one launch: one workgroup of 16 wavefronts per (sequence, KV head) holds the row in
+// registers (NC chunks of 4096 scores), so the select is a chain of phases in LDS:
+//   bins     as topk_hist_kernel lays them, from a sample of 1024 scores; those below the first bin,
+//            half of a row and more, are only counted
+//   refine   while the threshold bin holds more than kRowPairs scores that are not all kept: 2048
+//            equal steps of the score key over it, and again, down to a single key (three rounds
+//            at most: exact for any bins)
+//   cut      up to kRowPairs scores are ranked in pairs on (score, smaller position first); more
+//            only where they tie on one key: the smallest positions, by a scan.  The selection is
+//            what is not below one (key, position)
+//   emit     slots in position order, from a scan over the kept scores
+// Nothing is kept between calls; no scratch.
+// Bound by the instructions of one compute unit (40 a score) behind 6 us of launch, loads and phases.
+// us a select, this kernel / three launches: 8 rows of 1000 scores 7.4 / 12.1, 4096 7.8 / 12.9, 12000
+// 9.7 / 13.2, 20000 11.7 / 13.5, 24000 12.6 / 13.3, 32768 15.4 / 13.2; 128 rows of 3000 7.9 / 13.0,
+// 16384 10.9 / 20.2, 32768 15.5 / 29.9, 49000 20.4 / 36.9; 64 rows of 32768 14.8 / 20.5, 32 rows 14.7
+// / 14.7.  So up to kRowRegions regions of 4096 scores always, up to kRowRegionsMany from kRowRowsMany
+// rows on, where three launches fill the card.  Rows whose cut falls among close scores cost a round
+// or two more (20000 scores, 128 rows 18.0 / 33.0; equal scores 26.4 / 100).
+// ---------------------------------------------------------------------------------------
+constexpr int kRowThreads = 1024, kRowWaves = kRowThreads / 64;
+constexpr int kRowPairs = 256;
+constexpr int kRowRegions = 5, kRowRegionsMany = 12, kRowRowsMany = 64;
+static_assert(kSlice == 4 * kRowThreads, "a chunk is four scores a thread");
+
+// exclusive prefix sum over the workgroup; *total gets the sum
+__device__ __forceinline__ uint32_t row_excl_scan(uint32_t v, uint32_t *total, uint32_t *tmp) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t x = wave_incl_scan(v);
+    if (lane == 63) tmp[threadIdx.x >> 6] = x;
+    __syncthreads();
+    const uint32_t t = wave_incl_scan(lane < kRowWaves ? tmp[lane] : 0u);
+    __syncthreads();
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)t, kRowWaves - 1);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    return (w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)t, w > 0 ? w - 1 : 0) : 0u) + x - v;
+}
+
+template <int NC>
+__global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
+    __shared__ __align__(16) uint32_t h[kHistBins];
+    __shared__ __align__(16) unsigned long long ck[kRowPairs + 4];
+    __shared__ __align__(16) uint32_t tot[256];                  // [chunk][wavefront]
+    __shared__ uint32_t tmp[kRowWaves], s_valid[kRowWaves], res[3], s_n;
+    __shared__ float s_part[2][4][kRowWaves];
+    __shared__ uint2 s_keys;
+    __shared__ unsigned long long s_cut, s_next;
+    static_assert(NC * kRowWaves <= 256, "four totals a lane");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bh = blockIdx.x, b = bh / a.Hkv;
+    const float ninf = -__builtin_inff();
+    const float *row = a.scores + (int64_t)bh * a.max_n;
+    u32x4_t w[NC];                                               // the scores' bits, or their keys if the cut is negative
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int i = c * kSlice + 4 * tid;
+        w[c] = __float_as_uint(ninf);
+        if (i < a.max_n) w[c] = *(const u32x4_t *)(row + i);
+    }
+    const int seq = clamp_len(a.seq_len[b], a.max_n);
+    const uint32_t kreq = (uint32_t)clamp_len(a.k[b], a.max_k);
+    for (int j = tid; j < kHistBins; j += kRowThreads) h[j] = 0;
+    if (tid == 0) s_n = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if ((c + 1) * kSlice > seq) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (c * kSlice + 4 * tid + j >= seq) w[c][j] = __float_as_uint(ninf);
+        }
+
+    // ---- bins: a wavefront's sample is every fourth of its 256 scores of one chunk
+    float lo, inv;
+    {
+        const int live = max(1, (seq + kSlice - 1) / kSlice), mine = wave % live;
+        float v = __uint_as_float(w[0][0]);
+#pragma unroll
+        for (int c = 1; c < NC; ++c)
+            if (c == mine) v = __uint_as_float(w[c][0]);
+        const bool there = mine * kSlice + 4 * tid < seq;
+        bool use = there && fabsf(v) < 3.0e38f;                  // (false for NaN and both infinities)
+        float mu = 0.0f, sigma = 0.0f, finite = 0.0f, sampled = 0.0f;
+#pragma unroll
+        for (int round = 0; round < 2; ++round) {
+            const float n0 = row_sum<64>(use ? 1.0f : 0.0f), n1 = row_sum<64>(use ? v : 0.0f);
+            const float n3 = round == 0 ? row_sum<64>(there ? 1.0f : 0.0f) : 0.0f;
+            if (lane == 0) {
+                s_part[round][0][wave] = n0;
+                s_part[round][1][wave] = n1;
+                s_part[round][3][wave] = n3;
+            }
+            __syncthreads();
+            const float cnt = row_sum<16>(s_part[round][0][lane & 15]);
+            mu = row_sum<16>(s_part[round][1][lane & 15]) / fmaxf(cnt, 1.0f);
+            if (round == 0) {
+                finite = cnt;
+                sampled = row_sum<16>(s_part[0][3][lane & 15]);
+            }
+            const float d = use ? v - mu : 0.0f;
+            const float n2 = row_sum<64>(d * d);
+            if (lane == 0) s_part[round][2][wave] = n2;
+            __syncthreads();
+            sigma = sqrtf(row_sum<16>(s_part[round][2][lane & 15]) / fmaxf(cnt, 1.0f));
+            use = use && fabsf(v - mu) <= 4.0f * sigma;
+        }
+        sigma = fminf(fmaxf(sigma, fmaxf(fabsf(mu) * 1e-6f, 1e-30f)), 1.0e37f);
+        const float share = (float)kreq * sampled / fmaxf((float)seq * finite, 1.0f);   // of the finite scores
+        lo = mu - (share <= 0.1f ? 0.5f : share <= 0.25f ? 1.0f : 4.0f) * sigma;
+        inv = 1.0f / (share <= 0.25f ? sigma : 4.0f * sigma);
+        lo = fabsf(lo) < 3.0e38f && lo != 0.0f ? lo : -0.0f;     // (never +0: what compares as not below lo has lo's key or a larger one)
+    }
+    uint32_t valid = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float v = __uint_as_float(w[c][j]);
+            valid += (uint32_t)__popcll(__ballot(v >= -3.40282347e38f));   // (selectable(); the compiler's ballot of v > -inf counts NaN)
+            if (v >= lo) atomicAdd(&h[sampled_bin(v, lo, inv)], 1u);
+        }
+    if (lane == 0) s_valid[wave] = valid;
+    __syncthreads();
+
+    // the bin of h with the target-th score from the top in it: the bin, the scores above it, those in
+    // it (in res, complete after the barrier); returns the number of scores in h
+    auto find = [&](uint32_t target) {
+        const uint2 c = *(const uint2 *)&h[kHistBins - 2 - 2 * tid];
+        uint32_t total;
+        const uint32_t above = row_excl_scan(c.x + c.y, &total, tmp);
+        if (above < target && target <= above + c.x + c.y) {
+            const bool upper = target <= above + c.y;
+            res[0] = (uint32_t)(kHistBins - 2 - 2 * tid + (upper ? 1 : 0));
+            res[1] = upper ? above : above + c.y;
+            res[2] = upper ? c.y : c.x;
+        }
+        __syncthreads();
+        return total;
+    };
+    const uint32_t n_valid = (uint32_t)row_sum<16>((float)s_valid[lane & 15]);
+    const uint32_t k_eff = min(kreq, n_valid);
+    int32_t *out = a.idx + (int64_t)bh * a.max_k;
+    if (tid == 0) a.n_selected[bh] = (int32_t)k_eff;
+    for (int i = (int)k_eff + tid; i < a.max_k; i += kRowThreads) out[i] = -1;
+    if (k_eff == 0) return;
+
+    // ---- the scores in question: keys k0 .. k0 + span - 1, n_in of them, `need` to keep
+    const uint32_t total = find(k_eff);
+    const bool below = total < k_eff;                            // the cut lies below the bins
+    if (wave == 0) {
+        const uint2 keys = below ? make_uint2(1, order_key(lo)) : bin_keys(res[0], [&](float v) { return v >= lo ? sampled_bin(v, lo, inv) : 0u; });
+        if (lane == 0) s_keys = keys;
+    }
+    uint32_t need = k_eff - (below ? total : res[1]), n_in = below ? n_valid - total : res[2];
+    __syncthreads();
+    uint32_t k0 = s_keys.x, span = s_keys.y - k0;
+    // Scores from +0 on compare by their bits, counted from +0; a cut below that takes keys (0 for
+    // what is never selected, NaN and -inf)
+    uint32_t zero = 0x80000000u;                                 // the key that w counts from
+    if (k0 < zero) {
+        zero = 0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float v = __uint_as_float(w[c][j]);
+                w[c][j] = selectable(v) ? order_key(v) : 0u;
+            }
+    }
+    while (n_in != need && n_in > (uint32_t)kRowPairs && span > 1) {
+        const int bits = 32 - __clz((int)(span - 1)), shift = bits > kHistBits ? bits - kHistBits : 0;
+        for (int j = tid; j < kHistBins; j += kRowThreads) h[j] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t off = w[c][j] - (k0 - zero), d = off >> shift;
+                if (off < span) {                                // (lanes with the first one's step add together: equal scores come by the thousand)
+                    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+                    const uint64_t same = __ballot(d == first);
+                    if (d != first) atomicAdd(&h[d], 1u);
+                    else if (lane == __ffsll((unsigned long long)same) - 1) atomicAdd(&h[d], (uint32_t)__popcll(same));
+                }
+            }
+        __syncthreads();
+        find(need);
+        const uint32_t step = res[0] << shift;
+        k0 += step;
+        span = min(span - step, 1u << shift);
+        need -= res[1];
+        n_in = res[2];
+        __syncthreads();
+    }
+    // slots in position order of the scores that flags(c) picks: at[c] = those before this thread's four of chunk c
+    uint32_t at[NC];
+    auto place = [&](auto flags) {
+        constexpr int NP = (NC + 1) / 2;
+        uint32_t excl[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {                           // two chunks to a word: a wavefront has 256 scores of each
+            const uint32_t n = (uint32_t)__popc(flags(2 * p)) | (2 * p + 1 < NC ? (uint32_t)__popc(flags(2 * p + 1)) << 16 : 0u);
+            const uint32_t x = wave_incl_scan(n);
+            excl[p] = x - n;
+            if (lane == 63) {
+                tot[(2 * p) * kRowWaves + wave] = x & 0xffffu;
+                if (2 * p + 1 < NC) tot[(2 * p + 1) * kRowWaves + wave] = x >> 16;
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (4 * lane < NC * kRowWaves) v = *(const uint4 *)&tot[4 * lane];
+            const uint32_t sum = v.x + v.y + v.z + v.w, e = wave_incl_scan(sum) - sum;
+            *(uint4 *)&tot[4 * lane] = make_uint4(e, e + v.x, e + v.x + v.y, e + v.x + v.y + v.z);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < NC; ++c) at[c] = tot[c * kRowWaves + wave] + ((excl[c >> 1] >> (16 * (c & 1))) & 0xffffu);
+    };
+    // ---- selected: keys from cut on; with ties across the cut, those equal to it only up to position cut_pos
+    uint32_t cut = k0;
+    int32_t cut_pos = 0x7fffffff;
+    if (n_in != need && n_in <= (uint32_t)kRowPairs) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t off = w[c][j] - (k0 - zero);
+                if (off < span) {
+                    const uint32_t n = atomicAdd(&s_n, 1u);      // (n_in of them)
+                    if (n < (uint32_t)kRowPairs) ck[n] = ((unsigned long long)(k0 + off) << 32) | (0x7fffffffu - (uint32_t)(c * kSlice + 4 * tid + j));
+                }
+            }
+        if (tid < 4) ck[n_in + tid] = 0;                         // (whole quads; beats nobody)
+        __syncthreads();
+        const uint32_t i = (uint32_t)tid >> 2;                   // four lanes share a candidate
+        if (i < n_in) {
+            const unsigned long long me = ck[i];
+            uint32_t rank = 0;
+            for (uint32_t o = 4 * (tid & 3); o < n_in; o += 16) {
+                const ulonglong2 c0 = *(const ulonglong2 *)&ck[o], c1 = *(const ulonglong2 *)&ck[o + 2];
+                rank += (c0.x > me) + (c0.y > me) + (c1.x > me) + (c1.y > me);
+            }
+            rank += (uint32_t)__builtin_amdgcn_mov_dpp((int)rank, 0xB1, 0xF, 0xF, true);    // lane ^ 1
+            rank += (uint32_t)__builtin_amdgcn_mov_dpp((int)rank, 0x4E, 0xF, 0xF, true);    // lane ^ 2
+            if (rank == need - 1) s_cut = me;                    // the last one kept (its four lanes)
+            if (rank == need) s_next = me;                       // the first one left
+        }
+        __syncthreads();
+        cut = (uint32_t)(s_cut >> 32);
+        if ((uint32_t)(s_next >> 32) == cut) cut_pos = (int32_t)(0x7fffffffu - (uint32_t)s_cut);
+    } else if (n_in != need) {                                   // ties on one key: the position of the need-th of them
+        auto ties = [&](int c) {
+            uint32_t f = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f |= (uint32_t)(w[c][j] == k0 - zero) << j;
+            return f;
+        };
+        place(ties);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            uint32_t f = ties(c);
+            if (at[c] < need && need <= at[c] + (uint32_t)__popc(f)) {
+                for (uint32_t m = need - at[c]; m > 1; --m) f &= f - 1;
+                s_cut = (unsigned long long)(c * kSlice + 4 * tid + __ffs((int)f) - 1);
+            }
+        }
+        __syncthreads();
+        cut_pos = (int32_t)s_cut;
+    }
+    // ---- the row of positions, in ascending order
+    const uint32_t from = cut - zero, top = 0xff800000u - cut;   // kept: from .. +inf, with ties less those behind cut_pos
+    uint32_t flags[(NC + 7) / 8] = {};                           // four bits a chunk
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) flags[c / 8] |= (uint32_t)(w[c][j] - from <= top) << (4 * (c % 8) + j);
+    if (cut_pos != 0x7fffffff)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (w[c][j] == from && c * kSlice + 4 * tid + j > cut_pos) flags[c / 8] &= ~(1u << (4 * (c % 8) + j));
+    auto kept = [&](int c) { return (flags[c / 8] >> (4 * (c % 8))) & 15u; };
+    place(kept);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        for (uint32_t f = kept(c), i = at[c]; f != 0; f &= f - 1, ++i) out[i] = c * kSlice + 4 * tid + __ffs((int)f) - 1;
+}
+
+typedef void (*row_fn_t)(TopkArgs);
+template <int NC> static row_fn_t row_kernel(int n_regions) {
+    if constexpr (NC > kRowRegionsMany) return nullptr;
+    else return n_regions == NC ? topk_row_kernel<NC> : row_kernel<NC + 1>(n_regions);
+}
+// (by the context's capacity: the lengths are on the device)
+static row_fn_t pick_row(int n_regions, int rows) {
+    return n_regions <= (rows >= kRowRowsMany ? kRowRegionsMany : kRowRegions) ? row_kernel<1>(n_regions) : nullptr;
+}
+
 // Everything up to the sweep: the threshold and the two unordered lists (selected outright,
 // candidates in the threshold bin).  The fused decode step continues from those lists.
 static void launch_sweep(const TopkArgs &a, dim3 grid, hipStream_t st) {
@@ -603,6 +911,12 @@ int launch_topk(socket_ctx *ctx, const float *scores, const int32_t *seq_len, co
                 int batch, int32_t *idx, int32_t *n_selected, int hist_mode, hipStream_t st) {
     const dim3 grid(ctx->g.n_regions, batch * ctx->g.Hkv);
     TopkArgs a = topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode);
+    const int rows = batch * ctx->g.Hkv;
+    const row_fn_t row_fn = hist_mode == kHistNone ? pick_row(ctx->g.n_regions, rows) : nullptr;
+    if (row_fn) {
+        hipLaunchKernelGGL(row_fn, dim3(rows), dim3(kRowThreads), 0, st, a);
+        return record_hip(ctx, hipGetLastError());
+    }
     if (hist_mode == kHistNone) {                // bins from the scores themselves
         a.adaptive = a.refine = 1;
         hipLaunchKernelGGL(topk_hist_kernel, grid, dim3(kTopkThreads), 0, st, a);

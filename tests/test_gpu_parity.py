@@ -520,6 +520,31 @@ def test_topk_rows_of_any_shape(n, ks):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,H,n", [(1, 3, 16), (1, 3, 4096), (1, 3, 4112), (1, 3, 20480), (1, 3, 20496), (8, 8, 36880), (8, 8, 49152), (8, 8, 49168)])
+def test_topk_of_short_rows(B, H, n):
+    """Rows at the edges of the one-launch select's chunks and of its rule, cuts below zero, among zeros
+    of both signs and among ties, lengths short of the capacity: the oracle's selection exactly."""
+    _need_gpu()
+    rng = np.random.default_rng(n)
+    kinds = SKEWED + ["zeros", "empty"]
+    s = np.full((B, H, n), np.nan, dtype=np.float32)
+    lens = [n if b % 3 == 0 else max(1, int(n * rng.random())) for b in range(B)]
+    for r in range(B * H):
+        name = kinds[(r + n // 16) % len(kinds)]
+        row = np.where(rng.random(n) < 0.5, np.float32(-0.0), np.float32(0.0)) if name == "zeros" else np.full(n, -np.inf) if name == "empty" else _skewed_row(rng, name, n)
+        if name == "zeros":
+            row[rng.integers(0, n, n // 16)] = -1e-42
+        s[r // H, r % H] = row
+    order = np.where(np.isnan(s), -np.inf, np.where((s == 0) & np.signbit(s), -1e-300, s.astype(np.float64)))   # -0.0 ranks below +0.0
+    most = min(n, 3000)
+    ctx = sk.Context(sk.make_params(64, H, H, 16, 4, sk.BF16, B, n, most))
+    for share in (0.001, 0.03, 0.5, 1.0):
+        k = [max(1, int(share * m)) for m in lens]
+        idx, nsel = run_topk(ctx, s, lens, k, B, H, most)
+        check_topk(idx, nsel, order, lens, k)
+    ctx.close()
+
+
 @pytest.mark.parametrize("name", ["counts", "hot keys", "cluster in a cluster", "counts with a soft part", "negative tail", "seventy decades"])
 def test_topk_time_does_not_depend_on_the_rows_shape(name):
     """No row costs three times what a bell costs, unless tens of thousands of its scores are equal."""
