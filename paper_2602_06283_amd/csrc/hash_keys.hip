@@ -576,58 +576,61 @@ __global__ __launch_bounds__(512, D <= 128 ? 4 : 2) void hash_mfma_kernel(HashAr
 // (16 channels x 32 keys); accumulator i of lane (key n, half g) is row 8 (i/4) + 4g + i%4.
 // Row m is given plane (table e, plane pl) with 8e + pl = 16 g + i, so that the 16 sign bits a
 // lane collects from its accumulators are, in order, one half of the key's 32-bit sign word.
-// hash_wfrag_kernel lays W out that way once per call; the main kernel copies it into LDS.
+// cut_fragments lays W out that way.
 // ---------------------------------------------------------------------------------------
-template <int D, int S, int P>
-__global__ __launch_bounds__(256) void hash_wfrag_kernel(HashArgs a, uint4 *wfrag) {
-    constexpr int BPG = P / 2;                 // 32-column blocks per position group of 16 ids (P = 8: 4, P = 4: 2)
-    constexpr int KS = D / 16;
-    const int p = blockIdx.x, chunk = blockIdx.y % a.n_chunks, h = blockIdx.y / a.n_chunks;
-    const int first_table = chunk * 64;
-    const int ntab = min(64, a.L - first_table);
-    const int sub = p / BPG, q = p % BPG;
-    const uint16_t *W = (const uint16_t *)a.W + (int64_t)h * D * a.LP;
-    uint4 *dst = wfrag + ((int64_t)blockIdx.y * (BPG * S) + p) * KS * 64;
-    for (int f = threadIdx.x; f < KS * 64; f += 256) {
-        const int ks = f >> 6, lane = f & 63;
-        const int g = lane >> 5, m = lane & 31;
-        const int bit = 16 * ((m >> 2) & 1) + 4 * (m >> 3) + (m & 3);
-        // (a block holds 32 / P tables: table e of the block in bits [P e, P e + P) of the sign word)
-        const int tt = sub + S * ((32 / P) * q + bit / P);     // chunk-local table
-        const int col = (first_table + tt) * P + bit % P;
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
-        if (tt < ntab) {
-            uint16_t e[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) e[i] = W[(int64_t)(ks * 16 + g * 8 + i) * a.LP + col];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) w[i >> 1] |= (uint32_t)e[i] << (16 * (i & 1));
-        }
-        dst[f] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-}
-
 template <int V> struct IntTag { static constexpr int value = V; };
 
 constexpr int kHash8Threads = 1024;
 
-// the A fragments of `N` 16-byte pieces a workgroup works with, into LDS, up to eight loads in flight per thread
-template <int N, int NT>
-__device__ __forceinline__ void fragments_to_lds(uint4 *wl, const uint4 *src, int tid) {
-    constexpr int PER = (N + NT - 1) / NT, NB = PER < 8 ? PER : 8;
-    constexpr bool EVEN = PER * NT == N && PER % NB == 0;
+// The A fragments of a workgroup of the two fast kernels, cut from W into LDS by the workgroup itself:
+// a thread takes one table (P columns) and eight channels, eight loads of 2 P bytes in flight, and
+// transposes them in registers into P pieces of eight channels each.  (A launch of its own that laid
+// the fragments out in memory first cost 4 to 5 us by itself, 2 to 3 back to back with this one:
+// 777 + 333 rows of (10, 60) with their value norms 18.8 us with it, 16.2 now; 4 heads x 32768 keys,
+// d = 256, 36.1 / 33.9; 4 sequences of 65536 keys, 8 heads of (8, 64), 238.8 / 238.3.)
+// The workgroup's tables are tab0 + (i / NG) * S + i % NG: NG of the S interleaved position groups.
+// Column P j + pl of position group `sub` (j = its j-th table) is bit u % 32 of sign word u / 32,
+// u = P j + pl; wl holds word q of the workgroup's group sl as block sl BPG + q.
+// Pieces of a block are kept at lane ^ frag_turn(sl, q), or the tables that the lanes of a
+// wavefront write side by side would share banks.
+__device__ __forceinline__ int frag_turn(int sl, int q) { return (sl ^ q) & 3; }
+
+template <int D, int S, int P, int NG, int NT>
+__device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int h, int first_table, int ntab, int sub0, int tid) {
+    constexpr int KS = D / 16, BPG = P / 2, NTAB = 16 * NG, ITEMS = NTAB * (D / 8), ND = P / 2;   // ND: dwords of a table's row
+    constexpr int PER = (ITEMS + NT - 1) / NT;
+    static_assert(ND == 2 || ND == 4 || ND == 5, "4, 8 or 10 planes");
+    // rows of W start at any element: L P and the caller's pointer say nothing about alignment
+    struct __attribute__((packed, aligned(2))) Row { uint32_t w[ND]; };
+    const uint16_t *W = (const uint16_t *)a.W + ((int64_t)h * D * a.LP + (int64_t)first_table * P);
 #pragma unroll 1
-    for (int u0 = 0; u0 < PER; u0 += NB) {
-        uint4 v[NB];
+    for (int k = 0; k < PER; ++k) {
+        const int i = tid + k * NT;
+        if (ITEMS % NT != 0 && i >= ITEMS) break;
+        int ti = i % NTAB;
+        const int oct = i / NTAB;                      // channels 8 oct .. 8 oct + 7
+        // (eight adjacent lanes: four groups, both halves of a sign word)
+        if (S == 4 && NG == 4 && P == 8) ti = (ti & ~12) | ((ti >> 1) & 4) | ((ti << 1) & 8);
+        const int j = ti / NG, sl = ti % NG, tt = j * S + sub0 + sl;   // chunk-local table
+        Row r[8];
+        if (tt < ntab) {
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int i = tid + (u0 + u) * NT;
-            v[u] = src[EVEN || i < N ? i : N - 1];
+            for (int c = 0; c < 8; ++c) r[c] = *(const Row *)(W + (int64_t)(oct * 8 + c) * a.LP + tt * P);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+#pragma unroll
+                for (int w = 0; w < ND; ++w) r[c].w[w] = 0u;
         }
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int i = tid + (u0 + u) * NT;
-            if (EVEN || i < N) wl[i] = v[u];
+        for (int pl = 0; pl < P; ++pl) {
+            const uint32_t pick = pl & 1 ? 0x07060302u : 0x05040100u;   // the high or the low halves of two words
+            uint32_t o[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[c] = __builtin_amdgcn_perm(r[2 * c + 1].w[pl >> 1], r[2 * c].w[pl >> 1], pick);
+            const int u = P * j + pl, q = u >> 5, bit = u & 31;
+            const int m = 8 * ((bit >> 2) & 3) + 4 * (bit >> 4) + (bit & 3);   // the MFMA row that becomes this bit
+            wl[((sl * BPG + q) * KS + (oct >> 1)) * 64 + (((oct & 1) * 32 + m) ^ frag_turn(sl, q))] = make_uint4(o[0], o[1], o[2], o[3]);
         }
     }
 }
@@ -647,7 +650,7 @@ template <int D, int S, int P> constexpr int hash8_groups() { return D <= 128 ||
 template <int D> constexpr int hash8_threads() { return D <= 128 ? kHash8Threads : 512; }
 
 template <int D, int S, int P, bool SHARE>
-__global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs a, const uint4 *wfrag) {
+__global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs a) {
     static_assert(P == 8 || P == 4, "one-byte ids of 8 planes, or of 4 (a block's eight nibbles are spread over two words)");
     constexpr int KS = D / 16;                 // MFMA k-steps
     constexpr int BPG = P / 2;                 // 32-column blocks per position group of 16 ids
@@ -673,7 +676,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     const int first_table = chunk * 64;
     const int ntab = min(64, a.L - first_table);
 
-    fragments_to_lds<NCB * KS * 64, NT>(wl, wfrag + (int64_t)row * NCB * KS * 64, tid);
+    cut_fragments<D, S, P, NG, NT>(wl, a, h, first_table, ntab, sub0, tid);
     __syncthreads();
 
     uint32_t *mybits = bits + wave * 256;
@@ -724,7 +727,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
 #pragma unroll 1
         for (int p = 0; p < NCB; ++p) {
             const int sl = p / BPG, sub = sub0 + sl, q = p % BPG;
-            const uint4 *af = wl + (p * KS) * 64 + lane;
+            const uint4 *af = wl + (p * KS) * 64 + (lane ^ frag_turn(sl, q));
             floatx16_t acc0, acc1;
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc0[i] = acc1[i] = 0.0f;
@@ -795,39 +798,11 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
 // string is plane u % 10 of table sub + S (u / 10).  The stored string is that one rotated right
 // by 10 (t mod 16) bits: a rotation of the five words and one funnel shift.
 // ---------------------------------------------------------------------------------------
-template <int D, int S>
-__global__ __launch_bounds__(256) void hash_wfrag10_kernel(HashArgs a, uint4 *wfrag) {
-    constexpr int KS = D / 16;
-    const int p = blockIdx.x, grp = blockIdx.y % a.n_chunks, h = blockIdx.y / a.n_chunks;
-    const int first_table = grp * 16 * S;
-    const int ntab = min(16 * S, a.L - first_table);
-    const int sub = p / 5, q = p % 5;
-    const uint16_t *W = (const uint16_t *)a.W + (int64_t)h * D * a.LP;
-    uint4 *dst = wfrag + ((int64_t)blockIdx.y * (5 * S) + p) * KS * 64;
-    for (int f = threadIdx.x; f < KS * 64; f += 256) {
-        const int ks = f >> 6, lane = f & 63;
-        const int g = lane >> 5, m = lane & 31;
-        const int bit = 16 * ((m >> 2) & 1) + 4 * (m >> 3) + (m & 3);   // bit of the sign word that MFMA row m becomes
-        const int u = 32 * q + bit;
-        const int tt = sub + S * (u / 10);                     // group-local table
-        const int col = (first_table + tt) * 10 + u % 10;
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
-        if (tt < ntab) {
-            uint16_t e[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) e[i] = W[(int64_t)(ks * 16 + g * 8 + i) * a.LP + col];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) w[i >> 1] |= (uint32_t)e[i] << (16 * (i & 1));
-        }
-        dst[f] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-}
-
 // (d = 256: one string per workgroup, 80 KB of fragments)
 template <int D, int S> constexpr int hash10_strings() { return D <= 128 ? S : 1; }
 
 template <int D, int S, bool SHARE>
-__global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArgs a, const uint4 *wfrag) {
+__global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArgs a) {
     constexpr int KS = D / 16;                 // MFMA k-steps
     constexpr int NS = hash10_strings<D, S>(); // strings of the workgroup
     constexpr int NCB = 5 * NS;                // its 32-column blocks
@@ -850,7 +825,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
     }
     const int ntab = max(0, min(GT, a.L - grp * GT));
 
-    fragments_to_lds<NCB * KS * 64, NT>(wl, wfrag + (int64_t)row * NCB * KS * 64, tid);
+    cut_fragments<D, S, 10, NS, NT>(wl, a, h, grp * GT, ntab, sub0, tid);
     __syncthreads();
 
     uint32_t *mybits = bits + wave * 320;
@@ -896,7 +871,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
 #pragma unroll 1
         for (int p = 0; p < NCB; ++p) {
             const int sl = p >= 5 ? 1 : 0, sub = sub0 + sl, q = p - 5 * sl;
-            const uint4 *af = wl + (p * KS) * 64 + lane;
+            const uint4 *af = wl + (p * KS) * 64 + (lane ^ frag_turn(sl, q));
             floatx16_t acc0, acc1;
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc0[i] = acc1[i] = 0.0f;
@@ -980,8 +955,8 @@ static int share_groups(HashArgs *a) {
 // `alone` would have more than one block of the longest run, or one round of workgroups would not do.
 // (A workgroup without a block copies its slab for nothing; asking for the run's length first cost
 // every short run 0.3 us, 4 % at 5000 keys of 16 tables, and gained nothing in ragged batches.)
-typedef void (*fragment_kernel_t)(HashArgs, const uint4 *);
-static void launch_blocks(fragment_kernel_t alone, fragment_kernel_t shared, HashArgs a, const uint4 *wfrag, int rows,
+typedef void (*fragment_kernel_t)(HashArgs);
+static void launch_blocks(fragment_kernel_t alone, fragment_kernel_t shared, HashArgs a, int rows,
                           int batch, int max_rows, int threads, size_t lds, hipStream_t st) {
     const int nblocks = (max_rows + 63) / 64;
     int groups = batch, per = std::max(1, std::min(nblocks, 256 / (rows * batch)));
@@ -991,7 +966,7 @@ static void launch_blocks(fragment_kernel_t alone, fragment_kernel_t shared, Has
         per = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)nblocks * a.group, 256 / (rows * groups)));
     }
     // (shared: slab by slab, so that few of the slabs go through each XCD's L2)
-    hipLaunchKernelGGL(share ? shared : alone, share ? dim3(rows, per, groups) : dim3(per, rows, groups), dim3(threads), lds, st, a, wfrag);
+    hipLaunchKernelGGL(share ? shared : alone, share ? dim3(rows, per, groups) : dim3(per, rows, groups), dim3(threads), lds, st, a);
 }
 
 // dynamic LDS of hash_mfma8_kernel: the W slab as fragments, one id-word row per key of every wavefront's block
@@ -1028,44 +1003,41 @@ template <int D> static int hash_prepare_d() {
 int hash_prepare(int d) { return d == 64 ? hash_prepare_d<64>() : d == 128 ? hash_prepare_d<128>() : hash_prepare_d<256>(); }
 
 template <int D, int S, int P>
-static int launch_mfma8(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_rows, hipStream_t st) {
+static int launch_mfma8(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
     constexpr int NT = hash8_threads<D>(), PARTS = S / hash8_groups<D, S, P>();
     a.tables_per_chunk = 16 * S;
     a.n_chunks = S == 4 ? (a.L + 63) / 64 : 1;
-    // W as MFMA fragments, once per call
-    hipLaunchKernelGGL((hash_wfrag_kernel<D, S, P>), dim3(P / 2 * S, Hkv * a.n_chunks), dim3(256), 0, st, a, wfrag);
     fragment_kernel_t shared = nullptr;
     if constexpr (D == 256) shared = hash_mfma8_kernel<D, S, P, true>;
-    launch_blocks(hash_mfma8_kernel<D, S, P, false>, shared, a, wfrag, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash8_lds<D, S, P>(), st);
+    launch_blocks(hash_mfma8_kernel<D, S, P, false>, shared, a, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash8_lds<D, S, P>(), st);
     return SOCKET_OK;
 }
 template <int D, int P>
-static int launch_mfma8(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_rows, hipStream_t st) {
-    return a.S == 4 ? launch_mfma8<D, 4, P>(a, wfrag, Hkv, batch, max_rows, st)
-         : a.S == 2 ? launch_mfma8<D, 2, P>(a, wfrag, Hkv, batch, max_rows, st)
-                    : launch_mfma8<D, 1, P>(a, wfrag, Hkv, batch, max_rows, st);
+static int launch_mfma8(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
+    return a.S == 4 ? launch_mfma8<D, 4, P>(a, Hkv, batch, max_rows, st)
+         : a.S == 2 ? launch_mfma8<D, 2, P>(a, Hkv, batch, max_rows, st)
+                    : launch_mfma8<D, 1, P>(a, Hkv, batch, max_rows, st);
 }
 template <int D>
-static int launch_mfma8(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_rows, hipStream_t st) {
-    return a.P == 8 ? launch_mfma8<D, 8>(a, wfrag, Hkv, batch, max_rows, st)
-                    : launch_mfma8<D, 4>(a, wfrag, Hkv, batch, max_rows, st);
+static int launch_mfma8(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
+    return a.P == 8 ? launch_mfma8<D, 8>(a, Hkv, batch, max_rows, st)
+                    : launch_mfma8<D, 4>(a, Hkv, batch, max_rows, st);
 }
 
 template <int D, int S>
-static int launch_mfma10(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_rows, hipStream_t st) {
+static int launch_mfma10(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
     constexpr int NT = hash8_threads<D>(), PARTS = S / hash10_strings<D, S>();
     a.tables_per_chunk = 16 * S;
     a.n_chunks = a.Lpad / (16 * S);            // groups, padding groups included (their ids are zero)
-    hipLaunchKernelGGL((hash_wfrag10_kernel<D, S>), dim3(5 * S, Hkv * a.n_chunks), dim3(256), 0, st, a, wfrag);
     fragment_kernel_t shared = nullptr;
     if constexpr (D == 256) shared = hash_mfma10_kernel<D, S, true>;
-    launch_blocks(hash_mfma10_kernel<D, S, false>, shared, a, wfrag, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash10_lds<D, S>(), st);
+    launch_blocks(hash_mfma10_kernel<D, S, false>, shared, a, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash10_lds<D, S>(), st);
     return SOCKET_OK;
 }
 template <int D>
-static int launch_mfma10(HashArgs a, uint4 *wfrag, int Hkv, int batch, int max_rows, hipStream_t st) {
-    return a.GT == 32 ? launch_mfma10<D, 2>(a, wfrag, Hkv, batch, max_rows, st)
-                      : launch_mfma10<D, 1>(a, wfrag, Hkv, batch, max_rows, st);
+static int launch_mfma10(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
+    return a.GT == 32 ? launch_mfma10<D, 2>(a, Hkv, batch, max_rows, st)
+                      : launch_mfma10<D, 1>(a, Hkv, batch, max_rows, st);
 }
 
 // Runs of up to four rows stay with the FMA kernel's one-row workgroups while W is small: both are a
@@ -1177,17 +1149,17 @@ int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int
     } else if (max_rows < 64) {
         rc = launch_f32<uint16_t>(a, g.Hkv, batch, max_rows, st);
     } else {
-        const bool fast8 = ctx->wfrag != nullptr && (g.P == 8 || g.P == 4);   // one-byte ids of 8 or 4 planes
-        const bool fast10 = ctx->wfrag != nullptr && g.P == 10;    // packed ids in groups of 32 or 16 tables
+        const bool fast8 = ctx->fast_hash && (g.P == 8 || g.P == 4);   // one-byte ids of 8 or 4 planes
+        const bool fast10 = ctx->fast_hash && g.P == 10;    // packed ids in groups of 32 or 16 tables
         switch (g.d) {
-            case 64: rc = fast8 ? launch_mfma8<64>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
-                          : fast10 ? launch_mfma10<64>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
+            case 64: rc = fast8 ? launch_mfma8<64>(a, g.Hkv, batch, max_rows, st)
+                          : fast10 ? launch_mfma10<64>(a, g.Hkv, batch, max_rows, st)
                                    : launch_mfma<64>(a, g.Hkv, batch, max_rows, st); break;
-            case 128: rc = fast8 ? launch_mfma8<128>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
-                           : fast10 ? launch_mfma10<128>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
+            case 128: rc = fast8 ? launch_mfma8<128>(a, g.Hkv, batch, max_rows, st)
+                           : fast10 ? launch_mfma10<128>(a, g.Hkv, batch, max_rows, st)
                                     : launch_mfma<128>(a, g.Hkv, batch, max_rows, st); break;
-            case 256: rc = fast8 ? launch_mfma8<256>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
-                           : fast10 ? launch_mfma10<256>(a, (uint4 *)ctx->wfrag, g.Hkv, batch, max_rows, st)
+            case 256: rc = fast8 ? launch_mfma8<256>(a, g.Hkv, batch, max_rows, st)
+                           : fast10 ? launch_mfma10<256>(a, g.Hkv, batch, max_rows, st)
                                     : launch_mfma<256>(a, g.Hkv, batch, max_rows, st); break;
             default: return SOCKET_EUNSUPPORTED;
         }

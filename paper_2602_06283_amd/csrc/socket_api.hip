@@ -197,9 +197,7 @@ int socket_create(socket_ctx **out, const socket_params *p) {
     const bool fast8 = g.kv_dtype == SOCKET_BF16 && (g.P == 8 || g.P == 4) && g.cb == 1 && g.mode == kDirect;
     // the same for 10-plane tables with packed ids (groups of 32 tables, or one group of 16)
     const bool fast10 = g.kv_dtype == SOCKET_BF16 && g.P == 10 && g.mode == kSplit && (g.GT == 32 || g.GT == 16);
-    const bool fast_hash = fast8 || fast10;
-    const int64_t sz_wfrag = fast8 ? (int64_t)g.Hkv * ((g.L + 63) / 64) * g.d * 1024
-                             : fast10 ? (int64_t)g.Hkv * (g.Lpad / g.GT) * (5 * g.GT / 16) * (g.d / 16) * 1024 : 0;
+    ctx->fast_hash = fast8 || fast10;
     const int64_t sz_hist = 2 * BH * kHistBins * 4;   // first- and second-digit histograms
     const int64_t sz_cnt = BH * (kCounterStride + kThrStride) * 4;
     const int64_t sz_cand = BH * g.max_n * 4;
@@ -207,12 +205,12 @@ int socket_create(socket_ctx **out, const socket_params *p) {
     const int64_t sz_regions = BH * g.n_regions * kSlice * 4, sz_selcnt = BH * g.n_regions * 4;
     const int64_t sz_seq = (int64_t)g.max_batch * 4;
     const int64_t sz_part = (int64_t)g.max_batch * g.Hq * kMaxSplits * (g.d + 2) * 4;
-    ctx->scratch_bytes = sz_wfrag + sz_tables + sz_tstats + sz_sub + sz_hist + sz_cnt + 2 * sz_cand + sz_staged + sz_regions + sz_selcnt + sz_part + sz_seq;
+    ctx->scratch_bytes = sz_tables + sz_tstats + sz_sub + sz_hist + sz_cnt + 2 * sz_cand + sz_staged + sz_regions + sz_selcnt + sz_part + sz_seq;
     bool ok = score_prepare(g) == SOCKET_OK &&
               hipMalloc((void **)&ctx->tables, sz_tables) == hipSuccess &&
               hipMalloc((void **)&ctx->tstats, sz_tstats) == hipSuccess &&
               (sz_sub == 0 || hipMalloc((void **)&ctx->subprobs, sz_sub) == hipSuccess) &&
-              (!fast_hash || (hipMalloc(&ctx->wfrag, sz_wfrag) == hipSuccess && hash_prepare(g.d) == SOCKET_OK)) &&
+              (!ctx->fast_hash || hash_prepare(g.d) == SOCKET_OK) &&
               hipMalloc((void **)&ctx->hist, sz_hist) == hipSuccess &&
               hipMalloc((void **)&ctx->counters, sz_cnt) == hipSuccess &&
               hipMalloc((void **)&ctx->cand_key, sz_cand) == hipSuccess &&
@@ -240,7 +238,7 @@ int socket_create(socket_ctx **out, const socket_params *p) {
 
 int socket_destroy(socket_ctx *ctx) {
     if (!ctx) return SOCKET_EINVAL;
-    void *bufs[] = {ctx->tables, ctx->tstats, ctx->subprobs, ctx->wfrag, ctx->hist, ctx->counters, ctx->cand_key, ctx->cand_idx, ctx->staged, ctx->sel_regions, ctx->sel_cnt, ctx->partials, ctx->seq_scratch};
+    void *bufs[] = {ctx->tables, ctx->tstats, ctx->subprobs, ctx->hist, ctx->counters, ctx->cand_key, ctx->cand_idx, ctx->staged, ctx->sel_regions, ctx->sel_cnt, ctx->partials, ctx->seq_scratch};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     delete ctx;

@@ -88,7 +88,7 @@ struct socket_ctx {
     float *subprobs;      // ids that share bytes only: [max_batch*Hkv][Lu][2^Pu] group-mean probabilities of the caller's tables
     const float *vnorm_sampled;   // the value-norm array the last projection pass sampled (or null)
     int pending_hist;     // HistMode of what socket_score_keys_binned left for socket_topk_select_binned
-    void *wfrag;          // W cut into MFMA fragments for the fast prefill hash (null when that path does not apply)
+    bool fast_hash;       // the fast prefill hash applies (hash_mfma8_kernel, hash_mfma10_kernel)
     uint32_t *hist;       // [2][max_batch*Hkv][kHistBins]
     uint32_t *counters;   // [max_batch*Hkv][kCounterStride] counters, then [max_batch*Hkv][kThrStride] records
     uint32_t *cand_key;   // [max_batch*Hkv][max_n]

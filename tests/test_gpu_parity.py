@@ -149,6 +149,25 @@ def test_hash_keys_unaligned_row_ranges_through_the_mfma_kernels():
         ctx.close()
 
 
+@pytest.mark.parametrize("d,L,P", [(64, 64, 8), (128, 64, 8), (128, 17, 8), (128, 65, 4), (128, 61, 10), (256, 45, 10)])
+def test_hash_keys_projections_at_any_element(d, L, P):
+    """The fast kernels cut W in pieces of a table's planes: a W that starts at an odd element, in a
+    buffer that ends with it, gives the ids of an aligned one bit for bit."""
+    _need_gpu()
+    layer = small_layer(seed=17, B=1, Hq=2, Hkv=2, d=d, n=128, L=L, P=P, k=16)
+    ctx = hz.make_ctx(layer)
+    K, W = hz.dev(layer.K, layer.kv_dtype), hz.dev(layer.W, layer.kv_dtype)
+    odd = torch.empty(W.numel() + 1, dtype=W.dtype, device="cuda")
+    odd[1:] = W.reshape(-1)
+    got = []
+    for w in (W, odd[1:].view(W.shape)):
+        got.append(hz.new_codes((1, 2), 128, L, P, fill=0x55))
+        ctx.hash_keys(K, w, hz.i32([0]), hz.i32([128]), 1, 128, got[-1])
+    check_codes(layer, got[0], lambda b: (0, 128))
+    assert torch.equal(got[0], got[1])
+    ctx.close()
+
+
 @pytest.mark.parametrize("L,P", [(64, 8), (100, 8), (24, 8), (9, 8), (64, 4), (65, 4), (31, 4), (7, 4), (60, 10), (20, 10), (11, 10)])
 def test_hash_keys_wide_heads(L, P):
     """d = 256: a chunk's position groups (strings, for packed ids) are shared out to two workgroups;
