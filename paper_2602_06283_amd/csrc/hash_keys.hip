@@ -595,25 +595,23 @@ constexpr int kHash8Threads = 1024;
 // wavefront write side by side would share banks.
 __device__ __forceinline__ int frag_turn(int sl, int q) { return (sl ^ q) & 3; }
 
-template <int D, int S, int P, int NG, int NT>
-__device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int h, int first_table, int ntab, int sub0, int tid) {
+// `meanwhile` is called once, the thread's last loads of W on their way.
+template <int D, int S, int P, int NG, int NT, typename F>
+__device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int h, int first_table, int ntab, int sub0, int tid, F &&meanwhile) {
     constexpr int KS = D / 16, BPG = P / 2, NTAB = 16 * NG, ITEMS = NTAB * (D / 8), ND = P / 2;   // ND: dwords of a table's row
     constexpr int PER = (ITEMS + NT - 1) / NT;
     static_assert(ND == 2 || ND == 4 || ND == 5, "4, 8 or 10 planes");
     // rows of W start at any element: L P and the caller's pointer say nothing about alignment
     struct __attribute__((packed, aligned(2))) Row { uint32_t w[ND]; };
     const uint16_t *W = (const uint16_t *)a.W + ((int64_t)h * D * a.LP + (int64_t)first_table * P);
-#pragma unroll 1
-    for (int k = 0; k < PER; ++k) {
-        const int i = tid + k * NT;
-        if (ITEMS % NT != 0 && i >= ITEMS) break;
+    auto cut = [&](int i, auto &&between) __attribute__((always_inline)) {
         int ti = i % NTAB;
         const int oct = i / NTAB;                      // channels 8 oct .. 8 oct + 7
         // (eight adjacent lanes: four groups, both halves of a sign word)
         if (S == 4 && NG == 4 && P == 8) ti = (ti & ~12) | ((ti >> 1) & 4) | ((ti << 1) & 8);
         const int j = ti / NG, sl = ti % NG, tt = j * S + sub0 + sl;   // chunk-local table
         Row r[8];
-        if (tt < ntab) {
+        if ((ITEMS % NT == 0 || i < ITEMS) && tt < ntab) {
 #pragma unroll
             for (int c = 0; c < 8; ++c) r[c] = *(const Row *)(W + (int64_t)(oct * 8 + c) * a.LP + tt * P);
         } else {
@@ -622,6 +620,8 @@ __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int 
 #pragma unroll
                 for (int w = 0; w < ND; ++w) r[c].w[w] = 0u;
         }
+        between();
+        if (ITEMS % NT != 0 && i >= ITEMS) return;
 #pragma unroll
         for (int pl = 0; pl < P; ++pl) {
             const uint32_t pick = pl & 1 ? 0x07060302u : 0x05040100u;   // the high or the low halves of two words
@@ -632,13 +632,26 @@ __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int 
             const int m = 8 * ((bit >> 2) & 3) + 4 * (bit >> 4) + (bit & 3);   // the MFMA row that becomes this bit
             wl[((sl * BPG + q) * KS + (oct >> 1)) * 64 + (((oct & 1) * 32 + m) ^ frag_turn(sl, q))] = make_uint4(o[0], o[1], o[2], o[3]);
         }
-    }
+    };
+#pragma unroll 1
+    for (int k = 0; k + 1 < PER; ++k) cut(tid + k * NT, []() {});
+    cut(tid + (PER - 1) * NT, meanwhile);
 }
+
+// Barrier after LDS writes that leaves loads from memory in flight (__syncthreads waits for them).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 struct OneSequence {                                   // (what stands for SeqUnits where there is nothing to share out)
     __device__ __forceinline__ explicit OneSequence(const HashArgs &) {}
     __device__ __forceinline__ int total() const { return 0; }
     __device__ __forceinline__ void find(int, int *, int *, int *, int *) const {}
+};
+
+// What a launch of the fast kernels knows of its runs of keys
+enum HashRuns {
+    kRunsLong = 0,      // a wavefront works on several 64-key blocks of its sequence, or on none
+    kRunsShared = 1,    // the blocks of several sequences are dealt out as one row (SeqUnits)
+    kRunsShort = 2,     // no wavefront has more than one block
 };
 
 // Shape of a workgroup: NG of the chunk's S position groups (a chunk's workgroups are its S / NG
@@ -649,9 +662,10 @@ struct OneSequence {                                   // (what stands for SeqUn
 template <int D, int S, int P> constexpr int hash8_groups() { return D <= 128 || S * P / 2 <= 8 ? S : S / 2; }
 template <int D> constexpr int hash8_threads() { return D <= 128 ? kHash8Threads : 512; }
 
-template <int D, int S, int P, bool SHARE>
+template <int D, int S, int P, int RUNS>
 __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs a) {
     static_assert(P == 8 || P == 4, "one-byte ids of 8 planes, or of 4 (a block's eight nibbles are spread over two words)");
+    constexpr bool SHARE = RUNS == kRunsShared, SHORT = RUNS == kRunsShort;
     constexpr int KS = D / 16;                 // MFMA k-steps
     constexpr int BPG = P / 2;                 // 32-column blocks per position group of 16 ids
     constexpr int NG = hash8_groups<D, S, P>();
@@ -675,9 +689,6 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     const int sub0 = part * NG;                        // the workgroup's first position group
     const int first_table = chunk * 64;
     const int ntab = min(64, a.L - first_table);
-
-    cut_fragments<D, S, P, NG, NT>(wl, a, h, first_table, ntab, sub0, tid);
-    __syncthreads();
 
     uint32_t *mybits = bits + wave * 256;
     const int n = lane & 31, g = lane >> 5;
@@ -715,17 +726,36 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     // 64-key blocks are dealt round-robin, to the workgroups before their wavefronts: short runs and
     // last rounds then spread over the compute units (8 heads, 64 tables of 8 planes: 8192 keys
     // 18.6 us, 29.0 with whole workgroups filled first; 40000 keys 44 / 55; full rounds alike)
-    const int nblocks = SHARE ? runs.total() : (count + 63) >> 6;   // (not before the slab: nothing there waits for the lengths)
-    const int stride = slots * NW;
-    int blk = slot + wave * slots;
-    if (blk < nblocks) load_keys(blk);
+    // Short runs: while that leaves wavefronts without a block, two or four of them share one, NG / parts
+    // of its position groups each, and the keys are fetched while W is cut (8 heads, (8, 64): 777 keys
+    // 15.9 us with the launch that cut W, 7.4 now; 4096 16.7 / 10.8; (10, 60) 777 keys 12.9 / 7.1.  Long runs keep the loop of whole blocks: with bounds of its own for every
+    // wavefront 131072 keys took 132 us, 127 without).
+    int nblocks = 0, stride = slots * NW, blk = slot + wave * slots, parts = 1, p0 = 0;
+    cut_fragments<D, S, P, NG, NT>(wl, a, h, first_table, ntab, sub0, tid, [&]() __attribute__((always_inline)) {
+        if (!SHORT) return;
+        nblocks = (count + 63) >> 6;
+        parts = NG;
+        while (parts > 1 && nblocks > slots * (NW / parts)) parts >>= 1;
+        stride = slots * (NW / parts);
+        const int w = __builtin_amdgcn_readfirstlane(wave);
+        p0 = (w % parts) * (NCB / parts);
+        blk = slot + (w / parts) * slots;
+        if (blk < nblocks) load_keys(blk);
+    });
+    if (SHORT) lds_barrier();
+    else {
+        __syncthreads();
+        nblocks = SHARE ? runs.total() : (count + 63) >> 6;   // (not before the slab: nothing there waits for the lengths)
+        if (blk < nblocks) load_keys(blk);
+    }
+    const int pb = SHORT ? p0 : 0, pe = SHORT ? p0 + NCB / parts : NCB;
     for (; blk < nblocks; blk += stride) {
         const int r0 = SHARE ? shared_r0 : blk * 64;
         const int64_t prow = key_row(r0 + lane);        // the key this lane packs
         const int rot = (begin + r0 + lane) & 15;
         uint4 done[NG > 1 ? NG - 1 : 1];                // the key's position groups before the last, kept until the row is whole
 #pragma unroll 1
-        for (int p = 0; p < NCB; ++p) {
+        for (int p = pb; p < pe; ++p) {
             const int sl = p / BPG, sub = sub0 + sl, q = p % BPG;
             const uint4 *af = wl + (p * KS) * 64 + (lane ^ frag_turn(sl, q));
             floatx16_t acc0, acc1;
@@ -772,7 +802,9 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
                 o.w = __builtin_amdgcn_alignbyte(x0, x3, sh);
                 // the groups of a key go out together: 64 adjacent bytes (four groups), written back
                 // as one whole line instead of four partial ones a quarter of the block apart
-                if (NG > 1 && sl == 0) done[0] = o;
+                if (NG > 1 && SHORT && parts > 1) {
+                    if (prow >= 0) ((uint4 *)(Cb + prow * (int64_t)a.Lpad + first_table))[sub] = o;
+                } else if (NG > 1 && sl == 0) done[0] = o;
                 else if (NG > 2 && sl == 1) done[NG > 2 ? 1 : 0] = o;
                 else if (NG > 2 && sl == 2) done[NG > 2 ? 2 : 0] = o;
                 else if (prow >= 0) {
@@ -801,8 +833,9 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
 // (d = 256: one string per workgroup, 80 KB of fragments)
 template <int D, int S> constexpr int hash10_strings() { return D <= 128 ? S : 1; }
 
-template <int D, int S, bool SHARE>
+template <int D, int S, int RUNS>
 __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArgs a) {
+    constexpr bool SHARE = RUNS == kRunsShared, SHORT = RUNS == kRunsShort;
     constexpr int KS = D / 16;                 // MFMA k-steps
     constexpr int NS = hash10_strings<D, S>(); // strings of the workgroup
     constexpr int NCB = 5 * NS;                // its 32-column blocks
@@ -824,9 +857,6 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
         begin = a.row_begin[b];
     }
     const int ntab = max(0, min(GT, a.L - grp * GT));
-
-    cut_fragments<D, S, 10, NS, NT>(wl, a, h, grp * GT, ntab, sub0, tid);
-    __syncthreads();
 
     uint32_t *mybits = bits + wave * 320;
     const int n = lane & 31, g = lane >> 5;
@@ -858,10 +888,26 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
         return ~(both[0] | (both[1] << 16));
     };
 
-    const int nblocks = SHARE ? runs.total() : (count + 63) >> 6;   // (not before the slab: nothing there waits for the lengths)
-    const int stride = slots * NW;
-    int blk = slot + wave * slots;   // (as in hash_mfma8_kernel: workgroups first)
-    if (blk < nblocks) load_keys(blk);
+    // (as in hash_mfma8_kernel: workgroups first; of short runs the keys while W is cut, a block's strings
+    // by two wavefronts where there are enough)
+    int nblocks = 0, stride = slots * NW, blk = slot + wave * slots, parts = 1, p0 = 0;
+    cut_fragments<D, S, 10, NS, NT>(wl, a, h, grp * GT, ntab, sub0, tid, [&]() __attribute__((always_inline)) {
+        if (!SHORT) return;
+        nblocks = (count + 63) >> 6;
+        parts = NS == 2 && nblocks <= slots * (NW / 2) ? 2 : 1;
+        stride = slots * (NW / parts);
+        const int w = __builtin_amdgcn_readfirstlane(wave);
+        p0 = (w % parts) * (NCB / parts);
+        blk = slot + (w / parts) * slots;
+        if (blk < nblocks) load_keys(blk);
+    });
+    if (SHORT) lds_barrier();
+    else {
+        __syncthreads();
+        nblocks = SHARE ? runs.total() : (count + 63) >> 6;   // (not before the slab: nothing there waits for the lengths)
+        if (blk < nblocks) load_keys(blk);
+    }
+    const int pb = SHORT ? p0 : 0, pe = SHORT ? p0 + NCB / parts : NCB;
     for (; blk < nblocks; blk += stride) {
         const int r0 = SHARE ? shared_r0 : blk * 64;
         const int64_t prow = key_row(r0 + lane);        // the key this lane packs
@@ -869,7 +915,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
         uint4 head0 = make_uint4(0, 0, 0, 0);           // string 0, kept until string 1 is there too
         uint32_t tail0 = 0;
 #pragma unroll 1
-        for (int p = 0; p < NCB; ++p) {
+        for (int p = pb; p < pe; ++p) {
             const int sl = p >= 5 ? 1 : 0, sub = sub0 + sl, q = p - 5 * sl;
             const uint4 *af = wl + (p * KS) * 64 + (lane ^ frag_turn(sl, q));
             floatx16_t acc0, acc1;
@@ -903,14 +949,14 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
                 o.z = __builtin_amdgcn_alignbit(x3, x2, sh);
                 o.w = __builtin_amdgcn_alignbit(x4, x3, sh);
                 const uint32_t ot = __builtin_amdgcn_alignbit(x0, x4, sh);
-                if (NS == 2 && sl == 0) {
+                if (NS == 2 && (!SHORT || parts == 1) && sl == 0) {
                     head0 = o;
                     tail0 = ot;
                 } else if (prow >= 0) {
                     // the strings of the key's group together: 16 S adjacent bytes of the tile's
                     // main rows and 4 S of its tail rows
                     uint4 *dst = (uint4 *)(Cb + packed_main_row(prow, grp, a.Lpad, GT));
-                    if (NS == 2) {
+                    if (NS == 2 && (!SHORT || parts == 1)) {
                         dst[0] = head0;
                         dst[1] = o;
                         *(uint2 *)(Cb + packed_tail_row(prow, grp, a.Lpad, GT)) = make_uint2(tail0, ot);
@@ -956,7 +1002,7 @@ static int share_groups(HashArgs *a) {
 // (A workgroup without a block copies its slab for nothing; asking for the run's length first cost
 // every short run 0.3 us, 4 % at 5000 keys of 16 tables, and gained nothing in ragged batches.)
 typedef void (*fragment_kernel_t)(HashArgs);
-static void launch_blocks(fragment_kernel_t alone, fragment_kernel_t shared, HashArgs a, int rows,
+static void launch_blocks(fragment_kernel_t alone, fragment_kernel_t brief, fragment_kernel_t shared, HashArgs a, int rows,
                           int batch, int max_rows, int threads, size_t lds, hipStream_t st) {
     const int nblocks = (max_rows + 63) / 64;
     int groups = batch, per = std::max(1, std::min(nblocks, 256 / (rows * batch)));
@@ -965,6 +1011,7 @@ static void launch_blocks(fragment_kernel_t alone, fragment_kernel_t shared, Has
         groups = share_groups(&a);
         per = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)nblocks * a.group, 256 / (rows * groups)));
     }
+    if (!share && nblocks <= per * (threads / 64)) alone = brief;
     // (shared: slab by slab, so that few of the slabs go through each XCD's L2)
     hipLaunchKernelGGL(share ? shared : alone, share ? dim3(rows, per, groups) : dim3(per, rows, groups), dim3(threads), lds, st, a);
 }
@@ -986,18 +1033,19 @@ template <int D> static int hash_prepare_d() {
         if (e == hipSuccess && lds > 64 * 1024)
             e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     };
-    auto both = [&](auto share) {
-        constexpr bool SHARE = decltype(share)::value;
-        allow(hash_mfma8_kernel<D, 4, 8, SHARE>, hash8_lds<D, 4, 8>());
-        allow(hash_mfma8_kernel<D, 2, 8, SHARE>, hash8_lds<D, 2, 8>());
-        allow(hash_mfma8_kernel<D, 1, 8, SHARE>, hash8_lds<D, 1, 8>());
-        allow(hash_mfma8_kernel<D, 4, 4, SHARE>, hash8_lds<D, 4, 4>());
-        allow(hash_mfma8_kernel<D, 2, 4, SHARE>, hash8_lds<D, 2, 4>());
-        allow(hash_mfma10_kernel<D, 2, SHARE>, hash10_lds<D, 2>());
-        allow(hash_mfma10_kernel<D, 1, SHARE>, hash10_lds<D, 1>());
+    auto all = [&](auto runs) {
+        constexpr int RUNS = decltype(runs)::value;
+        allow(hash_mfma8_kernel<D, 4, 8, RUNS>, hash8_lds<D, 4, 8>());
+        allow(hash_mfma8_kernel<D, 2, 8, RUNS>, hash8_lds<D, 2, 8>());
+        allow(hash_mfma8_kernel<D, 1, 8, RUNS>, hash8_lds<D, 1, 8>());
+        allow(hash_mfma8_kernel<D, 4, 4, RUNS>, hash8_lds<D, 4, 4>());
+        allow(hash_mfma8_kernel<D, 2, 4, RUNS>, hash8_lds<D, 2, 4>());
+        allow(hash_mfma10_kernel<D, 2, RUNS>, hash10_lds<D, 2>());
+        allow(hash_mfma10_kernel<D, 1, RUNS>, hash10_lds<D, 1>());
     };
-    both(std::false_type());
-    if constexpr (D == 256) both(std::true_type());
+    all(IntTag<kRunsLong>());
+    all(IntTag<kRunsShort>());
+    if constexpr (D == 256) all(IntTag<kRunsShared>());
     return e == hipSuccess ? SOCKET_OK : SOCKET_EHIP;
 }
 int hash_prepare(int d) { return d == 64 ? hash_prepare_d<64>() : d == 128 ? hash_prepare_d<128>() : hash_prepare_d<256>(); }
@@ -1008,8 +1056,8 @@ static int launch_mfma8(HashArgs a, int Hkv, int batch, int max_rows, hipStream_
     a.tables_per_chunk = 16 * S;
     a.n_chunks = S == 4 ? (a.L + 63) / 64 : 1;
     fragment_kernel_t shared = nullptr;
-    if constexpr (D == 256) shared = hash_mfma8_kernel<D, S, P, true>;
-    launch_blocks(hash_mfma8_kernel<D, S, P, false>, shared, a, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash8_lds<D, S, P>(), st);
+    if constexpr (D == 256) shared = hash_mfma8_kernel<D, S, P, kRunsShared>;
+    launch_blocks(hash_mfma8_kernel<D, S, P, kRunsLong>, hash_mfma8_kernel<D, S, P, kRunsShort>, shared, a, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash8_lds<D, S, P>(), st);
     return SOCKET_OK;
 }
 template <int D, int P>
@@ -1030,8 +1078,8 @@ static int launch_mfma10(HashArgs a, int Hkv, int batch, int max_rows, hipStream
     a.tables_per_chunk = 16 * S;
     a.n_chunks = a.Lpad / (16 * S);            // groups, padding groups included (their ids are zero)
     fragment_kernel_t shared = nullptr;
-    if constexpr (D == 256) shared = hash_mfma10_kernel<D, S, true>;
-    launch_blocks(hash_mfma10_kernel<D, S, false>, shared, a, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash10_lds<D, S>(), st);
+    if constexpr (D == 256) shared = hash_mfma10_kernel<D, S, kRunsShared>;
+    launch_blocks(hash_mfma10_kernel<D, S, kRunsLong>, hash_mfma10_kernel<D, S, kRunsShort>, shared, a, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash10_lds<D, S>(), st);
     return SOCKET_OK;
 }
 template <int D>

@@ -168,6 +168,25 @@ def test_hash_keys_projections_at_any_element(d, L, P):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,L,P", [(64, 64, 8), (64, 20, 8), (64, 33, 4), (64, 60, 10), (256, 64, 8), (256, 60, 10)])
+def test_hash_keys_short_runs_share_blocks_among_wavefronts(d, L, P):
+    """Runs of which no wavefront has more than one block of 64 keys: whole blocks, halves and quarters
+    of one to a wavefront (by the length of the run) give the oracle's ids, and the same bit for bit."""
+    _need_gpu()
+    n, B, H = (2304, 8, 8) if d == 64 else (1152, 2, 4)
+    layer = small_layer(seed=18, B=B, Hq=H, Hkv=H, d=d, n=n, L=L, P=P, k=16)
+    ctx = hz.make_ctx(layer)
+    counts = [n, n - 1, 0, 65, n - 63, 1, 700, n // 2][:B]
+    whole = run_hash(ctx, layer, [0] * B, counts, n)
+    check_codes(layer, whole, lambda b: (0, counts[b]))
+    for step in (n // 2, n // 4):
+        codes = hz.new_codes((B, H), n, L, P, fill=0x55)
+        for at in range(0, n, step):
+            run_hash(ctx, layer, [at] * B, [max(0, min(step, c - at)) for c in counts], step, codes)
+        assert torch.equal(codes, whole)
+    ctx.close()
+
+
 @pytest.mark.parametrize("L,P", [(64, 8), (100, 8), (24, 8), (9, 8), (64, 4), (65, 4), (31, 4), (7, 4), (60, 10), (20, 10), (11, 10)])
 def test_hash_keys_wide_heads(L, P):
     """d = 256: a chunk's position groups (strings, for packed ids) are shared out to two workgroups;
