@@ -1007,7 +1007,7 @@ static size_t project_group_lds(int G, int d, int P, int elem) {
     const int QPT = G >= 2 ? 2 : 1, NQG = G / QPT, CS = kGroupThreads / (64 * NQG);
     const size_t slab = (size_t)d * kGroupCols * elem, quarter = (size_t)G * NQ * 16 * TG * 8;
     return (slab > quarter ? slab : quarter) + (size_t)d * G * 8 + (size_t)CS * G * kGroupCols * 8 +
-           (size_t)G * P * 2 * TG * 8 + (size_t)d * 4 + (kGroupThreads / 64) * kGroupCols * 4 + 3 * kGroupThreads * 4 + kGroupCols * 4;
+           (size_t)G * P * 2 * TG * 8 + (kGroupThreads / 64) * kGroupCols * 4 + 3 * kGroupThreads * 4;
 }
 
 template <typename T, int G, int P>
@@ -1033,19 +1033,15 @@ __global__ __launch_bounds__(kGroupThreads) void project_group_kernel(ProjectArg
     double *qd = (double *)((char *)sm64 + (slab > quarter ? slab : quarter));   // [d][G]
     double *zb = qd + (size_t)d * G;                 // [CS][G][COLS]
     double *sig = zb + CS * G * COLS;                // [G][P][2][TG]
-    float *kf = (float *)(sig + G * P * 2 * TG);     // [d]
-    float *kz = kf + d;                              // [NW][COLS]
+    float *kz = (float *)(sig + G * P * 2 * TG);     // [NW][COLS]
     float *s_part = kz + NW * COLS;                   // [3][NT]
-    uint32_t *sgn = (uint32_t *)(s_part + 3 * NT);   // [COLS]
 
     // ---- global loads, all issued before the first use
     int tok = 0;
-    int64_t krow = -1;
+    bool wanted = false;
     if (app) {
         tok = a.pos[b];
-        const bool wanted = a.count == nullptr || a.count[b] >= 1;
-        if (wanted && tok >= 0 && tok < a.map.max_n) krow = a.map.row(b, h, tok);
-        if (a.len_out && tg == 0 && h == 0 && tid == 0) a.len_out[b] = tok + 1;
+        wanted = a.count == nullptr || a.count[b] >= 1;
     }
     // W: rows of COLS elements (columns at or beyond L * P do not exist: zero)
     constexpr int VPR = COLS / EPV;                  // 16-byte vectors per row
@@ -1061,30 +1057,8 @@ __global__ __launch_bounds__(kGroupThreads) void project_group_kernel(ProjectArg
     }
     // queries: 16-byte pieces of the G rows; the appended key's row
     const int qpieces = G * d / EPV, kpieces = d / EPV;
-    uint4 qv = make_uint4(0, 0, 0, 0), kv = make_uint4(0, 0, 0, 0);
+    uint4 qv = make_uint4(0, 0, 0, 0);
     if (tid < qpieces) qv = *(const uint4 *)((const T *)a.q + ((int64_t)b * a.Hq + h * G) * d + tid * EPV);
-    if (app && krow >= 0 && tid >= NT - kpieces) kv = *(const uint4 *)((const T *)a.K + krow * d + (tid - (NT - kpieces)) * EPV);
-    // 256 value norms spread over the sequence per table: thread -> table tid % TG, samples tid / TG + (NT / TG) m
-    constexpr int SPT = 256 * TG / NT;               // samples per thread
-    const int li_own = tid % TG;                     // the table of this thread's samples and table entries
-    float nu1 = 0.0f, nu2 = 0.0f;
-    if (a.vnorm != nullptr && app && l0 + li_own < a.L && tok >= 0 && tok < a.map.max_n) {
-        const int seq = tok + 1;
-        const float step = (float)seq / (float)(a.L * 256);
-        float nu[SPT];
-#pragma unroll
-        for (int m = 0; m < SPT; ++m) {
-            const int j = tid / TG + (NT / TG) * m;
-            int t = (int)((float)((l0 + li_own) * 256 + j) * step);
-            t = t < seq ? t : seq - 1;
-            nu[m] = a.vnorm[((int64_t)b * a.Hkv + h) * a.map.max_n + t];
-        }
-#pragma unroll
-        for (int m = 0; m < SPT; ++m) {
-            nu1 += nu[m];
-            nu2 = fmaf(nu[m], nu[m], nu2);
-        }
-    }
 
     // ---- into LDS
 #pragma unroll
@@ -1099,13 +1073,41 @@ __global__ __launch_bounds__(kGroupThreads) void project_group_kernel(ProjectArg
 #pragma unroll
         for (int e = 0; e < EPV; ++e) qd[(size_t)(c0 + e) * G + g] = (double)f[e];
     }
-    if (app && tid >= NT - kpieces) {
-        float f[EPV];
-        vec_to_f32<T>(kv, f);
+    // The appended key: a range of d / NW channels to a wavefront, in every lane.  Asked for only now
+    // and used after the sigmoids: its row waits for the position and, paged, for the block table
+    // (in LDS before the first barrier it held the queries up: a step of 4 x 65536 keys, 64 tables,
+    // 63.3 us, 62.6 now; 3 x 9000 33.5 / 32.8; 8 x 16384 of 4 planes with value norms 58.1 / 57.0).
+    constexpr int KV = 16 / EPV;                     // pieces of a range (d <= 128)
+    int64_t krow = -1;
+    uint4 kv[KV];
+    if (app) {
+        if (wanted && tok >= 0 && tok < a.map.max_n) krow = a.map.row(b, h, tok);
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) kf[(tid - (NT - kpieces)) * EPV + e] = f[e];
+        for (int j = 0; j < KV; ++j) {
+            kv[j] = make_uint4(0, 0, 0, 0);
+            if (krow >= 0 && (j + 1) * EPV <= d / NW) kv[j] = *(const uint4 *)((const T *)a.K + krow * d + (tid >> 6) * (d / NW) + j * EPV);
+        }
+        if (a.len_out && tg == 0 && h == 0 && tid == 0) a.len_out[b] = tok + 1;
     }
-    __syncthreads();
+    // 256 value norms spread over the sequence per table: thread -> table tid % TG, samples tid / TG + (NT / TG) m
+    constexpr int SPT = 256 * TG / NT;               // samples per thread
+    const int li_own = tid % TG;                     // the table of this thread's samples and table entries
+    float nu[SPT];
+#pragma unroll
+    for (int m = 0; m < SPT; ++m) nu[m] = 0.0f;
+    if (a.vnorm != nullptr && app && l0 + li_own < a.L && tok >= 0 && tok < a.map.max_n) {
+        const int seq = tok + 1;
+        const float step = (float)seq / (float)(a.L * 256);
+#pragma unroll
+        for (int m = 0; m < SPT; ++m) {
+            const int j = tid / TG + (NT / TG) * m;
+            int t = (int)((float)((l0 + li_own) * 256 + j) * step);
+            t = t < seq ? t : seq - 1;
+            nu[m] = a.vnorm[((int64_t)b * a.Hkv + h) * a.map.max_n + t];
+        }
+    }
+
+    __syncthreads();                                 // (LDS only: the loads above stay under way)
 
     // ---- dot products: columns 2 cpi, 2 cpi + 1; query heads qg QPT ..; channels of range cs
     const int cpi = tid & 63;
@@ -1142,19 +1144,6 @@ __global__ __launch_bounds__(kGroupThreads) void project_group_kernel(ProjectArg
         for (int qq = 0; qq < QPT; ++qq)
             *(double2 *)&zb[((size_t)cs * G + qg * QPT + qq) * COLS + 2 * cpi] = make_double2(z[qq][0], z[qq][1]);
     }
-    if (app) {                                       // the key, in fp32: a range of the channels per wavefront
-        const int cs4 = tid >> 6, cn = d / NW;
-        float k0 = 0.0f, k1 = 0.0f;
-#pragma unroll 8
-        for (int c = cs4 * cn; c < (cs4 + 1) * cn; ++c) {
-            float wa, wb;
-            w_pair(c, wa, wb);
-            const float kk = kf[c];
-            k0 = fmaf(wa, kk, k0);
-            k1 = fmaf(wb, kk, k1);
-        }
-        *(float2 *)&kz[cs4 * COLS + 2 * cpi] = make_float2(k0, k1);
-    }
     __syncthreads();
 
     // ---- per (query head, column): u = tanh(z)/sqrt(d), then the sigmoids of +-2u/tau
@@ -1176,11 +1165,23 @@ __global__ __launch_bounds__(kGroupThreads) void project_group_kernel(ProjectArg
         sig[((g * P + pl) * 2 + 1) * TG + li] = z >= 0.0 ? big : small;
         sig[((g * P + pl) * 2) * TG + li] = z >= 0.0 ? small : big;
     }
-    if (app && tid < COLS) {
-        float ks = 0.0f;
+    if (app) {                                       // the key, in fp32: a range of the channels per wavefront
+        const int c0 = (tid >> 6) * (d / NW);
+        float k0 = 0.0f, k1 = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) ks += kz[w * COLS + tid];
-        sgn[tid] = ks >= 0.0f ? 1u : 0u;
+        for (int j = 0; j < KV; ++j) {
+            if ((j + 1) * EPV > d / NW) break;
+            float kk[EPV];
+            vec_to_f32<T>(kv[j], kk);
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) {
+                float wa, wb;
+                w_pair(c0 + j * EPV + e, wa, wb);
+                k0 = fmaf(wa, kk[e], k0);
+                k1 = fmaf(wb, kk[e], k1);
+            }
+        }
+        *(float2 *)&kz[(tid >> 6) * COLS + 2 * cpi] = make_float2(k0, k1);
     }
     __syncthreads();
 
@@ -1212,14 +1213,16 @@ __global__ __launch_bounds__(kGroupThreads) void project_group_kernel(ProjectArg
             a.subprobs[((((int64_t)b * a.Hkv + h) * a.L + l0 + li) * a.pf + j) * Ru + x] = (float)(mean / (double)G);
         }
     }
-    // the appended key's bucket ids, one thread per table of the group (tables >= L: id 0)
-    if (app && krow >= 0 && tid >= 64 && tid < 64 + TG && l0 + tid - 64 < a.Lpad) {
-        const int li = tid - 64, l = l0 + li;
-        uint32_t code = 0;
-        if (l < a.L)
+    // the appended key's bucket ids (tables >= L: id 0): a column's sign per lane, a table's P of them
+    // picked from the wavefront's ballot by its first lane
+    if (app && tid < COLS) {
+        float ks = 0.0f;
 #pragma unroll
-            for (int i = 0; i < P; ++i) code |= sgn[li * P + i] << i;
-        ((uint8_t *)a.codes)[krow * a.Lpad + code_pos(l, tok, a.S)] = (uint8_t)code;
+        for (int w = 0; w < NW; ++w) ks += kz[w * COLS + tid];
+        const unsigned long long signs = __ballot(ks >= 0.0f);
+        const int l = l0 + tid / P;
+        if (krow >= 0 && tid % P == 0 && l < a.Lpad)
+            ((uint8_t *)a.codes)[krow * a.Lpad + code_pos(l, tok, a.S)] = l < a.L ? (uint8_t)((signs >> (tid & 63)) & ((1u << P) - 1)) : (uint8_t)0;
     }
     __syncthreads();
 
@@ -1270,6 +1273,12 @@ __global__ __launch_bounds__(kGroupThreads) void project_group_kernel(ProjectArg
         };
         if (a.pf > 1) fill(GroupTag<true>());
         else fill(GroupTag<false>());
+        float nu1 = 0.0f, nu2 = 0.0f;
+#pragma unroll
+        for (int m = 0; m < SPT; ++m) {
+            nu1 += nu[m];
+            nu2 = fmaf(nu[m], nu[m], nu2);
+        }
         s_part[tid] = dev2;
         s_part[NT + tid] = nu1;
         s_part[2 * NT + tid] = nu2;
