@@ -1,6 +1,6 @@
 // Alg. 2 (SoftBucketProbs) and Alg. 5 (SoftHashCollisionScores, the soft score of Eq. 3).
 //
-//   project_kernel    builds, per (sequence, KV head), the table of bucket probabilities of
+//   project_*_kernel  build, per (sequence, KV head), the table of bucket probabilities of
 //                     the G queries that share the head.  Evaluated in fp64 and stored as
 //                     fp32.  A softmax over the corners of {+-1}^P factorises over the
 //                     planes, p(r) = prod_i sigmoid(+-2 u_i / tau), which is the form used.
@@ -90,14 +90,297 @@ __device__ __forceinline__ double group_sum_f64(double v, int n) {
 
 constexpr int kPlanePad = 16;        // per-plane sigmoids are kept [g][16]; planes >= P hold 1
 
-// One workgroup projects onto the P hyperplanes of ONE table of one KV head:
+// the four adjacent elements of a key row that a lane multiplies at a time
+template <typename T> struct Quad;
+template <> struct Quad<float> {
+    uint4 v;
+    __device__ __forceinline__ void load(const void *p) { v = *(const uint4 *)p; }
+    __device__ __forceinline__ void get(float *f) const { vec_to_f32<float>(v, f); }
+};
+template <> struct Quad<uint16_t> {
+    uint2 v;
+    __device__ __forceinline__ void load(const void *p) { v = *(const uint2 *)p; }
+    __device__ __forceinline__ void get(float *f) const {
+        f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
+        f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
+    }
+};
+
+// the bucket id of the appended key (cache row `krow`, position `tok`) for table l, written by one thread
+__device__ __forceinline__ void write_code(const ProjectArgs &a, int64_t krow, int tok, int l, uint32_t code) {
+    if (a.mode == kSplit) {
+        // packed ids: the 10 bits sit in one or two dwords that other tables (other
+        // workgroups) write too, so they are cleared and set with atomics
+        const int grp = l / a.GT, j = packed_pos(l % a.GT, tok, a.S);
+        const int sub = j >> 4, bit = 10 * (j & 15), wi = bit >> 5, sh = bit & 31;
+        uint32_t *w0 = (uint32_t *)((char *)a.codes + packed_word(krow, grp, sub, wi, a.Lpad, a.GT));
+        atomicAnd(w0, ~(0x3ffu << sh));
+        atomicOr(w0, code << sh);
+        if (sh > 22) {
+            uint32_t *w1 = (uint32_t *)((char *)a.codes + packed_word(krow, grp, sub, wi + 1, a.Lpad, a.GT));
+            atomicAnd(w1, ~(0x3ffu >> (32 - sh)));
+            atomicOr(w1, code >> (32 - sh));
+        }
+        return;
+    }
+    const int64_t at = krow * a.Lpad + code_pos(l, tok, a.S);
+    if (a.cb == 1) ((uint8_t *)a.codes)[at] = (uint8_t)code;
+    else ((uint16_t *)a.codes)[at] = (uint16_t)code;
+}
+
+// One workgroup projects onto the P hyperplanes of ONE table of one KV head, for tables with one
+// entry per bucket (up to 8 planes; SPLIT: 9 or 10):
 //   - the G queries of the head's group, in fp64, giving that table's bucket probabilities
 //     (Alg. 2; the softmax over corners is evaluated as a product of per-plane sigmoids);
-//   - optionally the key appended at position pos[b], in fp32 FMA, giving its bucket id for
-//     that table (Alg. 1 on one row).
-// The kernel is a chain of short dependent phases bounded by memory and LDS latency, so every
-// phase issues all of its independent loads before the first use, and every dot product is
-// cut into channel ranges that adjacent lanes sum with DPP moves.
+//   - WHAT = kQueriesKey or kKey: the key appended at position pos[b], in fp32 FMA, giving its bucket
+//     id for that table (Alg. 1 on one row).
+// The kernel is a chain of short dependent phases, bounded by their latencies and by the number of
+// instructions on the way (a wavefront issues them one by one, and they come cold from memory in
+// every launch), so it has nothing in it but the one path:
+//   dots     fp64 matrix instructions, rows = planes, columns = query heads, four channels each (a
+//            wavefront has a quarter of them): an element of W or of a query goes from memory into
+//            the one lane that multiplies it, no staging; the sum over channels needs no lane moves
+//   tables   an entry is a product of two (SPLIT: three) small per-head tables
+//   key      its row waits for the position (and, paged, for the block table after that): asked for
+//            behind everything else, multiplied after the tables are on their way
+// us, against W and the queries staged in LDS and the key before the tables (graph replays): the
+// queries' tables of 8 heads, 64 tables of 8 planes, 5.5 / 4.5; one appended key alone 3.8 / 3.0,
+// (10, 60) 5.0 / 3.6; a decode step of 32768 keys 30.2 / 29.1, of 30011 with (10, 60) 38.3 / 36.3.
+enum ProjectWhat { kQueries = 0, kQueriesKey = 1, kKey = 2 };
+typedef double doublex4_t __attribute__((ext_vector_type(4)));
+
+template <typename T, int G, int D, bool SPLIT, int WHAT>
+__global__ __launch_bounds__(256) void project_table_kernel(ProjectArgs a) {
+    constexpr bool SOFT = WHAT != kKey, APP = WHAT != kQueries;
+    constexpr int PM = SPLIT || WHAT == kKey ? 16 : 8;       // planes at most
+    constexpr int KS = D / 16;                               // matrix instructions of a wavefront
+    constexpr int DS = D + 4;                                // row stride in LDS: 16 planes x 4 channels on 64 banks
+    constexpr int kAb = SPLIT ? 36 : 32;                     // small tables: planes 0..3, 4..7 (and 8, 9)
+    __shared__ __align__(16) float wf[APP ? PM : 1][APP ? DS : 4];   // the table's columns of W
+    __shared__ double zp[SOFT ? 4 : 1][SOFT ? G * PM : 1];   // partial dot products of the wavefronts
+    __shared__ double sig[SOFT ? G * kPlanePad * 2 : 1];     // [G][16 planes][2] sigmoid(-2u/tau), sigmoid(+2u/tau)
+    __shared__ double ab[SOFT ? G * kAb : 1];
+    __shared__ __align__(16) uint32_t sgn[16];               // sign bits of the key's projections
+    __shared__ float s_dev[12];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Workgroups go to the 8 XCDs round-robin; the 8 tables whose columns of W share 128-byte
+    // lines are given to workgroups of one XCD, so each line is fetched into one L2 only.
+    const int x = blockIdx.x;
+    const int l = (x & 7) * (a.Lpad >> 3) + (x >> 3);        // table (Lpad is a multiple of 16)
+    const int h = blockIdx.y, b = blockIdx.z;                // KV head, sequence
+    const int P = a.P;
+    const bool live = l < a.L;                               // tables >= L are padding: zero rows, id 0
+    // (every line of the argument block is asked for at once: a line first touched by a later phase is
+    // a memory latency there)
+    asm volatile("" ::"s"(a.cols_magic), "s"(a.table_words));
+
+    // ---- every load is issued here, those that wait for another one last.  Rows and columns of a
+    //      matrix that do not exist repeat the last one (a result row depends on its own row only).
+    int tok = 0, cnt = 1;
+    if (APP) {
+        tok = a.pos[b];
+        if (a.count) cnt = a.count[b];
+    }
+    const int lr = lane & 15, c0 = wave * (D / 4) + (lane >> 4);   // row / column, channel of step 0
+    const T *Wg = (const T *)a.W + ((int64_t)h * D + c0) * a.LP + (live ? l : a.L - 1) * P + min(lr, P - 1);
+    T wv[KS], qv[SOFT ? KS : 1];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) wv[s] = Wg[(int64_t)(4 * s) * a.LP];
+    if (SOFT) {
+        const T *qg = (const T *)a.q + ((int64_t)b * a.Hq + h * G + min(lr, G - 1)) * D + c0;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qv[s] = qg[4 * s];
+    }
+    const int pl = tid >> 4, kpart = tid & 15;               // the key: 16 planes x 16 lanes, a 16th of the channels each
+    constexpr int KQ = D / 64;                               // channel quads kpart, kpart + 16, ...
+    int64_t krow = -1;
+    Quad<T> kq[APP ? KQ : 1];
+    float nu = 0.0f;
+    if (APP) {
+        if (cnt >= 1 && tok >= 0 && tok < a.map.max_n) krow = a.map.row(b, h, tok);
+        const T *kr = (const T *)a.K + (krow < 0 ? 0 : krow) * D + kpart * 4;   // (no key: a row that exists, not used)
+#pragma unroll
+        for (int c = 0; c < KQ; ++c) kq[c].load(kr + c * 64);
+        // 256 value norms spread over the sequence (tok + 1 tokens): their mean and spread scale the
+        // histogram bins of the weighted scores
+        if (SOFT && a.vnorm != nullptr && live && tok >= 0 && tok < a.map.max_n) {
+            const int seq = tok + 1;
+            int t = (int)((float)(l * 256 + tid) * ((float)seq / (float)(a.L * 256)));
+            t = t < seq ? t : seq - 1;
+            nu = a.vnorm[((int64_t)b * a.Hkv + h) * a.map.max_n + t];
+        }
+    }
+
+    // ---- dot products
+    if (SOFT) {
+        doublex4_t acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            acc[s & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)elem_to_f32<T>(wv[s]), (double)elem_to_f32<T>(qv[s]), acc[s & 1], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {                        // row 4 r + lane / 16, column lane % 16
+            const int i = 4 * r + (lane >> 4);
+            if (i < P && lr < G) zp[wave][lr * PM + i] = acc[0][r] + acc[1][r];
+        }
+        if (tid < G * kPlanePad * 2) sig[tid] = 1.0;         // (an unused plane holds 1)
+    }
+    if (APP) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            if (lr < P) wf[lr][c0 + 4 * s] = elem_to_f32<T>(wv[s]);
+        if (tid < 16) sgn[tid] = 0;
+        if (a.len_out && x == 0 && h == 0 && tid == 0) a.len_out[b] = tok + 1;
+    }
+    __syncthreads();                                         // (LDS only: loads stay under way)
+
+    auto key_signs = [&]() __attribute__((always_inline)) {
+        float acc = 0.0f;
+        if (pl < P) {
+            const float *w4 = &wf[pl < PM ? pl : 0][kpart * 4];
+#pragma unroll
+            for (int c = 0; c < KQ; ++c) {
+                const float4 ww = *(const float4 *)(w4 + c * 64);
+                float kk[4];
+                kq[c].get(kk);
+                acc = fmaf(kk[0], ww.x, acc);
+                acc = fmaf(kk[1], ww.y, acc);
+                acc = fmaf(kk[2], ww.z, acc);
+                acc = fmaf(kk[3], ww.w, acc);
+            }
+        }
+        acc = row_sum<16>(acc);
+        if (pl < P && kpart == 0) sgn[pl] = acc >= 0.0f ? 1u : 0u;
+    };
+    auto key_code = [&]() __attribute__((always_inline)) {   // (one thread, after key_signs and a barrier)
+        uint32_t code = 0;
+        if (live) {
+            uint4 sg[4];                                     // all 16 sign words in one LDS round trip
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sg[i] = ((const uint4 *)sgn)[i];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                code |= (sg[i].x << (4 * i)) | (sg[i].y << (4 * i + 1)) | (sg[i].z << (4 * i + 2)) | (sg[i].w << (4 * i + 3));
+        }
+        write_code(a, krow, tok, l, code);
+    };
+    if (!SOFT) {
+        key_signs();
+        __syncthreads();
+        if (krow >= 0 && tid == 0) key_code();
+        return;
+    }
+
+    // ---- u = tanh(z)/sqrt(d), then the per-plane sigmoids of +-2u/tau
+    if (tid < G * P) {
+        const int g = (tid * a.cols_magic) >> 16, j = tid - g * P;   // tid / P
+        const int at = g * PM + j;
+        const double z = (zp[0][at] + zp[1][at]) + (zp[2][at] + zp[3][at]);
+        // tanh|z| = (1 - t)/(1 + t) with t = exp(-2|z|); sigmoid(+-x) from e = exp(-|x|)
+        const double t = exp(-2.0 * fabs(z));
+        const double th = (1.0 - t) * rcp64(1.0 + t);
+        const double e = exp(-a.x_scale * th);               // x = 2 tanh|z| / (sqrt(d) tau) >= 0
+        double big = rcp64(1.0 + e), small = e * big;
+        if (a.hard) {                                        // the limit tau -> 0: all mass on the query's side of the plane
+            big = 1.0;
+            small = 0.0;
+        }
+        sig[(g * kPlanePad + j) * 2 + 1] = z >= 0.0 ? big : small;
+        sig[(g * kPlanePad + j) * 2] = z >= 0.0 ? small : big;
+    }
+    __syncthreads();
+
+    // ---- the small tables: products over planes 0..3, 4..7 (and 8, 9) for every value of those bits.
+    //      Ids that share a byte (pf tables of Pu planes each): a look-up with the byte gives the sum
+    //      of the pf tables' probabilities, so a half holds a 4-plane table, or the sum of two 2-plane
+    //      or four 1-plane ones.
+    for (int i = tid; i < G * kAb; i += 256) {
+        const int g = i / kAb, e = i - g * kAb;
+        const int s0 = e < 16 ? 0 : e < 32 ? 4 : 8, bits = e < 32 ? (e & 15) : e - 32;
+        const double *sp = sig + (g * kPlanePad + s0) * 2;
+        const double f0 = sp[bits & 1], f1 = sp[2 + ((bits >> 1) & 1)], f2 = sp[4 + ((bits >> 2) & 1)], f3 = sp[6 + ((bits >> 3) & 1)];
+        double v = (f0 * f1) * (f2 * f3);                    // (planes 10 and 11 do not exist: 1)
+        if (!SPLIT && a.pf > 2) v = a.pf == 4 ? f0 * f1 + f2 * f3 : (f0 + f1) + (f2 + f3);
+        ab[i] = live ? v : 0.0;
+    }
+    if (!SPLIT && a.pf > 1 && live && tid < a.pf << a.Pu) {
+        // the caller's tables one by one, for the read-back
+        const int j = tid >> a.Pu, bits = tid & ((1 << a.Pu) - 1);
+        double mean = 0.0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            double pr = 1.0;
+            for (int i = 0; i < a.Pu; ++i) pr *= sig[(g * kPlanePad + j * a.Pu + i) * 2 + ((bits >> i) & 1)];
+            mean += pr;
+        }
+        a.subprobs[((((int64_t)b * a.Hkv + h) * a.L + l) * a.pf + j) * (1 << a.Pu) + bits] = (float)(mean / (double)G);
+    }
+    __syncthreads();
+
+    // ---- the table: p(r) over all planes, averaged over the G queries.  The key's signs and the sampled
+    //      norms before the entries go out: their loads are in, and nothing waits for a store.
+    if (APP) key_signs();
+    float *Tg = a.tables + ((int64_t)b * a.Hkv + h) * a.table_words;
+    const double inv_g = 1.0 / (double)G, inv_r = 1.0 / (double)a.R;
+    float dev2 = 0.0f, v[SPLIT ? 4 : 1];
+    if (SPLIT) {
+        // four consecutive buckets per thread, stored as one 16-byte piece: a group's table
+        // is kept as [bucket / 4][table][4] (the other tables of the group come from other
+        // workgroups, so longer contiguous runs per table mean fewer partial writes)
+        double mean[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const double *t = ab + g * kAb;
+            const double up = t[16 + ((tid >> 2) & 15)] * t[32 + (tid >> 6)];   // bits 4..7 and 8, 9 of the id
+#pragma unroll
+            for (int j = 0; j < 4; ++j) mean[j] = fma(t[(tid & 3) * 4 + j], up, mean[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            mean[j] *= inv_g;
+            const double dv = live && tid < a.R >> 2 ? mean[j] - inv_r : 0.0;
+            dev2 += (float)(dv * dv);
+            v[j] = (float)mean[j];
+        }
+    } else {
+        double mean = 0.0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const double lo = ab[g * kAb + (tid & 15)], hi = ab[g * kAb + 16 + (tid >> 4)];
+            mean = a.pf > 1 ? mean + (lo + hi) : fma(lo, hi, mean);
+        }
+        mean *= inv_g;
+        const double dv = live && tid < a.R ? mean - a.tmean : 0.0;   // a table's entries sum to 1: their mean is 1/R
+        dev2 = (float)(dv * dv);                             // (pf tables' entries summed: pf / 2^Pu)
+        v[0] = (float)mean;
+    }
+    // ---- spread of this table's entries, from which the scoring pass sizes its histogram bins
+    dev2 = row_sum<64>(dev2);
+    const float nu1 = row_sum<64>(nu), nu2 = row_sum<64>(nu * nu);
+    if (lane == 0) {
+        s_dev[wave] = dev2;
+        s_dev[4 + wave] = nu1;
+        s_dev[8 + wave] = nu2;
+    }
+    if (SPLIT) {
+        if (tid < a.R >> 2)
+            *(float4 *)&Tg[(((int64_t)(l / a.GT) * (a.R >> 2) + tid) * a.GT + l % a.GT) * 4] = make_float4(v[0], v[SPLIT ? 1 : 0], v[SPLIT ? 2 : 0], v[SPLIT ? 3 : 0]);
+    } else if (tid < a.R) {
+        const int lw = a.Lpad < 64 ? a.Lpad : 64, copies = 64 / lw;   // distinct tables per 64-word row
+        float *dst = Tg + ((int64_t)(l >> 6) * a.R + tid) * 64 + (l & 63);
+        for (int cp = 0; cp < copies; ++cp) dst[cp * lw] = v[0];
+    }
+    __syncthreads();
+    if (tid < 3) {
+        const float *part = s_dev + 4 * tid;
+        const double sum = (double)(part[0] + part[1] + part[2] + part[3]);
+        a.tstats[(((int64_t)b * a.Hkv + h) * a.Lpad + l) * 3 + tid] = (float)(tid == 0 ? sum * inv_r : sum);
+    }
+    if (APP && krow >= 0 && tid == 64) key_code();           // off the first wavefront's path
+}
+
+// The same for tables in factor form (two small tables per query head): every phase issues all of its
+// independent loads before the first use, and every dot product is cut into channel ranges that
+// adjacent lanes sum with DPP moves.
 // DW: the dword fetch of the W slab is compiled in (bf16 tables whose planes are whole dwords
 // but not whole 16-byte vectors, e.g. 10 planes); the other instantiations stay as lean as
 // they were.
@@ -116,7 +399,7 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
     const bool live = l < a.L;                               // tables >= L are padding: zero rows
     const bool soft = a.q != nullptr, app = a.K != nullptr;
 
-    // Plane j lives in slot j, except that the high planes of the factor form start at slot 8:
+    // Plane j of the low factor lives in slot j, the high planes start at slot 8:
     // any product over 8 consecutive slots then needs no bounds (an unused slot holds 1).
     double *sig = sm64;                                      // [G][16 slots][2] sigmoid(-2u/tau), sigmoid(+2u/tau)
     double *qd = sig + G * kPlanePad * 2;                    // [G][d]  queries
@@ -124,7 +407,6 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
     float *wf = (float *)(wd + cols * d);                    // [P][d]  the same in fp32 (key path)
     float *kf = wf + cols * d;                               // [d]
     uint32_t *sgn = (uint32_t *)(kf + d);                    // [16] sign bits of the key's projections
-    float *s_dev = (float *)(sgn + 16);                      // [12]
 
     // ---- every global load of the kernel is issued here, before the first one is used
     int tok = 0;
@@ -193,17 +475,6 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
         if (krow >= 0 && live && tid < d / EPV) kv = *(const uint4 *)((const T *)a.K + krow * d + tid * EPV);
         if (a.len_out && x == 0 && h == 0 && tid == 0) a.len_out[b] = tok + 1;
     }
-    // 256 value norms spread over the sequence (tok + 1 tokens): their mean and spread scale the
-    // histogram bins of the weighted scores
-    float nu = 0.0f;
-    const bool sampling = a.vnorm != nullptr && app && soft && live && tok >= 0 && tok < a.map.max_n;
-    if (sampling) {
-        const int seq = tok + 1;
-        int t = (int)((float)(l * 256 + tid) * ((float)seq / (float)(a.L * 256)));
-        t = t < seq ? t : seq - 1;
-        nu = a.vnorm[((int64_t)b * a.Hkv + h) * a.map.max_n + t];
-    }
-
     // ---- into LDS as fp32 / fp64, W transposed to [plane][channel]
     if (live && wvec) {
 #pragma unroll
@@ -331,7 +602,7 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
                 big = 1.0;
                 small = 0.0;
             }
-            const int slot = (a.mode == kFactor && j >= a.Plo) ? 8 + j - a.Plo : j;
+            const int slot = j >= a.Plo ? 8 + j - a.Plo : j;
             sig[(g * kPlanePad + slot) * 2 + 1] = z >= 0.0 ? big : small;
             sig[(g * kPlanePad + slot) * 2] = z >= 0.0 ? small : big;
         }
@@ -339,7 +610,7 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
     __syncthreads();
 
     // the appended key's bucket id for this table, written by one thread
-    auto write_code = [&]() {
+    auto emit_code = [&]() {
         uint32_t code = 0;
         if (live) {
             uint4 sg[4];                             // all 16 sign words in one LDS round trip
@@ -349,28 +620,11 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
             for (int i = 0; i < 4; ++i)
                 code |= (sg[i].x << (4 * i)) | (sg[i].y << (4 * i + 1)) | (sg[i].z << (4 * i + 2)) | (sg[i].w << (4 * i + 3));
         }
-        if (a.mode == kSplit) {
-            // packed ids: the 10 bits sit in one or two dwords that other tables (other
-            // workgroups) write too, so they are cleared and set with atomics
-            const int grp = l / a.GT, j = packed_pos(l % a.GT, tok, a.S);
-            const int sub = j >> 4, bit = 10 * (j & 15), wi = bit >> 5, sh = bit & 31;
-            uint32_t *w0 = (uint32_t *)((char *)a.codes + packed_word(krow, grp, sub, wi, a.Lpad, a.GT));
-            atomicAnd(w0, ~(0x3ffu << sh));
-            atomicOr(w0, code << sh);
-            if (sh > 22) {
-                uint32_t *w1 = (uint32_t *)((char *)a.codes + packed_word(krow, grp, sub, wi + 1, a.Lpad, a.GT));
-                atomicAnd(w1, ~(0x3ffu >> (32 - sh)));
-                atomicOr(w1, code >> (32 - sh));
-            }
-            return;
-        }
-        const int64_t at = krow * a.Lpad + code_pos(l, tok, a.S);
-        if (a.cb == 1) ((uint8_t *)a.codes)[at] = (uint8_t)code;
-        else ((uint16_t *)a.codes)[at] = (uint16_t)code;
+        sk::write_code(a, krow, tok, l, code);
     };
     const bool code_due = app && krow >= 0;
     if (!soft) {
-        if (code_due && tid == 0) write_code();
+        if (code_due && tid == 0) emit_code();
         return;
     }
 
@@ -386,124 +640,19 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
         for (int i = 0; i < 8; ++i) f[i] = sig[(g * kPlanePad + s0 + i) * 2 + ((bits >> i) & 1)];
         return ((f[0] * f[1]) * (f[2] * f[3])) * ((f[4] * f[5]) * (f[6] * f[7]));
     };
-    // ids that share a byte (pf tables of Pu planes each): a look-up with the byte gives the sum
-    // of the pf tables' probabilities, each a product over its own Pu planes
-    auto shared_sum = [&](int g, int bits) -> double {
-        double f[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) f[i] = sig[(g * kPlanePad + i) * 2 + ((bits >> i) & 1)];
-        if (a.pf == 2) return (f[0] * f[1]) * (f[2] * f[3]) + (f[4] * f[5]) * (f[6] * f[7]);
-        if (a.pf == 4) return (f[0] * f[1] + f[2] * f[3]) + (f[4] * f[5] + f[6] * f[7]);
-        return ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
-    };
-    if (a.pf > 1 && live && tid < a.pf << a.Pu) {
-        // the caller's tables one by one, for the read-back
-        const int j = tid >> a.Pu, x = tid & ((1 << a.Pu) - 1);
-        double mean = 0.0;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            double pr = 1.0;
-            for (int i = 0; i < a.Pu; ++i) pr *= sig[(g * kPlanePad + j * a.Pu + i) * 2 + ((x >> i) & 1)];
-            mean += pr;
+    // products over the low and the high planes: p(r) = lo[r & (Rlo-1)] * hi[r >> Plo]
+    const int hrows = a.Rlo + a.Rhi;
+    for (int i = tid; i < hrows * G; i += 256) {
+        const int row = i % hrows, g = i / hrows;
+        double p = 0.0;
+        if (live) {
+            p = row < a.Rlo ? plane_product(g, 0, row) / (double)G   // the 1/G of the group mean rides on the low factor
+                            : plane_product(g, 8, row - a.Rlo);
         }
-        a.subprobs[((((int64_t)b * a.Hkv + h) * a.L + l) * a.pf + j) * (1 << a.Pu) + x] = (float)(mean / (double)G);
+        for (int cp = 0; cp < copies; ++cp)
+            Tg[(((int64_t)g * a.rounds + c64) * hrows + row) * 64 + lp + cp * lw] = (float)p;
     }
-    if (a.mode == kDirect || a.mode == kSplit) {
-        // p(r) over all planes, averaged over the G queries: one entry per thread and pass
-        // (planes 8 and 9 of the split form sit in slots 8 and 9)
-        const double inv_g = 1.0 / (double)G, inv_r = 1.0 / (double)a.R;
-        const bool split = a.mode == kSplit;
-        // split form: the products over planes 0..3, 4..7 and 8, 9 for every value of those bits,
-        // once per query head; an entry is then a product of three of them
-        constexpr int kAb = 16 + 16 + 4;
-        double *ab = (double *)(s_dev + 12);         // [G][kAb]
-        if (split) {
-            for (int i = tid; i < G * kAb; i += 256) {
-                const int g = i / kAb, e = i - g * kAb;
-                const int s0 = e < 16 ? 0 : e < 32 ? 4 : 8, bits = e < 32 ? (e & 15) : e - 32;
-                const double *sp = sig + (g * kPlanePad + s0) * 2;
-                double v = sp[bits & 1] * sp[2 + ((bits >> 1) & 1)];
-                if (e < 32) v *= sp[4 + ((bits >> 2) & 1)] * sp[6 + ((bits >> 3) & 1)];
-                ab[i] = live ? v : 0.0;
-            }
-            __syncthreads();
-        }
-        float dev2 = 0.0f;
-        if (split) {
-            // four consecutive buckets per thread, stored as one 16-byte piece: a group's table
-            // is kept as [bucket / 4][table][4] (the other tables of the group come from other
-            // workgroups, so longer contiguous runs per table mean fewer partial writes)
-            for (int r4 = tid; r4 < (a.R >> 2); r4 += 256) {
-                double mean[4] = {0.0, 0.0, 0.0, 0.0};
-                if (live) {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const double *t = ab + g * kAb;
-                        const double up = t[16 + ((r4 >> 2) & 15)] * t[32 + (r4 >> 6)];   // bits 4..7 and 8, 9 of the id
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) mean[j] = fma(t[(r4 & 3) * 4 + j], up, mean[j]);
-                    }
-                }
-                float v[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    mean[j] *= inv_g;
-                    if (live) {
-                        const double dv = mean[j] - inv_r;
-                        dev2 += (float)(dv * dv);
-                    }
-                    v[j] = (float)mean[j];
-                }
-                *(float4 *)&Tg[(((int64_t)(l / a.GT) * (a.R >> 2) + r4) * a.GT + l % a.GT) * 4] =
-                    make_float4(v[0], v[1], v[2], v[3]);
-            }
-        }
-        for (int r = tid; r < a.R && !split; r += 256) {
-            double mean = 0.0;
-            if (live) {
-                if (a.pf == 1) {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) mean += plane_product(g, 0, r);
-                } else {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) mean += shared_sum(g, r);
-                }
-                mean *= inv_g;
-                const double dv = mean - a.tmean;    // a table's entries sum to 1: their mean is 1/R
-                dev2 += (float)(dv * dv);            // (pf tables' entries summed: pf / 2^Pu)
-            }
-            for (int cp = 0; cp < copies; ++cp) Tg[((int64_t)c64 * a.R + r) * 64 + lp + cp * lw] = (float)mean;
-        }
-        // spread of this table's entries, from which the scoring pass sizes its histogram bins
-        dev2 = row_sum<64>(dev2);
-        const float nu1 = row_sum<64>(nu), nu2 = row_sum<64>(nu * nu);
-        if ((tid & 63) == 0) {
-            s_dev[tid >> 6] = dev2;
-            s_dev[4 + (tid >> 6)] = nu1;
-            s_dev[8 + (tid >> 6)] = nu2;
-        }
-        __syncthreads();
-        if (tid < 3) {
-            const float *part = s_dev + 4 * tid;
-            const double sum = (double)(part[0] + part[1] + part[2] + part[3]);
-            a.tstats[(((int64_t)b * a.Hkv + h) * a.Lpad + l) * 3 + tid] = (float)(tid == 0 ? sum * inv_r : sum);
-        }
-        if (code_due && tid == 64) write_code();     // off the first wavefront's path
-    } else {
-        // products over the low and the high planes: p(r) = lo[r & (Rlo-1)] * hi[r >> Plo]
-        const int hrows = a.Rlo + a.Rhi;
-        for (int i = tid; i < hrows * G; i += 256) {
-            const int row = i % hrows, g = i / hrows;
-            double p = 0.0;
-            if (live) {
-                p = row < a.Rlo ? plane_product(g, 0, row) / (double)G   // the 1/G of the group mean rides on the low factor
-                                : plane_product(g, 8, row - a.Rlo);
-            }
-            for (int cp = 0; cp < copies; ++cp)
-                Tg[(((int64_t)g * a.rounds + c64) * hrows + row) * 64 + lp + cp * lw] = (float)p;
-        }
-        if (code_due && tid == 64) write_code();
-    }
+    if (code_due && tid == 64) emit_code();
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2082,6 +2231,35 @@ static int set_lds_limit(const void *fn, size_t lds) {
                ? SOCKET_OK : SOCKET_EHIP;
 }
 
+typedef void (*project_fn_t)(ProjectArgs);
+
+template <typename T, int G, int D>
+static project_fn_t pick_project_table(bool split, bool app) {
+    if (split) return app ? project_table_kernel<T, G, D, true, kQueriesKey> : project_table_kernel<T, G, D, true, kQueries>;
+    return app ? project_table_kernel<T, G, D, false, kQueriesKey> : project_table_kernel<T, G, D, false, kQueries>;
+}
+template <typename T, int D>
+static project_fn_t pick_project_g(int G, bool split, bool soft, bool app) {
+    if (!soft) return project_table_kernel<T, 1, D, false, kKey>;
+    switch (G) {
+        case 1: return pick_project_table<T, 1, D>(split, app);
+        case 2: return pick_project_table<T, 2, D>(split, app);
+        case 4: return pick_project_table<T, 4, D>(split, app);
+        case 8: return pick_project_table<T, 8, D>(split, app);
+        default: return nullptr;
+    }
+}
+template <typename T>
+static project_fn_t pick_project(const Geometry &g, bool soft, bool app) {
+    const bool split = g.mode == kSplit;
+    switch (g.d) {
+        case 64: return pick_project_g<T, 64>(g.G, split, soft, app);
+        case 128: return pick_project_g<T, 128>(g.G, split, soft, app);
+        case 256: return pick_project_g<T, 256>(g.G, split, soft, app);
+        default: return nullptr;
+    }
+}
+
 int launch_project(socket_ctx *ctx, const void *q, const void *proj, float tau, const void *K,
                    void *codes, const int32_t *block_table, const int32_t *pos, const int32_t *count,
                    int32_t *len_out, int batch, hipStream_t st, const float *vnorm) {
@@ -2102,9 +2280,7 @@ int launch_project(socket_ctx *ctx, const void *q, const void *proj, float tau, 
     a.pf = g.pf; a.Pu = g.Pu; a.tmean = (double)g.pf / (double)(1 << g.Pu); a.subprobs = ctx->subprobs;
     a.cols_magic = (65536 + g.P - 1) / g.P;
     const size_t lds = (size_t)(2 * g.G * kPlanePad + g.G * g.d + g.P * g.d) * sizeof(double) +
-                       (size_t)(g.P * g.d + g.d) * 4 + 64 + 48 +
-                       (g.mode == kSplit ? (size_t)g.G * 36 * sizeof(double) : 0);
-    typedef void (*project_fn_t)(ProjectArgs);
+                       (size_t)(g.P * g.d + g.d) * 4 + 64;
     project_fn_t fn = nullptr;
     const bool f32 = g.kv_dtype == SOCKET_F32;
     a.batch = batch; a.nb = 1;
@@ -2150,6 +2326,12 @@ int launch_project(socket_ctx *ctx, const void *q, const void *proj, float tau, 
         return record_hip(ctx, hipGetLastError());
     }
     dim3 grid(g.Lpad, g.Hkv, batch);
+    if (g.mode != kFactor) {
+        fn = f32 ? pick_project<float>(g, q != nullptr, K != nullptr) : pick_project<uint16_t>(g, q != nullptr, K != nullptr);
+        if (!fn) return SOCKET_EUNSUPPORTED;
+        hipLaunchKernelGGL(fn, grid, dim3(256), 0, st, a);
+        return record_hip(ctx, hipGetLastError());
+    }
     const bool dw = !f32 && (g.P * 2) % 16 != 0 && (g.P * 2) % 4 == 0;    // see project_kernel
     switch (g.G) {
         case 1: fn = f32 ? project_kernel<float, 1, false> : dw ? project_kernel<uint16_t, 1, true> : project_kernel<uint16_t, 1, false>; break;

@@ -1422,6 +1422,28 @@ def test_bucket_probs_match_oracle_entry_by_entry(L, P, G, kv_dtype):
         ctx.close()
 
 
+@pytest.mark.parametrize("d,kv_dtype,G,L,P", [(64, wl.F32, 8, 13, 1), (64, wl.BF16, 1, 16, 3), (128, wl.BF16, 2, 7, 7), (128, wl.F32, 8, 65, 8),
+                                              (256, wl.BF16, 8, 20, 9), (256, wl.F32, 4, 33, 10), (256, wl.BF16, 2, 100, 8)])
+def test_bucket_probs_of_one_sequence(d, kv_dtype, G, L, P):
+    """Alg. 2 for one sequence, a workgroup per table: head widths, plane counts that leave rows of
+    its matrices empty, groups that fill them, tables that are padding; each entry a fp64 product
+    rounded to fp32."""
+    _need_gpu()
+    Hkv = 2
+    layer = small_layer(seed=141, B=1, Hq=Hkv * G, Hkv=Hkv, d=d, n=64, L=L, P=P, k=8, kv_dtype=kv_dtype)
+    ctx = hz.make_ctx(layer)
+    qd, Wd = hz.dev(layer.q, layer.kv_dtype), hz.dev(layer.W, layer.kv_dtype)
+    probs = torch.full((1, Hkv, L, 1 << P), -1.0, dtype=torch.float32, device="cuda")
+    ctx.soft_hash(qd, Wd, 0.5, 1)
+    ctx.bucket_probs(1, probs)
+    torch.cuda.synchronize()
+    got = probs.cpu().numpy().astype(np.float64)
+    for h in range(Hkv):
+        want = hz.oracle_probs(layer, 0, h, tau=0.5).mean(axis=0)
+        assert np.all(np.abs(got[0, h] - want) <= 3e-7 * want + 1e-37), h
+    ctx.close()
+
+
 @pytest.mark.parametrize("d,kv_dtype,G,P", [(64, wl.BF16, 4, 8), (64, wl.F32, 2, 8), (64, wl.F32, 8, 4), (256, wl.BF16, 2, 8)])
 def test_bucket_probs_other_head_widths(d, kv_dtype, G, P):
     """Alg. 2 for a batch of three sequences at head widths 64 and 256 (the batched projection
