@@ -229,7 +229,10 @@ int socket_score_keys(socket_ctx *ctx, const void *codes, const float *vnorm,
  * probabilities the context holds, or leading digits of the score when those do not apply);
  * socket_topk_select_binned is socket_topk_select starting from that histogram instead of
  * making its own.  Same scores, same selection.  The two calls come in pairs on one context:
- * a socket_topk_select_binned without the other before it returns SOCKET_EINVAL.
+ * a socket_topk_select_binned without the other before it returns SOCKET_EINVAL.  A
+ * socket_topk_select or socket_decode_step between the two discards the histogram (a fill kernel
+ * more, once), and the select then makes its own.  A second socket_score_keys_binned before the
+ * select needs a socket_reset first, or it counts on top of the other.
  */
 int socket_score_keys_binned(socket_ctx *ctx, const void *codes, const float *vnorm,
                              const int32_t *block_table, const int32_t *seq_len, int32_t batch,

@@ -328,13 +328,21 @@ int socket_score_keys_binned(socket_ctx *ctx, const void *codes, const float *vn
     return rc;
 }
 
+// A histogram whose select has not come yet is in the way of a call that starts from an empty one (it
+// would count on top of it, and take its lists for twice as long as they are).
+static int drop_pending(socket_ctx *ctx, hipStream_t st) {
+    if (ctx->pending_hist == sk::kHistNone || ctx->pending_hist == sk::kHistDropped) return SOCKET_OK;
+    ctx->pending_hist = sk::kHistDropped;
+    return launch_clear_hist(ctx, st);
+}
+
 int socket_topk_select_binned(socket_ctx *ctx, const float *scores, const int32_t *seq_len,
                               const int32_t *k, int32_t batch, int32_t *idx, int32_t *n_selected,
                               void *stream) {
     if (!ctx || !scores || !seq_len || !k || !idx || !n_selected) return SOCKET_EINVAL;
     if (!batch_ok(ctx, batch)) return SOCKET_EINVAL;
     if (ctx->pending_hist == sk::kHistNone) return SOCKET_EINVAL;    // no socket_score_keys_binned before it
-    const int mode = ctx->pending_hist;
+    const int mode = ctx->pending_hist == sk::kHistDropped ? sk::kHistNone : ctx->pending_hist;
     ctx->pending_hist = sk::kHistNone;
     return launch_topk(ctx, scores, seq_len, k, batch, idx, n_selected, mode, (hipStream_t)stream);
 }
@@ -360,6 +368,8 @@ int socket_topk_select(socket_ctx *ctx, const float *scores, const int32_t *seq_
                        void *stream) {
     if (!ctx || !scores || !seq_len || !k || !idx || !n_selected) return SOCKET_EINVAL;
     if (!batch_ok(ctx, batch)) return SOCKET_EINVAL;
+    const int rc = drop_pending(ctx, (hipStream_t)stream);
+    if (rc != SOCKET_OK) return rc;
     return launch_topk(ctx, scores, seq_len, k, batch, idx, n_selected, sk::kHistNone, (hipStream_t)stream);
 }
 
@@ -386,8 +396,10 @@ int socket_decode_step(socket_ctx *ctx, const void *q, const void *K, const void
     if (!(scale == scale) || scale > 3.0e38f || scale < -3.0e38f) return SOCKET_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     int32_t *len = ctx->seq_scratch;
+    int rc = drop_pending(ctx, st);
+    if (rc != SOCKET_OK) return rc;
     // 1. hash the appended key and soft-hash the queries (one launch); len = pos + 1
-    int rc = launch_project(ctx, q, proj, tau, K, codes, block_table, pos, nullptr, len, batch, st, vnorm);
+    rc = launch_project(ctx, q, proj, tau, K, codes, block_table, pos, nullptr, len, batch, st, vnorm);
     if (rc != SOCKET_OK) return rc;
     // 2. score every key; the leading-digit histogram of the scores comes out of the same pass
     int hist_mode = sk::kHistNone;

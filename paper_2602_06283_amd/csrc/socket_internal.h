@@ -46,7 +46,9 @@ enum TableMode { kDirect = 0, kFactor = 1, kSplit = 2 };
 //   adaptive : counts per bin of score_bin() with the (offset, reciprocal width) pair stored in
 //              the threshold record; the bins are narrow where the scores are dense, so the
 //              threshold bin alone already isolates a short candidate list
-enum HistMode { kHistNone = 0, kHistDigit = 1, kHistAdaptive = 2 };
+//   dropped  : (pending_hist only) the histogram left for socket_topk_select_binned was cleared for
+//              another call on the context; that select, if it still comes, makes its own
+enum HistMode { kHistNone = 0, kHistDigit = 1, kHistAdaptive = 2, kHistDropped = 3 };
 
 struct Geometry {
     // Ids of 1, 2 or 4 bits are kept 8 / P to a byte when L is a multiple of that: the byte of
@@ -146,6 +148,7 @@ int launch_dense_decode(socket_ctx *ctx, const void *q, const void *K, const voi
                         int out_dtype, void *out, hipStream_t st);
 int launch_bucket_probs(socket_ctx *ctx, int batch, float *probs, hipStream_t st);
 int launch_reset(socket_ctx *ctx, hipStream_t st);
+int launch_clear_hist(socket_ctx *ctx, hipStream_t st);   // the first-level histogram only
 int launch_stream_read(const void *buf, int64_t bytes, uint32_t *sink, hipStream_t st);
 int launch_value_norms(socket_ctx *ctx, const void *V, const int32_t *block_table,
                        const int32_t *row_begin, const int32_t *row_count, int batch, int max_rows,

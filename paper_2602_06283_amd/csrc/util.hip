@@ -59,14 +59,20 @@ __global__ __launch_bounds__(256) void clear_words_kernel(uint32_t *p, int64_t n
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0u;
 }
 
+static void clear_words(uint32_t *p, int64_t n, hipStream_t st) {
+    hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024)), dim3(256), 0, st, p, n);
+}
+
+int launch_clear_hist(socket_ctx *ctx, hipStream_t st) {
+    clear_words(ctx->hist, (int64_t)ctx->g.max_batch * ctx->g.Hkv * kHistBins, st);
+    return record_hip(ctx, hipGetLastError());
+}
+
 int launch_reset(socket_ctx *ctx, hipStream_t st) {
     const Geometry &g = ctx->g;
     const int64_t BH = (int64_t)g.max_batch * g.Hkv;
-    const int64_t n_hist = 2 * BH * kHistBins, n_cnt = BH * (kCounterStride + kThrStride);
-    hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((n_hist + 255) / 256 < 1024 ? (n_hist + 255) / 256 : 1024)), dim3(256), 0, st,
-                       ctx->hist, n_hist);
-    hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((n_cnt + 255) / 256 < 1024 ? (n_cnt + 255) / 256 : 1024)), dim3(256), 0, st,
-                       ctx->counters, n_cnt);
+    clear_words(ctx->hist, 2 * BH * kHistBins, st);
+    clear_words(ctx->counters, BH * (kCounterStride + kThrStride), st);
     ctx->pending_hist = kHistNone;
     return record_hip(ctx, hipGetLastError());
 }

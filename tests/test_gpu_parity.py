@@ -1508,3 +1508,58 @@ def test_binned_score_and_select_pair_equals_the_plain_calls():
     torch.cuda.synchronize()
     assert torch.equal(i3, i1) and torch.equal(c3, c1)
     ctx.close()
+
+
+@pytest.mark.parametrize("norms", [False, True])
+@pytest.mark.parametrize("n", [9008, 24592])
+def test_other_calls_between_a_binned_score_and_its_select(n, norms):
+    """A select or a fused step that comes before socket_topk_select_binned does not count on top of
+    the waiting histogram, and the late select still gives its own scores' selection (rows of the
+    one-launch select and longer ones; adaptive bins, and digits where norms were not sampled)."""
+    _need_gpu()
+    Hkv, G, L, P, k = 2, 4, 32, 8, 300
+    layer = small_layer(seed=135, B=1, Hq=Hkv * G, Hkv=Hkv, n=n, L=L, P=P, k=[k], seq_len=[n - 5])
+    codes = None
+    Kd, Vd, qd, Wd = (hz.dev(x, layer.kv_dtype) for x in (layer.K, layer.V, layer.q, layer.W))
+    ln, kk, pos = hz.i32(layer.seq_len), hz.i32([k]), hz.i32([n - 6])
+    rng = np.random.default_rng(136)
+    vn = torch.from_numpy(np.exp(rng.standard_normal((1, Hkv, n))).astype(np.float32)).cuda() if norms else None
+    other = torch.from_numpy(rng.standard_normal((1, Hkv, n)).astype(np.float32)).cuda()
+
+    def selection():
+        return torch.zeros((1, Hkv, k), dtype=torch.int32, device="cuda"), torch.zeros((1, Hkv), dtype=torch.int32, device="cuda")
+    got = {}
+    for name in ("alone", "between"):
+        ctx = hz.make_ctx(layer)
+        if codes is None:
+            codes = run_hash(ctx, layer, [0], layer.seq_len, n)
+        scores = torch.zeros((1, Hkv, n), dtype=torch.float32, device="cuda")
+        out = torch.zeros((1, Hkv * G, layer.d), dtype=torch.float32, device="cuda")
+        plain, late, step = selection(), selection(), selection()
+
+        def binned():
+            if name == "between":
+                ctx.soft_hash(qd, Wd, 0.5, 1)
+                ctx.score_keys_binned(codes, ln, 1, scores, vnorm=vn)
+        binned()
+        ctx.topk_select(other, ln, kk, 1, *plain)
+        if name == "between":
+            ctx.topk_select_binned(scores, ln, kk, 1, *late)
+        binned()
+        step_scores = torch.zeros_like(scores)
+        for _ in range(2):
+            ctx.decode_step(qd, Kd, Vd, codes, Wd, 0.5, pos, kk, 1, 1.0, step_scores, *step, out, vnorm=vn)
+        if name == "between":
+            ctx.topk_select_binned(scores, ln, kk, 1, *late)
+            with pytest.raises(sk.SocketError):
+                ctx.topk_select_binned(scores, ln, kk, 1, *late)
+        else:
+            ctx.soft_hash(qd, Wd, 0.5, 1)
+            ctx.score_keys(codes, ln, 1, scores, vnorm=vn)
+            ctx.topk_select(scores, ln, kk, 1, *late)
+        torch.cuda.synchronize()
+        got[name] = (scores, step_scores, out) + plain + late + step
+        ctx.close()
+    for a, b in zip(got["alone"], got["between"]):
+        assert torch.equal(a, b)
+    check_topk(got["between"][3].cpu().numpy(), got["between"][4].cpu().numpy(), other.cpu().numpy(), layer.seq_len, [k])
