@@ -638,9 +638,6 @@ __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int 
     cut(tid + (PER - 1) * NT, meanwhile);
 }
 
-// Barrier after LDS writes that leaves loads from memory in flight (__syncthreads waits for them).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 struct OneSequence {                                   // (what stands for SeqUnits where there is nothing to share out)
     __device__ __forceinline__ explicit OneSequence(const HashArgs &) {}
     __device__ __forceinline__ int total() const { return 0; }
@@ -742,9 +739,8 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
         blk = slot + (w / parts) * slots;
         if (blk < nblocks) load_keys(blk);
     });
-    if (SHORT) lds_barrier();
-    else {
-        __syncthreads();
+    __syncthreads();                           // (waits for LDS only: a short run's keys stay under way)
+    if (!SHORT) {
         nblocks = SHARE ? runs.total() : (count + 63) >> 6;   // (not before the slab: nothing there waits for the lengths)
         if (blk < nblocks) load_keys(blk);
     }
@@ -901,9 +897,8 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
         blk = slot + (w / parts) * slots;
         if (blk < nblocks) load_keys(blk);
     });
-    if (SHORT) lds_barrier();
-    else {
-        __syncthreads();
+    __syncthreads();                           // (waits for LDS only: a short run's keys stay under way)
+    if (!SHORT) {
         nblocks = SHARE ? runs.total() : (count + 63) >> 6;   // (not before the slab: nothing there waits for the lengths)
         if (blk < nblocks) load_keys(blk);
     }
