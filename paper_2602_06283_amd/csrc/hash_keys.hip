@@ -586,8 +586,9 @@ constexpr int kHash8Threads = 1024;
 // a thread takes one table (P columns) and eight channels, eight loads of 2 P bytes in flight, and
 // transposes them in registers into P pieces of eight channels each.  (A launch of its own that laid
 // the fragments out in memory first cost 4 to 5 us by itself, 2 to 3 back to back with this one:
-// 777 + 333 rows of (10, 60) with their value norms 18.8 us with it, 16.2 now; 4 heads x 32768 keys,
-// d = 256, 36.1 / 33.9; 4 sequences of 65536 keys, 8 heads of (8, 64), 238.8 / 238.3.)
+// 777 + 333 rows of (10, 60) with their value norms 18.8 us with it, 16.2 without (15.4 since short runs
+// share blocks); 4 heads x 32768 keys, d = 256, 37.8 / 35.1; 4 sequences of 65536 keys, 8 heads of
+// (8, 64), 241.6 / 240.3, where two runs of one side differ by 0.7.)
 // The workgroup's tables are tab0 + (i / NG) * S + i % NG: NG of the S interleaved position groups.
 // Column P j + pl of position group `sub` (j = its j-th table) is bit u % 32 of sign word u / 32,
 // u = P j + pl; wl holds word q of the workgroup's group sl as block sl BPG + q.
@@ -654,7 +655,7 @@ enum HashRuns {
 // Shape of a workgroup: NG of the chunk's S position groups (a chunk's workgroups are its S / NG
 // parts), their fragments in LDS.  d = 256: a block's fragments are 16 KB, so eight blocks, and a
 // 64-key block of keys takes 128 registers, so eight wavefronts; the keys are read once per part
-// (4 heads x 32768 keys, 64 tables of 8 planes: 36.6 us = 0.94 PFLOP/s, against 72.9 through
+// (4 heads x 32768 keys, 64 tables of 8 planes: 35.1 us = 0.98 PFLOP/s, against 72.9 through
 // hash_mfma_kernel, which stages the keys through LDS and packs ids generically).
 template <int D, int S, int P> constexpr int hash8_groups() { return D <= 128 || S * P / 2 <= 8 ? S : S / 2; }
 template <int D> constexpr int hash8_threads() { return D <= 128 ? kHash8Threads : 512; }
@@ -721,12 +722,14 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     };
 
     // 64-key blocks are dealt round-robin, to the workgroups before their wavefronts: short runs and
-    // last rounds then spread over the compute units (8 heads, 64 tables of 8 planes: 8192 keys
-    // 18.6 us, 29.0 with whole workgroups filled first; 40000 keys 44 / 55; full rounds alike)
+    // last rounds then spread over the compute units (8 heads, 64 tables of 8 planes, both ways with
+    // the launch that cut W: 8192 keys 18.6 us, 29.0 with whole workgroups filled first; 40000 keys
+    // 44 / 55; full rounds alike.  Without that launch 16.9 and 42.6)
     // Short runs: while that leaves wavefronts without a block, two or four of them share one, NG / parts
     // of its position groups each, and the keys are fetched while W is cut (8 heads, (8, 64): 777 keys
-    // 15.9 us with the launch that cut W, 7.4 now; 4096 16.7 / 10.8; (10, 60) 777 keys 12.9 / 7.1.  Long runs keep the loop of whole blocks: with bounds of its own for every
-    // wavefront 131072 keys took 132 us, 127 without).
+    // 15.9 us with the launch that cut W, 7.1 now; 4096 16.7 / 10.3; (10, 60) 777 keys 12.9 / 6.8.  Long
+    // runs keep the loop of whole blocks: with bounds of its own for every wavefront 131072 keys took
+    // 132 us, 127 without).
     int nblocks = 0, stride = slots * NW, blk = slot + wave * slots, parts = 1, p0 = 0;
     cut_fragments<D, S, P, NG, NT>(wl, a, h, first_table, ntab, sub0, tid, [&]() __attribute__((always_inline)) {
         if (!SHORT) return;

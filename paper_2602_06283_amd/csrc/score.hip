@@ -382,7 +382,7 @@ __global__ __launch_bounds__(256) void project_table_kernel(ProjectArgs a) {
 // independent loads before the first use, and every dot product is cut into channel ranges that
 // adjacent lanes sum with DPP moves.
 // DW: the dword fetch of the W slab is compiled in (bf16 tables whose planes are whole dwords
-// but not whole 16-byte vectors, e.g. 10 planes); the other instantiations stay as lean as
+// but not whole 16-byte vectors, e.g. 12 planes); the other instantiations stay as lean as
 // they were.
 template <typename T, int G, bool DW>
 __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a) {
     const T *Wg = (const T *)a.W + (int64_t)h * d * a.LP + col0;
     const int row_bytes = cols * (int)sizeof(T);
     // Three ways to fetch the slab: 16-byte vectors when a channel's planes are whole vectors
-    // (8 planes of bf16), dwords when they are whole dwords (10 planes of bf16: 5 each), else
+    // (8 planes of bf16), dwords when they are whole dwords (12 planes of bf16: 6 each), else
     // element by element.  i / n for i < 4096 and n <= 16 is a multiplication by ceil(2^16 / n).
     const bool wvec = (row_bytes & 15) == 0 && ((a.LP * (int)sizeof(T)) & 15) == 0;
     const bool wdw = DW && !wvec && sizeof(T) == 2 && (row_bytes & 3) == 0 && ((a.LP * (int)sizeof(T)) & 3) == 0 &&
