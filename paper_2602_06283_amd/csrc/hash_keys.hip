@@ -997,7 +997,7 @@ static int share_groups(HashArgs *a) {
 // most of its LDS) over `rows` heads, chunks and parts.  `shared` (null: there is none): the kernel
 // that deals the blocks of several sequences out as one, for batches in which a wavefront of
 // `alone` would have more than one block of the longest run, or one round of workgroups would not do.
-// (A workgroup without a block copies its slab for nothing; asking for the run's length first cost
+// (A workgroup without a block cuts its slab for nothing; asking for the run's length first cost
 // every short run 0.3 us, 4 % at 5000 keys of 16 tables, and gained nothing in ragged batches.)
 typedef void (*fragment_kernel_t)(HashArgs);
 static void launch_blocks(fragment_kernel_t alone, fragment_kernel_t brief, fragment_kernel_t shared, HashArgs a, int rows,

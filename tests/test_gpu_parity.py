@@ -168,12 +168,13 @@ def test_hash_keys_projections_at_any_element(d, L, P):
     ctx.close()
 
 
-@pytest.mark.parametrize("d,L,P", [(64, 64, 8), (64, 20, 8), (64, 33, 4), (64, 60, 10), (256, 64, 8), (256, 60, 10)])
-def test_hash_keys_short_runs_share_blocks_among_wavefronts(d, L, P):
+@pytest.mark.parametrize("d,L,P,n,B,H", [(64, 64, 8, 2304, 8, 8), (64, 20, 8, 2304, 8, 8), (64, 33, 4, 2304, 8, 8), (64, 60, 10, 2304, 8, 8),
+                                         (256, 64, 8, 1152, 2, 4), (256, 60, 10, 1152, 2, 4), (256, 64, 8, 1024, 8, 8), (256, 33, 4, 2048, 8, 8)])
+def test_hash_keys_short_runs_share_blocks_among_wavefronts(d, L, P, n, B, H):
     """Runs of which no wavefront has more than one block of 64 keys: whole blocks, halves and quarters
-    of one to a wavefront (by the length of the run) give the oracle's ids, and the same bit for bit."""
+    of one to a wavefront (by the length of the run and the number of runs; as many of them as a
+    workgroup has position groups) give the oracle's ids, and the same bit for bit."""
     _need_gpu()
-    n, B, H = (2304, 8, 8) if d == 64 else (1152, 2, 4)
     layer = small_layer(seed=18, B=B, Hq=H, Hkv=H, d=d, n=n, L=L, P=P, k=16)
     ctx = hz.make_ctx(layer)
     counts = [n, n - 1, 0, 65, n - 63, 1, 700, n // 2][:B]
