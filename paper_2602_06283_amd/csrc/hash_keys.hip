@@ -582,6 +582,17 @@ template <int V> struct IntTag { static constexpr int value = V; };
 
 constexpr int kHash8Threads = 1024;
 
+typedef float floatx2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+
+// Two adjacent channels in two bf16 pieces, rounded to nearest: the hi pieces, lo gets the others.
+__device__ __forceinline__ uint32_t cut_pair(floatx2_t v, uint32_t *lo) {
+    const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+    const floatx2_t left = {v.x - __uint_as_float(hi << 16), v.y - __uint_as_float(hi & 0xffff0000u)};
+    *lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(left, bf16x2_t));
+    return hi;
+}
+
 // The A fragments of a workgroup of the two fast kernels, cut from W into LDS by the workgroup itself:
 // a thread takes one table (P columns) and eight channels, eight loads of 2 P bytes in flight, and
 // transposes them in registers into P pieces of eight channels each.  (A launch of its own that laid
@@ -596,23 +607,29 @@ constexpr int kHash8Threads = 1024;
 // wavefront write side by side would share banks.
 __device__ __forceinline__ int frag_turn(int sl, int q) { return (sl ^ q) & 3; }
 
+// fp32: W goes in two bf16 pieces, a block's hi fragments before its lo fragments.  Columns without a
+// table repeat the last one's there (a sum of zero would look like a sign too close to call).
 // `meanwhile` is called once, the thread's last loads of W on their way.
-template <int D, int S, int P, int NG, int NT, typename F>
+template <typename T, int D, int S, int P, int NG, int NT, typename F>
 __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int h, int first_table, int ntab, int sub0, int tid, F &&meanwhile) {
-    constexpr int KS = D / 16, BPG = P / 2, NTAB = 16 * NG, ITEMS = NTAB * (D / 8), ND = P / 2;   // ND: dwords of a table's row
+    constexpr bool SPLIT = sizeof(T) == 4;
+    constexpr int KS = D / 16, KF = SPLIT ? 2 * KS : KS, BPG = P / 2, NTAB = 16 * NG, ITEMS = NTAB * (D / 8);
+    constexpr int ND = P * (int)sizeof(T) / 4;         // dwords of a table's row
     constexpr int PER = (ITEMS + NT - 1) / NT;
-    static_assert(ND == 2 || ND == 4 || ND == 5, "4, 8 or 10 planes");
+    static_assert(P == 4 || P == 8 || P == 10, "whole dwords");
     // rows of W start at any element: L P and the caller's pointer say nothing about alignment
-    struct __attribute__((packed, aligned(2))) Row { uint32_t w[ND]; };
-    const uint16_t *W = (const uint16_t *)a.W + ((int64_t)h * D * a.LP + (int64_t)first_table * P);
+    struct __attribute__((packed, aligned(sizeof(T)))) Row { uint32_t w[ND]; };
+    const T *W = (const T *)a.W + ((int64_t)h * D * a.LP + (int64_t)first_table * P);
     auto cut = [&](int i, auto &&between) __attribute__((always_inline)) {
         int ti = i % NTAB;
         const int oct = i / NTAB;                      // channels 8 oct .. 8 oct + 7
         // (eight adjacent lanes: four groups, both halves of a sign word)
         if (S == 4 && NG == 4 && P == 8) ti = (ti & ~12) | ((ti >> 1) & 4) | ((ti << 1) & 8);
-        const int j = ti / NG, sl = ti % NG, tt = j * S + sub0 + sl;   // chunk-local table
+        const int j = ti / NG, sl = ti % NG;
+        int tt = j * S + sub0 + sl;                    // chunk-local table
+        if (SPLIT) tt = min(tt, ntab - 1);
         Row r[8];
-        if ((ITEMS % NT == 0 || i < ITEMS) && tt < ntab) {
+        if ((ITEMS % NT == 0 || i < ITEMS) && (SPLIT ? ntab > 0 : tt < ntab)) {
 #pragma unroll
             for (int c = 0; c < 8; ++c) r[c] = *(const Row *)(W + (int64_t)(oct * 8 + c) * a.LP + tt * P);
         } else {
@@ -625,19 +642,204 @@ __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int 
         if (ITEMS % NT != 0 && i >= ITEMS) return;
 #pragma unroll
         for (int pl = 0; pl < P; ++pl) {
-            const uint32_t pick = pl & 1 ? 0x07060302u : 0x05040100u;   // the high or the low halves of two words
-            uint32_t o[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) o[c] = __builtin_amdgcn_perm(r[2 * c + 1].w[pl >> 1], r[2 * c].w[pl >> 1], pick);
             const int u = P * j + pl, q = u >> 5, bit = u & 31;
             const int m = 8 * ((bit >> 2) & 3) + 4 * (bit >> 4) + (bit & 3);   // the MFMA row that becomes this bit
-            wl[((sl * BPG + q) * KS + (oct >> 1)) * 64 + (((oct & 1) * 32 + m) ^ frag_turn(sl, q))] = make_uint4(o[0], o[1], o[2], o[3]);
+            uint4 *dst = wl + ((sl * BPG + q) * KF + (oct >> 1)) * 64 + (((oct & 1) * 32 + m) ^ frag_turn(sl, q));
+            uint32_t o[4];
+            if constexpr (SPLIT) {
+                uint32_t lo[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) o[c] = cut_pair(floatx2_t{__uint_as_float(r[2 * c].w[pl]), __uint_as_float(r[2 * c + 1].w[pl])}, lo + c);
+                dst[KS * 64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            } else {
+                const uint32_t pick = pl & 1 ? 0x07060302u : 0x05040100u;   // the high or the low halves of two words
+#pragma unroll
+                for (int c = 0; c < 4; ++c) o[c] = __builtin_amdgcn_perm(r[2 * c + 1].w[pl >> 1], r[2 * c].w[pl >> 1], pick);
+            }
+            dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
         }
     };
 #pragma unroll 1
     for (int k = 0; k + 1 < PER; ++k) cut(tid + k * NT, []() {});
     cut(tid + (PER - 1) * NT, meanwhile);
 }
+
+// ---------------------------------------------------------------------------------------
+// fp32 keys on the bf16 matrix cores.  Keys and W are cut into two bf16 pieces each, x = hi + lo + rest
+// with |lo| <= 2^-8 |x| and |rest| <= 2^-8 |lo|, and lo*hi + hi*lo, then hi*hi, are summed: three
+// products at 16 times the fp32 matrix rate a product.  An id only takes the sign of a sum, so what the
+// pieces leave out matters near zero alone: where |sum| is not above a bound on its distance to the sum
+// that the FMA kernel forms (three projections in ten thousand for normal keys), the projection goes on
+// the wavefront's list and is formed anew, channel by channel as the FMA kernel does; if the sign is the
+// other one (one in ten million) its bit is turned in memory.  The ids are those of the FMA kernel bit
+// for bit.
+// The bound, for a key k and a column w, with A >= the norm of a vector and B = the norm of its lo
+// pieces (Cauchy-Schwarz turns norms into sums of magnitudes):
+//   dropped products  lo*lo <= B_k B_w, rest*w <= 2^-8 B_k A_w, k*rest <= 2^-8 A_k B_w
+//   FMA kernel        D roundings of 2^-24 of at most A_k A_w
+//   matrix cores      D additions to the sum of hi*hi, each off by 2^-23 of at most A_k A_w if it
+//                     truncates; the lo sums before them are 2^-7 as large (within the hundredth)
+// close_part gives a key's (x, y), bound = x A_w + y B_w.  Where squares leave the range of floats, with
+// infinities and NaN, the bound is infinite and every projection formed anew.  The sums of an all-zero
+// key are zero: it needs none.
+// ---------------------------------------------------------------------------------------
+template <int D> __device__ __forceinline__ float2 close_part(float A, float B) {
+    float2 e = make_float2(1.01f * (A * (D * 1.8e-7f) + B * 0.00391f), 1.01f * (B * 1.01f + A * 0.00391f));
+    if (!(A > 1e-10f && A < 1e15f)) e = A == 0.0f ? make_float2(-1.0f, 0.0f) : make_float2(__builtin_inff(), __builtin_inff());
+    return e;
+}
+// sum of the squares of eight bf16 pieces, on top of `sum`
+__device__ __forceinline__ float add_squares(bf16x8_t v, float sum) {
+    const uint4 w = __builtin_bit_cast(uint4, v);
+    sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w.x), __builtin_bit_cast(bf16x2_t, w.x), sum, false);
+    sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w.y), __builtin_bit_cast(bf16x2_t, w.y), sum, false);
+    sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w.z), __builtin_bit_cast(bf16x2_t, w.z), sum, false);
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w.w), __builtin_bit_cast(bf16x2_t, w.w), sum, false);
+}
+// cols: the largest A and B of the columns of a block, whose fragments these are (wave-wide; an
+// infinity where one of them is out of range)
+template <int KS> __device__ __forceinline__ float2 close_columns(const uint4 *frag) {
+    float hi = 0.0f, lo = 0.0f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        hi = add_squares(__builtin_bit_cast(bf16x8_t, frag[ks * 64]), hi);
+        lo = add_squares(__builtin_bit_cast(bf16x8_t, frag[(KS + ks) * 64]), lo);
+    }
+    const float B = 1.01f * sqrtf(xor32_sum(lo)), A = 1.001f * sqrtf(xor32_sum(hi)) + B;
+    const bool odd = __ballot(!(A < 1e15f)) != 0;              // (a NaN would be lost in the largest)
+    const float most = wave_max(A);
+    return make_float2(odd || !(most > 1e-10f) ? __builtin_inff() : most, wave_max(B));
+}
+
+struct CloseEntry {
+    int64_t row;       // the key's row in K and in the ids
+    int tok;
+    uint32_t col;      // column of the workgroup's tables; top bit: the bit its id has
+};
+
+// A wavefront's list.  Entries are settled when it is half full and after the last block, a lane each.
+template <int D, int P, int S, int CAP> struct CloseList {
+    static_assert(CAP <= 64, "a lane each");
+    const HashArgs &a;
+    CloseEntry *list;
+    const float *W;                            // [D][LP], the workgroup's tables from column 0 on
+    int first_table, ntab, n = 0;
+
+    __device__ __forceinline__ CloseList(const HashArgs &args, CloseEntry *mine, int h, int first, int tables)
+        : a(args), list(mine), W((const float *)args.W + (int64_t)h * D * args.LP + (int64_t)first * P), first_table(first), ntab(tables) {}
+
+    __device__ __forceinline__ float sum_of(int64_t row, int col) const {
+        const f32x4_t *k = (const f32x4_t *)((const float *)a.K + row * D);
+        const float *w = W + col;
+        float sum = 0.0f;
+#pragma unroll 8
+        for (int c = 0; c < D / 4; ++c) {
+            const f32x4_t x = k[c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum = fmaf(x[e], w[(int64_t)(4 * c + e) * a.LP], sum);
+        }
+        return sum;
+    }
+
+    // Accumulator i of half g is bit 32 q + 16 g + i of position group `sub` of the lane's key;
+    // bit i of neg its sign.  row(): the key's row in K, or -1.
+    template <typename F>
+    __device__ __forceinline__ void add(const floatx16_t &acc, uint32_t &neg, float2 key, float2 cols, int q, int sub, int tok, F &&row) {
+        float least = fabsf(acc[0]);
+#pragma unroll
+        for (int i = 1; i < 16; ++i) least = fminf(least, fabsf(acc[i]));   // (a NaN comes with an infinite bound)
+        const float bound = cols.x < __builtin_inff() ? fmaf(key.x, cols.x, key.y * cols.y) : __builtin_inff();
+        if (__ballot(!(least > bound)) == 0 || ntab <= 0) return;
+        uint32_t near = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) near |= (fabsf(acc[i]) > bound ? 0u : 1u) << i;
+        const int lane = threadIdx.x & 63;
+        const int64_t gr = row();
+        if (gr < 0) near = 0;
+        while (__ballot(near != 0) != 0) {
+            const int i = __ffs((int)near) - 1, u = 32 * q + 16 * (lane >> 5) + i, tt = (u / P) * S + sub;
+            const bool mine = near != 0 && tt < ntab;
+            near &= near - 1;
+            const uint64_t m = __ballot(mine);
+            const int at = n + __popcll(m & ((1ull << lane) - 1)), col = tt * P + u % P;
+            if (mine && at < CAP) list[at] = CloseEntry{gr, tok, (uint32_t)col | ((neg >> i) & 1u ? 0u : 1u << 31)};
+            if (mine && at >= CAP) neg = (neg & ~(1u << i)) | (sum_of(gr, col) >= 0.0f ? 0u : 1u) << i;   // (keys by the hundred at right angles to W, or out of range)
+            n = min(n + (int)__popcll(m), CAP);
+        }
+    }
+
+    // the list's projections anew, and the ids that have the other sign mended
+    __device__ __forceinline__ void settle() {
+        if (n == 0) return;
+        const int lane = threadIdx.x & 63;
+        bool flip = false;
+        uint8_t *byte = nullptr;
+        uint32_t bit = 0;
+        if (lane < n) {
+            const CloseEntry e = list[lane];
+            const int col = (int)(e.col & 0x7fffffffu), l = first_table + col / P;
+            flip = (sum_of(e.row, col) >= 0.0f) != ((e.col >> 31) != 0);
+            bit = (uint32_t)(col % P);
+            byte = (uint8_t *)a.codes + e.row * a.Lpad + code_pos(l, e.tok, S);
+        }
+        // (one after the other, behind the ids themselves: two may share a byte; a byte at a time: the
+        // ones beside it may be another workgroup's)
+        __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0)
+        for (uint64_t todo = __ballot(flip); todo != 0; todo &= todo - 1)
+            if (lane == __ffsll((unsigned long long)todo) - 1) {
+                const uint8_t old = __hip_atomic_load(byte, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(byte, (uint8_t)(old ^ (1u << (bit & 7))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __builtin_amdgcn_s_waitcnt(0x0f70);
+            }
+        n = 0;
+    }
+};
+
+// The keys of a wavefront's 64-key block as B operands: bf16 as stored, fp32 in pieces
+template <typename T, int KS> struct KeyBlock;
+template <int KS> struct KeyBlock<uint16_t, KS> {
+    bf16x8_t hi[2][KS];
+    __device__ __forceinline__ void load(int nb, const char *src, int g) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) hi[nb][ks] = *(const bf16x8_t *)(src + g * 16 + ks * 32);
+    }
+    __device__ __forceinline__ void cut() {}
+};
+template <int KS> struct KeyBlock<float, KS> {
+    Row8<float> raw[2][KS];
+    bf16x8_t hi[2][KS], lo[2][KS];
+    float2 close[2];
+    __device__ __forceinline__ void load(int nb, const char *src, int g) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) raw[nb][ks].load(src + g * 32 + ks * 64);
+    }
+    __device__ __forceinline__ void cut() {
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+            uint32_t any = 0;
+            float h2 = 0.0f, l2 = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                float f[8];
+                raw[nb][ks].get(f);
+                uint32_t h[4], l[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    any |= __float_as_uint(f[2 * c]) | __float_as_uint(f[2 * c + 1]);
+                    h[c] = cut_pair(floatx2_t{f[2 * c], f[2 * c + 1]}, l + c);
+                }
+                hi[nb][ks] = __builtin_bit_cast(bf16x8_t, make_uint4(h[0], h[1], h[2], h[3]));
+                lo[nb][ks] = __builtin_bit_cast(bf16x8_t, make_uint4(l[0], l[1], l[2], l[3]));
+                h2 = add_squares(hi[nb][ks], h2);
+                l2 = add_squares(lo[nb][ks], l2);
+            }
+            const float B = 1.01f * __builtin_amdgcn_sqrtf(xor32_sum(l2)), A = 1.001f * __builtin_amdgcn_sqrtf(xor32_sum(h2)) + B;
+            const uint64_t some = __ballot((any << 1) != 0);   // (zero but for signs)
+            const bool zero = ((some | (some >> 32)) >> (threadIdx.x & 31) & 1) == 0;
+            close[nb] = close_part<16 * KS>(zero ? 0.0f : fmaxf(A, 1e-30f), B);
+        }
+    }
+};
 
 struct OneSequence {                                   // (what stands for SeqUnits where there is nothing to share out)
     __device__ __forceinline__ explicit OneSequence(const HashArgs &) {}
@@ -659,19 +861,29 @@ enum HashRuns {
 // hash_mfma_kernel, which stages the keys through LDS and packs ids generically).
 template <int D, int S, int P> constexpr int hash8_groups() { return D <= 128 || S * P / 2 <= 8 ? S : S / 2; }
 template <int D> constexpr int hash8_threads() { return D <= 128 ? kHash8Threads : 512; }
+// which launches may deal the blocks of several sequences out as one (launch_blocks)
+template <typename T, int D> constexpr bool hash_shares() { return sizeof(T) == 4 || D == 256; }
 
-template <int D, int S, int P, int RUNS>
-__global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs a) {
+// fp32: the shape of bf16 rows of 256 channels, d = 64 too (eight wavefronts, registers for a block's raw
+// keys beside the pieces).
+template <typename T, int D> constexpr int hash_width() { return sizeof(T) == 4 ? 256 : D; }
+
+template <typename T, int D, int S, int P, int RUNS>
+__global__ __launch_bounds__((hash8_threads<hash_width<T, D>()>())) void hash_mfma8_kernel(HashArgs a) {
     static_assert(P == 8 || P == 4, "one-byte ids of 8 planes, or of 4 (a block's eight nibbles are spread over two words)");
     constexpr bool SHARE = RUNS == kRunsShared, SHORT = RUNS == kRunsShort;
+    constexpr bool SPLIT = sizeof(T) == 4;     // bf16 pieces of fp32
     constexpr int KS = D / 16;                 // MFMA k-steps
+    constexpr int KF = SPLIT ? 2 * KS : KS;    // fragments of a block
+    constexpr int WD = hash_width<T, D>();
     constexpr int BPG = P / 2;                 // 32-column blocks per position group of 16 ids
-    constexpr int NG = hash8_groups<D, S, P>();
+    constexpr int NG = hash8_groups<WD, S, P>();
     constexpr int NCB = BPG * NG;              // 32-column blocks of the workgroup
-    constexpr int NT = hash8_threads<D>(), NW = NT / 64;
-    extern __shared__ uint32_t smem[];
-    uint4 *wl = (uint4 *)smem;                         // [NCB][KS][64 lanes] A fragments
-    uint32_t *bits = smem + NCB * KS * 64 * 4;         // [NW waves][64 keys][4 words]
+    constexpr int NT = hash8_threads<WD>(), NW = NT / 64;
+    extern __shared__ __align__(16) uint32_t hash8_lds_words[];
+    uint32_t *smem = hash8_lds_words;
+    uint4 *wl = (uint4 *)smem;                         // [NCB][KF][64 lanes] A fragments
+    uint32_t *bits = smem + NCB * KF * 64 * 4;         // [NW waves][64 keys][4 words]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int row = SHARE ? blockIdx.x : blockIdx.y, slot = SHARE ? blockIdx.y : blockIdx.x, slots = SHARE ? gridDim.y : gridDim.x;
@@ -679,7 +891,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     const int chunk = hc % a.n_chunks, h = hc / a.n_chunks;
     // the 64-key blocks it takes part in: those of sequence blockIdx.z, or (SHARE) of that group
     int b = blockIdx.z, count = 0, begin = 0, shared_r0 = 0;
-    const typename std::conditional<SHARE, SeqUnits<6>, OneSequence>::type runs(a);
+    const typename std::conditional<SHARE && !SPLIT, SeqUnits<6>, OneSequence>::type runs(a);
     if (!SHARE) {
         count = a.row_count[b];
         begin = a.row_begin[b];
@@ -690,6 +902,10 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
 
     uint32_t *mybits = bits + wave * 256;
     const int n = lane & 31, g = lane >> 5;
+    constexpr int CAP = SPLIT ? 64 : 1;                // entries of a CloseList
+    __shared__ float2 cols[SPLIT ? NCB : 1];           // A and B of the blocks' columns
+    __shared__ CloseEntry close_lds[SPLIT ? NW : 1][CAP];
+    CloseList<D, P, S, CAP> close(a, close_lds[SPLIT ? wave : 0], h, first_table, ntab);
     const char *Kb = (const char *)a.K;
     char *Cb = (char *)a.codes;
 
@@ -699,24 +915,25 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     };
     // Branch-free: a key that does not exist reads row 0 of the cache instead (its ids are never
     // stored).
-    bf16x8_t kf[2][KS];
+    KeyBlock<T, KS> keys;
     auto load_keys = [&](int blk) {
-        if (SHARE) runs.find(blk, &b, &count, &begin, &shared_r0);
-        const int r0 = SHARE ? shared_r0 : blk * 64;
+        if (SHARE && !SPLIT) runs.find(blk, &b, &count, &begin, &shared_r0);
+        const int r0 = SHARE && !SPLIT ? shared_r0 : blk * 64;
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb) {
             const int64_t row = key_row(r0 + nb * 32 + n);
-            const char *src = Kb + (row >= 0 ? row : 0) * (int64_t)(D * 2) + g * 16;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) kf[nb][ks] = *(const bf16x8_t *)(src + ks * 32);
+            keys.load(nb, Kb + (row >= 0 ? row : 0) * (int64_t)(D * sizeof(T)), g);
         }
     };
     // 32 sign bits of one key from the accumulators of a 32-row block: bit p = 1 when the
     // projection onto plane p is >= 0.  A lane's 16 accumulators are bits 16g .. 16g+15.
-    auto sign_word = [&](const floatx16_t &acc) -> uint32_t {
+    auto signs = [&](const floatx16_t &acc) -> uint32_t {
         uint32_t neg = __float_as_uint(acc[15]) >> 31;
 #pragma unroll
         for (int i = 14; i >= 0; --i) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[i]), 31);
+        return neg;
+    };
+    auto sign_word = [&](uint32_t neg) -> uint32_t {
         auto both = __builtin_amdgcn_permlane32_swap(neg, neg, false, false);   // g = 0 and g = 1 halves, in every lane
         return ~(both[0] | (both[1] << 16));
     };
@@ -731,7 +948,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
     // runs keep the loop of whole blocks: with bounds of its own for every wavefront 131072 keys took
     // 132 us, 127 without).
     int nblocks = 0, stride = slots * NW, blk = slot + wave * slots, parts = 1, p0 = 0;
-    cut_fragments<D, S, P, NG, NT>(wl, a, h, first_table, ntab, sub0, tid, [&]() __attribute__((always_inline)) {
+    cut_fragments<T, D, S, P, NG, NT>(wl, a, h, first_table, ntab, sub0, tid, [&]() __attribute__((always_inline)) {
         if (!SHORT) return;
         nblocks = (count + 63) >> 6;
         parts = NG;
@@ -743,31 +960,74 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
         if (blk < nblocks) load_keys(blk);
     });
     __syncthreads();                           // (waits for LDS only: a short run's keys stay under way)
-    if (!SHORT) {
+    if constexpr (SPLIT) {
+        for (int p = wave; p < NCB; p += NW) {
+            const float2 c = close_columns<KS>(wl + (p * KF) * 64 + lane);
+            if (lane == 0) cols[p] = c;
+        }
+        __syncthreads();
+    }
+    // SPLIT && SHARE: from sequence to sequence with the blocks counted on, in scalar registers (the keys
+    // and their pieces leave none for SeqUnits); blk is the block of sequence b
+    const int b_end = min(a.batch, (b + 1) * a.group);
+    auto walk = [&]() {
+        while (blk >= nblocks && b + 1 < b_end) {
+            blk -= nblocks;
+            ++b;
+            count = min(a.row_count[b], a.max_rows);
+            begin = a.row_begin[b];
+            nblocks = (max(count, 0) + 63) >> 6;
+        }
+    };
+    if constexpr (SPLIT && SHARE) {
+        blk = slot + __builtin_amdgcn_readfirstlane(wave) * slots;
+        b = b * a.group - 1;
+        walk();
+    } else if (SPLIT && !SHORT) {
+        nblocks = (count + 63) >> 6;
+    } else if (!SHORT) {
         nblocks = SHARE ? runs.total() : (count + 63) >> 6;   // (not before the slab: nothing there waits for the lengths)
         if (blk < nblocks) load_keys(blk);
     }
     const int pb = SHORT ? p0 : 0, pe = SHORT ? p0 + NCB / parts : NCB;
-    for (; blk < nblocks; blk += stride) {
-        const int r0 = SHARE ? shared_r0 : blk * 64;
+    while (blk < nblocks) {
+        const int r0 = SHARE && !SPLIT ? shared_r0 : blk * 64;
+        if (SPLIT && !SHORT) load_keys(blk);
+        keys.cut();
         const int64_t prow = key_row(r0 + lane);        // the key this lane packs
         const int rot = (begin + r0 + lane) & 15;
         uint4 done[NG > 1 ? NG - 1 : 1];                // the key's position groups before the last, kept until the row is whole
 #pragma unroll 1
         for (int p = pb; p < pe; ++p) {
             const int sl = p / BPG, sub = sub0 + sl, q = p % BPG;
-            const uint4 *af = wl + (p * KS) * 64 + (lane ^ frag_turn(sl, q));
+            const uint4 *af = wl + (p * KF) * 64 + (lane ^ frag_turn(sl, q));
             floatx16_t acc0, acc1;
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc0[i] = acc1[i] = 0.0f;
+            auto frag = [&](int i) { return __builtin_bit_cast(bf16x8_t, af[i * 64]); };
+            if constexpr (SPLIT) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {               // (the small products first)
+                    const bf16x8_t fh = frag(ks), fl = frag(KS + ks);
+                    acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fl, keys.hi[0][ks], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fl, keys.hi[1][ks], acc1, 0, 0, 0);
+                    acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fh, keys.lo[0][ks], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fh, keys.lo[1][ks], acc1, 0, 0, 0);
+                }
+            }
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                union { uint4 u; bf16x8_t v; } fa;
-                fa.u = af[ks * 64];
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.v, kf[0][ks], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa.v, kf[1][ks], acc1, 0, 0, 0);
+                const bf16x8_t fa = frag(ks);
+                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, keys.hi[0][ks], acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, keys.hi[1][ks], acc1, 0, 0, 0);
             }
-            const uint32_t w0 = sign_word(acc0), w1 = sign_word(acc1);
+            uint32_t neg0 = signs(acc0), neg1 = signs(acc1);
+            if constexpr (SPLIT) {
+                const float2 c = cols[p];
+                close.add(acc0, neg0, keys.close[0], c, q, sub, begin + r0 + n, [&]() { return key_row(r0 + n); });
+                close.add(acc1, neg1, keys.close[1], c, q, sub, begin + r0 + 32 + n, [&]() { return key_row(r0 + 32 + n); });
+            }
+            const uint32_t w0 = sign_word(neg0), w1 = sign_word(neg1);
             const uint32_t w = lane < 32 ? w0 : w1;                     // lane = key n or 32 + n
             if (P == 8) {
                 // bytes whose table (sub + S (4q + e)) lies beyond the chunk's live tables stay zero
@@ -814,8 +1074,12 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma8_kernel(HashArgs
                 }
             }
         }
-        if (blk + stride < nblocks) load_keys(blk + stride);
+        if (SPLIT && close.n > CAP / 2) close.settle();
+        blk += stride;
+        if (SPLIT && SHARE) walk();
+        else if (!SPLIT && blk < nblocks) load_keys(blk);
     }
+    if (SPLIT) close.settle();
 }
 
 // ---------------------------------------------------------------------------------------
@@ -890,7 +1154,7 @@ __global__ __launch_bounds__(hash8_threads<D>()) void hash_mfma10_kernel(HashArg
     // (as in hash_mfma8_kernel: workgroups first; of short runs the keys while W is cut, a block's strings
     // by two wavefronts where there are enough)
     int nblocks = 0, stride = slots * NW, blk = slot + wave * slots, parts = 1, p0 = 0;
-    cut_fragments<D, S, 10, NS, NT>(wl, a, h, grp * GT, ntab, sub0, tid, [&]() __attribute__((always_inline)) {
+    cut_fragments<uint16_t, D, S, 10, NS, NT>(wl, a, h, grp * GT, ntab, sub0, tid, [&]() __attribute__((always_inline)) {
         if (!SHORT) return;
         nblocks = (count + 63) >> 6;
         parts = NS == 2 && nblocks <= slots * (NW / 2) ? 2 : 1;
@@ -1015,8 +1279,9 @@ static void launch_blocks(fragment_kernel_t alone, fragment_kernel_t brief, frag
 }
 
 // dynamic LDS of hash_mfma8_kernel: the W slab as fragments, one id-word row per key of every wavefront's block
-template <int D, int S, int P> constexpr size_t hash8_lds() {
-    return (size_t)(P / 2 * hash8_groups<D, S, P>()) * (D / 16) * 64 * 16 + (size_t)hash8_threads<D>() * 16;
+template <typename T, int D, int S, int P> constexpr size_t hash8_lds() {
+    constexpr int WD = hash_width<T, D>();
+    return (size_t)(P / 2 * hash8_groups<WD, S, P>()) * (D * sizeof(T) / 32) * 64 * 16 + (size_t)hash8_threads<WD>() * 16;
 }
 
 template <int D, int S> constexpr size_t hash10_lds() {
@@ -1025,7 +1290,7 @@ template <int D, int S> constexpr size_t hash10_lds() {
 
 // once per context that uses a fast hash: more than 64 KB of dynamic LDS has to be allowed
 // before the first launch
-template <int D> static int hash_prepare_d() {
+template <typename T, int D> static int hash_prepare_d() {
     hipError_t e = hipSuccess;
     auto allow = [&](auto kernel, size_t lds) {
         if (e == hipSuccess && lds > 64 * 1024)
@@ -1033,41 +1298,47 @@ template <int D> static int hash_prepare_d() {
     };
     auto all = [&](auto runs) {
         constexpr int RUNS = decltype(runs)::value;
-        allow(hash_mfma8_kernel<D, 4, 8, RUNS>, hash8_lds<D, 4, 8>());
-        allow(hash_mfma8_kernel<D, 2, 8, RUNS>, hash8_lds<D, 2, 8>());
-        allow(hash_mfma8_kernel<D, 1, 8, RUNS>, hash8_lds<D, 1, 8>());
-        allow(hash_mfma8_kernel<D, 4, 4, RUNS>, hash8_lds<D, 4, 4>());
-        allow(hash_mfma8_kernel<D, 2, 4, RUNS>, hash8_lds<D, 2, 4>());
-        allow(hash_mfma10_kernel<D, 2, RUNS>, hash10_lds<D, 2>());
-        allow(hash_mfma10_kernel<D, 1, RUNS>, hash10_lds<D, 1>());
+        allow(hash_mfma8_kernel<T, D, 4, 8, RUNS>, hash8_lds<T, D, 4, 8>());
+        allow(hash_mfma8_kernel<T, D, 2, 8, RUNS>, hash8_lds<T, D, 2, 8>());
+        allow(hash_mfma8_kernel<T, D, 1, 8, RUNS>, hash8_lds<T, D, 1, 8>());
+        allow(hash_mfma8_kernel<T, D, 4, 4, RUNS>, hash8_lds<T, D, 4, 4>());
+        allow(hash_mfma8_kernel<T, D, 2, 4, RUNS>, hash8_lds<T, D, 2, 4>());
+        if constexpr (sizeof(T) == 2) {
+            allow(hash_mfma10_kernel<D, 2, RUNS>, hash10_lds<D, 2>());
+            allow(hash_mfma10_kernel<D, 1, RUNS>, hash10_lds<D, 1>());
+        }
     };
     all(IntTag<kRunsLong>());
     all(IntTag<kRunsShort>());
-    if constexpr (D == 256) all(IntTag<kRunsShared>());
+    if constexpr (hash_shares<T, D>()) all(IntTag<kRunsShared>());
     return e == hipSuccess ? SOCKET_OK : SOCKET_EHIP;
 }
-int hash_prepare(int d) { return d == 64 ? hash_prepare_d<64>() : d == 128 ? hash_prepare_d<128>() : hash_prepare_d<256>(); }
+int hash_prepare(int d, int kv_dtype) {
+    if (kv_dtype == SOCKET_F32) return d == 64 ? hash_prepare_d<float, 64>() : hash_prepare_d<float, 128>();
+    return d == 64 ? hash_prepare_d<uint16_t, 64>() : d == 128 ? hash_prepare_d<uint16_t, 128>() : hash_prepare_d<uint16_t, 256>();
+}
 
-template <int D, int S, int P>
+template <typename T, int D, int S, int P>
 static int launch_mfma8(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
-    constexpr int NT = hash8_threads<D>(), PARTS = S / hash8_groups<D, S, P>();
+    constexpr int WD = hash_width<T, D>(), NT = hash8_threads<WD>(), PARTS = S / hash8_groups<WD, S, P>();
     a.tables_per_chunk = 16 * S;
     a.n_chunks = S == 4 ? (a.L + 63) / 64 : 1;
+    const int rows = Hkv * a.n_chunks * PARTS;
     fragment_kernel_t shared = nullptr;
-    if constexpr (D == 256) shared = hash_mfma8_kernel<D, S, P, kRunsShared>;
-    launch_blocks(hash_mfma8_kernel<D, S, P, kRunsLong>, hash_mfma8_kernel<D, S, P, kRunsShort>, shared, a, Hkv * a.n_chunks * PARTS, batch, max_rows, NT, hash8_lds<D, S, P>(), st);
+    if constexpr (hash_shares<T, D>()) shared = hash_mfma8_kernel<T, D, S, P, kRunsShared>;
+    launch_blocks(hash_mfma8_kernel<T, D, S, P, kRunsLong>, hash_mfma8_kernel<T, D, S, P, kRunsShort>, shared, a, rows, batch, max_rows, NT, hash8_lds<T, D, S, P>(), st);
     return SOCKET_OK;
 }
-template <int D, int P>
+template <typename T, int D, int P>
 static int launch_mfma8(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
-    return a.S == 4 ? launch_mfma8<D, 4, P>(a, Hkv, batch, max_rows, st)
-         : a.S == 2 ? launch_mfma8<D, 2, P>(a, Hkv, batch, max_rows, st)
-                    : launch_mfma8<D, 1, P>(a, Hkv, batch, max_rows, st);
+    return a.S == 4 ? launch_mfma8<T, D, 4, P>(a, Hkv, batch, max_rows, st)
+         : a.S == 2 ? launch_mfma8<T, D, 2, P>(a, Hkv, batch, max_rows, st)
+                    : launch_mfma8<T, D, 1, P>(a, Hkv, batch, max_rows, st);
 }
-template <int D>
+template <typename T, int D>
 static int launch_mfma8(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
-    return a.P == 8 ? launch_mfma8<D, 8>(a, Hkv, batch, max_rows, st)
-                    : launch_mfma8<D, 4>(a, Hkv, batch, max_rows, st);
+    return a.P == 8 ? launch_mfma8<T, D, 8>(a, Hkv, batch, max_rows, st)
+                    : launch_mfma8<T, D, 4>(a, Hkv, batch, max_rows, st);
 }
 
 template <int D, int S>
@@ -1175,6 +1446,8 @@ static int launch_mfma(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t
     return SOCKET_OK;
 }
 
+constexpr int kSplitRows = 64;
+
 int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int32_t *block_table,
                      const int32_t *row_begin, const int32_t *row_count, int batch, int max_rows,
                      void *codes, hipStream_t st) {
@@ -1190,6 +1463,8 @@ int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int
         // one appended key per sequence: the projection kernel with its W slab staged in LDS
         return launch_project(ctx, nullptr, proj, 1.0f, K, codes, block_table, row_begin, row_count,
                               nullptr, batch, st);
+    } else if (g.kv_dtype == SOCKET_F32 && ctx->fast_hash && max_rows >= kSplitRows) {
+        rc = g.d == 64 ? launch_mfma8<float, 64>(a, g.Hkv, batch, max_rows, st) : launch_mfma8<float, 128>(a, g.Hkv, batch, max_rows, st);
     } else if (g.kv_dtype == SOCKET_F32) {
         rc = launch_f32<float>(a, g.Hkv, batch, max_rows, st);
     } else if (max_rows < 64) {
@@ -1198,13 +1473,13 @@ int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int
         const bool fast8 = ctx->fast_hash && (g.P == 8 || g.P == 4);   // one-byte ids of 8 or 4 planes
         const bool fast10 = ctx->fast_hash && g.P == 10;    // packed ids in groups of 32 or 16 tables
         switch (g.d) {
-            case 64: rc = fast8 ? launch_mfma8<64>(a, g.Hkv, batch, max_rows, st)
+            case 64: rc = fast8 ? launch_mfma8<uint16_t, 64>(a, g.Hkv, batch, max_rows, st)
                           : fast10 ? launch_mfma10<64>(a, g.Hkv, batch, max_rows, st)
                                    : launch_mfma<64>(a, g.Hkv, batch, max_rows, st); break;
-            case 128: rc = fast8 ? launch_mfma8<128>(a, g.Hkv, batch, max_rows, st)
+            case 128: rc = fast8 ? launch_mfma8<uint16_t, 128>(a, g.Hkv, batch, max_rows, st)
                            : fast10 ? launch_mfma10<128>(a, g.Hkv, batch, max_rows, st)
                                     : launch_mfma<128>(a, g.Hkv, batch, max_rows, st); break;
-            case 256: rc = fast8 ? launch_mfma8<256>(a, g.Hkv, batch, max_rows, st)
+            case 256: rc = fast8 ? launch_mfma8<uint16_t, 256>(a, g.Hkv, batch, max_rows, st)
                            : fast10 ? launch_mfma10<256>(a, g.Hkv, batch, max_rows, st)
                                     : launch_mfma<256>(a, g.Hkv, batch, max_rows, st); break;
             default: return SOCKET_EUNSUPPORTED;

@@ -192,9 +192,10 @@ int socket_create(socket_ctx **out, const socket_params *p) {
     const int64_t sz_tables = BH * g.table_words * 4;
     const int64_t sz_tstats = BH * g.Lpad * 3 * 4;
     const int64_t sz_sub = g.pf > 1 ? BH * g.Lu * (1 << g.Pu) * 4 : 0;   // shared-byte ids: the small tables, for the read-back
-    // fast prefill hash: bf16 keys, one-byte ids of 8 or 4 planes, W slab of a chunk of up to 64 tables
-    // (at d = 256 and 8 planes: of half of it, a workgroup each) in LDS
-    const bool fast8 = g.kv_dtype == SOCKET_BF16 && (g.P == 8 || g.P == 4) && g.cb == 1 && g.mode == kDirect;
+    // fast prefill hash: bf16 keys, or fp32 keys of up to 128 channels; one-byte ids of 8 or 4 planes,
+    // W slab of a chunk of up to 64 tables (or of half of it, a workgroup each) in LDS
+    const bool fast_keys = g.kv_dtype == SOCKET_BF16 || g.d <= 128;
+    const bool fast8 = fast_keys && (g.P == 8 || g.P == 4) && g.cb == 1 && g.mode == kDirect;
     // the same for 10-plane tables with packed ids (groups of 32 tables, or one group of 16)
     const bool fast10 = g.kv_dtype == SOCKET_BF16 && g.P == 10 && g.mode == kSplit && (g.GT == 32 || g.GT == 16);
     ctx->fast_hash = fast8 || fast10;
@@ -210,7 +211,7 @@ int socket_create(socket_ctx **out, const socket_params *p) {
               hipMalloc((void **)&ctx->tables, sz_tables) == hipSuccess &&
               hipMalloc((void **)&ctx->tstats, sz_tstats) == hipSuccess &&
               (sz_sub == 0 || hipMalloc((void **)&ctx->subprobs, sz_sub) == hipSuccess) &&
-              (!ctx->fast_hash || hash_prepare(g.d) == SOCKET_OK) &&
+              (!ctx->fast_hash || hash_prepare(g.d, g.kv_dtype) == SOCKET_OK) &&
               hipMalloc((void **)&ctx->hist, sz_hist) == hipSuccess &&
               hipMalloc((void **)&ctx->counters, sz_cnt) == hipSuccess &&
               hipMalloc((void **)&ctx->cand_key, sz_cand) == hipSuccess &&
