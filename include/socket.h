@@ -153,7 +153,8 @@ int64_t socket_scratch_bytes(const socket_ctx *ctx);
  * appended key.  `max_rows` (host) bounds every row_count[b] and sizes the
  * launch; rows beyond row_count[b] are not touched.
  * bf16 keys use bf16 MFMA with fp32 accumulation (runs below 64 rows: fp32 products); fp32 keys
- * use fp32 FMA, on the vector or the matrix units: the same sums bit for bit.
+ * use fp32 FMA, on the vector or the matrix units (long runs: bf16 pieces on the matrix units,
+ * and FMA where a sum is too close to zero for them): the same ids bit for bit.
  * row_begin, row_count: device int32 [batch].  block_table: device, paged only
  * (NULL otherwise).
  */

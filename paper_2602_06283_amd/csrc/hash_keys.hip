@@ -1,15 +1,16 @@
 // Alg. 1 (PrecomputeKeyHashes): sign random projections of cached keys, packed into bucket ids.
 //
 // Kernels:
-//   hash_mfma8_kernel  bf16 keys, 8- or 4-plane tables (one-byte ids): the W slab of a
-//                      chunk of up to 64 tables (half a chunk at d = 256) sits in LDS as MFMA fragments, keys go from
+//   hash_mfma8_kernel  8- or 4-plane tables (one-byte ids), bf16 keys, and long runs of fp32 keys of up to
+//                      128 channels in bf16 pieces: the W slab of a chunk of up to 64 tables (half a
+//                      chunk at d = 256 and of fp32) sits in LDS as MFMA fragments, keys go from
 //                      memory straight into registers, the ids are assembled in registers.
 //   hash_mfma10_kernel the same structure for 10-plane tables with packed 10-bit ids.
 //   hash_mfma_kernel   bf16 keys, any other shape: K[rows x d] * W[d x L*P] on bf16 MFMA
 //                      (v_mfma_f32_32x32x16_bf16, fp32 accumulate), W held in registers,
 //                      key tiles staged through LDS, sign bits taken from the accumulators'
 //                      sign bit and packed into a per-key bit matrix in LDS.
-//   hash_f32_kernel    fp32 keys, or fewer than 64 rows of bf16 keys: fp32 MFMA
+//   hash_f32_kernel    other fp32 keys, or fewer than 64 rows of bf16 keys: fp32 MFMA
 //                      (v_mfma_f32_32x32x2_f32), W held in registers.
 //   hash_rows_kernel   up to four rows, or groups too wide for hash_f32_kernel (9 or 10 planes at
 //                      d = 256, in groups of 32 tables): fp32 FMA, one
@@ -225,10 +226,10 @@ __global__ __launch_bounds__(256) void hash_rows_kernel(HashArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 MFMA kernel: fp32 caches, and short runs of bf16 keys.  Long runs are bound by the fp32
-// matrix rate (147 TFLOP/s in a large product on this card): 8 heads x 8192 keys, 32 tables of
-// 8 planes 42 us = 101 TFLOP/s, 128 us through the FMA kernel above, which re-reads W from L2 for
-// every 16 rows; 64 tables 74 us = 114 TFLOP/s (245).  Short runs are bound by the fetch of W:
+// fp32 MFMA kernel: fp32 caches (not long runs of ids of 4 and 8 planes and up to 128 channels: see
+// CloseList), and short runs of bf16 keys.  Long runs are bound by the fp32 matrix rate (147 TFLOP/s in a
+// large product on this card): 8 heads x 8192 keys, 60 tables of 10 planes 123 us = 102 TFLOP/s; the FMA
+// kernel above takes three times as long, for it re-reads W from L2 for every 16 rows.  Short runs are bound by the fetch of W:
 // 17 rows of 64 tables 13 us (33 through the FMA kernel, whose W loads wait for each other).
 // v_mfma_f32_32x32x2_f32 adds its two products to the accumulator one after the other, each
 // as an FMA, channel 2 s before channel 2 s + 1: a projection here is bit for bit the sum that
@@ -559,7 +560,7 @@ __global__ __launch_bounds__(512, D <= 128 ? 4 : 2) void hash_mfma_kernel(HashAr
 }
 
 // ---------------------------------------------------------------------------------------
-// bf16 MFMA kernel for 8- and 4-plane tables (one-byte ids): the fast path.
+// bf16 MFMA kernel for 8- and 4-plane tables (one-byte ids): the fast path (fp32 keys: in pieces, CloseList).
 // A workgroup keeps the W slab of one 64-table chunk (512 columns) in LDS, already cut into
 // MFMA A-operand fragments, and each of its 16 wavefronts works on 64-key blocks of its own:
 // the keys go from memory straight into B-operand registers, so there is no staging, no
@@ -673,6 +674,10 @@ __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int 
 // the wavefront's list and is formed anew, channel by channel as the FMA kernel does; if the sign is the
 // other one (one in ten million) its bit is turned in memory.  The ids are those of the FMA kernel bit
 // for bit.
+// 8 heads, 32 tables of 8 planes, 128 channels: 8192 keys 25.5 us (42.6 on the fp32 matrix cores), 32768 65
+// (154), where a block's matrix work is 12 of its 20 us and the rest the keys' way from memory, two
+// wavefronts a SIMD being all that the registers allow; of a short run's time 14 us are launch, W and
+// instructions that come cold.
 // The bound, for a key k and a column w, with A >= the norm of a vector and B = the norm of its lo
 // pieces (Cauchy-Schwarz turns norms into sums of magnitudes):
 //   dropped products  lo*lo <= B_k B_w, rest*w <= 2^-8 B_k A_w, k*rest <= 2^-8 A_k B_w
@@ -717,9 +722,8 @@ struct CloseEntry {
     uint32_t col;      // column of the workgroup's tables; top bit: the bit its id has
 };
 
-// A wavefront's list.  Entries are settled when it is half full and after the last block, a lane each.
+// A wavefront's list.  Entries are settled when it is half full and after the last block.
 template <int D, int P, int S, int CAP> struct CloseList {
-    static_assert(CAP <= 64, "a lane each");
     const HashArgs &a;
     CloseEntry *list;
     const float *W;                            // [D][LP], the workgroup's tables from column 0 on
@@ -732,7 +736,7 @@ template <int D, int P, int S, int CAP> struct CloseList {
         const f32x4_t *k = (const f32x4_t *)((const float *)a.K + row * D);
         const float *w = W + col;
         float sum = 0.0f;
-#pragma unroll 8
+#pragma unroll 2
         for (int c = 0; c < D / 4; ++c) {
             const f32x4_t x = k[c];
 #pragma unroll
@@ -768,29 +772,46 @@ template <int D, int P, int S, int CAP> struct CloseList {
         }
     }
 
-    // the list's projections anew, and the ids that have the other sign mended
+    // The list's projections anew, and the ids that have the other sign mended: eight lanes to an entry,
+    // each with an eighth of the channels, all loads at once; the sum goes from lane to lane.  (A lane to
+    // an entry, 32 channels a round of loads, took 14 thousand cycles for one entry: memory latencies, and
+    // instructions that come cold.)
     __device__ __forceinline__ void settle() {
-        if (n == 0) return;
-        const int lane = threadIdx.x & 63;
-        bool flip = false;
-        uint8_t *byte = nullptr;
-        uint32_t bit = 0;
-        if (lane < n) {
-            const CloseEntry e = list[lane];
-            const int col = (int)(e.col & 0x7fffffffu), l = first_table + col / P;
-            flip = (sum_of(e.row, col) >= 0.0f) != ((e.col >> 31) != 0);
-            bit = (uint32_t)(col % P);
-            byte = (uint8_t *)a.codes + e.row * a.Lpad + code_pos(l, e.tok, S);
-        }
-        // (one after the other, behind the ids themselves: two may share a byte; a byte at a time: the
-        // ones beside it may be another workgroup's)
-        __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0)
-        for (uint64_t todo = __ballot(flip); todo != 0; todo &= todo - 1)
-            if (lane == __ffsll((unsigned long long)todo) - 1) {
-                const uint8_t old = __hip_atomic_load(byte, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(byte, (uint8_t)(old ^ (1u << (bit & 7))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __builtin_amdgcn_s_waitcnt(0x0f70);
+        constexpr int CH = D / 8;
+        const int lane = threadIdx.x & 63, part = lane & 7;
+        for (int base = 0; base < n; base += 8) {
+            const CloseEntry e = list[min(base + (lane >> 3), n - 1)];
+            const int col = (int)(e.col & 0x7fffffffu);
+            const f32x4_t *k = (const f32x4_t *)((const float *)a.K + e.row * D + part * CH);
+            const float *wc = W + (int64_t)(part * CH) * a.LP + col;
+            f32x4_t x[CH / 4];
+            float w[CH];
+#pragma unroll
+            for (int c = 0; c < CH; ++c) w[c] = wc[(int64_t)c * a.LP];
+#pragma unroll
+            for (int c = 0; c < CH / 4; ++c) x[c] = k[c];
+            float sum = 0.0f;
+#pragma unroll 1
+            for (int s = 0; s < 8; ++s) {              // lane s is right from round s on
+                const float before = dpp_f32<0x111>(sum);   // row_shr:1
+                sum = part == 0 ? 0.0f : before;
+#pragma unroll
+                for (int c = 0; c < CH; ++c) sum = fmaf(x[c / 4][c % 4], w[c], sum);
             }
+            const bool flip = part == 7 && base + (lane >> 3) < n && (sum >= 0.0f) != ((e.col >> 31) != 0);
+            // (one after the other, behind the ids themselves: two may share a byte; a byte at a time: the
+            // ones beside it may be another workgroup's)
+            uint64_t todo = __ballot(flip);
+            if (todo == 0) continue;
+            uint8_t *byte = (uint8_t *)a.codes + e.row * a.Lpad + code_pos(first_table + col / P, e.tok, S);
+            __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0)
+            for (; todo != 0; todo &= todo - 1)
+                if (lane == __ffsll((unsigned long long)todo) - 1) {
+                    const uint8_t old = __hip_atomic_load(byte, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(byte, (uint8_t)(old ^ (1u << (col % P))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __builtin_amdgcn_s_waitcnt(0x0f70);
+                }
+        }
         n = 0;
     }
 };
@@ -1365,8 +1386,9 @@ static bool f32_fma_rows(const HashArgs &a, int max_rows) { return max_rows <= 4
 // columns of W a workgroup of hash_f32_kernel holds at most (32 a wavefront)
 template <int D> constexpr int f32_columns() { return D <= 128 ? 512 : 256; }
 
+// `split`: the context's ids are hash_mfma8_kernel's, which takes fp32 keys of up to 128 channels
 template <typename T, int D>
-static int launch_f32(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t st) {
+static int launch_f32(HashArgs a, int Hkv, int batch, int max_rows, bool split, hipStream_t st) {
     if (a.GT) {
         a.tables_per_chunk = a.GT;             // packed ids: whole groups, padding groups included
         a.n_chunks = a.Lpad / a.GT;
@@ -1381,6 +1403,13 @@ static int launch_f32(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t 
     const int slots = 256 * ((D <= 128 ? 16 : 8) / waves), rows = Hkv * a.n_chunks;
     const int seq_tiles = (max_rows + kF32Tile - 1) / kF32Tile;
     int64_t share = ((int64_t)seq_tiles * rows * batch + slots - 1) / slots;
+    // More than one tile to a workgroup: the pieces on the bf16 matrix cores.  One tile is over before
+    // their W is cut and their first instructions are there (8 heads, us here / there: 32 tables of 8
+    // planes 1024 keys 9.9 / 15.1, 2048 16.9 / 15.8, 8192 45 / 28, 32768 154 / 65; 64 tables 1024 16.7 /
+    // 17.2, 2048 25.6 / 20.4, 8192 74 / 39; d = 64, 64 tables 1024 9.4 / 11.1, 2048 14.3 / 12.6, 32768
+    // 160 / 62).
+    if constexpr (sizeof(T) == 4 && D <= 128)
+        if (split && share > 1) return launch_mfma8<float, D>(a, Hkv, batch, max_rows, st);
     if (share > 16) share = 16;
     a.rows_per_wg = (int)share * kF32Tile;
     int64_t per = (seq_tiles + share - 1) / share;
@@ -1408,14 +1437,14 @@ static int launch_f32(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t 
 }
 
 template <typename T>
-static int launch_f32(const HashArgs &a, int Hkv, int batch, int max_rows, hipStream_t st) {
+static int launch_f32(const HashArgs &a, int Hkv, int batch, int max_rows, bool split, hipStream_t st) {
     // (a group of 32 tables of 9 or 10 planes is wider than a workgroup at d = 256)
     if (f32_fma_rows(a, max_rows) || a.GT * a.P > (a.d <= 128 ? f32_columns<128>() : f32_columns<256>()))
         return launch_rows<T>(a, Hkv, batch, max_rows, st);
     switch (a.d) {
-        case 64: return launch_f32<T, 64>(a, Hkv, batch, max_rows, st);
-        case 128: return launch_f32<T, 128>(a, Hkv, batch, max_rows, st);
-        case 256: return launch_f32<T, 256>(a, Hkv, batch, max_rows, st);
+        case 64: return launch_f32<T, 64>(a, Hkv, batch, max_rows, split, st);
+        case 128: return launch_f32<T, 128>(a, Hkv, batch, max_rows, split, st);
+        case 256: return launch_f32<T, 256>(a, Hkv, batch, max_rows, split, st);
         default: return SOCKET_EUNSUPPORTED;
     }
 }
@@ -1446,8 +1475,6 @@ static int launch_mfma(HashArgs a, int Hkv, int batch, int max_rows, hipStream_t
     return SOCKET_OK;
 }
 
-constexpr int kSplitRows = 64;
-
 int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int32_t *block_table,
                      const int32_t *row_begin, const int32_t *row_count, int batch, int max_rows,
                      void *codes, hipStream_t st) {
@@ -1463,12 +1490,10 @@ int launch_hash_keys(socket_ctx *ctx, const void *K, const void *proj, const int
         // one appended key per sequence: the projection kernel with its W slab staged in LDS
         return launch_project(ctx, nullptr, proj, 1.0f, K, codes, block_table, row_begin, row_count,
                               nullptr, batch, st);
-    } else if (g.kv_dtype == SOCKET_F32 && ctx->fast_hash && max_rows >= kSplitRows) {
-        rc = g.d == 64 ? launch_mfma8<float, 64>(a, g.Hkv, batch, max_rows, st) : launch_mfma8<float, 128>(a, g.Hkv, batch, max_rows, st);
     } else if (g.kv_dtype == SOCKET_F32) {
-        rc = launch_f32<float>(a, g.Hkv, batch, max_rows, st);
+        rc = launch_f32<float>(a, g.Hkv, batch, max_rows, ctx->fast_hash, st);
     } else if (max_rows < 64) {
-        rc = launch_f32<uint16_t>(a, g.Hkv, batch, max_rows, st);
+        rc = launch_f32<uint16_t>(a, g.Hkv, batch, max_rows, false, st);
     } else {
         const bool fast8 = ctx->fast_hash && (g.P == 8 || g.P == 4);   // one-byte ids of 8 or 4 planes
         const bool fast10 = ctx->fast_hash && g.P == 10;    // packed ids in groups of 32 or 16 tables

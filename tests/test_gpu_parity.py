@@ -280,6 +280,41 @@ def test_hash_keys_long_and_ragged_batches(kv_dtype, d, L, P, Hkv, counts):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,L,P,Hkv,counts", [
+    (128, 32, 8, 8, [8200]), (128, 64, 8, 8, [2500]), (128, 100, 8, 4, [3000, 0, 2999, 1, 64]), (128, 13, 8, 16, [4500]),
+    (128, 65, 4, 8, [2500, 700]), (128, 31, 4, 16, [2100]), (64, 64, 8, 8, [9000]), (64, 128, 4, 8, [700, 0, 5000]), (64, 16, 4, 32, [4100]),
+])
+def test_hash_keys_fp32_close_sums(d, L, P, Hkv, counts):
+    """Long runs of fp32 keys (bf16 pieces on the matrix cores) against the same keys in short runs (fp32
+    products): the same ids bit for bit, also of keys at right angles to a column of W (their sums are
+    rounding errors), of zero keys, of keys too small, too large or too far from numbers for the bound on the
+    pieces (every projection is formed anew: more than a wavefront lists)."""
+    _need_gpu()
+    B, n = len(counts), (max(counts) + 47) // 48 * 48
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    K = torch.randn((B, Hkv, n, d), generator=gen, device="cuda")
+    W = torch.randn((Hkv, d, L * P), generator=gen, device="cuda")
+    rows = torch.arange(0, n, 3, device="cuda")
+    w = W.transpose(1, 2)[:, rows % (L * P)].double()                    # a column for every third key
+    k = K[:, :, rows].double()
+    K[:, :, rows] = (k - (k * w).sum(-1, keepdim=True) / (w * w).sum(-1, keepdim=True) * w).float()
+    K[:, :, 64:130] *= 1e-30
+    K[:, :, 130:140] = 0.0
+    K[:, :, 140:150] *= 1e18
+    K[:, :, 150, 5], K[:, :, 151, 6], K[:, :, 152, 7] = float("inf"), float("-inf"), float("nan")
+    K[:, :, 160:200, ::2] = 0.0
+    ctx = sk.Context(sk.make_params(d, Hkv, Hkv, L, P, sk.F32, B, n, 16))
+    whole, pieces = (hz.new_codes((B, Hkv), n, L, P, fill=0x55) for _ in range(2))
+    _hash_device(ctx, K, W, [0] * B, counts, whole)
+    for b in range(B):
+        for at in range(0, counts[b], 96):
+            c = min(96, counts[b] - at)
+            # (one row at most would be an appended key, whose sums have another order)
+            ctx.hash_keys(K[b:b + 1], W, hz.i32([at]), hz.i32([c]), 1, max(c, 2), pieces[b:b + 1])
+    assert torch.equal(whole, pieces), (whole != pieces).nonzero()[:20]
+    ctx.close()
+
+
 @pytest.mark.parametrize("kv_dtype,d,L,P,counts", [
     (wl.F32, 128, 32, 8, [97, 161, 0]), (wl.F32, 64, 60, 10, [97, 161, 5]), (wl.F32, 256, 64, 8, [161, 33, 1]),
     (wl.F32, 128, 40, 12, [97, 161, 2]), (wl.BF16, 128, 64, 8, [37, 63, 2]), (wl.BF16, 64, 16, 10, [63, 5, 0]), (wl.BF16, 256, 24, 5, [37, 63, 9]),
