@@ -593,27 +593,31 @@ constexpr size_t kEmitLds = (size_t)(kRankMax + 4) * 8 + (size_t)kRankMax * 4;
 // ---------------------------------------------------------------------------------------
 // Short rows in one launch: one workgroup of 16 wavefronts per (sequence, KV head) holds the row in
 // registers (NC chunks of 4096 scores), so the select is a chain of phases in LDS:
-//   bins     as topk_hist_kernel lays them, from a sample of 1024 scores; those below the first bin,
-//            half of a row and more, are only counted
+//   bins     2048 equal steps of the score key (four instructions a score) between a score that the cut
+//            should lie above, by the mean and the deviation of 1024 sampled scores, and the largest of
+//            those; scores beyond are in the last bin, those before in none.  Lower bins once more where
+//            that was too high, and where the cut lies lower still the scores there are refined
 //   refine   while the threshold bin holds more than kRowPairs scores that are not all kept: 2048
-//            equal steps of the score key over it, and again, down to a single key (three rounds
-//            at most: exact for any bins)
+//            equal steps from its least to its largest key, and again, down to a single key (three
+//            rounds at most: exact for any bins)
 //   cut      up to kRowPairs scores are ranked in pairs on (score, smaller position first); more
 //            only where they tie on one key: the smallest positions, by a scan.  The selection is
 //            what is not below one (key, position)
 //   emit     slots in position order, from a scan over the kept scores
 // Nothing is kept between calls; no scratch.
-// Bound by the instructions of one compute unit (40 a score) behind 6 us of launch, loads and phases.
-// us a select, this kernel / three launches: 8 rows of 1000 scores 7.4 / 12.1, 4096 7.8 / 12.9, 12000
-// 9.7 / 13.2, 20000 11.7 / 13.5, 24000 12.6 / 13.3, 32768 15.4 / 13.2; 128 rows of 3000 7.9 / 13.0,
-// 16384 10.9 / 20.2, 32768 15.5 / 29.9, 49000 20.4 / 36.9; 64 rows of 32768 14.8 / 20.5, 32 rows 14.7
-// / 14.7.  So up to kRowRegions regions of 4096 scores always, up to kRowRegionsMany from kRowRowsMany
-// rows on, where three launches fill the card.  Rows whose cut falls among close scores cost a round
-// or two more (20000 scores, 128 rows 18.0 / 33.0; equal scores 26.4 / 100).
+// Bound by the instructions of one compute unit behind 6 us of launch, loads and phases.
+// us a select, this kernel / three launches, 8 rows like a bell: 12000 scores 8.2 / 13.2, 20000 9.3 / 13.5,
+// 24000 9.8 / 13.5, 32768 11.1 / 13.8, 36864 11.8 / 13.8, 40960 12.4 / 13.9, 49152 13.9 / 14.1; rows of a few
+// dozen different scores 20000 12.5 / 20, 32768 17.0 / 20.0, 40960 19.8 / 19.8, 49152 22.8 / 20.2; 64 rows like
+// a bell 32768 11.2 / 20.5, 49152 14.0 / 29.  (With bins by sampled_bin, 40 instructions a score, and no look
+// at the least and largest key: 12000 9.5, 20000 11.5, 32768 15.4; 64 rows of 49152 19.1; of a few dozen
+// different scores 20000 19.1, 32768 30.9.)  So up to kRowRegions regions of 4096 scores always, where rows
+// with many close scores at the cut still break even (32768: a cluster in a cluster 20.7 / 20.8, a heavy
+// tail 15.8 / 13.4), up to kRowRegionsMany from kRowRowsMany rows on, where three launches fill the card.
 // ---------------------------------------------------------------------------------------
 constexpr int kRowThreads = 1024, kRowWaves = kRowThreads / 64;
 constexpr int kRowPairs = 256;
-constexpr int kRowRegions = 5, kRowRegionsMany = 12, kRowRowsMany = 64;
+constexpr int kRowRegions = 9, kRowRegionsMany = 12, kRowRowsMany = 64;
 static_assert(kSlice == 4 * kRowThreads, "a chunk is four scores a thread");
 
 // exclusive prefix sum over the workgroup; *total gets the sum
@@ -629,15 +633,28 @@ __device__ __forceinline__ uint32_t row_excl_scan(uint32_t v, uint32_t *total, u
     return (w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)t, w > 0 ? w - 1 : 0) : 0u) + x - v;
 }
 
+// largest over the 64 lanes; every lane ends with it
+__device__ __forceinline__ uint32_t wave_umax(uint32_t v) {
+    auto with = [&](uint32_t o) { v = max(v, o); };
+    with((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true));
+    with((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xF, 0xF, true));
+    with((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true));
+    with((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true));
+    auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = max(r[0], r[1]);
+    r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return max(r[0], r[1]);
+}
+
 template <int NC>
 __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
     __shared__ __align__(16) uint32_t h[kHistBins];
     __shared__ __align__(16) unsigned long long ck[kRowPairs + 4];
     __shared__ __align__(16) uint32_t tot[256];                  // [chunk][wavefront]
     __shared__ uint32_t tmp[kRowWaves], s_valid[kRowWaves], res[3], s_n;
-    __shared__ float s_part[2][4][kRowWaves];
-    __shared__ uint2 s_keys;
+    __shared__ float s_part[2][3][kRowWaves], s_most[kRowWaves];
     __shared__ unsigned long long s_cut, s_next;
+    __shared__ uint2 s_ends[kRowWaves];
     static_assert(NC * kRowWaves <= 256, "four totals a lane");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bh = blockIdx.x, b = bh / a.Hkv;
@@ -662,8 +679,9 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
                 if (c * kSlice + 4 * tid + j >= seq) w[c][j] = __float_as_uint(ninf);
         }
 
-    // ---- bins: a wavefront's sample is every fourth of its 256 scores of one chunk
-    float lo, inv;
+    // ---- the first score that is binned, and the last bin's: a wavefront's sample is every fourth of its
+    //      256 scores of one chunk
+    float mu = 0.0f, sigma = 0.0f, hi, share;
     {
         const int live = max(1, (seq + kSlice - 1) / kSlice), mine = wave % live;
         float v = __uint_as_float(w[0][0]);
@@ -672,47 +690,46 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
             if (c == mine) v = __uint_as_float(w[c][0]);
         const bool there = mine * kSlice + 4 * tid < seq;
         bool use = there && fabsf(v) < 3.0e38f;                  // (false for NaN and both infinities)
-        float mu = 0.0f, sigma = 0.0f, finite = 0.0f, sampled = 0.0f;
+        float finite = 0.0f, cnt = 0.0f;
 #pragma unroll
         for (int round = 0; round < 2; ++round) {
             const float n0 = row_sum<64>(use ? 1.0f : 0.0f), n1 = row_sum<64>(use ? v : 0.0f);
-            const float n3 = round == 0 ? row_sum<64>(there ? 1.0f : 0.0f) : 0.0f;
+            const float most = round == 0 ? wave_max(use ? v : -3.0e38f) : 0.0f;
             if (lane == 0) {
                 s_part[round][0][wave] = n0;
                 s_part[round][1][wave] = n1;
-                s_part[round][3][wave] = n3;
+                if (round == 0) s_most[wave] = most;
             }
             __syncthreads();
-            const float cnt = row_sum<16>(s_part[round][0][lane & 15]);
-            mu = row_sum<16>(s_part[round][1][lane & 15]) / fmaxf(cnt, 1.0f);
-            if (round == 0) {
-                finite = cnt;
-                sampled = row_sum<16>(s_part[0][3][lane & 15]);
-            }
+            cnt = fmaxf(row_sum<16>(s_part[round][0][lane & 15]), 1.0f);
+            if (round == 0) finite = cnt;
+            mu = row_sum<16>(s_part[round][1][lane & 15]) / cnt;
             const float d = use ? v - mu : 0.0f;
             const float n2 = row_sum<64>(d * d);
             if (lane == 0) s_part[round][2][wave] = n2;
             __syncthreads();
-            sigma = sqrtf(row_sum<16>(s_part[round][2][lane & 15]) / fmaxf(cnt, 1.0f));
+            sigma = sqrtf(row_sum<16>(s_part[round][2][lane & 15]) / cnt);
             use = use && fabsf(v - mu) <= 4.0f * sigma;
         }
         sigma = fminf(fmaxf(sigma, fmaxf(fabsf(mu) * 1e-6f, 1e-30f)), 1.0e37f);
-        const float share = (float)kreq * sampled / fmaxf((float)seq * finite, 1.0f);   // of the finite scores
-        lo = mu - (share <= 0.1f ? 0.5f : share <= 0.25f ? 1.0f : 4.0f) * sigma;
-        inv = 1.0f / (share <= 0.25f ? sigma : 4.0f * sigma);
-        lo = fabsf(lo) < 3.0e38f && lo != 0.0f ? lo : -0.0f;     // (never +0: what compares as not below lo has lo's key or a larger one)
+        share = (float)kreq / fmaxf((float)seq, 1.0f);
+        // (a lone spike does not widen the bins; as many scores far out as are wanted do)
+        const float most = wave_max(s_most[lane & 15]);
+        hi = fmaxf((finite - cnt >= 0.5f * share * finite ? most : fminf(most, mu + 16.0f * sigma)) + 0.25f * sigma, mu + 2.0f * sigma);
+        hi = fabsf(hi) < 3.0e38f ? hi : 3.0e38f;
     }
-    uint32_t valid = 0;
+    // Scores from +0 on compare by their bits, counted from +0; where the bins start below, w takes keys (0
+    // for what is never selected, NaN and -inf)
+    auto to_keys = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+        for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float v = __uint_as_float(w[c][j]);
-            valid += (uint32_t)__popcll(__ballot(v >= -3.40282347e38f));   // (selectable(); the compiler's ballot of v > -inf counts NaN)
-            if (v >= lo) atomicAdd(&h[sampled_bin(v, lo, inv)], 1u);
-        }
-    if (lane == 0) s_valid[wave] = valid;
-    __syncthreads();
+            for (int j = 0; j < 4; ++j) {
+                const float v = __uint_as_float(w[c][j]);
+                w[c][j] = selectable(v) ? order_key(v) : 0u;
+            }
+    };
+    uint32_t zero = 0x80000000u;                                 // the key that w counts from
 
     // the bin of h with the target-th score from the top in it: the bin, the scores above it, those in
     // it (in res, complete after the barrier); returns the number of scores in h
@@ -729,37 +746,92 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
         __syncthreads();
         return total;
     };
-    const uint32_t n_valid = (uint32_t)row_sum<16>((float)s_valid[lane & 15]);
-    const uint32_t k_eff = min(kreq, n_valid);
-    int32_t *out = a.idx + (int64_t)bh * a.max_k;
-    if (tid == 0) a.n_selected[bh] = (int32_t)k_eff;
-    for (int i = (int)k_eff + tid; i < a.max_k; i += kRowThreads) out[i] = -1;
-    if (k_eff == 0) return;
-
-    // ---- the scores in question: keys k0 .. k0 + span - 1, n_in of them, `need` to keep
-    const uint32_t total = find(k_eff);
-    const bool below = total < k_eff;                            // the cut lies below the bins
-    if (wave == 0) {
-        const uint2 keys = below ? make_uint2(1, order_key(lo)) : bin_keys(res[0], [&](float v) { return v >= lo ? sampled_bin(v, lo, inv) : 0u; });
-        if (lane == 0) s_keys = keys;
-    }
-    uint32_t need = k_eff - (below ? total : res[1]), n_in = below ? n_valid - total : res[2];
-    __syncthreads();
-    uint32_t k0 = s_keys.x, span = s_keys.y - k0;
-    // Scores from +0 on compare by their bits, counted from +0; a cut below that takes keys (0 for
-    // what is never selected, NaN and -inf)
-    uint32_t zero = 0x80000000u;                                 // the key that w counts from
-    if (k0 < zero) {
-        zero = 0;
+    // ---- the scores in question: keys k0 .. k0 + span - 1, n_in of them, `need` to keep.  The tenth of a
+    //      bell lies above mean + 0.75 deviations; where it does not, the bins start lower
+    uint32_t k_eff = kreq, total = 0, n_valid = 0, klo = 0, up = 0;
+    int shift0 = 0;
+    bool below = false;                                          // the cut lies below the bins
+#pragma unroll 1
+    for (int low = share <= 0.1f ? 0 : 1; low < 2; ++low) {
+        float lo = mu + (low == 0 ? 0.75f : share <= 0.1f ? -0.5f : share <= 0.25f ? -1.0f : -4.0f) * sigma;
+        lo = fabsf(lo) < 3.0e38f ? lo : 0.0f;
+        if (!(lo > 0.0f) && zero != 0) {
+            zero = 0;
+            to_keys();
+        }
+        klo = order_key(lo);
+        up = 0xff800000u - klo;                                  // +inf is `up` above klo
+        const uint32_t range = max(order_key(hi), klo + 1) - klo;
+        const int bits = 32 - __clz((int)range);
+        shift0 = bits > kHistBits ? bits - kHistBits : 0;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float v = __uint_as_float(w[c][j]);
-                w[c][j] = selectable(v) ? order_key(v) : 0u;
+                const uint32_t off = w[c][j] - (klo - zero);
+                if (off <= up) atomicAdd(&h[min(off >> shift0, (uint32_t)(kHistBins - 1))], 1u);
             }
+        __syncthreads();
+        if (kreq > 0) total = find(kreq);
+        if (total >= kreq || low == 1) break;
+        for (int j = tid; j < kHistBins; j += kRowThreads) h[j] = 0;
+        __syncthreads();
     }
+    if (total < kreq) {                                          // (or there are fewer scores: all of them)
+        uint32_t valid = 0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                // (selectable(); the compiler's ballot of v > -inf counts NaN)
+                const bool ok = zero == 0 ? w[c][j] != 0u : __uint_as_float(w[c][j]) >= -3.40282347e38f;
+                valid += (uint32_t)__popcll(__ballot(ok));
+            }
+        if (lane == 0) s_valid[wave] = valid;
+        __syncthreads();
+        n_valid = (uint32_t)row_sum<16>((float)s_valid[lane & 15]);
+        k_eff = min(kreq, n_valid);
+        below = total < k_eff;
+        if (!below && k_eff > 0) find(k_eff);
+    }
+    int32_t *out = a.idx + (int64_t)bh * a.max_k;
+    if (tid == 0) a.n_selected[bh] = (int32_t)k_eff;
+    for (int i = (int)k_eff + tid; i < a.max_k; i += kRowThreads) out[i] = -1;
+    if (k_eff == 0) return;
+    uint32_t k0, span, need, n_in;
+    if (below) {
+        if (zero != 0) {
+            zero = 0;
+            to_keys();
+        }
+        k0 = 1; span = klo - 1; need = k_eff - total; n_in = n_valid - total;
+    } else {
+        const uint32_t step = res[0] << shift0;
+        k0 = klo + step; need = k_eff - res[1]; n_in = res[2];
+        span = res[0] == kHistBins - 1 ? up - step + 1 : 1u << shift0;
+        span = min(span, up - step + 1);
+    }
+    __syncthreads();
     while (n_in != need && n_in > (uint32_t)kRowPairs && span > 1) {
+        // (from the least to the largest key there: equal scores by the thousand are one key at once)
+        uint32_t inv = 0, most = 0;                              // largest ~offset, largest offset
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t off = w[c][j] - (k0 - zero);
+                inv = off < span ? max(inv, ~off) : inv;
+                most = off < span ? max(most, off) : most;
+            }
+        inv = wave_umax(inv);
+        most = wave_umax(most);
+        if (lane == 0) s_ends[wave] = make_uint2(inv, most);
+        __syncthreads();
+        const uint2 ends = s_ends[lane & 15];
+        const uint32_t least = ~wave_umax(ends.x);
+        k0 += least;
+        span = wave_umax(ends.y) - least + 1;
+        if (span == 1) break;
         const int bits = 32 - __clz((int)(span - 1)), shift = bits > kHistBits ? bits - kHistBits : 0;
         for (int j = tid; j < kHistBins; j += kRowThreads) h[j] = 0;
         __syncthreads();

@@ -594,7 +594,8 @@ def test_topk_rows_of_any_shape(n, ks):
     ctx.close()
 
 
-@pytest.mark.parametrize("B,H,n", [(1, 3, 16), (1, 3, 4096), (1, 3, 4112), (1, 3, 20480), (1, 3, 20496), (8, 8, 36880), (8, 8, 49152), (8, 8, 49168)])
+@pytest.mark.parametrize("B,H,n", [(1, 3, 16), (1, 3, 4096), (1, 3, 4112), (1, 3, 20480), (1, 3, 20496), (1, 14, 36864), (1, 14, 36880),
+                                   (8, 8, 36880), (8, 8, 49152), (8, 8, 49168)])
 def test_topk_of_short_rows(B, H, n):
     """Rows at the edges of the one-launch select's chunks and of its rule, cuts below zero, among zeros
     of both signs and among ties, lengths short of the capacity: the oracle's selection exactly."""
