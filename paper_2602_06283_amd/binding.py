@@ -133,7 +133,11 @@ def _ptr(t):
 
 
 def _stream(stream):
-    return (stream if stream is not None else torch.cuda.current_stream()).cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # the current stream's handle, 0.2 us; a Stream object made for it (torch.cuda.current_stream()) takes 2.8,
+    # a third of a call
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 class Context:
