@@ -49,12 +49,12 @@ struct DecodeArgs {
     void *out;
     RowMap map;
     float scale;
-    int Hq, G, max_k, n_split, out_dtype;
+    int Hq, G, max_k, n_split, per, out_dtype;     // per: slots of the row that a split owns
     const int32_t *seq_len;   // dense variant, and kRowsSweep: tokens of each sequence
     // kRowsSweep: the lists and the threshold record of the select's sweep
     const int32_t *sel_regions;
     const uint32_t *sel_cnt;
-    int n_regions, ssr, rpg;
+    int n_regions, ssr, ssr_log2, rpg;      // (ssr is a power of two)
     int emit_idx;             // the splits write the ordered index row (a.idx) themselves
     const uint32_t *cand_key;
     const int32_t *cand_idx;
@@ -132,6 +132,12 @@ __device__ __forceinline__ bool decode_body(const DecodeArgs &a, int split, int 
     __shared__ int64_t s_own[kHeadEntries];          // kRowsSweep: the K/V rows of the first NT entries
     T (*s_v)[D] = (T (*)[D])dyn;                     // [VROWS][D]
 
+    // The arguments of the first loads in one trip to memory, not each where it is first used; so too
+    // the sweep's record and the length below, which were four trips, each behind a branch on the last
+    // (32768 keys, 36 splits x 8 heads: 8.1 -> 7.7 us).
+    if (SRC == kRowsSweep)
+        asm volatile("" ::"s"(a.q), "s"(a.sel_regions), "s"(a.sel_cnt), "s"(a.cand_key), "s"(a.cand_idx), "s"(a.thr), "s"(a.seq_len),
+                     "s"(a.K), "s"(a.V), "s"(a.map.block_table), "s"(a.idx), "s"(a.max_k), "s"(a.ssr), "s"(a.Hq));
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int bh = b * a.map.Hkv + h;
     const int sub = lane % LPR, rl = lane / LPR;     // this lane's 8-element slice and row slot
@@ -140,9 +146,8 @@ __device__ __forceinline__ bool decode_body(const DecodeArgs &a, int split, int 
 
     // Splits own fixed ranges of the max_k slots, so no load has to wait for the selected
     // count; slots at or beyond the count are ignored.  (Dense: whole chunks of the sequence.)
-    const int per = (a.max_k + a.n_split - 1) / a.n_split;
-    const int r_begin = split * per;
-    int r_end = min(a.max_k, r_begin + per);
+    const int r_begin = split * a.per;
+    int r_end = min(a.max_k, r_begin + a.per);
 
     // ---- every load that needs nothing else first, issued before anything waits: the queries,
     //      the first chunk's list entries, the counts and (kRowsSweep) one candidate per thread
@@ -172,25 +177,14 @@ __device__ __forceinline__ bool decode_body(const DecodeArgs &a, int split, int 
             reg0 = split * a.rpg;
             reg1 = min(a.n_regions, reg0 + a.rpg);
         } else {
-            reg0 = split / a.ssr;
+            reg0 = split >> a.ssr_log2;
             reg1 = reg0 + 1;
             sub_i = split - reg0 * a.ssr;
             sub_n = a.ssr;
         }
-        // regions past the end of the sequence hold nothing: an empty partial result, at once
-        // (in a batch of mixed lengths that is a good part of the workgroups)
-        if ((int64_t)reg0 * kSlice >= a.seq_len[b]) {
-            float *part = a.partials + ((int64_t)(b * a.Hq + h * G) * a.n_split) * (D + 2);
-            if (tid < G) {
-                part[((int64_t)tid * a.n_split + split) * (D + 2) + 0] = ninf;
-                part[((int64_t)tid * a.n_split + split) * (D + 2) + 1] = 0.0f;
-            }
-            for (int i = tid; i < G * D; i += NT) part[((int64_t)(i / D) * a.n_split + split) * (D + 2) + 2 + i % D] = 0.0f;
-            return false;
-        }
         list = a.sel_regions + (int64_t)bh * a.n_regions * kSlice;
         first = list[(int64_t)reg0 * kSlice + sub_i + tid * sub_n];   // (inside the region's kSlice words: sub_n <= 16)
-        count = (int)a.sel_cnt[(int64_t)bh * a.n_regions + reg0];
+        count = (int)scalar_load(&a.sel_cnt[(int64_t)bh * a.n_regions + reg0]);
         if (a.emit_idx) {
             cnt_before = tid < reg0 ? a.sel_cnt[(int64_t)bh * a.n_regions + tid] : 0u;
             if (sub_i == 0) head = list[(int64_t)reg0 * kSlice + tid];   // (inside the region's kSlice words)
@@ -203,11 +197,25 @@ __device__ __forceinline__ bool decode_body(const DecodeArgs &a, int split, int 
         }
         // the selection: every position of the regions, and the `need` best candidates of the threshold bin
         const uint32_t *thr = a.thr + (int64_t)bh * kThrStride;
-        const int k_eff = min((int)thr[0], a.max_k);
-        const int above = k_eff ? min((int)thr[5], k_eff) : 0;
-        n_cand = k_eff ? (int)thr[6] : 0;
-        need = k_eff - above;
+        const int k_thr = (int)scalar_load(&thr[0]), above_thr = (int)scalar_load(&thr[5]), cand_thr = (int)scalar_load(&thr[6]);
+        const int len = scalar_load(&a.seq_len[b]);
+        asm volatile("" ::"s"(k_thr), "s"(above_thr), "s"(cand_thr), "s"(len), "s"(count));   // (one trip for all of them)
+        const int k_eff = min(k_thr, a.max_k);
+        n_cand = k_eff ? cand_thr : 0;
+        need = k_eff - (k_eff ? min(above_thr, k_eff) : 0);
         if (k_eff == 0) count = 0;
+        // regions past the end of the sequence hold nothing: an empty partial result, at once
+        // (in a batch of mixed lengths that is a good part of the workgroups).  Behind the loads: they
+        // are inside the buffers whatever the length is, and before it they would wait for it.
+        if ((int64_t)reg0 * kSlice >= len) {
+            float *part = a.partials + ((int64_t)(b * a.Hq + h * G) * a.n_split) * (D + 2);
+            if (tid < G) {
+                part[((int64_t)tid * a.n_split + split) * (D + 2) + 0] = ninf;
+                part[((int64_t)tid * a.n_split + split) * (D + 2) + 1] = 0.0f;
+            }
+            for (int i = tid; i < G * D; i += NT) part[((int64_t)(i / D) * a.n_split + split) * (D + 2) + 2 + i % D] = 0.0f;
+            return false;
+        }
     }
     // too many candidates to rank here: the caller attends the head from the ordered row instead
     if (SRC == kRowsSweep && n_cand > kSweepCand) return true;
@@ -235,7 +243,8 @@ __device__ __forceinline__ bool decode_body(const DecodeArgs &a, int split, int 
     }
     // kRowsSweep: the K/V row of this thread's entry (paged: a block-table lookup, in flight while
     // the candidates are ranked)
-    const int n_first = count > sub_i ? (count - sub_i + sub_n - 1) / sub_n : 0;   // entries of this split in its first region
+    int n_first = count > sub_i ? count - sub_i + sub_n - 1 : 0;     // entries of this split in its first region
+    n_first >>= a.ssr_log2;
     int64_t own_row = -1;
     if (SRC == kRowsSweep && tid < n_first && first >= 0 && first < a.map.max_n) own_row = a.map.row(b, h, first);
 
@@ -608,7 +617,7 @@ __device__ __forceinline__ bool decode_body(const DecodeArgs &a, int split, int 
             // ---- this split's share of its regions, then its candidates
             for (int reg = reg0; reg < reg1; ++reg) {
                 const int cnt = reg == reg0 ? count : (int)a.sel_cnt[(int64_t)bh * a.n_regions + reg];
-                const int n_here = cnt > sub_i ? (cnt - sub_i + sub_n - 1) / sub_n : 0;     // entries of this split in the region
+                const int n_here = reg == reg0 ? n_first : cnt;      // entries of this split in the region (several regions: not shared)
                 const int n_rows = n_here + (reg == reg1 - 1 ? n_mine : 0);
                 // the rows of chunk c0 into s_row[buf]
                 auto fill = [&](int c0, int buf) __attribute__((always_inline)) {
@@ -686,21 +695,25 @@ __global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(DecodeArg
 // after the partial pass: no fence, no signalling.
 //
 // Bound by latency and by instructions that come cold: a launch of a few workgroups runs each of
-// them once.  So the splits go in batches of eight behind one uniform branch (a load, a bounds test
+// them once.  So there is a body for 8, for 16 and for all splits a thread (a load, a bounds test
 // and an FMA of each of the 32 possible ones cost as much with 9 splits as with 128), the group is a
 // scalar and the rows' addresses with it, and the heads of a KV head come as an argument, not by a
-// division.  merge_finish at 36 splits of 32 query heads 4.4 -> 3.9 us, at 9 of 512 5.6 -> 5.0,
-// a fused step at 32768 keys 29.9 -> 29.2.
+// division.  merge_finish at 36 splits of 32 query heads 4.4 -> 3.4 us, at 9 of 512 5.6 -> 5.0.
 constexpr int kMergeThreads = 512;
 
-template <int D, int NT>
-__device__ __forceinline__ void merge_body(const DecodeArgs &a, int g, int h, int b) {
+// the threshold record of a head with more candidates than a decode workgroup ranks
+__device__ __forceinline__ bool too_many(uint32_t k_eff, uint32_t n_cand) { return k_eff != 0 && n_cand > (uint32_t)kSweepCand; }
+
+template <int D, int NT> struct MergeLds {
+    float w[kMaxSplits];
+    float red[NT / D][D];
+    float den;
+};
+
+// PER: splits per thread
+template <int D, int NT, int PER>
+__device__ __forceinline__ void merge_splits(const DecodeArgs &a, int g, int h, int b, const uint32_t *thr, MergeLds<D, NT> &lds) {
     constexpr int NG = NT / D;                       // groups of D threads
-    constexpr int PER = kMaxSplits / NG;             // splits per thread
-    static_assert(NT % D == 0 && NG >= 2 && PER <= 64, "groups of D threads, at most 64 loads in flight each");
-    __shared__ float s_w[kMaxSplits];
-    __shared__ float s_den;
-    __shared__ float s_red[NG][D];
     const int tid = threadIdx.x;
     const int c = tid % D, sg = __builtin_amdgcn_readfirstlane(tid / D);   // (whole wavefronts to a group)
     const int G = a.G;                               // (a division at the start of a kernel this short is 25 instructions)
@@ -716,49 +729,52 @@ __device__ __forceinline__ void merge_body(const DecodeArgs &a, int g, int h, in
         m[j] = live ? part[(int64_t)(tid + 64 * j) * (D + 2)] : ninf;
         l[j] = live ? part[(int64_t)(tid + 64 * j) * (D + 2) + 1] : 0.0f;
     }
-    // (eight at a time, and no instruction for splits that there are not: the code comes cold)
     float acc[PER];
 #pragma unroll
-    for (int j0 = 0; j0 < PER; j0 += 8)
-        if (j0 * NG < a.n_split) {
-#pragma unroll
-            for (int j = j0; j < j0 + 8; ++j) {
-                const int s = min(sg + j * NG, a.n_split - 1);
-                acc[j] = (part + (int64_t)s * (D + 2) + 2)[c];
-            }
-        }
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t s = (uint32_t)min(sg + j * NG, a.n_split - 1);
+        acc[j] = ((const float *)((const char *)part + s * (uint32_t)((D + 2) * 4)) + 2)[c];
+    }
+    // merge_finish: a head that its splits left alone (looked at behind the loads, which would wait for it)
+    if (thr && too_many(scalar_load(&thr[0]), scalar_load(&thr[6]))) return;
     if (tid < 64) {
         const float top = wave_max(fmaxf(m[0], m[1]));
         const float w0 = (m[0] == ninf) ? 0.0f : expf(m[0] - top), w1 = (m[1] == ninf) ? 0.0f : expf(m[1] - top);
         const float den = row_sum<64>(w0 * l[0] + w1 * l[1]);
-        s_w[tid] = w0;
-        s_w[tid + 64] = w1;
-        if (tid == 0) s_den = den;
+        lds.w[tid] = w0;
+        lds.w[tid + 64] = w1;
+        if (tid == 0) lds.den = den;
     }
     __syncthreads();
     float num = 0.0f;
 #pragma unroll
-    for (int j0 = 0; j0 < PER; j0 += 8)
-        if (j0 * NG < a.n_split) {
-#pragma unroll
-            for (int j = j0; j < j0 + 8; ++j) {
-                const int s = sg + j * NG;
-                const float sum = fmaf(s_w[s], acc[j], num);
-                num = s < a.n_split ? sum : num;
-            }
-        }
-    s_red[sg][c] = num;
+    for (int j = 0; j < PER; ++j) {
+        const int s = sg + j * NG;
+        const float sum = fmaf(lds.w[s], acc[j], num);
+        num = s < a.n_split ? sum : num;
+    }
+    lds.red[sg][c] = num;
     __syncthreads();
     if (sg == 0) {
-        float total = s_red[0][c];
+        float total = lds.red[0][c];
 #pragma unroll
-        for (int gg = 1; gg < NG; ++gg) total += s_red[gg][c];
-        const float den = s_den;
+        for (int gg = 1; gg < NG; ++gg) total += lds.red[gg][c];
+        const float den = lds.den;
         const float y = den > 0.0f ? total / den : 0.0f;
         if (a.out_dtype == SOCKET_F32) ((float *)a.out)[head * D + c] = y;
         else ((uint16_t *)a.out)[head * D + c] = f32_to_bf16_rne(y);
     }
     __syncthreads();                                 // the LDS arrays may be rewritten by a following call
+}
+
+template <int D, int NT>
+__device__ __forceinline__ void merge_body(const DecodeArgs &a, int g, int h, int b, const uint32_t *thr = nullptr) {
+    constexpr int NG = NT / D, MOST = kMaxSplits / NG;
+    static_assert(NT % D == 0 && NG >= 2 && MOST >= 16 && MOST <= 64, "groups of D threads, at most 64 loads in flight each");
+    __shared__ MergeLds<D, NT> lds;
+    if (a.n_split <= 8 * NG) merge_splits<D, NT, 8>(a, g, h, b, thr, lds);
+    else if (a.n_split <= 16 * NG) merge_splits<D, NT, 16>(a, g, h, b, thr, lds);
+    else if constexpr (MOST > 16) merge_splits<D, NT, MOST>(a, g, h, b, thr, lds);
 }
 
 template <int D>
@@ -777,13 +793,14 @@ template <typename T, int D, int G>
 __global__ __launch_bounds__(kTopkThreads, 6) void merge_finish_kernel(DecodeArgs a, TopkArgs t) {
     extern __shared__ __align__(16) char decode_lds[];
     const int h = blockIdx.y, b = blockIdx.z, bh = b * a.map.Hkv + h, tid = threadIdx.x;
+    asm volatile("" ::"s"(a.partials), "s"(a.out), "s"(a.out_dtype), "s"(t.thr));   // (arguments in one trip)
     const uint32_t *thr = t.thr + (int64_t)bh * kThrStride;
-    const uint32_t k_eff = thr[0];
-    const bool redo = k_eff != 0 && thr[6] > (uint32_t)kSweepCand;
     if ((int)blockIdx.x < G) {
-        if (!redo) merge_body<D, kTopkThreads>(a, blockIdx.x, h, b);
+        merge_body<D, kTopkThreads>(a, blockIdx.x, h, b, thr);
         return;
     }
+    const uint32_t k_eff = scalar_load(&thr[0]);
+    const bool redo = too_many(k_eff, scalar_load(&thr[6]));
     if (a.emit_idx && !redo) {
         int32_t *out = t.idx + (int64_t)bh * t.max_k;
         for (int i = (int)min(k_eff, (uint32_t)t.max_k) + tid; i < t.max_k; i += kTopkThreads) out[i] = -1;
@@ -868,8 +885,8 @@ static DecodeArgs decode_args(const Geometry &g, float *partials, const void *q,
     a.q = q; a.K = K; a.V = V; a.idx = nullptr; a.n_selected = nullptr; a.seq_len = nullptr;
     a.partials = partials; a.out = out;
     a.map = row_map(g, block_table);
-    a.scale = scale; a.Hq = g.Hq; a.G = g.G; a.max_k = g.max_k; a.n_split = n_split; a.out_dtype = out_dtype;
-    a.sel_regions = nullptr; a.sel_cnt = nullptr; a.n_regions = 0; a.ssr = 1; a.rpg = 1; a.emit_idx = 0;
+    a.scale = scale; a.Hq = g.Hq; a.G = g.G; a.max_k = g.max_k; a.n_split = n_split; a.per = (g.max_k + n_split - 1) / n_split; a.out_dtype = out_dtype;
+    a.sel_regions = nullptr; a.sel_cnt = nullptr; a.n_regions = 0; a.ssr = 1; a.ssr_log2 = 0; a.rpg = 1; a.emit_idx = 0;
     a.cand_key = nullptr; a.cand_idx = nullptr; a.thr = nullptr;
     return a;
 }
@@ -986,7 +1003,7 @@ int launch_sweep_decode(socket_ctx *ctx, const void *q, const void *K, const voi
     const TopkArgs t = topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode);
     DecodeArgs a = decode_args(ctx, q, K, V, block_table, scale, out_dtype, out, g.n_split_sweep);
     a.idx = idx; a.n_selected = n_selected;
-    a.sel_regions = t.sel_regions; a.sel_cnt = t.sel_cnt; a.n_regions = g.n_regions; a.ssr = g.ssr; a.rpg = g.rpg;
+    a.sel_regions = t.sel_regions; a.sel_cnt = t.sel_cnt; a.n_regions = g.n_regions; a.ssr = g.ssr; a.ssr_log2 = __builtin_ctz((unsigned)g.ssr); a.rpg = g.rpg;
     a.emit_idx = g.rpg == 1 && g.n_regions <= kDecodeThreads;
     a.seq_len = seq_len;
     a.cand_key = t.cand_key; a.cand_idx = t.cand_idx; a.thr = t.thr;
