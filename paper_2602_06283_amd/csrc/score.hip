@@ -172,14 +172,16 @@ __global__ __launch_bounds__(256) void project_table_kernel(ProjectArgs a) {
     const bool live = l < a.L;                               // tables >= L are padding: zero rows, id 0
     // (every line of the argument block is asked for at once: a line first touched by a later phase is
     // a memory latency there)
-    asm volatile("" ::"s"(a.cols_magic), "s"(a.table_words));
+    asm volatile("" ::"s"(a.cols_magic), "s"(a.table_words), "s"(a.W), "s"(a.K), "s"(a.pos), "s"(a.tables), "s"(a.codes), "s"(a.x_scale),
+                 "s"(a.hard), "s"(a.tstats), "s"(a.pf), "s"(a.L), "s"(a.map.block_table), "s"(a.len_out));
 
     // ---- every load is issued here, those that wait for another one last.  Rows and columns of a
     //      matrix that do not exist repeat the last one (a result row depends on its own row only).
     int tok = 0, cnt = 1;
     if (APP) {
-        tok = a.pos[b];
-        if (a.count) cnt = a.count[b];
+        tok = scalar_load(&a.pos[b]);                        // (as a vector load all others would wait for it)
+        const int n = scalar_load((a.count ? a.count : a.pos) + b);
+        cnt = a.count ? n : 1;
     }
     const int lr = lane & 15, c0 = wave * (D / 4) + (lane >> 4);   // row / column, channel of step 0
     const T *Wg = (const T *)a.W + ((int64_t)h * D + c0) * a.LP + (live ? l : a.L - 1) * P + min(lr, P - 1);
@@ -1185,35 +1187,36 @@ __global__ __launch_bounds__(kGroupThreads) void project_group_kernel(ProjectArg
     float *kz = (float *)(sig + G * P * 2 * TG);     // [NW][COLS]
     float *s_part = kz + NW * COLS;                   // [3][NT]
 
-    // ---- global loads, all issued before the first use
-    int tok = 0;
-    bool wanted = false;
+    // ---- global loads, all issued before the first use (and so without a condition: at a load under one,
+    //      the copy of its zero waits for the loads before it)
+    int tok = 0, cnt = 1;
     if (app) {
-        tok = a.pos[b];
-        wanted = a.count == nullptr || a.count[b] >= 1;
+        tok = scalar_load(&a.pos[b]);
+        const int n = scalar_load((a.count ? a.count : a.pos) + b);
+        cnt = a.count ? n : 1;
     }
+    const bool wanted = app && cnt >= 1;
     // W: rows of COLS elements (columns at or beyond L * P do not exist: zero)
     constexpr int VPR = COLS / EPV;                  // 16-byte vectors per row
     constexpr int WV = 2048 / NT;                    // vectors per thread: d * VPR <= 2048
-    const T *Wg = (const T *)a.W + (int64_t)h * d * a.LP + (int64_t)l0 * P;
+    const T *Wh = (const T *)a.W + (int64_t)h * d * a.LP;
     uint4 wv[WV];
 #pragma unroll
     for (int j = 0; j < WV; ++j) {
         const int i = tid + j * NT;
-        const int c = i / VPR, v = i % VPR;
-        wv[j] = make_uint4(0, 0, 0, 0);
-        if (c < d && l0 * P + (v + 1) * EPV <= a.LP) wv[j] = *(const uint4 *)(Wg + (int64_t)c * a.LP + v * EPV);
+        const int c = min(i / VPR, d - 1), v = i % VPR;
+        wv[j] = *(const uint4 *)(Wh + (l0 * P + (v + 1) * EPV <= a.LP ? (int64_t)c * a.LP + l0 * P + v * EPV : 0));   // (no such column: not used)
     }
     // queries: 16-byte pieces of the G rows; the appended key's row
     const int qpieces = G * d / EPV, kpieces = d / EPV;
-    uint4 qv = make_uint4(0, 0, 0, 0);
-    if (tid < qpieces) qv = *(const uint4 *)((const T *)a.q + ((int64_t)b * a.Hq + h * G) * d + tid * EPV);
+    const uint4 qv = *(const uint4 *)((const T *)a.q + ((int64_t)b * a.Hq + h * G) * d + min(tid, qpieces - 1) * EPV);
 
     // ---- into LDS
 #pragma unroll
     for (int j = 0; j < WV; ++j) {
         const int i = tid + j * NT;
-        if (i < d * VPR) *(uint4 *)(ws + (size_t)i * EPV) = wv[j];
+        const bool in = l0 * P + (i % VPR + 1) * EPV <= a.LP;
+        if (i < d * VPR) *(uint4 *)(ws + (size_t)i * EPV) = in ? wv[j] : make_uint4(0, 0, 0, 0);
     }
     if (tid < qpieces) {
         float f[EPV];
@@ -1630,7 +1633,7 @@ __global__ __launch_bounds__(kScoreThreads, (MODE == kDirect && S == 4 && PAGED)
             if (BATCHED) {
                 seq = s_len[b];
             } else {
-                seq = a.seq_len[0];
+                seq = scalar_load(&a.seq_len[0]);
                 seq = seq < 0 ? 0 : (seq > max_n ? max_n : seq);
             }
             const int nu = (seq + WKEYS - 1) / WKEYS;
@@ -1759,13 +1762,23 @@ __global__ __launch_bounds__(kScoreThreads, (MODE == kDirect && S == 4 && PAGED)
             // Adaptive histogram: if the keys' bucket ids were uniform, a score would have mean L/R
             // and variance sum_l var_l; bins are laid from four deviations below that mean upwards.
             float var_part = 0.0f, nu1_part = 0.0f, nu2_part = 0.0f;
-            if (adaptive && wave == 0)
-                for (int l = lane; l < a.Lpad; l += 64) {
-                    const float *ts = a.tstats + (bh * a.Lpad + l) * 3;
-                    var_part += ts[0];
-                    nu1_part += ts[1];
-                    nu2_part += ts[2];
+            if (adaptive && wave == 0) {
+                if (ONE_ROUND) {                     // (64 tables at most: a loop's sum would wait here, before the table is asked for)
+                    if (lane < a.Lpad) {
+                        const float *ts = a.tstats + (bh * a.Lpad + lane) * 3;
+                        var_part = ts[0];
+                        nu1_part = ts[1];
+                        nu2_part = ts[2];
+                    }
+                } else {
+                    for (int l = lane; l < a.Lpad; l += 64) {
+                        const float *ts = a.tstats + (bh * a.Lpad + l) * 3;
+                        var_part += ts[0];
+                        nu1_part += ts[1];
+                        nu2_part += ts[2];
+                    }
                 }
+            }
             if (!first_segment) __syncthreads();     // every wavefront is done with the previous table
             first_segment = false;
             if (PAGED && ONE_ROUND) stage_blks(0);

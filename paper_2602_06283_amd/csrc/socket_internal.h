@@ -322,6 +322,13 @@ __host__ __device__ __forceinline__ int packed_pos(int tl, int t, int S) {
     return (tl % S) * 16 + ((tl / S - t) & 15);
 }
 
+// A word that is the same for the whole workgroup and that no one writes during the launch, as a
+// scalar load also where the compiler cannot tell (behind inline asm or a store it takes such a
+// load to the vector unit, and waits for it alone).
+template <typename T> __device__ __forceinline__ T scalar_load(const T *p) {
+    return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
+
 // Row index (in units of rows of the [.., Hkv, tokens, width] tensor) of token t of
 // sequence b, KV head h; handles contiguous and paged storage.
 struct RowMap {

@@ -58,14 +58,14 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(TopkArgs a) {
     __shared__ uint32_t h[kHistBins];
     __shared__ float part[2][3][NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bh = blockIdx.y, b = bh / a.Hkv;
+    const int b = blockIdx.z, bh = b * a.Hkv + blockIdx.y;
     const int key0 = blockIdx.x * kSlice;
     const int i = key0 + tid * kPer;
     const float *row = a.scores + (int64_t)bh * a.max_n;
     float e[kPer];
     load_scores(row, i, a.max_n, e);
-    const int seq = clamp_len(a.seq_len[b], a.max_n);
-    const int kreq = clamp_len(a.k[b], a.max_k);
+    const int seq = clamp_len(scalar_load(&a.seq_len[b]), a.max_n);
+    const int kreq = clamp_len(scalar_load(&a.k[b]), a.max_k);
     const int key1 = min(key0 + kSlice, seq);
     if (key0 >= key1 && blockIdx.x != 0) return;       // workgroup 0 always publishes the bins
     const float v = seq > 0 ? row[(int)(((int64_t)tid * seq) / kTopkThreads)] : 0.0f;
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist2_kernel(TopkArgs a) {
     __shared__ uint32_t tmp[16];
     __shared__ uint32_t res[4];
     const int tid = threadIdx.x;
-    const int bh = blockIdx.y, b = bh / a.Hkv;
+    const int b = blockIdx.z, bh = b * a.Hkv + blockIdx.y;
     const int key0 = blockIdx.x * kSlice;
     const int i = key0 + tid * kPer;
     float e[kPer];
@@ -217,8 +217,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_filter_kernel(TopkArgs a) {
     __shared__ uint32_t tmp[16];
     __shared__ uint32_t res[4];
     __shared__ uint32_t s_base[2];
+    asm volatile("" ::"s"(a.scores), "s"(a.hist), "s"(a.thr), "s"(a.sel_cnt), "s"(a.seq_len), "s"(a.k), "s"(a.max_k), "s"(a.n_regions),
+                 "s"(a.counters), "s"(a.cand_key), "s"(a.sel_regions));          // (arguments in one trip)
     const int tid = threadIdx.x;
-    const int bh = blockIdx.y, b = bh / a.Hkv;
+    const int b = blockIdx.z, bh = b * a.Hkv + blockIdx.y;
     const int key0 = blockIdx.x * kSlice;
     const int i = key0 + tid * kPer;
     float e[kPer];
@@ -228,16 +230,22 @@ __global__ __launch_bounds__(kTopkThreads) void topk_filter_kernel(TopkArgs a) {
 #pragma unroll
     for (int j = 0; j < PER; ++j) c2[j] = gh[tid + j * kTopkThreads];
     uint32_t *thr = a.thr + (int64_t)bh * kThrStride;
-    const int key1 = min(key0 + kSlice, clamp_len(a.seq_len[b], a.max_n));
+    // (the length, the request and the record in one trip, not one behind the other)
+    const int len = scalar_load(&a.seq_len[b]);
+    const uint32_t kreq = (uint32_t)clamp_len(scalar_load(&a.k[b]), a.max_k);
+    const float rec_lo = __uint_as_float(scalar_load(&thr[kThrBinLo])), rec_inv = __uint_as_float(scalar_load(&thr[kThrBinInv]));
+    const uint32_t rec0 = scalar_load(&thr[0]), rec1 = scalar_load(&thr[1]), rec2 = scalar_load(&thr[2]);
+    if (ADAPT) asm volatile("" ::"s"(len), "s"(kreq), "s"(rec_lo), "s"(rec_inv));
+    else asm volatile("" ::"s"(len), "s"(rec0), "s"(rec1), "s"(rec2));
+    const int key1 = min(key0 + kSlice, clamp_len(len, a.max_n));
     // this workgroup's region of the selected list: empty unless the sweep below says otherwise
     uint32_t *selcnt = a.sel_cnt + (int64_t)bh * a.n_regions + blockIdx.x;
     if (tid == 0) *selcnt = 0u;
     uint32_t k_eff, pair, above, n_cand;
     float bin_lo = 0.0f, bin_inv = 0.0f;
     if (ADAPT) {
-        bin_lo = __uint_as_float(thr[kThrBinLo]);
-        bin_inv = __uint_as_float(thr[kThrBinInv]);
-        const uint32_t kreq = (uint32_t)clamp_len(a.k[b], a.max_k);
+        bin_lo = rec_lo;
+        bin_inv = rec_inv;
         if (key0 >= key1 && blockIdx.x != 0) return;   // workgroup 0 always publishes the record
 #pragma unroll
         for (int j = 0; j < PER; ++j) h[padded<PER>(tid + j * kTopkThreads)] = c2[j];
@@ -260,8 +268,8 @@ __global__ __launch_bounds__(kTopkThreads) void topk_filter_kernel(TopkArgs a) {
         }
         if (k_eff == 0) return;
     } else {
-        k_eff = thr[0];
-        const uint32_t tb1 = thr[1], above1 = thr[2];
+        k_eff = rec0;
+        const uint32_t tb1 = rec1, above1 = rec2;
         if (k_eff == 0) return;
         if (key0 >= key1 && blockIdx.x != 0) return;
 #pragma unroll
@@ -497,7 +505,7 @@ __global__ __launch_bounds__(kTopkThreads, 4) void topk_emit_kernel(TopkArgs a) 
     __shared__ uint32_t s_sum[2][NW];            // entries of earlier regions; kept candidates of earlier regions
     __shared__ uint32_t s_nown;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int reg = blockIdx.x, bh = blockIdx.y;
+    const int reg = blockIdx.x, bh = blockIdx.z * a.Hkv + blockIdx.y;
     // ---- every load that needs no other one (inside the buffers whatever the counts are)
     const uint32_t *thr = a.thr + (int64_t)bh * kThrStride;
     const uint32_t t0 = thr[0], t5 = thr[5], t6 = thr[6];
@@ -975,13 +983,13 @@ static void launch_sweep(const TopkArgs &a, dim3 grid, hipStream_t st) {
 }
 int launch_topk_sweep(socket_ctx *ctx, const float *scores, const int32_t *seq_len, const int32_t *k,
                       int batch, int32_t *idx, int32_t *n_selected, int hist_mode, hipStream_t st) {
-    launch_sweep(topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode), dim3(ctx->g.n_regions, batch * ctx->g.Hkv), st);
+    launch_sweep(topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode), dim3(ctx->g.n_regions, ctx->g.Hkv, batch), st);
     return record_hip(ctx, hipGetLastError());
 }
 
 int launch_topk(socket_ctx *ctx, const float *scores, const int32_t *seq_len, const int32_t *k,
                 int batch, int32_t *idx, int32_t *n_selected, int hist_mode, hipStream_t st) {
-    const dim3 grid(ctx->g.n_regions, batch * ctx->g.Hkv);
+    const dim3 grid(ctx->g.n_regions, ctx->g.Hkv, batch);
     TopkArgs a = topk_args(ctx, scores, seq_len, k, idx, n_selected, hist_mode);
     const int rows = batch * ctx->g.Hkv;
     const row_fn_t row_fn = hist_mode == kHistNone ? pick_row(ctx->g.n_regions, rows) : nullptr;

@@ -7,13 +7,6 @@
 
 namespace sk {
 
-// A word that is the same for the whole workgroup and that no one writes during the launch, as a
-// scalar load also where the compiler cannot tell (behind inline asm or a store it takes such a
-// load to the vector unit, and waits for it alone).
-template <typename T> __device__ __forceinline__ T scalar_load(const T *p) {
-    return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
-}
-
 constexpr int kRefineBins = 4096;                // bins of a candidate-refinement digit
 constexpr int kBitmapWords = 4096;               // 16 KB of LDS
 constexpr int kBitmapTokens = kBitmapWords * 32; // tokens one LDS bitmap pass covers
