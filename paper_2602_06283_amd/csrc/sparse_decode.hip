@@ -695,7 +695,7 @@ __global__ __launch_bounds__(kDecodeThreads) void sparse_decode_kernel(DecodeArg
 // after the partial pass: no fence, no signalling.
 //
 // Bound by latency and by instructions that come cold: a launch of a few workgroups runs each of
-// them once.  So there is a body for 8, for 16 and for all splits a thread (a load, a bounds test
+// them once.  So there is a body for 8, 16, 24 and for all splits a thread (a load, a bounds test
 // and an FMA of each of the 32 possible ones cost as much with 9 splits as with 128), the group is a
 // scalar and the rows' addresses with it, and the heads of a KV head come as an argument, not by a
 // division.  merge_finish at 36 splits of 32 query heads 4.4 -> 3.4 us, at 9 of 512 5.6 -> 5.0.
@@ -774,7 +774,10 @@ __device__ __forceinline__ void merge_body(const DecodeArgs &a, int g, int h, in
     __shared__ MergeLds<D, NT> lds;
     if (a.n_split <= 8 * NG) merge_splits<D, NT, 8>(a, g, h, b, thr, lds);
     else if (a.n_split <= 16 * NG) merge_splits<D, NT, 16>(a, g, h, b, thr, lds);
-    else if constexpr (MOST > 16) merge_splits<D, NT, MOST>(a, g, h, b, thr, lds);
+    else if constexpr (MOST > 16) {
+        if (a.n_split <= 24 * NG) merge_splits<D, NT, 24>(a, g, h, b, thr, lds);
+        else merge_splits<D, NT, MOST>(a, g, h, b, thr, lds);
+    }
 }
 
 template <int D>
