@@ -601,27 +601,29 @@ constexpr size_t kEmitLds = (size_t)(kRankMax + 4) * 8 + (size_t)kRankMax * 4;
 // ---------------------------------------------------------------------------------------
 // Short rows in one launch: one workgroup of 16 wavefronts per (sequence, KV head) holds the row in
 // registers (NC chunks of 4096 scores), so the select is a chain of phases in LDS:
-//   bins     2048 equal steps of the score key (four instructions a score) between a score that the cut
-//            should lie above, by the mean and the deviation of 1024 sampled scores, and the largest of
-//            those; scores beyond are in the last bin, those before in none.  Lower bins once more where
-//            that was too high, and where the cut lies lower still the scores there are refined
+//   window   two scores of a sample of 1024 between which the cut should lie: as many ranks above and
+//            below the wanted share as three of its deviations
+//   bins     2048 equal steps of the score key between the two, five instructions a score; the scores
+//            above are only counted.  Where the cut lies outside the window after all, the scores on
+//            that side are refined
 //   refine   while the threshold bin holds more than kRowPairs scores that are not all kept: 2048
-//            equal steps from its least to its largest key, and again, down to a single key (three
-//            rounds at most: exact for any bins)
+//            equal steps of the key over it, and again, down to a single key (three rounds of bins at
+//            most: exact for any), which a look at the least and the largest key there finds at once
 //   cut      up to kRowPairs scores are ranked in pairs on (score, smaller position first); more
 //            only where they tie on one key: the smallest positions, by a scan.  The selection is
 //            what is not below one (key, position)
 //   emit     slots in position order, from a scan over the kept scores
 // Nothing is kept between calls; no scratch.
 // Bound by the instructions of one compute unit behind 6 us of launch, loads and phases.
-// us a select, this kernel / three launches, 8 rows like a bell: 12000 scores 8.2 / 13.2, 20000 9.3 / 13.5,
-// 24000 9.8 / 13.5, 32768 11.1 / 13.8, 36864 11.8 / 13.8, 40960 12.4 / 13.9, 49152 13.9 / 14.1; rows of a few
-// dozen different scores 20000 12.5 / 20, 32768 17.0 / 20.0, 40960 19.8 / 19.8, 49152 22.8 / 20.2; 64 rows like
-// a bell 32768 11.2 / 20.5, 49152 14.0 / 29.  (With bins by sampled_bin, 40 instructions a score, and no look
-// at the least and largest key: 12000 9.5, 20000 11.5, 32768 15.4; 64 rows of 49152 19.1; of a few dozen
-// different scores 20000 19.1, 32768 30.9.)  So up to kRowRegions regions of 4096 scores always, where rows
-// with many close scores at the cut still break even (32768: a cluster in a cluster 20.7 / 20.8, a heavy
-// tail 15.8 / 13.4), up to kRowRegionsMany from kRowRowsMany rows on, where three launches fill the card.
+// us a select of a 32nd of 8 rows, this kernel / three launches: like a bell 20496 scores 9.5 / 14.2, 24576 9.7 /
+// 13.9, 28672 10.4 / 13.8, 32768 11.1 / 13.8, 36864 11.8 / 13.9; counts 32768 15.2 / 19.4; a heavy tail 32768 11.1 /
+// 13.0; a cluster in a cluster 36864 16.7 / 21.2.  An eighth of 36864: a bell 12.4 / 14.0, counts 18.0 / 20.3, counts
+// with a soft part 22.9 / 21.0.  64 rows like a bell 36864 12.2 / 16.1, 49152 14.6 / 19.4.  So up to kRowRegions
+// regions of 4096 scores always: of 12 shapes of rows with a 32nd, an eighth and a third selected the last-named
+// alone is slower there.  Up to kRowRegionsMany from kRowRowsMany rows on, where three launches fill the card.
+// (A window by the mean and the deviation of the sample: a bell the same, but rows whose cut lay below it were binned
+// twice and those with a window across zero in steps of an octave: a 32nd of 36864 with infinities 30.2 / 11.9 now, an
+// eighth of counts with a soft part 35.5 / 22.9, a third of 20480 rising scores 27.2 / 10.2.)
 // ---------------------------------------------------------------------------------------
 constexpr int kRowThreads = 1024, kRowWaves = kRowThreads / 64;
 constexpr int kRowPairs = 256;
@@ -660,9 +662,8 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
     __shared__ __align__(16) unsigned long long ck[kRowPairs + 4];
     __shared__ __align__(16) uint32_t tot[256];                  // [chunk][wavefront]
     __shared__ uint32_t tmp[kRowWaves], s_valid[kRowWaves], res[3], s_n;
-    __shared__ float s_part[2][3][kRowWaves], s_most[kRowWaves];
     __shared__ unsigned long long s_cut, s_next;
-    __shared__ uint2 s_ends[kRowWaves];
+    __shared__ uint2 s_ends[2][kRowWaves], s_count[2][kRowWaves];
     static_assert(NC * kRowWaves <= 256, "four totals a lane");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bh = blockIdx.x, b = bh / a.Hkv;
@@ -687,44 +688,52 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
                 if (c * kSlice + 4 * tid + j >= seq) w[c][j] = __float_as_uint(ninf);
         }
 
-    // ---- the first score that is binned, and the last bin's: a wavefront's sample is every fourth of its
-    //      256 scores of one chunk
-    float mu = 0.0f, sigma = 0.0f, hi, share;
+    // ---- keys klo .. khi - 1, between which the cut should lie: those of two scores of a sample, as many
+    //      ranks above and below the wanted share as three of its deviations.  The sample is a score a thread,
+    //      the chunks in turn
+    uint32_t klo, khi;
     {
-        const int live = max(1, (seq + kSlice - 1) / kSlice), mine = wave % live;
-        float v = __uint_as_float(w[0][0]);
+        const int live = max(1, (seq + kSlice - 1) / kSlice);
+        const int mine = tid - live * ((tid * (65536 / live + 1)) >> 16);      // tid % live
+        uint32_t v = w[0][0];
 #pragma unroll
         for (int c = 1; c < NC; ++c)
-            if (c == mine) v = __uint_as_float(w[c][0]);
-        const bool there = mine * kSlice + 4 * tid < seq;
-        bool use = there && fabsf(v) < 3.0e38f;                  // (false for NaN and both infinities)
-        float finite = 0.0f, cnt = 0.0f;
-#pragma unroll
-        for (int round = 0; round < 2; ++round) {
-            const float n0 = row_sum<64>(use ? 1.0f : 0.0f), n1 = row_sum<64>(use ? v : 0.0f);
-            const float most = round == 0 ? wave_max(use ? v : -3.0e38f) : 0.0f;
-            if (lane == 0) {
-                s_part[round][0][wave] = n0;
-                s_part[round][1][wave] = n1;
-                if (round == 0) s_most[wave] = most;
-            }
-            __syncthreads();
-            cnt = fmaxf(row_sum<16>(s_part[round][0][lane & 15]), 1.0f);
-            if (round == 0) finite = cnt;
-            mu = row_sum<16>(s_part[round][1][lane & 15]) / cnt;
-            const float d = use ? v - mu : 0.0f;
-            const float n2 = row_sum<64>(d * d);
-            if (lane == 0) s_part[round][2][wave] = n2;
-            __syncthreads();
-            sigma = sqrtf(row_sum<16>(s_part[round][2][lane & 15]) / cnt);
-            use = use && fabsf(v - mu) <= 4.0f * sigma;
+            if (c == mine) v = w[c][0];
+        const uint32_t key = selectable(__uint_as_float(v)) ? order_key(__uint_as_float(v)) : 0u;   // (-inf behind the end)
+        auto lanes16 = [&](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_umax(x)); };
+        const uint32_t sampled = (uint32_t)__popcll(__ballot(mine * kSlice + 4 * tid < seq));
+        const uint32_t wmax = wave_umax(key), wmin = wave_umax(key ? ~key : 0u);
+        if (lane == 0) {
+            s_ends[0][wave] = make_uint2(wmin, wmax);
+            s_count[0][wave] = make_uint2(sampled, 0);
         }
-        sigma = fminf(fmaxf(sigma, fmaxf(fabsf(mu) * 1e-6f, 1e-30f)), 1.0e37f);
-        share = (float)kreq / fmaxf((float)seq, 1.0f);
-        // (a lone spike does not widen the bins; as many scores far out as are wanted do)
-        const float most = wave_max(s_most[lane & 15]);
-        hi = fmaxf((finite - cnt >= 0.5f * share * finite ? most : fminf(most, mu + 16.0f * sigma)) + 0.25f * sigma, mu + 2.0f * sigma);
-        hi = fabsf(hi) < 3.0e38f ? hi : 3.0e38f;
+        __syncthreads();
+        const uint2 ends = s_ends[0][lane & 15];
+        const uint32_t least = ~lanes16(ends.x), most = lanes16(ends.y);
+        const int bits = most > least ? 32 - __clz((int)(most - least)) : 0, shift = bits > kHistBits ? bits - kHistBits : 0;
+        const uint32_t bin = (key - least) >> shift;
+        if (key) atomicAdd(&h[bin], 1u);
+        const float r = (float)kreq * row_sum<16>((float)s_count[0][lane & 15].x) / fmaxf((float)seq, 1.0f), dev = 3.0f * sqrtf(r) + 3.0f;
+        __syncthreads();
+        const uint2 c = *(const uint2 *)&h[kHistBins - 2 - 2 * tid];
+        uint32_t all;
+        const uint32_t above = row_excl_scan(c.x + c.y, &all, tmp);
+        const uint32_t rank_lo = min((uint32_t)(r + dev) + 1, all), rank_hi = (uint32_t)fmaxf(r - dev, 1.0f);
+        auto here = [&](uint32_t rank, uint32_t *at) {
+            if (above < rank && rank <= above + c.x + c.y) *at = (uint32_t)(kHistBins - 2 - 2 * tid + (rank <= above + c.y ? 1 : 0));
+        };
+        here(rank_lo, &res[0]);
+        here(rank_hi, &res[1]);
+        *(uint2 *)&h[kHistBins - 2 - 2 * tid] = make_uint2(0, 0);
+        __syncthreads();
+        const uint32_t lo = wave_umax(key && bin >= res[0] ? ~key : 0u);
+        const uint32_t hi = wave_umax(key < 0xff800000u && bin <= res[1] ? key : 0u);       // (+inf would stretch the bins)
+        if (lane == 0) s_ends[1][wave] = make_uint2(lo, hi);
+        __syncthreads();
+        const uint2 cut = s_ends[1][lane & 15];
+        klo = ~lanes16(cut.x);
+        khi = max(lanes16(cut.y), klo) + 1;
+        if (most == 0) klo = 1, khi = 2;                         // (nothing but NaN and -inf)
     }
     // Scores from +0 on compare by their bits, counted from +0; where the bins start below, w takes keys (0
     // for what is never selected, NaN and -inf)
@@ -739,12 +748,12 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
     };
     uint32_t zero = 0x80000000u;                                 // the key that w counts from
 
-    // the bin of h with the target-th score from the top in it: the bin, the scores above it, those in
-    // it (in res, complete after the barrier); returns the number of scores in h
-    auto find = [&](uint32_t target) {
+    // the bin of h with the rank(number of scores in h)-th score from the top in it: the bin, the scores above
+    // it, those in it (in res, complete after the barrier); returns the number of scores in h
+    auto find = [&](auto rank) {
         const uint2 c = *(const uint2 *)&h[kHistBins - 2 - 2 * tid];
         uint32_t total;
-        const uint32_t above = row_excl_scan(c.x + c.y, &total, tmp);
+        const uint32_t above = row_excl_scan(c.x + c.y, &total, tmp), target = rank(total);
         if (above < target && target <= above + c.x + c.y) {
             const bool upper = target <= above + c.y;
             res[0] = (uint32_t)(kHistBins - 2 - 2 * tid + (upper ? 1 : 0));
@@ -754,109 +763,105 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
         __syncthreads();
         return total;
     };
-    // ---- the scores in question: keys k0 .. k0 + span - 1, n_in of them, `need` to keep.  The tenth of a
-    //      bell lies above mean + 0.75 deviations; where it does not, the bins start lower
-    uint32_t k_eff = kreq, total = 0, n_valid = 0, klo = 0, up = 0;
-    int shift0 = 0;
-    bool below = false;                                          // the cut lies below the bins
-#pragma unroll 1
-    for (int low = share <= 0.1f ? 0 : 1; low < 2; ++low) {
-        float lo = mu + (low == 0 ? 0.75f : share <= 0.1f ? -0.5f : share <= 0.25f ? -1.0f : -4.0f) * sigma;
-        lo = fabsf(lo) < 3.0e38f ? lo : 0.0f;
-        if (!(lo > 0.0f) && zero != 0) {
-            zero = 0;
-            to_keys();
-        }
-        klo = order_key(lo);
-        up = 0xff800000u - klo;                                  // +inf is `up` above klo
-        const uint32_t range = max(order_key(hi), klo + 1) - klo;
-        const int bits = 32 - __clz((int)range);
-        shift0 = bits > kHistBits ? bits - kHistBits : 0;
+    if (klo < zero) {
+        zero = 0;
+        to_keys();
+    }
+    // ---- how many there are from klo on, and those before khi in bins (one key: only counted, equal scores
+    //      come by the thousand)
+    const uint32_t range = khi - klo, top0 = 0xff800000u - klo;  // +inf is top0 above klo
+    const int bits0 = 32 - __clz((int)(range - 1)), shift0 = bits0 > kHistBits ? bits0 - kHistBits : 0;
+    uint32_t from_lo = 0, between = 0;
+    if (range > 1) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t off = w[c][j] - (klo - zero);
-                if (off <= up) atomicAdd(&h[min(off >> shift0, (uint32_t)(kHistBins - 1))], 1u);
+                from_lo += off <= top0 ? 1u : 0u;
+                if (off < range) atomicAdd(&h[off >> shift0], 1u);
             }
-        __syncthreads();
-        if (kreq > 0) total = find(kreq);
-        if (total >= kreq || low == 1) break;
-        for (int j = tid; j < kHistBins; j += kRowThreads) h[j] = 0;
-        __syncthreads();
-    }
-    if (total < kreq) {                                          // (or there are fewer scores: all of them)
-        uint32_t valid = 0;
+    } else {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                // (selectable(); the compiler's ballot of v > -inf counts NaN)
-                const bool ok = zero == 0 ? w[c][j] != 0u : __uint_as_float(w[c][j]) >= -3.40282347e38f;
-                valid += (uint32_t)__popcll(__ballot(ok));
+                const uint32_t off = w[c][j] - (klo - zero);
+                from_lo += off <= top0 ? 1u : 0u;
+                between += off == 0 ? 1u : 0u;
             }
+    }
+    from_lo = (uint32_t)row_sum<64>((float)from_lo);
+    between = (uint32_t)row_sum<64>((float)between);
+    if (lane == 0) s_count[1][wave] = make_uint2(from_lo, between);
+    __syncthreads();
+    {
+        const uint2 n = s_count[1][lane & 15];
+        from_lo = (uint32_t)row_sum<16>((float)n.x);
+        between = (uint32_t)row_sum<16>((float)n.y);
+    }
+    if (range > 1) between = find([&](uint32_t total) { return kreq + total - from_lo; });   // (wraps where the cut lies elsewhere)
+    // ---- the scores in question: keys k0 .. k0 + span - 1, n_in of them, `need` to keep
+    uint32_t k_eff = kreq, k0, span, need, n_in;
+    if (from_lo < kreq) {                                        // the cut lies below, or there are fewer scores
+        if (zero != 0) {
+            zero = 0;
+            to_keys();
+        }
+        uint32_t valid = 0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) valid += (uint32_t)__popcll(__ballot(w[c][j] != 0u));
         if (lane == 0) s_valid[wave] = valid;
         __syncthreads();
-        n_valid = (uint32_t)row_sum<16>((float)s_valid[lane & 15]);
+        const uint32_t n_valid = (uint32_t)row_sum<16>((float)s_valid[lane & 15]);
         k_eff = min(kreq, n_valid);
-        below = total < k_eff;
-        if (!below && k_eff > 0) find(k_eff);
+        k0 = 1; span = klo - 1; need = k_eff - from_lo; n_in = n_valid - from_lo;
+    } else if (from_lo - between >= kreq) {                      // above
+        k0 = khi; span = 0xff800000u - khi + 1; need = kreq; n_in = from_lo - between;
+    } else if (range == 1) {
+        k0 = klo; span = 1; need = kreq - (from_lo - between); n_in = between;
+    } else {
+        const uint32_t step = res[0] << shift0;
+        k0 = klo + step; span = min(range - step, 1u << shift0); need = kreq - (from_lo - between) - res[1]; n_in = res[2];
     }
     int32_t *out = a.idx + (int64_t)bh * a.max_k;
     if (tid == 0) a.n_selected[bh] = (int32_t)k_eff;
     for (int i = (int)k_eff + tid; i < a.max_k; i += kRowThreads) out[i] = -1;
     if (k_eff == 0) return;
-    uint32_t k0, span, need, n_in;
-    if (below) {
-        if (zero != 0) {
-            zero = 0;
-            to_keys();
-        }
-        k0 = 1; span = klo - 1; need = k_eff - total; n_in = n_valid - total;
-    } else {
-        const uint32_t step = res[0] << shift0;
-        k0 = klo + step; need = k_eff - res[1]; n_in = res[2];
-        span = res[0] == kHistBins - 1 ? up - step + 1 : 1u << shift0;
-        span = min(span, up - step + 1);
-    }
     __syncthreads();
-    while (n_in != need && n_in > (uint32_t)kRowPairs && span > 1) {
-        // (from the least to the largest key there: equal scores by the thousand are one key at once)
+    for (bool ends_only = n_in > (uint32_t)seq / 16; n_in != need && n_in > (uint32_t)kRowPairs && span > 1; ends_only = false) {
+        // (where there are many of them they are likely equal scores, which would add up one behind the
+        // other: only their ends first)
+        const int bits = 32 - __clz((int)(span - 1)), shift = bits > kHistBits ? bits - kHistBits : 0;
+        for (int j = tid; j < kHistBins; j += kRowThreads) h[j] = 0;
+        __syncthreads();
         uint32_t inv = 0, most = 0;                              // largest ~offset, largest offset
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t off = w[c][j] - (k0 - zero);
-                inv = off < span ? max(inv, ~off) : inv;
-                most = off < span ? max(most, off) : most;
+                if (off < span) {
+                    if (!ends_only) atomicAdd(&h[off >> shift], 1u);
+                    inv = max(inv, ~off);
+                    most = max(most, off);
+                }
             }
         inv = wave_umax(inv);
         most = wave_umax(most);
-        if (lane == 0) s_ends[wave] = make_uint2(inv, most);
+        if (lane == 0) s_ends[0][wave] = make_uint2(inv, most);
         __syncthreads();
-        const uint2 ends = s_ends[lane & 15];
-        const uint32_t least = ~wave_umax(ends.x);
-        k0 += least;
-        span = wave_umax(ends.y) - least + 1;
-        if (span == 1) break;
-        const int bits = 32 - __clz((int)(span - 1)), shift = bits > kHistBits ? bits - kHistBits : 0;
-        for (int j = tid; j < kHistBins; j += kRowThreads) h[j] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t off = w[c][j] - (k0 - zero), d = off >> shift;
-                if (off < span) {                                // (lanes with the first one's step add together: equal scores come by the thousand)
-                    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
-                    const uint64_t same = __ballot(d == first);
-                    if (d != first) atomicAdd(&h[d], 1u);
-                    else if (lane == __ffsll((unsigned long long)same) - 1) atomicAdd(&h[d], (uint32_t)__popcll(same));
-                }
-            }
-        __syncthreads();
-        find(need);
+        const uint2 ends = s_ends[0][lane & 15];
+        const uint32_t least = ~wave_umax(ends.x), last = wave_umax(ends.y);
+        if (last == least || ends_only) {                        // (equal scores are one key at once)
+            k0 += least;
+            span = last - least + 1;
+            __syncthreads();
+            continue;
+        }
+        find([&](uint32_t) { return need; });
         const uint32_t step = res[0] << shift;
         k0 += step;
         span = min(span - step, 1u << shift);
