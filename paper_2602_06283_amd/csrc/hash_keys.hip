@@ -719,11 +719,14 @@ template <int KS> __device__ __forceinline__ float2 close_columns(const uint4 *f
 struct CloseEntry {
     int64_t row;       // the key's row in K and in the ids
     int tok;
-    uint32_t col;      // column of the workgroup's tables; top bit: the bit its id has
+    uint32_t col;      // column of the workgroup's tables, and from bit 16 on the id as it was stored
 };
 
 // A wavefront's list.  Entries are settled when it is half full and after the last block.
+// An id is mended by storing it whole, as the list knows it, and never from what memory holds: the
+// row may be another wavefront's too (sequences that share a block), whose ids come before or after.
 template <int D, int P, int S, int CAP> struct CloseList {
+    static_assert(CAP <= 64, "a lane an entry");
     const HashArgs &a;
     CloseEntry *list;
     const float *W;                            // [D][LP], the workgroup's tables from column 0 on
@@ -745,30 +748,47 @@ template <int D, int P, int S, int CAP> struct CloseList {
         return sum;
     }
 
-    // Accumulator i of half g is bit 32 q + 16 g + i of position group `sub` of the lane's key;
-    // bit i of neg its sign.  row(): the key's row in K, or -1.
+    // The sums of a block's two keys of a lane: accumulator i of half g is bit 32 q + 16 g + i of position
+    // group `sub`.  neg: their signs, the second key's from bit 16 on.  row(nb): the key's row in K, or -1.
     template <typename F>
-    __device__ __forceinline__ void add(const floatx16_t &acc, uint32_t &neg, float2 key, float2 cols, int q, int sub, int tok, F &&row) {
-        float least = fabsf(acc[0]);
+    __device__ __forceinline__ void add(const floatx16_t &acc0, const floatx16_t &acc1, uint32_t &neg, const float2 *key, float2 cols, int q, int sub, int tok, F &&row) {
+        auto bound = [&](int nb) { return cols.x < __builtin_inff() ? fmaf(key[nb].x, cols.x, key[nb].y * cols.y) : __builtin_inff(); };
+        const float bound0 = bound(0), bound1 = bound(1);
+        float least0 = fabsf(acc0[0]), least1 = fabsf(acc1[0]);
 #pragma unroll
-        for (int i = 1; i < 16; ++i) least = fminf(least, fabsf(acc[i]));   // (a NaN comes with an infinite bound)
-        const float bound = cols.x < __builtin_inff() ? fmaf(key.x, cols.x, key.y * cols.y) : __builtin_inff();
-        if (__ballot(!(least > bound)) == 0 || ntab <= 0) return;
+        for (int i = 1; i < 16; ++i) {                 // (a NaN comes with an infinite bound)
+            least0 = fminf(least0, fabsf(acc0[i]));
+            least1 = fminf(least1, fabsf(acc1[i]));
+        }
+        if (__ballot(!(least0 > bound0 && least1 > bound1)) == 0 || ntab <= 0) return;
         uint32_t near = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) near |= (fabsf(acc[i]) > bound ? 0u : 1u) << i;
-        const int lane = threadIdx.x & 63;
-        const int64_t gr = row();
-        if (gr < 0) near = 0;
-        while (__ballot(near != 0) != 0) {
-            const int i = __ffs((int)near) - 1, u = 32 * q + 16 * (lane >> 5) + i, tt = (u / P) * S + sub;
-            const bool mine = near != 0 && tt < ntab;
-            near &= near - 1;
-            const uint64_t m = __ballot(mine);
-            const int at = n + __popcll(m & ((1ull << lane) - 1)), col = tt * P + u % P;
-            if (mine && at < CAP) list[at] = CloseEntry{gr, tok, (uint32_t)col | ((neg >> i) & 1u ? 0u : 1u << 31)};
-            if (mine && at >= CAP) neg = (neg & ~(1u << i)) | (sum_of(gr, col) >= 0.0f ? 0u : 1u) << i;   // (keys by the hundred at right angles to W, or out of range)
-            n = min(n + (int)__popcll(m), CAP);
+        for (int i = 0; i < 16; ++i) near |= (fabsf(acc0[i]) > bound0 ? 0u : 1u) << i | (fabsf(acc1[i]) > bound1 ? 0u : 1u) << (16 + i);
+        const int lane = threadIdx.x & 63, u0 = 32 * q + 16 * (lane >> 5);
+        auto table = [&](int i) { return (u0 + (i & 15)) / P * S + sub; };
+        if ((32 * q + 31) / P * S + sub >= ntab) {
+#pragma unroll
+            for (int i = 0; i < 16; i += P)
+                if (table(i) >= ntab) near &= ~(0x10001u * (((1u << P) - 1) << i));
+        }
+        const int64_t row0 = row(0), row1 = row(1);
+        near &= (row0 < 0 ? 0u : 0xffffu) | (row1 < 0 ? 0u : 0xffff0000u);
+        const int before = n;
+        uint64_t m;
+        for (uint32_t left = near; (m = __ballot(left != 0)) != 0; left &= left - 1) {
+            const int i = __ffs((int)left) - 1, more = (int)__popcll(m);
+            if (n + more > CAP) {                      // (keys by the hundred at right angles to W, or out of range)
+                n = before;
+                for (; near != 0; near &= near - 1) {
+                    const int j = __ffs((int)near) - 1;
+                    neg = (neg & ~(1u << j)) | (sum_of(j < 16 ? row0 : row1, table(j) * P + j % P) >= 0.0f ? 0u : 1u) << j;
+                }
+                return;
+            }
+            const uint32_t id = ~(neg >> (i & ~(P - 1))) & ((1u << P) - 1);
+            if (left != 0)
+                list[n + __popcll(m & ((1ull << lane) - 1))] = CloseEntry{i < 16 ? row0 : row1, tok + (i < 16 ? 0 : 32), (uint32_t)(table(i) * P + i % P) | id << 16};
+            n += more;
         }
     }
 
@@ -780,8 +800,9 @@ template <int D, int P, int S, int CAP> struct CloseList {
         constexpr int CH = D / 8;
         const int lane = threadIdx.x & 63, part = lane & 7;
         for (int base = 0; base < n; base += 8) {
-            const CloseEntry e = list[min(base + (lane >> 3), n - 1)];
-            const int col = (int)(e.col & 0x7fffffffu);
+            const int at = min(base + (lane >> 3), n - 1);
+            const CloseEntry e = list[at];
+            const int col = (int)(e.col & 0xffffu);
             const f32x4_t *k = (const f32x4_t *)((const float *)a.K + e.row * D + part * CH);
             const float *wc = W + (int64_t)(part * CH) * a.LP + col;
             f32x4_t x[CH / 4];
@@ -798,19 +819,19 @@ template <int D, int P, int S, int CAP> struct CloseList {
 #pragma unroll
                 for (int c = 0; c < CH; ++c) sum = fmaf(x[c / 4][c % 4], w[c], sum);
             }
-            const bool flip = part == 7 && base + (lane >> 3) < n && (sum >= 0.0f) != ((e.col >> 31) != 0);
-            // (one after the other, behind the ids themselves: two may share a byte; a byte at a time: the
-            // ones beside it may be another workgroup's)
-            uint64_t todo = __ballot(flip);
-            if (todo == 0) continue;
-            uint8_t *byte = (uint8_t *)a.codes + e.row * a.Lpad + code_pos(first_table + col / P, e.tok, S);
-            __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0)
-            for (; todo != 0; todo &= todo - 1)
-                if (lane == __ffsll((unsigned long long)todo) - 1) {
-                    const uint8_t old = __hip_atomic_load(byte, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(byte, (uint8_t)(old ^ (1u << (col % P))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __builtin_amdgcn_s_waitcnt(0x0f70);
-                }
+            const bool flip = part == 7 && base + (lane >> 3) < n && (sum >= 0.0f) != ((e.col >> (16 + col % P) & 1) != 0);
+            const uint64_t flips = __ballot(flip);
+            if (flips == 0) continue;
+            for (uint64_t todo = flips; todo != 0; todo &= todo - 1) {   // all entries of the id learn of its new bit
+                const int from = __ffsll((unsigned long long)todo) - 1;
+                const int64_t row = list[base + (from >> 3)].row;
+                const uint32_t was = (uint32_t)__builtin_amdgcn_readlane((int)e.col, from), bit = 1u << (16 + (was & 0xffffu) % P);
+                const CloseEntry mine = list[min(lane, n - 1)];
+                if (lane < n && mine.row == row && (mine.col & 0xffffu) / P == (was & 0xffffu) / P) list[lane].col = (mine.col & ~bit) | (~was & bit);
+            }
+            __builtin_amdgcn_wave_barrier();           // (the list as the other lanes left it)
+            __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0): behind the ids themselves
+            if (flip) ((uint8_t *)a.codes)[e.row * a.Lpad + code_pos(first_table + col / P, e.tok, S)] = (uint8_t)(list[at].col >> 16);
         }
         n = 0;
     }
@@ -1044,9 +1065,10 @@ __global__ __launch_bounds__((hash8_threads<hash_width<T, D>()>())) void hash_mf
             }
             uint32_t neg0 = signs(acc0), neg1 = signs(acc1);
             if constexpr (SPLIT) {
-                const float2 c = cols[p];
-                close.add(acc0, neg0, keys.close[0], c, q, sub, begin + r0 + n, [&]() { return key_row(r0 + n); });
-                close.add(acc1, neg1, keys.close[1], c, q, sub, begin + r0 + 32 + n, [&]() { return key_row(r0 + 32 + n); });
+                uint32_t neg = neg0 | neg1 << 16;
+                close.add(acc0, acc1, neg, keys.close, cols[p], q, sub, begin + r0 + n, [&](int nb) { return key_row(r0 + 32 * nb + n); });
+                neg0 = neg & 0xffffu;
+                neg1 = neg >> 16;
             }
             const uint32_t w0 = sign_word(neg0), w1 = sign_word(neg1);
             const uint32_t w = lane < 32 ? w0 : w1;                     // lane = key n or 32 + n

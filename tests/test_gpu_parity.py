@@ -315,6 +315,38 @@ def test_hash_keys_fp32_close_sums(d, L, P, Hkv, counts):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,L,P,page,begins,counts,kind", [
+    (128, 64, 8, 16, [0, 0, 0], [1500] * 3, "shared"), (64, 32, 8, 48, [5] * 4, [1501] * 4, "shared"), (128, 64, 4, 16, [0] * 8, [400] * 8, "shared"),
+])
+def test_hash_keys_fp32_close_sums_on_paged_caches(d, L, P, page, begins, counts, kind):
+    """The same on blocks in random order, against short runs of one sequence at a time: sequences that share
+    their blocks ("shared", every id written by all of them) get the ids that one alone gets."""
+    _need_gpu()
+    B, Hkv = len(counts), 8
+    per = (max(b + c for b, c in zip(begins, counts)) + page - 1) // page
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    K = torch.randn((B * per, Hkv, page, d), generator=gen, device="cuda")
+    W = torch.randn((Hkv, d, L * P), generator=gen, device="cuda")
+    rows = torch.arange(0, B * per, 3, device="cuda")                    # every key of every third block
+    w = W.transpose(1, 2)[:, rows * 7 % (L * P)].transpose(0, 1)[:, :, None].double()
+    k = K[rows].double()
+    K[rows] = (k - (k * w).sum(-1, keepdim=True) / (w * w).sum(-1, keepdim=True) * w).float()
+    table = torch.randperm(B * per, generator=gen, device="cuda").to(torch.int32).view(B, per)
+    if kind == "shared":
+        table[:] = table[0].clone()
+    ctx = sk.Context(sk.make_params(d, Hkv, Hkv, L, P, sk.F32, B, per * page, 16, page, per, B * per))
+    want = hz.new_codes((B * per, Hkv), page, L, P, fill=0x55)
+    for b in range(B):
+        for at in range(0, counts[b], 96):
+            c = min(96, counts[b] - at)
+            ctx.hash_keys(K, W, hz.i32([begins[b] + at]), hz.i32([c]), 1, max(c, 2), want, block_table=table[b:b + 1])
+    for _ in range(4):
+        got = hz.new_codes((B * per, Hkv), page, L, P, fill=0x55)
+        _hash_device(ctx, K, W, begins, counts, got, table=table)
+        assert torch.equal(got, want), (got != want).nonzero()[:20]
+    ctx.close()
+
+
 @pytest.mark.parametrize("kv_dtype,d,L,P,counts", [
     (wl.F32, 128, 32, 8, [97, 161, 0]), (wl.F32, 64, 60, 10, [97, 161, 5]), (wl.F32, 256, 64, 8, [161, 33, 1]),
     (wl.F32, 128, 40, 12, [97, 161, 2]), (wl.BF16, 128, 64, 8, [37, 63, 2]), (wl.BF16, 64, 16, 10, [63, 5, 0]), (wl.BF16, 256, 24, 5, [37, 63, 9]),
