@@ -672,8 +672,12 @@ __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int 
 // pieces leave out matters near zero alone: where |sum| is not above a bound on its distance to the sum
 // that the FMA kernel forms (three projections in ten thousand for normal keys), the projection goes on
 // the wavefront's list and is formed anew, channel by channel as the FMA kernel does; if the sign is the
-// other one (one in ten million) its bit is turned in memory.  The ids are those of the FMA kernel bit
-// for bit.
+// other one (one in ten million) the id is stored again.  A block with more of them than the list holds is
+// formed anew whole, on the fp32 matrix cores.  The ids are those of the FMA kernel bit for bit.
+// That block makes the time depend on the data where sums are close to zero by the dozen (8 heads, 8192
+// keys, 32 tables, 28 us else and 48 on the fp32 matrix cores alone): all keys or all of W too small or too
+// large for the bound 100, one key in a hundred of that kind 91, every key at right angles to one column
+// of W 70.  (Sum by sum, a lane each, these took 1130, 201 and 88.)
 // 8 heads, 32 tables of 8 planes, 128 channels: 8192 keys 25.5 us (42.6 on the fp32 matrix cores), 32768 65
 // (154), where a block's matrix work is 12 of its 20 us and the rest the keys' way from memory, two
 // wavefronts a SIMD being all that the registers allow; of a short run's time 14 us are launch, W and
@@ -735,54 +739,70 @@ template <int D, int P, int S, int CAP> struct CloseList {
     __device__ __forceinline__ CloseList(const HashArgs &args, CloseEntry *mine, int h, int first, int tables)
         : a(args), list(mine), W((const float *)args.W + (int64_t)h * D * args.LP + (int64_t)first * P), first_table(first), ntab(tables) {}
 
-    __device__ __forceinline__ float sum_of(int64_t row, int col) const {
-        const f32x4_t *k = (const f32x4_t *)((const float *)a.K + row * D);
-        const float *w = W + col;
-        float sum = 0.0f;
-#pragma unroll 2
-        for (int c = 0; c < D / 4; ++c) {
-            const f32x4_t x = k[c];
+    // The signs (as in add) of a block's first or second keys, or both, where one of them is `near`: on the
+    // fp32 matrix cores, whose sums are the FMA kernel's bit for bit (hash_f32_kernel), both operands
+    // straight from memory.
+    __device__ __forceinline__ uint32_t block_signs(uint32_t neg, uint32_t near, int q, int sub, int64_t row0, int64_t row1) const {
+        const int lane = threadIdx.x & 63, g = lane >> 5;
+        const int u = 32 * q + (lane & 3) + 4 * ((lane >> 3) & 3) + 16 * ((lane >> 2) & 1);   // (the rows of the fragments: cut_fragments)
+        const float *w = W + (int64_t)g * a.LP + min(u / P * S + sub, ntab - 1) * P + u % P;
+#pragma unroll 1
+        for (int nb = 0; nb < 2; ++nb) {
+            if (__ballot((near >> (16 * nb) & 0xffffu) != 0) == 0) continue;
+            const int64_t row = nb ? row1 : row0;
+            const f32x4_t *k = (const f32x4_t *)((const float *)a.K + (row >= 0 ? row : 0) * D);
+            floatx16_t acc;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum = fmaf(x[e], w[(int64_t)(4 * c + e) * a.LP], sum);
+            for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+#pragma unroll 4
+            for (int c = 0; c < D / 4; ++c) {          // channels 4 c + g, then 4 c + 2 + g
+                const f32x4_t x = k[c];
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[(int64_t)(4 * c) * a.LP], g ? x.y : x.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[(int64_t)(4 * c + 2) * a.LP], g ? x.w : x.z, acc, 0, 0, 0);
+            }
+            uint32_t signs = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) signs |= (acc[i] >= 0.0f ? 0u : 1u) << i;
+            neg = nb ? (neg & 0xffffu) | signs << 16 : (neg & 0xffff0000u) | signs;
         }
-        return sum;
+        return neg;
     }
 
     // The sums of a block's two keys of a lane: accumulator i of half g is bit 32 q + 16 g + i of position
     // group `sub`.  neg: their signs, the second key's from bit 16 on.  row(nb): the key's row in K, or -1.
     template <typename F>
     __device__ __forceinline__ void add(const floatx16_t &acc0, const floatx16_t &acc1, uint32_t &neg, const float2 *key, float2 cols, int q, int sub, int tok, F &&row) {
-        auto bound = [&](int nb) { return cols.x < __builtin_inff() ? fmaf(key[nb].x, cols.x, key[nb].y * cols.y) : __builtin_inff(); };
-        const float bound0 = bound(0), bound1 = bound(1);
-        float least0 = fabsf(acc0[0]), least1 = fabsf(acc1[0]);
-#pragma unroll
-        for (int i = 1; i < 16; ++i) {                 // (a NaN comes with an infinite bound)
-            least0 = fminf(least0, fabsf(acc0[i]));
-            least1 = fminf(least1, fabsf(acc1[i]));
-        }
-        if (__ballot(!(least0 > bound0 && least1 > bound1)) == 0 || ntab <= 0) return;
-        uint32_t near = 0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) near |= (fabsf(acc0[i]) > bound0 ? 0u : 1u) << i | (fabsf(acc1[i]) > bound1 ? 0u : 1u) << (16 + i);
         const int lane = threadIdx.x & 63, u0 = 32 * q + 16 * (lane >> 5);
+        // one of the two: the sums that are not above the bound (near zero), none of a key without a row
+        auto look = [&](const floatx16_t &acc, int nb, int64_t *at) __attribute__((always_inline)) {
+            const float inf = __builtin_inff(), bound = cols.x < inf ? fmaf(key[nb].x, cols.x, key[nb].y * cols.y) : inf;
+            float least = fabsf(acc[0]);
+#pragma unroll
+            for (int i = 1; i < 16; ++i) least = fminf(least, fabsf(acc[i]));   // (a NaN comes with an infinite bound)
+            uint32_t near = 0;
+            if (__ballot(!(least > bound)) == 0) return near;
+#pragma unroll
+            for (int i = 15; i >= 0; --i) near = __builtin_amdgcn_alignbit(near, __float_as_uint(fabsf(acc[i]) - bound), 31);
+            *at = row(nb);
+            return *at < 0 ? 0u : bound < inf ? near : 0xffffu;
+        };
+        int64_t row0 = -1, row1 = -1;
+        uint32_t near = look(acc0, 0, &row0);
+        near |= look(acc1, 1, &row1) << 16;
+        if (__ballot(near != 0) == 0 || ntab <= 0) return;
         auto table = [&](int i) { return (u0 + (i & 15)) / P * S + sub; };
         if ((32 * q + 31) / P * S + sub >= ntab) {
 #pragma unroll
             for (int i = 0; i < 16; i += P)
                 if (table(i) >= ntab) near &= ~(0x10001u * (((1u << P) - 1) << i));
         }
-        const int64_t row0 = row(0), row1 = row(1);
-        near &= (row0 < 0 ? 0u : 0xffffu) | (row1 < 0 ? 0u : 0xffff0000u);
         const int before = n;
         uint64_t m;
         for (uint32_t left = near; (m = __ballot(left != 0)) != 0; left &= left - 1) {
             const int i = __ffs((int)left) - 1, more = (int)__popcll(m);
             if (n + more > CAP) {                      // (keys by the hundred at right angles to W, or out of range)
                 n = before;
-                for (; near != 0; near &= near - 1) {
-                    const int j = __ffs((int)near) - 1;
-                    neg = (neg & ~(1u << j)) | (sum_of(j < 16 ? row0 : row1, table(j) * P + j % P) >= 0.0f ? 0u : 1u) << j;
-                }
+                neg = block_signs(neg, near, q, sub, row0, row1);
                 return;
             }
             const uint32_t id = ~(neg >> (i & ~(P - 1))) & ((1u << P) - 1);
