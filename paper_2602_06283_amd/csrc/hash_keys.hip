@@ -690,7 +690,7 @@ __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int 
 //                     truncates; the lo sums before them are 2^-7 as large (within the hundredth)
 // close_part gives a key's (x, y), bound = x A_w + y B_w.  Where squares leave the range of floats, with
 // infinities and NaN, the bound is infinite and every projection formed anew.  The sums of an all-zero
-// key are zero: it needs none.
+// key or column are zero: they need none.
 // ---------------------------------------------------------------------------------------
 template <int D> __device__ __forceinline__ float2 close_part(float A, float B) {
     float2 e = make_float2(1.01f * (A * (D * 1.8e-7f) + B * 0.00391f), 1.01f * (B * 1.01f + A * 0.00391f));
@@ -705,19 +705,33 @@ __device__ __forceinline__ float add_squares(bf16x8_t v, float sum) {
     sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w.z), __builtin_bit_cast(bf16x2_t, w.z), sum, false);
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w.w), __builtin_bit_cast(bf16x2_t, w.w), sum, false);
 }
-// cols: the largest A and B of the columns of a block, whose fragments these are (wave-wide; an
-// infinity where one of them is out of range)
-template <int KS> __device__ __forceinline__ float2 close_columns(const uint4 *frag) {
+// What a block's columns have in common: the largest A and B (an infinity where one of them is out of
+// range), and which of them are all zero, a bit for each as in a sign word.
+struct CloseColumns {
+    float A, B;
+    uint32_t zero;
+};
+// frag: the block's fragments, of lane's MFMA row.  w: the row's column of W (the pieces of a number too
+// small for bf16 are zero, its products may not be)
+template <int D> __device__ __forceinline__ CloseColumns close_columns(const uint4 *frag, const float *w, int LP) {
+    constexpr int KS = D / 16;
     float hi = 0.0f, lo = 0.0f;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         hi = add_squares(__builtin_bit_cast(bf16x8_t, frag[ks * 64]), hi);
         lo = add_squares(__builtin_bit_cast(bf16x8_t, frag[(KS + ks) * 64]), lo);
     }
-    const float B = 1.01f * sqrtf(xor32_sum(lo)), A = 1.001f * sqrtf(xor32_sum(hi)) + B;
+    const float h2 = xor32_sum(hi), B = 1.01f * sqrtf(xor32_sum(lo)), A = 1.001f * sqrtf(h2) + B;
     const bool odd = __ballot(!(A < 1e15f)) != 0;              // (a NaN would be lost in the largest)
     const float most = wave_max(A);
-    return make_float2(odd || !(most > 1e-10f) ? __builtin_inff() : most, wave_max(B));
+    uint32_t zero = 0;
+    if (__ballot(h2 == 0.0f) != 0) {
+        uint32_t any = 0;
+        for (int c = 0; c < D; ++c) any |= __float_as_uint(w[(int64_t)c * LP]) << 1;
+        const uint32_t rows = (uint32_t)__ballot(any == 0);    // by MFMA row: nibbles 0, 2, .. are the first half of the word
+        for (int i = 0; i < 8; ++i) zero |= (rows >> (4 * i) & 15u) << (4 * (i >> 1) + 16 * (i & 1));
+    }
+    return CloseColumns{odd || !(most > 1e-10f) ? __builtin_inff() : most, wave_max(B), zero};
 }
 
 struct CloseEntry {
@@ -739,13 +753,18 @@ template <int D, int P, int S, int CAP> struct CloseList {
     __device__ __forceinline__ CloseList(const HashArgs &args, CloseEntry *mine, int h, int first, int tables)
         : a(args), list(mine), W((const float *)args.W + (int64_t)h * D * args.LP + (int64_t)first * P), first_table(first), ntab(tables) {}
 
+    // The column of W that is the lane's MFMA row in block q of position group `sub` (cut_fragments)
+    __device__ __forceinline__ const float *column(int q, int sub) const {
+        const int lane = threadIdx.x & 63, u = 32 * q + (lane & 3) + 4 * ((lane >> 3) & 3) + 16 * ((lane >> 2) & 1);
+        return W + max(min(u / P * S + sub, ntab - 1), 0) * P + u % P;
+    }
+
     // The signs (as in add) of a block's first or second keys, or both, where one of them is `near`: on the
     // fp32 matrix cores, whose sums are the FMA kernel's bit for bit (hash_f32_kernel), both operands
     // straight from memory.
     __device__ __forceinline__ uint32_t block_signs(uint32_t neg, uint32_t near, int q, int sub, int64_t row0, int64_t row1) const {
         const int lane = threadIdx.x & 63, g = lane >> 5;
-        const int u = 32 * q + (lane & 3) + 4 * ((lane >> 3) & 3) + 16 * ((lane >> 2) & 1);   // (the rows of the fragments: cut_fragments)
-        const float *w = W + (int64_t)g * a.LP + min(u / P * S + sub, ntab - 1) * P + u % P;
+        const float *w = column(q, sub) + (int64_t)g * a.LP;
 #pragma unroll 1
         for (int nb = 0; nb < 2; ++nb) {
             if (__ballot((near >> (16 * nb) & 0xffffu) != 0) == 0) continue;
@@ -771,11 +790,12 @@ template <int D, int P, int S, int CAP> struct CloseList {
     // The sums of a block's two keys of a lane: accumulator i of half g is bit 32 q + 16 g + i of position
     // group `sub`.  neg: their signs, the second key's from bit 16 on.  row(nb): the key's row in K, or -1.
     template <typename F>
-    __device__ __forceinline__ void add(const floatx16_t &acc0, const floatx16_t &acc1, uint32_t &neg, const float2 *key, float2 cols, int q, int sub, int tok, F &&row) {
+    __device__ __forceinline__ void add(const floatx16_t &acc0, const floatx16_t &acc1, uint32_t &neg, const float2 *key, CloseColumns cols, int q, int sub, int tok, F &&row) {
         const int lane = threadIdx.x & 63, u0 = 32 * q + 16 * (lane >> 5);
-        // one of the two: the sums that are not above the bound (near zero), none of a key without a row
+        // one of the two: the sums that are not above the bound (near zero); none of a key without a row,
+        // or of a column of zeros, whose sums are zero (but for infinities and NaN)
         auto look = [&](const floatx16_t &acc, int nb, int64_t *at) __attribute__((always_inline)) {
-            const float inf = __builtin_inff(), bound = cols.x < inf ? fmaf(key[nb].x, cols.x, key[nb].y * cols.y) : inf;
+            const float inf = __builtin_inff(), bound = cols.A < inf ? fmaf(key[nb].x, cols.A, key[nb].y * cols.B) : inf;
             float least = fabsf(acc[0]);
 #pragma unroll
             for (int i = 1; i < 16; ++i) least = fminf(least, fabsf(acc[i]));   // (a NaN comes with an infinite bound)
@@ -784,7 +804,8 @@ template <int D, int P, int S, int CAP> struct CloseList {
 #pragma unroll
             for (int i = 15; i >= 0; --i) near = __builtin_amdgcn_alignbit(near, __float_as_uint(fabsf(acc[i]) - bound), 31);
             *at = row(nb);
-            return *at < 0 ? 0u : bound < inf ? near : 0xffffu;
+            const uint32_t zero = key[nb].x < inf ? cols.zero >> (lane & 32 ? 16 : 0) : 0u;
+            return *at < 0 ? 0u : (bound < inf ? near : 0xffffu) & ~zero;
         };
         int64_t row0 = -1, row1 = -1;
         uint32_t near = look(acc0, 0, &row0);
@@ -965,7 +986,7 @@ __global__ __launch_bounds__((hash8_threads<hash_width<T, D>()>())) void hash_mf
     uint32_t *mybits = bits + wave * 256;
     const int n = lane & 31, g = lane >> 5;
     constexpr int CAP = SPLIT ? 64 : 1;                // entries of a CloseList
-    __shared__ float2 cols[SPLIT ? NCB : 1];           // A and B of the blocks' columns
+    __shared__ CloseColumns cols[SPLIT ? NCB : 1];     // of each block
     __shared__ CloseEntry close_lds[SPLIT ? NW : 1][CAP];
     CloseList<D, P, S, CAP> close(a, close_lds[SPLIT ? wave : 0], h, first_table, ntab);
     const char *Kb = (const char *)a.K;
@@ -1024,7 +1045,8 @@ __global__ __launch_bounds__((hash8_threads<hash_width<T, D>()>())) void hash_mf
     __syncthreads();                           // (waits for LDS only: a short run's keys stay under way)
     if constexpr (SPLIT) {
         for (int p = wave; p < NCB; p += NW) {
-            const float2 c = close_columns<KS>(wl + (p * KF) * 64 + lane);
+            const int sl = p / BPG, q = p % BPG;
+            const CloseColumns c = close_columns<D>(wl + (p * KF) * 64 + (lane ^ frag_turn(sl, q)), close.column(q, sub0 + sl), a.LP);
             if (lane == 0) cols[p] = c;
         }
         __syncthreads();

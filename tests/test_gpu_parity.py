@@ -414,11 +414,11 @@ def test_hash_keys_a_long_run_among_short_ones_is_shared_out(kv_dtype, d, L, P):
     ctx.close()
 
 
-@pytest.mark.parametrize("data", ["small keys", "keys with infinities"])
-def test_hash_keys_fp32_time_of_close_sums(data):
+@pytest.mark.parametrize("data,times", [("small keys", 6), ("keys with infinities", 6), ("planes of zeros", 2)])
+def test_hash_keys_fp32_time_of_close_sums(data, times):
     """Keys that leave no sum its sign (the bound on the pieces is infinite) cost a few times what others do,
-    for a block of them is formed anew on the fp32 matrix cores, not sum by sum.  (3.7 times and 1.5 to 3
-    were measured; 40 and 7 sum by sum.)"""
+    for a block of them is formed anew on the fp32 matrix cores, not sum by sum; planes of zeros cost
+    nothing.  (3.7 times, 1.5 to 3, and 1.1 were measured; 40, 7 and 7 sum by sum.)"""
     _need_gpu()
     d, L, P, H, n = 128, 32, 8, 8, 8192
     gen = torch.Generator(device="cuda").manual_seed(5)
@@ -429,10 +429,12 @@ def test_hash_keys_fp32_time_of_close_sums(data):
     usual = _least_us(lambda: ctx.hash_keys(K, W, zero, count, 1, n, codes))
     if data == "small keys":
         K *= 1e-14
+    elif data == "planes of zeros":
+        W[:, :, 7::8] = 0
     else:
         K[:, :, ::200, 3] = float("inf")
     us = _least_us(lambda: ctx.hash_keys(K, W, zero, count, 1, n, codes))
-    assert us <= 6 * usual, (us, usual)
+    assert us <= times * usual, (us, usual)
     ctx.close()
 
 
