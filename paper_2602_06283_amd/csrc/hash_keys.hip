@@ -1038,6 +1038,7 @@ __global__ __launch_bounds__((hash8_threads<hash_width<T, D>()>())) void hash_mf
     cut_fragments<T, D, S, P, NG, NT>(wl, a, h, first_table, ntab, sub0, tid, [&]() __attribute__((always_inline)) {
         if (!SHORT) return;
         nblocks = (count + 63) >> 6;
+        if (SPLIT) nblocks = min(nblocks, slots * NW);   // (a row_count beyond max_rows: a wavefront's keys are fetched once)
         parts = NG;
         while (parts > 1 && nblocks > slots * (NW / parts)) parts >>= 1;
         stride = slots * (NW / parts);

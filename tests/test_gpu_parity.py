@@ -414,6 +414,23 @@ def test_hash_keys_a_long_run_among_short_ones_is_shared_out(kv_dtype, d, L, P):
     ctx.close()
 
 
+def test_hash_keys_fp32_rows_beyond_max_rows():
+    """A row_count larger than max_rows: rows up to max_rows get their ids, those behind get them or keep what they had."""
+    _need_gpu()
+    d, L, P, H, n, bound = 128, 64, 8, 8, 9008, 4096
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    K = torch.randn((1, H, n, d), generator=gen, device="cuda")
+    W = torch.randn((H, d, L * P), generator=gen, device="cuda")
+    ctx = sk.Context(sk.make_params(d, H, H, L, P, sk.F32, 1, n, 16))
+    want, got = (hz.new_codes((1, H), n, L, P, fill=0x55) for _ in range(2))
+    ctx.hash_keys(K, W, hz.i32([0]), hz.i32([n]), 1, n, want)
+    ctx.hash_keys(K, W, hz.i32([0]), hz.i32([n]), 1, bound, got)
+    assert torch.equal(got[:, :, :bound], want[:, :, :bound])
+    kept = (got == 0x55).all(-1)
+    assert ((got == want).all(-1) | kept).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("data,times", [("small keys", 6), ("keys with infinities", 6), ("planes of zeros", 2)])
 def test_hash_keys_fp32_time_of_close_sums(data, times):
     """Keys that leave no sum its sign (the bound on the pieces is infinite) cost a few times what others do,
