@@ -317,23 +317,34 @@ def test_hash_keys_fp32_close_sums(d, L, P, Hkv, counts):
 
 @pytest.mark.parametrize("d,L,P,page,begins,counts,kind", [
     (128, 64, 8, 16, [0, 0, 0], [1500] * 3, "shared"), (64, 32, 8, 48, [5] * 4, [1501] * 4, "shared"), (128, 64, 4, 16, [0] * 8, [400] * 8, "shared"),
+    # one sequence, short and long runs; several dealt out as one: odd beginnings, empty ones, one row
+    (128, 64, 8, 48, [37], [2501], "own"), (64, 31, 4, 16, [3], [9001], "absent"), (128, 32, 8, 16, [11], [12000], "absent"),
+    (128, 100, 8, 16, [5, 0, 777, 21], [1999, 0, 1, 3000], "absent"), (64, 70, 4, 48, [1, 0, 50, 13], [2100, 63, 0, 5000], "absent"),
+    (128, 16, 8, 16, [7, 19], [9000, 5000], "absent"), (64, 128, 4, 16, [15, 1], [4000, 4100], "own"),
 ])
 def test_hash_keys_fp32_close_sums_on_paged_caches(d, L, P, page, begins, counts, kind):
-    """The same on blocks in random order, against short runs of one sequence at a time: sequences that share
-    their blocks ("shared", every id written by all of them) get the ids that one alone gets."""
+    """The same on blocks in random order, against short runs of one sequence at a time, W with columns of
+    zeros and of a number that bf16 does not hold: rows that are not meant and rows without a block
+    ("absent") keep what they had, and sequences that share their blocks ("shared", every id written by all
+    of them) get the ids that one alone gets."""
     _need_gpu()
     B, Hkv = len(counts), 8
     per = (max(b + c for b, c in zip(begins, counts)) + page - 1) // page
     gen = torch.Generator(device="cuda").manual_seed(11)
     K = torch.randn((B * per, Hkv, page, d), generator=gen, device="cuda")
     W = torch.randn((Hkv, d, L * P), generator=gen, device="cuda")
+    W[:, :, 3], W[:, :, 6] = 0.0, -0.0
+    W[:, :, 5] = 0.0
+    W[:, 2, 5] = -1e-44
     rows = torch.arange(0, B * per, 3, device="cuda")                    # every key of every third block
-    w = W.transpose(1, 2)[:, rows * 7 % (L * P)].transpose(0, 1)[:, :, None].double()
+    w = W.transpose(1, 2)[:, 7 + rows * 7 % (L * P - 7)].transpose(0, 1)[:, :, None].double()
     k = K[rows].double()
     K[rows] = (k - (k * w).sum(-1, keepdim=True) / (w * w).sum(-1, keepdim=True) * w).float()
     table = torch.randperm(B * per, generator=gen, device="cuda").to(torch.int32).view(B, per)
     if kind == "shared":
         table[:] = table[0].clone()
+    if kind == "absent":
+        table[:, 1::7], table[:, 4::9] = -1, B * per
     ctx = sk.Context(sk.make_params(d, Hkv, Hkv, L, P, sk.F32, B, per * page, 16, page, per, B * per))
     want = hz.new_codes((B * per, Hkv), page, L, P, fill=0x55)
     for b in range(B):
