@@ -230,22 +230,28 @@ __global__ __launch_bounds__(kTopkThreads) void topk_filter_kernel(TopkArgs a) {
 #pragma unroll
     for (int j = 0; j < PER; ++j) c2[j] = gh[tid + j * kTopkThreads];
     uint32_t *thr = a.thr + (int64_t)bh * kThrStride;
-    // (the length, the request and the record in one trip, not one behind the other)
+    // (the length, the request and the record in one trip, not one behind the other; of the record only
+    // what an earlier launch has written, the rest is for workgroup 0 to write)
     const int len = scalar_load(&a.seq_len[b]);
-    const uint32_t kreq = (uint32_t)clamp_len(scalar_load(&a.k[b]), a.max_k);
-    const float rec_lo = __uint_as_float(scalar_load(&thr[kThrBinLo])), rec_inv = __uint_as_float(scalar_load(&thr[kThrBinInv]));
-    const uint32_t rec0 = scalar_load(&thr[0]), rec1 = scalar_load(&thr[1]), rec2 = scalar_load(&thr[2]);
-    if (ADAPT) asm volatile("" ::"s"(len), "s"(kreq), "s"(rec_lo), "s"(rec_inv));
-    else asm volatile("" ::"s"(len), "s"(rec0), "s"(rec1), "s"(rec2));
+    uint32_t kreq = 0, rec0 = 0, rec1 = 0, rec2 = 0;
+    float bin_lo = 0.0f, bin_inv = 0.0f;
+    if constexpr (ADAPT) {
+        kreq = (uint32_t)clamp_len(scalar_load(&a.k[b]), a.max_k);
+        bin_lo = __uint_as_float(scalar_load(&thr[kThrBinLo]));
+        bin_inv = __uint_as_float(scalar_load(&thr[kThrBinInv]));
+        asm volatile("" ::"s"(len), "s"(kreq), "s"(bin_lo), "s"(bin_inv));
+    } else {
+        rec0 = scalar_load(&thr[0]);
+        rec1 = scalar_load(&thr[1]);
+        rec2 = scalar_load(&thr[2]);
+        asm volatile("" ::"s"(len), "s"(rec0), "s"(rec1), "s"(rec2));
+    }
     const int key1 = min(key0 + kSlice, clamp_len(len, a.max_n));
     // this workgroup's region of the selected list: empty unless the sweep below says otherwise
     uint32_t *selcnt = a.sel_cnt + (int64_t)bh * a.n_regions + blockIdx.x;
     if (tid == 0) *selcnt = 0u;
     uint32_t k_eff, pair, above, n_cand;
-    float bin_lo = 0.0f, bin_inv = 0.0f;
     if (ADAPT) {
-        bin_lo = rec_lo;
-        bin_inv = rec_inv;
         if (key0 >= key1 && blockIdx.x != 0) return;   // workgroup 0 always publishes the record
 #pragma unroll
         for (int j = 0; j < PER; ++j) h[padded<PER>(tid + j * kTopkThreads)] = c2[j];
