@@ -132,12 +132,20 @@ def _ptr(t):
     return t.data_ptr()                     # (the declared argument types make it a pointer)
 
 
+_raw_stream, _device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+if _device is None:
+    _raw_stream = None
+
+
 def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
     # the current stream's handle, 0.2 us; a Stream object made for it (torch.cuda.current_stream()) takes 2.8,
-    # a third of a call
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    # a third of a call.  The public call where torch does not have these, and where it has to start the
+    # device first or to refuse it (a forked child)
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 class Context:

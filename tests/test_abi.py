@@ -147,3 +147,16 @@ def test_null_arguments_are_rejected_without_a_gpu():
                                   None, None, 1, None, None) == sk.EINVAL
     assert lib.socket_graph_begin(None) == sk.EINVAL
     assert lib.socket_scratch_bytes(None) == 0
+
+
+@pytest.mark.parametrize("private_calls,started", [(True, True), (True, False), (False, True)])
+def test_the_current_stream_without_torchs_private_calls(monkeypatch, private_calls, started):
+    """The current stream's handle comes from torch's public call where torch has no quicker one and where
+    it has not started the device (or refuses to, in a forked child)."""
+    torch = sk.torch
+    monkeypatch.setattr(sk, "_raw_stream", (lambda device: 100 + device) if private_calls else None)
+    monkeypatch.setattr(sk, "_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: started)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 7}))
+    assert sk._stream(None) == (103 if private_calls and started else 7)
+    assert sk._stream(type("Stream", (), {"cuda_stream": 9})) == 9
