@@ -735,7 +735,8 @@ __device__ __forceinline__ void merge_splits(const DecodeArgs &a, int g, int h, 
         const uint32_t s = (uint32_t)min(sg + j * NG, a.n_split - 1);
         acc[j] = ((const float *)((const char *)part + s * (uint32_t)((D + 2) * 4)) + 2)[c];
     }
-    // merge_finish: a head that its splits left alone (looked at behind the loads, which would wait for it)
+    // merge_finish: a head that its splits left alone (looked at behind the loads, which would wait for it;
+    // what they brought may be half written, by the workgroup that attends the head anew: it is not used)
     if (thr && too_many(scalar_load(&thr[0]), scalar_load(&thr[6]))) return;
     if (tid < 64) {
         const float top = wave_max(fmaxf(m[0], m[1]));
