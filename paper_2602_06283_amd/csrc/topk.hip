@@ -607,8 +607,9 @@ constexpr size_t kEmitLds = (size_t)(kRankMax + 4) * 8 + (size_t)kRankMax * 4;
 // ---------------------------------------------------------------------------------------
 // Short rows in one launch: one workgroup of 16 wavefronts per (sequence, KV head) holds the row in
 // registers (NC chunks of 4096 scores), so the select is a chain of phases in LDS:
-//   window   two scores of a sample of 1024 between which the cut should lie: as many ranks above and
-//            below the wanted share as three of its deviations
+//   window   two keys between which the cut should lie: of a sample of 1024 scores, as many ranks above and
+//            below the wanted share as three of its deviations (to a bin of the sample's own histogram;
+//            where both lie in one bin, equal or close scores, the scores themselves)
 //   bins     2048 equal steps of the score key between the two, five instructions a score; the scores
 //            above are only counted.  Where the cut lies outside the window after all, the scores on
 //            that side are refined
@@ -694,9 +695,8 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
                 if (c * kSlice + 4 * tid + j >= seq) w[c][j] = __float_as_uint(ninf);
         }
 
-    // ---- keys klo .. khi - 1, between which the cut should lie: those of two scores of a sample, as many
-    //      ranks above and below the wanted share as three of its deviations.  The sample is a score a thread,
-    //      the chunks in turn
+    // ---- keys klo .. khi - 1, between which the cut should lie, from a sample: a score a thread, the chunks
+    //      in turn
     uint32_t klo, khi;
     {
         const int live = max(1, (seq + kSlice - 1) / kSlice);
@@ -732,13 +732,18 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
         here(rank_hi, &res[1]);
         *(uint2 *)&h[kHistBins - 2 - 2 * tid] = make_uint2(0, 0);
         __syncthreads();
-        const uint32_t lo = wave_umax(key && bin >= res[0] ? ~key : 0u);
-        const uint32_t hi = wave_umax(key < 0xff800000u && bin <= res[1] ? key : 0u);       // (+inf would stretch the bins)
-        if (lane == 0) s_ends[1][wave] = make_uint2(lo, hi);
-        __syncthreads();
-        const uint2 cut = s_ends[1][lane & 15];
-        klo = ~lanes16(cut.x);
-        khi = max(lanes16(cut.y), klo) + 1;
+        const uint32_t bin_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[0]), bin_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)res[1]);
+        klo = least + (bin_lo << shift);
+        khi = least + min(((bin_hi + 1) << shift) - 1, most - least) + 1;
+        if (bin_lo == bin_hi || khi > 0xff800000u) {             // equal or close scores, or infinities: the keys themselves
+            const uint32_t lo = wave_umax(key && bin >= bin_lo ? ~key : 0u);
+            const uint32_t hi = wave_umax(key < 0xff800000u && bin <= bin_hi ? key : 0u);   // (+inf would stretch the bins)
+            if (lane == 0) s_ends[1][wave] = make_uint2(lo, hi);
+            __syncthreads();
+            const uint2 cut = s_ends[1][lane & 15];
+            klo = ~lanes16(cut.x);
+            khi = max(lanes16(cut.y), klo) + 1;
+        }
         if (most == 0) klo = 1, khi = 2;                         // (nothing but NaN and -inf)
     }
     // Scores from +0 on compare by their bits, counted from +0; where the bins start below, w takes keys (0
