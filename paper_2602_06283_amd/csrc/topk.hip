@@ -622,15 +622,15 @@ constexpr size_t kEmitLds = (size_t)(kRankMax + 4) * 8 + (size_t)kRankMax * 4;
 //   emit     slots in position order, from a scan over the kept scores
 // Nothing is kept between calls; no scratch.
 // Bound by the instructions of one compute unit behind 6 us of launch, loads and phases.
-// us a select of a 32nd of 8 rows, this kernel / three launches: like a bell 20496 scores 9.5 / 14.2, 24576 9.7 /
-// 13.9, 28672 10.4 / 13.8, 32768 11.1 / 13.8, 36864 11.8 / 13.9; counts 32768 15.2 / 19.4; a heavy tail 32768 11.1 /
-// 13.0; a cluster in a cluster 36864 16.7 / 21.2.  An eighth of 36864: a bell 12.4 / 14.0, counts 18.0 / 20.3, counts
-// with a soft part 22.9 / 21.0.  64 rows like a bell 36864 12.2 / 16.1, 49152 14.6 / 19.4.  So up to kRowRegions
-// regions of 4096 scores always: of 12 shapes of rows with a 32nd, an eighth and a third selected the last-named
-// alone is slower there.  Up to kRowRegionsMany from kRowRowsMany rows on, where three launches fill the card.
-// (A window by the mean and the deviation of the sample: a bell the same, but rows whose cut lay below it were binned
-// twice and those with a window across zero in steps of an octave: a 32nd of 36864 with infinities 30.2 / 11.9 now, an
-// eighth of counts with a soft part 35.5 / 22.9, a third of 20480 rising scores 27.2 / 10.2.)
+// us a select of a 32nd of 8 rows, this kernel / three launches: like a bell 20496 scores 9.0 / 14.3, 24576 9.3 /
+// 13.5, 28672 10.2 / 13.7, 32768 10.7 / 13.8, 36864 11.4 / 14.2; counts 32768 14.7 / 19.2; a heavy tail 32768 10.8 /
+// 13.1; a cluster in a cluster 36864 16.7 / 21.0.  An eighth of 36864: a bell 12.1 / 14.1, counts 17.7 / 20.3, counts
+// with a soft part 19.7 / 20.9; a third 25.4 / 25.8.  64 rows like a bell 36864 11.8 / 16.4, 49152 13.7 / 19.3.  So
+// up to kRowRegions regions of 4096 scores always, where none of 12 shapes of rows with a 32nd, an eighth and a
+// third selected was slower; up to kRowRegionsMany from kRowRowsMany rows on, where three launches fill the card.
+// (A window by the mean and the deviation of the sample: a bell 0.4 us slower, and rows whose cut lay below it were
+// binned twice, those with a window across zero in steps of an octave: a 32nd of 36864 with infinities 30.1 / 11.9
+// now, an eighth of counts with a soft part 35.5 / 19.7, a third of 20480 rising scores 27.3 / 10.0.)
 // ---------------------------------------------------------------------------------------
 constexpr int kRowThreads = 1024, kRowWaves = kRowThreads / 64;
 constexpr int kRowPairs = 256;
@@ -842,9 +842,9 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
     for (int i = (int)k_eff + tid; i < a.max_k; i += kRowThreads) out[i] = -1;
     if (k_eff == 0) return;
     __syncthreads();
-    for (bool ends_only = n_in > (uint32_t)seq / 16; n_in != need && n_in > (uint32_t)kRowPairs && span > 1; ends_only = false) {
-        // (where there are many of them they are likely equal scores, which would add up one behind the
-        // other: only their ends first)
+    for (bool ends_only = n_in > (uint32_t)seq / 8; n_in != need && n_in > (uint32_t)kRowPairs && span > 1; ends_only = false) {
+        // (where an eighth of the row is in the bin they are likely equal scores, which would add up one behind
+        // the other: only their ends first.  A sixteenth: counts the same, counts with a soft part 22.7, not 19.7)
         const int bits = 32 - __clz((int)(span - 1)), shift = bits > kHistBits ? bits - kHistBits : 0;
         for (int j = tid; j < kHistBins; j += kRowThreads) h[j] = 0;
         __syncthreads();
