@@ -678,10 +678,10 @@ __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int 
 // keys, 32 tables, 28 us else and 48 on the fp32 matrix cores alone): all keys or all of W too small or too
 // large for the bound 100, one key in a hundred of that kind 91, every key at right angles to one column
 // of W 70.  (Sum by sum, a lane each, these took 1130, 201 and 88.)
-// 8 heads, 32 tables of 8 planes, 128 channels: 8192 keys 25.5 us (42.6 on the fp32 matrix cores), 32768 65
-// (154), where a block's matrix work is 12 of its 20 us and the rest the keys' way from memory, two
-// wavefronts a SIMD being all that the registers allow; of a short run's time 14 us are launch, W and
-// instructions that come cold.
+// 8 heads, 32 tables of 8 planes, 128 channels, many calls on two caches in turn: 8192 keys 28 us (45 on the
+// fp32 matrix cores), 32768 67 (154), where a block's matrix work is 12 of its 20 us and the rest the keys' way
+// from memory, two wavefronts a SIMD being all that the registers allow; of a short run's time 14 us are
+// launch, W and instructions that come cold.
 // The bound, for a key k and a column w, with A >= the norm of a vector and B = the norm of its lo
 // pieces (Cauchy-Schwarz turns norms into sums of magnitudes):
 //   dropped products  lo*lo <= B_k B_w, rest*w <= 2^-8 B_k A_w, k*rest <= 2^-8 A_k B_w
@@ -1473,10 +1473,11 @@ static int launch_f32(HashArgs a, int Hkv, int batch, int max_rows, bool split, 
     const int seq_tiles = (max_rows + kF32Tile - 1) / kF32Tile;
     int64_t share = ((int64_t)seq_tiles * rows * batch + slots - 1) / slots;
     // More than one tile to a workgroup: the pieces on the bf16 matrix cores.  One tile is over before
-    // their W is cut and their first instructions are there (8 heads, us here / there: 32 tables of 8
-    // planes 1024 keys 9.9 / 15.1, 2048 16.9 / 15.8, 8192 45 / 28, 32768 154 / 65; 64 tables 1024 16.7 /
-    // 17.2, 2048 25.6 / 20.4, 8192 74 / 39; d = 64, 64 tables 1024 9.4 / 11.1, 2048 14.3 / 12.6, 32768
-    // 160 / 62).
+    // their W is cut and their first instructions are there (8 heads, us here / there, many calls on two
+    // caches in turn: 32 tables of 8 planes 1024 keys 9.9 / 15.1, 2048 16.9 / 15.8 (still one tile), 8192
+    // 45 / 28, 32768 154 / 67; 64 tables 1024 16.7 / 17.2, 2048 25.6 / 20.4, 8192 74 / 40; d = 64, 64 tables
+    // 1024 9.4 / 11.1, 2048 14.3 / 12.6, 32768 160 / 63; on one cache, d = 128, 16 tables 3072 keys 14.9 /
+    // 13.6, 8192 27.7 / 17.0; 31 tables of 4 planes 3072 15.3 / 13.0; d = 64, 16 of 4 8192 11.8 / 8.7).
     if constexpr (sizeof(T) == 4 && D <= 128)
         if (split && share > 1) return launch_mfma8<float, D>(a, Hkv, batch, max_rows, st);
     if (share > 16) share = 16;
