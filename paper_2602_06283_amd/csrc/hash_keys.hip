@@ -689,15 +689,16 @@ __device__ __forceinline__ void cut_fragments(uint4 *wl, const HashArgs &a, int 
 //   matrix cores      D additions to the sum of hi*hi and a rounding of the result every 16, each off by
 //                     2^-23 of at most A_k A_w if it truncates; the 2 D additions of lo products before
 //                     them likewise, to sums 2^-7 as large
-// together (2^-24 + 1.08 * 2^-23) D A_k A_w = 1.9e-7 D A_k A_w for the last two, and 2.1e-7 taken.  That the
-// matrix cores lose no more than the last place of an addition is an assumption, not documented; the tests
-// compare the ids with the FMA kernel's where sums are rounding errors and nothing else.
+// together (2^-24 + 1.08 * 2^-23) D A_k A_w = 1.885e-7 D A_k A_w for the last two; 1.9e-7 and a hundredth more
+// are taken (2.1e-7: a tenth more close sums, 0.4 us of 27).  That the matrix cores lose no more than the
+// last place of an addition is an assumption, not documented; the tests compare the ids with the FMA
+// kernel's where sums are rounding errors and nothing else.
 // close_part gives a key's (x, y), bound = x A_w + y B_w.  Where squares leave the range of floats, with
 // infinities and NaN, the bound is infinite and every projection formed anew.  The sums of an all-zero
 // key or column are zero: they need none.
 // ---------------------------------------------------------------------------------------
 template <int D> __device__ __forceinline__ float2 close_part(float A, float B) {
-    float2 e = make_float2(1.01f * (A * (D * 2.1e-7f) + B * 0.00391f), 1.01f * (B * 1.01f + A * 0.00391f));
+    float2 e = make_float2(1.01f * (A * (D * 1.9e-7f) + B * 0.00391f), 1.01f * (B * 1.01f + A * 0.00391f));
     if (!(A > 1e-10f && A < 1e15f)) e = A == 0.0f ? make_float2(-1.0f, 0.0f) : make_float2(__builtin_inff(), __builtin_inff());
     return e;
 }
