@@ -724,7 +724,7 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs a) {
         const uint2 c = *(const uint2 *)&h[kHistBins - 2 - 2 * tid];
         uint32_t all;
         const uint32_t above = row_excl_scan(c.x + c.y, &all, tmp);
-        const uint32_t rank_lo = min((uint32_t)(r + dev) + 1, all), rank_hi = (uint32_t)fmaxf(r - dev, 1.0f);
+        const uint32_t rank_lo = min((uint32_t)(r + dev) + 1, all), rank_hi = min((uint32_t)fmaxf(r - dev, 1.0f), all);
         auto here = [&](uint32_t rank, uint32_t *at) {
             if (above < rank && rank <= above + c.x + c.y) *at = (uint32_t)(kHistBins - 2 - 2 * tid + (rank <= above + c.y ? 1 : 0));
         };

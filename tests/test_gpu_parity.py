@@ -704,6 +704,25 @@ def test_topk_of_short_rows(B, H, n):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,k,few", [(8192, 4000, 5), (8192, 20, 0), (36864, 9000, 3), (1008, 700, 2), (20480, 20000, 40)])
+def test_topk_of_short_rows_whose_sample_says_nothing(n, k, few):
+    """Rows in which next to none of the scores that the one-launch select samples can be selected (-inf and NaN), the
+    others all: fewer sampled ones than the rank that is asked for, and none."""
+    _need_gpu()
+    H, live = 4, (n + 4095) // 4096
+    rng = np.random.default_rng(n)
+    s = (0.5 + 0.5 * rng.random((1, H, n))).astype(np.float32)
+    at = np.array([(t % live) * 4096 + 4 * t for t in range(1024)])
+    at = at[at < n]
+    s[:, :, at[::2]], s[:, :, at[1::2]] = -np.inf, np.nan
+    s[:, 0, at[:few]], s[:, 1, at[:few]], s[:, 2, at[-few:] if few else []] = 0.1, 0.9, 0.7
+    ctx = sk.Context(sk.make_params(64, H, H, 16, 4, sk.BF16, 1, n, k))
+    for _ in range(3):
+        idx, nsel = run_topk(ctx, s, [n], [k], 1, H, k)
+        check_topk(idx, nsel, np.where(np.isnan(s), -np.inf, s), [n], [k])
+    ctx.close()
+
+
 @pytest.mark.parametrize("name,part", [("infinities", 32), ("counts with a soft part", 3), ("hot block", 3)])
 def test_topk_time_of_short_rows_does_not_depend_on_their_shape(name, part):
     """In the one-launch select a row that is no bell costs a refinement, not one binning after the other.
